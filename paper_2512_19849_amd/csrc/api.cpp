@@ -465,8 +465,9 @@ int ep_layout_static(const int32_t *d_topk_idx, int32_t S, int32_t T, int32_t K,
   if (!HIP_OK((hipError_t)static_layout_scratch(&a))) return EP_EHIP;
   // the array keeps what the last call left: the ticket has to start at zero (a fill kernel, not a memset
   // node, so that the call can be captured into a graph)
-  if (!HIP_OK((hipError_t)launch_fill_u32(a.ticket, 0u, 1, stream))) return EP_EHIP;
-  return HIP_OK((hipError_t)launch_layout(a, Tunables{}, stream, nullptr)) ? EP_OK : EP_EHIP;
+  const Tunables tune{};
+  if (!layout_takes_one_launch(a, tune) && !HIP_OK((hipError_t)launch_fill_u32(a.ticket, 0u, 1, stream))) return EP_EHIP;
+  return HIP_OK((hipError_t)launch_layout(a, tune, stream, nullptr)) ? EP_OK : EP_EHIP;
 }
 
 static uint32_t row_bytes_of(int H, int payload) {

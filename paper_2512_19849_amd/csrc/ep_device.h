@@ -233,6 +233,16 @@ EP_DEV int wave_inclusive_scan(int v, int lane) {
   return v;
 }
 
+// Sum over the 64 lanes, in every lane: adds within rows of 16 lanes, then across the four rows (DPP moves: no LDS).
+EP_DEV int wave_sum(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xF, 0xF, true);   // quad_perm [1,0,3,2]
+  v += __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xF, 0xF, true);   // quad_perm [2,3,0,1]
+  v += __builtin_amdgcn_update_dpp(0, v, 0x141, 0xF, 0xF, true);  // row_half_mirror
+  v += __builtin_amdgcn_update_dpp(0, v, 0x140, 0xF, 0xF, true);  // row_mirror
+  return __builtin_amdgcn_readlane(v, 0) + __builtin_amdgcn_readlane(v, 16) + __builtin_amdgcn_readlane(v, 32) +
+         __builtin_amdgcn_readlane(v, 48);
+}
+
 // One launch, with the kernel's own begin / end timestamps delivered into the caller's events when asked for.
 template <class Kernel, class Args>
 static inline void launch_kernel(Kernel kernel, dim3 grid, dim3 block, size_t lds, hipStream_t st, void *ev_start,

@@ -189,7 +189,7 @@ struct Tunables {
   int dispatch_pipeline = 0; // EP_DISPATCH_PIPELINE: 1 = ring-on dispatches run persistent workgroups with a command
                              // wave (measured: no faster in chunk mode, slower per token; see the kernel's comment)
   int combine_vpl = 0;       // EP_COMBINE_VPL: 16-byte column slices per lane
-  int layout_small = 1;      // EP_LAYOUT_SMALL: 0 keeps small routing tables on the two-kernel form
+  int layout_small = 1;      // EP_LAYOUT_SMALL: 0 keeps all routing tables on the two-kernel form
   int layout_tpb = 4;        // EP_LAYOUT_TPB: tiles per workgroup of the count kernel
   int ht_threads = 1024;     // EP_HT_THREADS: threads per workgroup of the ring-buffer channels
   int combine_fresh_mb = 224;  // EP_COMBINE_FRESH_MB: see EP_FLAG_CACHE_HINTS
@@ -202,6 +202,7 @@ struct Tunables {
 struct LaunchTiming {
   void *start, *stop;
 };
+bool layout_takes_one_launch(const LayoutArgs &a, const Tunables &tune);  // ... which uses none of the scratch in a
 int launch_layout(const LayoutArgs &a, const Tunables &tune, void *stream, const LaunchTiming *timing = nullptr);
 int launch_dispatch(const DispatchArgs &a, int payload, const Tunables &tune, void *stream,
                     const LaunchTiming *timing = nullptr);

@@ -217,130 +217,166 @@ __global__ __launch_bounds__(256) void layout_finish_kernel(LayoutArgs a) {
   a.dst_row[i] = a.expert_offset[e] + before + rank;
 }
 
-// ------------------------------------------------- small routing tables: one launch
-// A dozen flat tiles (768 tokens over all sources - a low-latency decode step) fit one workgroup:
-// wave f owns tile f, the bit masks of all tiles stay in LDS, one thread per expert walks the tiles
-// for the prefixes, and every wave finishes its own entries.  Nothing goes through memory between
-// the steps, which for such sizes is most of what the two kernels above spend (their floor is the
-// chain of round trips between them, about 12 us whatever the size).
-constexpr int kSmallTiles = 16;
+// ------------------------------------------------- one launch: a workgroup per expert
+// Workgroup e reads the WHOLE routing table and needs nothing from any other: the rows of expert e are the entries
+// equal to e in table order, and its first row is the number of entries with a smaller id, so a pass that counts
+// both gives every output of that expert.  No scratch, no histograms handed from one workgroup to another, no
+// second launch - which is what the two kernels above spend their time on, whatever the size of the table.
+//
+// Each wave owns a run of 256-entry groups, four consecutive entries (a quad) per lane.  A quad that holds e goes
+// to the wave's list in LDS (its place and which of the four entries); after one barrier the waves know how many
+// entries of e come before theirs and number their lists, 64 quads at a time.
+//
+// Bound by instruction issue: every compute unit looks at every entry, about 30 vector instructions per 256 of them
+// (compares with e, the smaller-id count in per-lane registers - the same with scalar popcounts was no faster -
+// and the next group's load in flight), so about 3 us per 32768 entries on top of 4 us of launch, first load,
+// barrier and stores.  Measured on MI355X against the forms before it (kernel time, us): 128 entries of 16 experts
+// 4.2 (one-workgroup form with LDS masks 5.3), 1024 of 256: 4.1 (7.5), 4096: 4.1 (11.0), 32768: 8.0 (two kernels
+// 16.7), 32768 over 32 sources: 11.8 (19.2), 32768 of 1024 experts: 14.6 (24.6).
+typedef int i32x4_any __attribute__((ext_vector_type(4), aligned(4)));  // 16 bytes at any 4-byte boundary
 
-__global__ __launch_bounds__(1024) void layout_small_kernel(LayoutArgs a) {
-  extern __shared__ unsigned long long q_lds[];
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int E = a.E, K = a.K, F = a.S * a.ntiles;
-  unsigned long long *mask = q_lds;                                         // [F][E]
-  unsigned short *pre = (unsigned short *)(q_lds + (size_t)kSmallTiles * E);  // [F][E] entries of e in earlier tiles
-  int *s_off = (int *)(pre + (size_t)kSmallTiles * E);                      // [E + 1]
-  int *s_tot = s_off + E + 1;                                               // [E]
-  for (int i = tid; i < F * E; i += blockDim.x) mask[i] = 0ull;
-  __syncthreads();
+__global__ __launch_bounds__(1024) void layout_expert_kernel(LayoutArgs a) {
+  extern __shared__ unsigned short s_list[];  // [waves][seg * 64]
+  __shared__ int s_cnt[16], s_lt[16], s_rl[16];
+  __shared__ int s_first[257];  // entries of e before source s
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), nw = blockDim.x >> 6;
+  const int e = blockIdx.x, E = a.E, S = a.S;
+  const unsigned rank_end = (unsigned)((e / a.E_loc + 1) * a.E_loc);
+  const bool first_of_rank = e % a.E_loc == 0;
+  const unsigned tk = (unsigned)a.T * a.K, n = (unsigned)S * tk, groups = (n + 255) / 256;
+  const unsigned seg = (groups + nw - 1) / nw;                         // groups of one wave
+  const unsigned i0 = wave * seg * 256, lim = min(n, i0 + seg * 256);  // its entries
+  unsigned short *list = s_list + (size_t)wave * seg * 64;
+  if (S > 1)
+    for (int s = tid; s <= S; s += blockDim.x) s_first[s] = 0;
 
-  const int f = wave, s = f < F ? f / a.ntiles : 0, tile = f < F ? f - s * a.ntiles : 0;
-  const int t = tile * kLayoutTile + lane;
-  const bool active = f < F && t < a.T;
-  const size_t ebase = ((size_t)s * a.T + (active ? t : 0)) * K;
-  const unsigned long long below = (1ull << lane) - 1ull;
-  int ev[8], rk[8];
+  auto load = [&](unsigned ib) {
+    const unsigned i = ib + lane * 4;
+    i32x4_any v = {-1, -1, -1, -1};
+    if (ib + 256 <= n) {
+      v = *(const i32x4_any *)(a.idx + i);
+    } else {
 #pragma unroll
-  for (int k = 0; k < 8; ++k) ev[k] = (active && k < K) ? a.idx[ebase + k] : -1;
-  if (f < F) {  // (wave-uniform)
-    unsigned long long *m = mask + (size_t)f * E;
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      const int e = ev[k];
-      bool pend = e >= 0 && e < E;
-      if (!pend && e != -1) dev_set_error(a.error, EP_EBOUNDS);
-      // the two most common experts of the wave are written by one lane each (see the count kernel)
-#pragma unroll
-      for (int round = 0; round < 2; ++round) {
-        const unsigned long long pm = __ballot(pend);
-        if (pm == 0) break;
-        const int leader = __builtin_ctzll(pm);
-        const int e0 = __builtin_amdgcn_readlane(e, leader);
-        const unsigned long long same = __ballot(pend && e == e0);
-        if (lane == leader) atomicOr(&m[e0], same);
-        pend = pend && e != e0;
+      for (int j = 0; j < 4; ++j)
+        if (i + j < n) v[j] = a.idx[i + j];
+    }
+    return v;
+  };
+  // entries without an expert get -1: the table is shared out over all waves of the grid for that
+  const unsigned i_mine = (e * nw + wave) * 64 + lane;
+  const int v_mine = i_mine < n ? a.idx[i_mine] : 0;
+  int quads = 0;                // list length
+  int cnt = 0, lt = 0, rl = 0;  // per lane: entries of e, of a smaller id, of an id below the end of e's rank
+  i32x4_any v, nxt;
+  if (i0 < lim) nxt = load(i0);
+#pragma nounroll
+  for (unsigned ib = i0; ib < lim; ib += 256) {
+    v = nxt;
+    if (ib + 256 < lim) nxt = load(ib + 256);
+    const bool hit = v[0] == e || v[1] == e || v[2] == e || v[3] == e;
+    const unsigned long long any = __ballot(hit);
+    if (any) {
+      if (hit) {
+        const unsigned nib = (v[0] == e ? 1u : 0u) | (v[1] == e ? 2u : 0u) | (v[2] == e ? 4u : 0u) | (v[3] == e ? 8u : 0u);
+        list[quads + __builtin_amdgcn_mbcnt_hi((unsigned)(any >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)any, 0u))] =
+            (unsigned short)((((ib - i0) >> 2) + lane) << 4 | nib);
+        cnt += __popc(nib);
       }
-      if (pend) atomicOr(&m[e], 1ull << lane);
+      quads += __popcll(any);
     }
-  }
-  __syncthreads();
-  if (f < F) {
-    const unsigned long long *m = mask + (size_t)f * E;
 #pragma unroll
-    for (int k = 0; k < 8; ++k) rk[k] = (ev[k] >= 0 && ev[k] < E) ? __popcll(m[ev[k]] & below) : 0;
-  }
-  // exclusive prefix over the flat tiles, one thread per expert; counts per source on the way
-  for (int e = tid; e < E; e += blockDim.x) {
-    int run = 0, src_first = 0;
-    for (int g = 0; g < F; ++g) {
-      if (g > 0 && g % a.ntiles == 0) {
-        a.count[(size_t)(g / a.ntiles - 1) * E + e] = run - src_first;
-        src_first = run;
-      }
-      pre[(size_t)g * E + e] = (unsigned short)run;
-      run += __popcll(mask[(size_t)g * E + e]);
+    for (int j = 0; j < 4; ++j) {
+      lt += (unsigned)v[j] < (unsigned)e;
+      rl += (unsigned)v[j] < rank_end;
     }
-    a.count[(size_t)(a.S - 1) * E + e] = run - src_first;
-    s_tot[e] = run;
-    a.expert_total[e] = run;
+  }
+  cnt = wave_sum(cnt);
+  lt = wave_sum(lt);
+  rl = wave_sum(rl);
+  if (lane == 0) {
+    s_cnt[wave] = cnt;
+    s_lt[wave] = lt;
+    s_rl[wave] = rl;
   }
   __syncthreads();
-  if (wave == 0) {  // exclusive scan over experts: 64 lanes x contiguous runs
-    const int per = (E + 63) / 64;
-    const int lo = min(E, lane * per), hi = min(E, lo + per);
-    int sum = 0;
-    for (int i = lo; i < hi; ++i) sum += s_tot[i];
-    const int incl = wave_inclusive_scan(sum, lane);
-    int run = incl - sum;
-    for (int i = lo; i < hi; ++i) {
-      s_off[i] = run;
-      a.expert_offset[i] = run;
-      run += s_tot[i];
-    }
-    if (lane == 63) {
-      s_off[E] = incl;
-      a.expert_offset[E] = incl;
+  int c_of = 0, lt_of = 0, rl_of = 0;  // lane q: wave q's
+  if (lane < nw) {
+    c_of = s_cnt[lane];
+    lt_of = s_lt[lane];
+    rl_of = s_rl[lane];
+  }
+  const int before = wave_sum(lane < wave ? c_of : 0), total = wave_sum(c_of), off = wave_sum(lt_of),
+            end = wave_sum(rl_of);
+  if (tid == 0) {
+    a.expert_total[e] = total;
+    a.expert_offset[e] = off;
+    if (e == E - 1) a.expert_offset[E] = a.rank_offset[a.R] = off + total;
+    if (first_of_rank) {
+      a.rank_offset[e / a.E_loc] = off;
+      a.rank_total[e / a.E_loc] = end - off;
     }
   }
-  __syncthreads();
-  if (active) {
-    const unsigned short *bp = pre + (size_t)f * E, *fp = pre + (size_t)s * a.ntiles * E;
-#pragma unroll
-    for (int k = 0; k < 8; ++k)
-      if (k < K) {
-        const int e = ev[k];
-        if (e >= 0 && e < E) {
-          const int before = bp[e];
-          a.slot[ebase + k] = before - (int)fp[e] + rk[k];
-          a.dst_row[ebase + k] = s_off[e] + before + rk[k];
-        } else {
-          a.slot[ebase + k] = -1;
-          a.dst_row[ebase + k] = -1;
+  if (S > 1) {  // entries of e per source, then their prefix
+    for (int p = lane; p < quads; p += 64)
+      for (unsigned q = list[p], nib = q & 15u; nib; nib &= nib - 1)
+        atomicAdd(&s_first[(i0 + (q >> 4) * 4 + __builtin_ctz(nib)) / tk + 1], 1);
+    __syncthreads();
+    if (wave == 0) {
+      int carry = 0;
+      for (int s0 = 0; s0 < S; s0 += 64) {
+        const int s = s0 + lane, c = s < S ? s_first[s + 1] : 0;
+        const int incl = carry + wave_inclusive_scan(c, lane);
+        if (s < S) {
+          s_first[s + 1] = incl;
+          a.count[(size_t)s * E + e] = c;
+          a.base[(size_t)s * E + e] = off + incl - c;
         }
+        carry = __builtin_amdgcn_readlane(incl, 63);
       }
+    }
+    __syncthreads();
+  } else if (tid == 0) {
+    a.count[e] = total;
+    a.base[e] = off;
   }
-  for (int i = tid; i < a.S * E; i += blockDim.x) {
-    const int ss = i / E, e = i - ss * E;
-    a.base[i] = s_off[e] + (int)pre[(size_t)ss * a.ntiles * E + e];
+  // the r-th entry of e in table order gets row off + r
+  int run = before;
+  for (int p0 = 0; p0 < quads; p0 += 64) {
+    const int p = p0 + lane;
+    const unsigned q = p < quads ? list[p] : 0u;
+    unsigned nib = q & 15u;
+    const int c = __popc(nib);
+    int r = run;
+    if (__ballot(c > 1) == 0) {  // (always so when 4 divides K: a token's experts are distinct)
+      r += lane;
+      run += min(64, quads - p0);
+    } else {
+      const int incl = wave_inclusive_scan(c, lane);
+      r += incl - c;
+      run += __builtin_amdgcn_readlane(incl, 63);
+    }
+    for (; nib; nib &= nib - 1, ++r) {
+      const unsigned i = i0 + (q >> 4) * 4 + __builtin_ctz(nib);
+      a.slot[i] = r - (S > 1 ? s_first[i / tk] : 0);
+      a.dst_row[i] = off + r;
+    }
   }
-  for (int r = tid; r <= a.R; r += blockDim.x) {
-    const int o = s_off[r * a.E_loc];  // r == R reads the end sentinel s_off[E]
-    a.rank_offset[r] = o;
-    if (r < a.R) a.rank_total[r] = s_off[(r + 1) * a.E_loc] - o;
+  for (unsigned i = i_mine; i < n; i += E * nw * 64) {
+    const int w = i == i_mine ? v_mine : a.idx[i];
+    if (w >= 0 && w < E) continue;
+    if (w != -1) dev_set_error(a.error, EP_EBOUNDS);
+    a.slot[i] = a.dst_row[i] = -1;
   }
 }
 
-// LDS bytes of the one-launch form, or 0 when the shape does not fit it.
-static size_t small_layout_lds(const LayoutArgs &a) {
-  const long long F = (long long)a.S * a.ntiles;
-  // measured on MI355X (E = 256, top-8): 4.3 us against 11.7 for one tile, 8.5 / 15.7 for 4, 11.3 / 15.4 for 8,
-  // 13.7 / 16.0 for 12; with all 16 waves busy the LDS atomics of the tiles slow each other down and
-  // nothing is gained (16.5 / 15.8)
-  if (a.T <= 0 || a.K > 8 || F <= 0 || F > 12) return 0;
-  const size_t bytes = (size_t)kSmallTiles * a.E * (8 + 2) + (size_t)(2 * a.E + 1) * 4;
-  return bytes <= 64 * 1024 ? bytes : 0;
+// The one-launch form takes every table up to 65536 entries (40960 with several sources or few experts, whose
+// busiest workgroup then has the more to number): beyond that, looking at every entry on every compute unit costs
+// more than the two kernels' fixed 14 us.  Kernel time in us, one launch / two kernels: 65536 entries of 128 experts
+// 13.1 / 16.5, of 16 experts 13.9 / 15.5 (queued back to back 14.1 / 13.0), of 256 over 32 sources 20.4 / 20.4 (20.5 /
+// 18.1), of 1024 experts 23 / 33; 131072 of 256: 24 / 23.
+bool layout_takes_one_launch(const LayoutArgs &a, const Tunables &tune) {
+  const long long n = (long long)a.S * a.T * a.K;
+  return tune.layout_small && n <= (a.S == 1 && a.E >= 64 ? 65536 : 40960);
 }
 
 // ------------------------------------------------- scratch that nobody allocates
@@ -389,8 +425,11 @@ int static_layout_scratch(LayoutArgs *a) {
 
 int launch_layout(const LayoutArgs &a, const Tunables &tune, void *stream, const LaunchTiming *timing) {
   hipStream_t st = (hipStream_t)stream;
-  if (const size_t lds = tune.layout_small ? small_layout_lds(a) : 0) {
-    launch_kernel(layout_small_kernel, dim3(1), dim3(1024), lds, st, timing ? timing->start : nullptr,
+  if (layout_takes_one_launch(a, tune)) {
+    const int groups = (int)(((long long)a.S * a.T * a.K + 255) / 256);
+    const int waves = groups < 1 ? 1 : (groups > 16 ? 16 : groups);
+    const size_t lds = (size_t)waves * ((groups + waves - 1) / waves) * 64 * sizeof(unsigned short);
+    launch_kernel(layout_expert_kernel, dim3(a.E), dim3(64 * waves), lds, st, timing ? timing->start : nullptr,
                   timing ? timing->stop : nullptr, a);
     return (int)hipGetLastError();
   }

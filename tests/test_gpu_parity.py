@@ -128,6 +128,27 @@ def test_layout_small_tables_both_forms(epmod, oracle, one_launch, monkeypatch):
         assert r.stats()["device_error"] == epmod.EP_EBOUNDS
 
 
+@pytest.mark.parametrize("S,T,K,E,R,maskp", [
+    (1, 51, 5, 16, 4, 0.0), (1, 64, 4, 16, 4, 0.0), (1, 257, 1, 64, 8, 0.1),           # 255 / 256 / 257 entries
+    (1, 585, 7, 24, 3, 0.0), (3, 683, 2, 40, 5, 0.2), (1, 513, 8, 256, 16, 0.0),       # 15 to 17 groups of 256
+    (7, 5, 3, 8, 2, 0.3), (256, 3, 2, 4, 4, 0.0), (65, 9, 6, 12, 1, 0.1),              # many sources in one group
+    (1, 8192, 8, 64, 8, 0.05), (1, 8193, 8, 64, 8, 0.0), (5, 1024, 8, 256, 32, 0.0),   # both sides of the line between
+    (5, 1025, 8, 256, 32, 0.0), (1, 5120, 8, 63, 7, 0.0), (1, 5121, 8, 63, 7, 0.0),    # the two forms
+    (1, 2000, 8, 1024, 256, 0.0), (1, 700, 64, 64, 2, 0.0)])
+def test_layout_one_workgroup_per_expert(epmod, oracle, S, T, K, E, R, maskp):
+    """The one-launch form at the edges of its groups (256 entries), of its waves' shares and of its range."""
+    rng = np.random.default_rng(S * 1000 + T)
+    idx = np.argsort(rng.random((S, T, E)), axis=-1)[..., :K].astype(np.int32)
+    idx[:, ::3, 0] = np.where((idx[:, ::3, 1:] == E - 1).any(-1), idx[:, ::3, 0], E - 1)  # a busy last expert
+    if maskp:
+        idx = g.mask_random(idx, maskp, seed=T)
+    with _runner(epmod, g.EPConfig("edges", T=T, H=128, E=E, K=K, R=R, S=S)) as r:
+        lay = r.layout(_dev(idx))
+        torch.cuda.synchronize()
+        _check_layout(oracle, lay.numpy(), idx, E, R)
+        assert r.stats()["device_error"] == 0
+
+
 # ---------------------------------------------------------- dispatch bf16
 def _dispatch_case(epmod, oracle, cfg, T, mask, cmd_mode, rank_filter=-1, src=0, extra_rows=3, proxy_writes=False,
                    extra_flags=0, **kw):
