@@ -141,9 +141,9 @@ def _check(fn: str, rc: int) -> None:
 
 
 def _ptr(t) -> Optional[int]:
-    """Device (or host) address of a torch tensor / numpy array / None."""
-    if t is None:
-        return None
+    """Device (or host) address of a torch tensor / numpy array / None; an int is an address already."""
+    if t is None or t.__class__ is int:
+        return t
     if hasattr(t, "data_ptr"):
         if not t.is_contiguous():
             raise ValueError("tensor must be contiguous")
@@ -151,10 +151,19 @@ def _ptr(t) -> Optional[int]:
     return t.ctypes.data
 
 
+_torch_c = None  # torch._C, once torch has initialised the device
+
+
 def _stream(stream) -> Optional[int]:
+    """The stream's handle; None is torch's current stream, whose raw handle costs 0.2 us a call (through a
+    torch.cuda.Stream object: 2.9 us, as much as a kernel launch)."""
+    global _torch_c
     if stream is None:
-        import torch
-        return torch.cuda.current_stream().cuda_stream
+        if _torch_c is None:
+            import torch
+            torch.cuda.current_stream()
+            _torch_c = torch._C
+        return _torch_c._cuda_getCurrentRawStream(_torch_c._cuda_getDevice())
     return getattr(stream, "cuda_stream", stream)
 
 

@@ -36,6 +36,13 @@ class LayoutOut:
         return {k: getattr(self, k).cpu().numpy() for k in self.__dataclass_fields__}
 
 
+def _row(t: torch.Tensor, src: int):
+    """t[src] as an address (making the tensor object costs 0.8 us)."""
+    if t.is_contiguous() and 0 <= src < t.shape[0]:
+        return t.data_ptr() + src * t.stride(0) * t.element_size()
+    return t[src]
+
+
 class EPRunner:
     """One handle plus the buffers of one workload shape."""
 
@@ -82,8 +89,8 @@ class EPRunner:
         L = self.lay
         slot, dst = L.slot, L.dst_row
         if T != self.T_cap:
-            slot = torch.zeros((S, T, K), dtype=torch.int32, device=self.dev)
-            dst = torch.zeros((S, T, K), dtype=torch.int32, device=self.dev)
+            slot = torch.empty((S, T, K), dtype=torch.int32, device=self.dev)  # (every entry is written)
+            dst = torch.empty((S, T, K), dtype=torch.int32, device=self.dev)
         ep.ep_layout(self.h, topk_idx, T, L.count, L.expert_total, L.rank_total, L.base, L.expert_offset,
                      L.rank_offset, slot, dst)
         return LayoutOut(L.count, L.expert_total, L.rank_total, L.base, L.expert_offset, L.rank_offset, slot, dst)
@@ -94,8 +101,8 @@ class EPRunner:
         """recv_rows: rows of the destination; defaults to recv's own row count (it differs when recv is the [T]
         message rows of a per-token FP8 dispatch that the proxy forwards)."""
         T = x.shape[0]
-        ep.ep_dispatch(self.h, x, topk_idx_s, lay.dst_row[src], lay.count[src], lay.base[src], T, src, rank_filter,
-                       payload, cmd_mode, recv, recv_scale, recv.shape[0] if recv_rows is None else recv_rows)
+        ep.ep_dispatch(self.h, x, topk_idx_s, _row(lay.dst_row, src), _row(lay.count, src), _row(lay.base, src), T, src,
+                       rank_filter, payload, cmd_mode, recv, recv_scale, recv.shape[0] if recv_rows is None else recv_rows)
 
     def fp8_unpack(self, msgs: torch.Tensor, recv: torch.Tensor, recv_scale: torch.Tensor) -> None:
         ep.ep_fp8_unpack(self.h, msgs, recv.shape[0], recv, recv_scale)
@@ -112,7 +119,7 @@ class EPRunner:
     def ht_dispatch(self, x: torch.Tensor, topk_idx_s: torch.Tensor, lay: LayoutOut, ring: torch.Tensor,
                     recv: torch.Tensor, src: int = 0, recv_scale: Optional[torch.Tensor] = None) -> None:
         payload = ep.EP_BF16 if recv_scale is None else ep.EP_FP8_E4M3
-        ep.ep_ht_dispatch(self.h, x, topk_idx_s, lay.dst_row[src], x.shape[0], src, ring, recv, recv.shape[0],
+        ep.ep_ht_dispatch(self.h, x, topk_idx_s, _row(lay.dst_row, src), x.shape[0], src, ring, recv, recv.shape[0],
                           payload=payload, recv_scale=recv_scale)
 
     def recv_wait(self, counts_out: Optional[torch.Tensor] = None, src: int = 0, rank_filter: int = -1) -> None:
