@@ -202,7 +202,15 @@ struct Tunables {
 struct LaunchTiming {
   void *start, *stop;
 };
-bool layout_takes_one_launch(const LayoutArgs &a, const Tunables &tune);  // ... which uses none of the scratch in a
+// The one-launch layout (layout_expert_kernel, no scratch) takes every table up to 65536 entries (40960 with several
+// sources or few experts, whose busiest workgroup then has the more to number): beyond that, looking at every entry
+// on every compute unit costs more than the two kernels' fixed 14 us.  Kernel time in us, one launch / two kernels:
+// 65536 entries of 128 experts 13.1 / 16.5, of 16 experts 13.9 / 15.5 (queued back to back 14.1 / 13.0), of 256 over 32
+// sources 20.4 / 20.4 (20.5 / 18.1), of 1024 experts 23 / 33; 131072 of 256: 24 / 23.
+inline bool layout_takes_one_launch(const LayoutArgs &a, const Tunables &tune) {
+  const long long n = (long long)a.S * a.T * a.K;
+  return tune.layout_small && n <= (a.S == 1 && a.E >= 64 ? 65536 : 40960);
+}
 int launch_layout(const LayoutArgs &a, const Tunables &tune, void *stream, const LaunchTiming *timing = nullptr);
 int launch_dispatch(const DispatchArgs &a, int payload, const Tunables &tune, void *stream,
                     const LaunchTiming *timing = nullptr);

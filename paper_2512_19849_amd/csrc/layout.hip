@@ -369,16 +369,6 @@ __global__ __launch_bounds__(1024) void layout_expert_kernel(LayoutArgs a) {
   }
 }
 
-// The one-launch form takes every table up to 65536 entries (40960 with several sources or few experts, whose
-// busiest workgroup then has the more to number): beyond that, looking at every entry on every compute unit costs
-// more than the two kernels' fixed 14 us.  Kernel time in us, one launch / two kernels: 65536 entries of 128 experts
-// 13.1 / 16.5, of 16 experts 13.9 / 15.5 (queued back to back 14.1 / 13.0), of 256 over 32 sources 20.4 / 20.4 (20.5 /
-// 18.1), of 1024 experts 23 / 33; 131072 of 256: 24 / 23.
-bool layout_takes_one_launch(const LayoutArgs &a, const Tunables &tune) {
-  const long long n = (long long)a.S * a.T * a.K;
-  return tune.layout_small && n <= (a.S == 1 && a.E >= 64 ? 65536 : 40960);
-}
-
 // ------------------------------------------------- scratch that nobody allocates
 // For callers that cannot allocate (ep_layout_static): the tile histograms, the tile prefixes, the ticket
 // and an error sink live in a file-scope device array.  Every GPU holds its own copy at its own address
