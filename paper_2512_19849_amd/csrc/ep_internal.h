@@ -128,10 +128,9 @@ struct CombinePartialArgs {
 };
 
 // A batch of peer writes the proxy performs on behalf of the GPU (registered heaps).  Descriptors
-// (offsets and lengths in 16-byte units) stay in pinned host memory; a workgroup fetches the 16 it
-// serves with ONE coalesced read (a descriptor read per workgroup cost a PCIe round trip each and
-// made the copy kernels 10x slower).
-constexpr int kCopyBatchMax = 4096, kCopyGroup = 16;
+// (offsets and lengths in 16-byte units) stay in pinned host memory; a workgroup fetches the kCopyGroup it
+// serves with ONE coalesced read.
+constexpr int kCopyBatchMax = 4096, kCopyGroup = 4;
 struct CopyDesc {
   unsigned src16, dst16, len16;
 };
@@ -143,8 +142,8 @@ struct CopyBatchArgs {
   int n;
   unsigned max_len16;
 };
-// Large copies (chunks) are few per batch and want a workgroup per (copy, piece): their descriptors
-// travel inside the kernel-argument block instead, up to this many per launch.
+// The descriptors of small batches and of chunks travel inside the kernel-argument block instead, up to this many
+// per launch.
 constexpr int kCopyArgMax = 256;
 struct CopyArgBatch {
   const char *src_base;

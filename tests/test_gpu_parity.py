@@ -328,6 +328,15 @@ def test_proxy_performs_chunk_writes(epmod, oracle, cid, T, mask, window, mode):
         assert out["stats"]["drains"] == 8
 
 
+# a row of 16 vectors, one of exactly / just over a 256-vector piece, the largest row that counts as a row (32 KiB) and
+# the smallest that counts as a chunk; many copies (batches beyond one argument block) and few
+@pytest.mark.parametrize("H,T", [(128, 3000), (2048, 1500), (2176, 1500), (16384, 40), (16384, 150), (16512, 120)])
+def test_proxy_copies_rows_at_the_edges_of_pieces(epmod, oracle, H, T):
+    cfg = g.EPConfig(f"edges{H}", T=T, H=H, E=32, K=6, R=4, routing="uniform")
+    out = _dispatch_case(epmod, oracle, cfg, T, 0.03, epmod.EP_CMD_PER_TOKEN, proxy_writes=True, num_proxy_threads=1)
+    _check_commands(epmod, oracle, cfg, out, "per_token")
+
+
 @pytest.mark.parametrize("cid,T,mask,window,mode,threads", [
     (3, None, 0.0, 0, "per_token", 4), (3, 50, 0.25, 5, "per_token", 1), (3, None, 0.2, 6, "chunk32", 2),
     (5, 700, 0.0, 16, "per_token", 3), (5, 1000, 0.05, 0, "chunk32", 4), (4, 300, 0.0, 8, "chunk32_ordered", 4),
