@@ -1282,6 +1282,24 @@ def test_ht_dedup_parity(epmod, oracle, cid, G, T, mask):
         assert r.stats()["device_error"] == 0
 
 
+# top-k that does not divide a workgroup's 256 threads, the largest, a single entry; tokens that leave a remainder
+@pytest.mark.parametrize("S,T,K,E,R,G", [(1, 1, 1, 8, 4, 2), (2, 129, 3, 12, 6, 3), (1, 52, 5, 16, 8, 1),
+                                         (3, 37, 7, 64, 16, 4), (1, 29, 33, 96, 12, 6), (2, 9, 64, 128, 8, 2)])
+def test_ht_dedup_top_k_edges(epmod, oracle, S, T, K, E, R, G):
+    rng = np.random.default_rng(K)
+    idx = np.stack([np.stack([rng.permutation(E)[:K] for _ in range(T)]) for _ in range(S)]).astype(np.int32)
+    idx = g.mask_random(idx, 0.15, seed=K)
+    wg, wf = oracle.dedup(idx, E // R, G)
+    cfg = g.EPConfig("dedup", T=T, H=128, E=E, K=K, R=R, S=S)
+    with _runner(epmod, cfg, num_proxy_threads=0) as r:
+        gi, fk = torch.full(idx.shape, -9, dtype=torch.int32, device="cuda"), torch.full(idx.shape, -9, dtype=torch.int32,
+                                                                                         device="cuda")
+        epmod.ep_dedup(r.h, _dev(idx), T, G, gi, fk)
+        torch.cuda.synchronize()
+        assert np.array_equal(gi.cpu().numpy(), wg) and np.array_equal(fk.cpu().numpy(), wf)
+        assert r.stats()["device_error"] == 0
+
+
 @pytest.mark.parametrize("cid,G,T,mask,mode", [(1, 1, None, 0.0, "per_token"), (1, 2, None, 0.25, "chunk32"),
                                                (4, 1, 600, 0.0, "chunk32"), (4, 8, 600, 0.1, "chunk32"),
                                                (5, 4, 500, 0.0, "per_token"), (4, 1, 4096, 0.0, "chunk32"),
