@@ -241,6 +241,9 @@ int launch_gather_index(const GatherIndexArgs &a, void *stream) {
 // First level of the hierarchical reduce: like the combine, but the K gathered
 // rows of a token are summed per group and every group's sum is written to the
 // group's own row.  Rows, weights and group leaders are wave-uniform.
+// The sums are stored past the caches: nothing outside this stream reads them before the kernel ends, and the final
+// reduce that follows finds more of them in the memory-side cache (4096 tokens x 7168 top-8 over 16 groups, partial /
+// final reduce in us: streaming stores 155 / 75, write-through 146 / 99, plain 150 / 100).
 template <int KT>
 __global__ __launch_bounds__(256) void combine_partial_kernel(CombinePartialArgs a) {
   const int wave = threadIdx.x >> 6, lane = lane_id();
@@ -299,7 +302,7 @@ __global__ __launch_bounds__(256) void combine_partial_kernel(CombinePartialArgs
     for (int j = 0; j < KT; ++j) {
       if (!((leaders >> j) & 1)) continue;
       const int pr = __builtin_amdgcn_readlane(prow, j);
-      store_payload((u32x4 *)a.partial + (size_t)pr * nvec + vi, res[j]);
+      __builtin_nontemporal_store(res[j], (u32x4 *)a.partial + (size_t)pr * nvec + vi);
     }
   } else {
     unsigned long long lm = leaders;
@@ -316,7 +319,7 @@ __global__ __launch_bounds__(256) void combine_partial_kernel(CombinePartialArgs
       const int pr = __builtin_amdgcn_readlane(prow, j);
       u32x4 o = {pack_bf16_rne(acc[0], acc[1]), pack_bf16_rne(acc[2], acc[3]),
                  pack_bf16_rne(acc[4], acc[5]), pack_bf16_rne(acc[6], acc[7])};
-      store_payload((u32x4 *)a.partial + (size_t)pr * nvec + vi, o);
+      __builtin_nontemporal_store(o, (u32x4 *)a.partial + (size_t)pr * nvec + vi);
     }
   }
 }
