@@ -39,15 +39,27 @@ EP_DEV void push_count_atomic(const DispatchArgs &a, int e, int value) {
             (unsigned)(a.src * a.E_loc) + le);
 }
 
-// Kernel prologue (workgroup 0, wavefront 0): the count Atomics that no row
-// completion will trigger - experts with count 0, or all of them when the
-// caller wants the atomics ahead of the writes.
+// The same by a whole wave, for the lanes with `push`.
+EP_DEV void push_count_atomics(const DispatchArgs &a, bool push, int e, int value, u32x4 *scratch) {
+  if (!push) e = 0;
+  const unsigned dr = (unsigned)(e / a.E_loc), le = (unsigned)(e - (int)dr * a.E_loc);
+  ring_push_sorted(a.ring, push, (unsigned)e % a.ring.channels, cmd_w0(EP_OP_ATOMIC, a.src, dr, le), (unsigned)value, 0u,
+                   (unsigned)(a.src * a.E_loc) + le, scratch);
+}
+
+// Workgroup 0, wavefront 0: the count Atomics that no row completion will trigger - experts with count 0, or all of
+// them when the caller wants the atomics ahead of the writes.
 EP_DEV void emit_leading_atomics(const DispatchArgs &a, int lane) {
+  extern __shared__ u32x4 s_dyn[];  // (per-token commands: the 2 KB of ring_push_sorted)
   const bool first = (a.cmd_mode & EP_CMD_ATOMICS_FIRST) != 0;
-  for (int e = lane; e < a.E; e += 64) {
-    if (a.filter >= 0 && e / a.E_loc != a.filter) continue;
-    const int c = a.count[e];
-    if (first || c == 0) push_count_atomic(a, e, c);
+  for (int e0 = 0; e0 < a.E; e0 += 64) {
+    const int e = e0 + lane;
+    const int c = e < a.E ? a.count[e] : -1;
+    const bool push = c >= 0 && (first || c == 0) && (a.filter < 0 || e / a.E_loc == a.filter);
+    if (a.blocks_per_group)
+      push_count_atomics(a, push, e, c, s_dyn);
+    else if (push)
+      push_count_atomic(a, e, c);
   }
 }
 
@@ -117,28 +129,51 @@ EP_DEV void emit_row_cmds(const DispatchArgs &a, const TokenMeta &m, int t) {
   if (finished_rows) account_rows(a, e, c, finished_rows);
 }
 
-// One command per row, several tokens per workgroup: the tokens' (expert, row) pairs meet in LDS
-// and the first wave pushes for all of them, sorted by channel, so that the commands of a channel
-// leave as one run of consecutive slots written by neighbouring lanes (see ring_push_sorted).
-EP_DEV void emit_block_cmds(const DispatchArgs &a, const TokenMeta &m, int part, int wave, int lane) {
-  extern __shared__ u32x4 s_dyn[];
-  int2 *s_pairs = (int2 *)s_dyn;  // [tokens_per_block][K], then the 2 KB of ring_push_sorted
-  if (part == 0 && lane < a.K) s_pairs[(wave / a.parts) * a.K + lane] = make_int2(m.valid ? m.e : -1, m.row);
+// One command per row: a group of workgroups holds about 64 (token, k) pairs, and the first wave of the group's last
+// workgroup to store its rows pushes for all of them, sorted by channel, so that the commands of a channel leave as one
+// run of consecutive slots written by neighbouring lanes (see ring_push_sorted).  The counters (chunk_cnt, which only the
+// chunk modes use otherwise) return to zero by themselves.
+// What a small dispatch waits for is the proxy, which misses its caches once for every write that reaches a polled line.
+// Whole steps, groups / every workgroup on its own (us, rows of 7168, top-8 of 256 experts): 128 tokens 30 / 36, 256: 34 /
+// 51, 512: 48 / 73; 512 tokens x 4096: 41 / 49.
+EP_DEV void emit_group_cmds(const DispatchArgs &a, int wave, int lane) {
+  extern __shared__ u32x4 s_dyn[];  // the 2 KB of ring_push_sorted
   __syncthreads();  // every wave has waited for its own stores before it came here
   if (wave != 0) return;
-  const int n = a.tokens_per_block * a.K;
-  u32x4 *scratch = (u32x4 *)(s_pairs + ((n + 1) & ~1));
+  const int gb = a.blocks_per_group, group = token_block(a) / gb;
+  if (gb > 1) {
+    int last = 0;
+    if (lane == 0) {
+      int *cnt = a.chunk_cnt + group;
+      last = __hip_atomic_fetch_add(cnt, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 ==
+             min(gb, (int)gridDim.x - group * gb);
+      if (last) __hip_atomic_store(cnt, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    if (!__builtin_amdgcn_readfirstlane(last)) return;
+  }
+  const int tokens = gb * a.tokens_per_block, t0 = group * tokens, n = min(tokens, a.T - t0) * a.K;
   for (int i0 = 0; i0 < n; i0 += 64) {
     const int i = i0 + lane;
-    const int2 p = i < n ? s_pairs[i] : make_int2(-1, -1);
-    const bool active = p.x >= 0;
-    const int e = active ? p.x : 0;
+    int e = -1, row = -1;
+    if (i < n) {
+      e = a.idx[(size_t)t0 * a.K + i];
+      row = a.dst_row[(size_t)t0 * a.K + i];
+    }
+    // (an entry out of range has been reported by its own wave)
+    const bool active = e >= 0 && e < a.E && row >= 0 && row < a.recv_rows && (a.filter < 0 || e / a.E_loc == a.filter);
+    if (!active) e = 0;
+    const int c = a.count[e];
     const unsigned dr = (unsigned)(e / a.E_loc), le = (unsigned)(e - (int)dr * a.E_loc);
-    const unsigned long long so = (unsigned long long)(token_block(a) * a.tokens_per_block + i / a.K) * a.row_bytes;
-    const unsigned long long dof = (unsigned long long)p.y * a.row_bytes;
+    const unsigned long long so = (unsigned long long)(t0 + i / a.K) * a.row_bytes;
+    const unsigned long long dof = (unsigned long long)row * a.row_bytes;
     ring_push_sorted(a.ring, active, (unsigned)e % a.ring.channels, cmd_w0(EP_OP_WRITE, a.src, dr, le),
-                     a.row_bytes >> 4, (unsigned)(so >> 4), (unsigned)(dof >> 4), scratch);
-    if (active) account_rows(a, e, a.count[e], 1);
+                     a.row_bytes >> 4, (unsigned)(so >> 4), (unsigned)(dof >> 4), s_dyn);
+    bool complete = false;  // (as account_rows)
+    if (active) {
+      complete = __hip_atomic_fetch_add(a.expert_done + e, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 == c;
+      if (complete) __hip_atomic_store(a.expert_done + e, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    push_count_atomics(a, complete && !(a.cmd_mode & EP_CMD_ATOMICS_FIRST), e, c, s_dyn);
   }
 }
 
@@ -209,8 +244,8 @@ __global__ void dispatch_bf16_kernel(DispatchArgs a) {
   }
   if (!ring_on) return;
   wait_for_own_stores();  // the rows are in memory before a counter or command mentions them
-  if (a.block_cmds) {
-    emit_block_cmds(a, m, part, wave, lane);
+  if (a.blocks_per_group) {
+    emit_group_cmds(a, wave, lane);
   } else {
     if (a.parts > 1) __syncthreads();
     if (part == 0 && m.valid) emit_row_cmds(a, m, t);
@@ -330,8 +365,8 @@ __global__ void dispatch_fp8_kernel(DispatchArgs a) {
   }
   if (!ring_on) return;
   wait_for_own_stores();
-  if (a.block_cmds) {
-    emit_block_cmds(a, m, part, wave, lane);
+  if (a.blocks_per_group) {
+    emit_group_cmds(a, wave, lane);
   } else {
     if (a.parts > 1) __syncthreads();
     if (part == 0 && m.valid) emit_row_cmds(a, m, t);
@@ -477,17 +512,22 @@ static int tuned_dispatch_fp8_vpl(int H, int T, int forced) {
   return split_for(H / 16, T, c, 3);
 }
 
-// One command per row: as many tokens per workgroup as 16 waves hold (their commands are pushed
-// together, see emit_block_cmds).  Returns the dynamic LDS bytes of the launch.
-static size_t block_cmds_setup(DispatchArgs &a, int waves) {
-  a.block_cmds = 0;
+// One command per row: as many tokens per workgroup as 16 waves hold, and as many workgroups per group as share 64
+// pairs (at least 16 groups, so that a handful of tokens does not wait for its slowest).  Above 12288 commands the kernel
+// is bound by its row stores and a group only keeps its last workgroup busy for longer: a workgroup pushes its own
+// (steps with groups / without, us: 2048 tokens x 7168 top-8 120 / 117, 4096 tokens 220 / 207; 1500 tokens 91 / 92, 1024
+// tokens 65 / 73).  Returns the dynamic LDS bytes of the launch.
+static size_t group_cmds_setup(DispatchArgs &a, int waves) {
+  a.blocks_per_group = 0;
   if ((a.cmd_mode & EP_CMD_MODE_MASK) != EP_CMD_PER_TOKEN) return 0;
   if (waves < 4 || waves > 16) waves = 16;  // (0 = not set)
   const int tpb = waves / a.parts;
-  if (tpb < 2) return 0;
-  a.tokens_per_block = tpb;
-  a.block_cmds = 1;
-  return (size_t)((tpb * a.K + 1) & ~1) * sizeof(int2) + 2048;
+  if (tpb >= 2) a.tokens_per_block = tpb;
+  a.blocks_per_group =
+      (long long)a.T * a.K > 12288 ? 1 : max(1, min(64 / a.K, a.T / 16) / a.tokens_per_block);
+  const long long tokens = (long long)a.blocks_per_group * a.tokens_per_block;
+  if ((a.T + tokens - 1) / tokens > (long long)a.E * a.chunks_per_expert) a.blocks_per_group = 1;  // (counters)
+  return 2048;
 }
 
 // Ring-on launches take the form with a command wave when it is switched on and the row needs at most 15 data
@@ -515,7 +555,7 @@ static void launch_dispatch_bf16_t(DispatchArgs a, const Tunables &tune, hipStre
   a.parts = (nvec + VPL * 64 - 1) / (VPL * 64);
   if (launch_pipelined<VPL, false>(a, tune, st, tm)) return;
   a.tokens_per_block = a.parts >= 4 ? 1 : 4 / a.parts;
-  const size_t lds = block_cmds_setup(a, tune.per_token_waves);
+  const size_t lds = group_cmds_setup(a, tune.per_token_waves);
   const int grid = max(1, (a.T + a.tokens_per_block - 1) / a.tokens_per_block);
   launch_kernel(dispatch_bf16_kernel<VPL>, dim3(grid), dim3(64 * a.parts * a.tokens_per_block), lds, st,
                 tm ? tm->start : nullptr, tm ? tm->stop : nullptr, a);
@@ -527,7 +567,7 @@ static void launch_dispatch_fp8_t(DispatchArgs a, const Tunables &tune, hipStrea
   a.parts = (npair + VPL * 64 - 1) / (VPL * 64);
   if (launch_pipelined<VPL, true>(a, tune, st, tm)) return;
   a.tokens_per_block = a.parts >= 4 ? 1 : 4 / a.parts;
-  const size_t lds = block_cmds_setup(a, tune.per_token_waves);
+  const size_t lds = group_cmds_setup(a, tune.per_token_waves);
   const int grid = max(1, (a.T + a.tokens_per_block - 1) / a.tokens_per_block);
   launch_kernel(dispatch_fp8_kernel<VPL>, dim3(grid), dim3(64 * a.parts * a.tokens_per_block), lds, st,
                 tm ? tm->start : nullptr, tm ? tm->stop : nullptr, a);

@@ -64,10 +64,13 @@ EP_DEV unsigned long long ring_push_grouped(const RingDev &r, unsigned c, unsign
 // lanes store neighbouring slots, and the memory pipeline turns the slots of one 64-byte line into one
 // write.  A line of host memory that the proxy is polling costs the PCIe root a round of coherence
 // traffic per write that lands in it, whatever the size of the write.
+// (The check for room reads the cached head after the reservation: read together with it, it is older, calls the channel
+// full more often, and a prefill dispatch of 65536 commands took 178 us instead of 162.)
 EP_DEV void ring_push_sorted(const RingDev &r, bool active, unsigned c, unsigned w0, unsigned w1, unsigned w2,
                              unsigned w3, u32x4 *scratch) {
   const int me = lane_id();
   const unsigned long long act = __ballot(active);
+  if (act == 0ull) return;
   unsigned long long same = 0ull;
   int less = 0;
   for (unsigned long long m = act; m;) {  // once per distinct channel

@@ -69,14 +69,14 @@ struct DispatchArgs {
   uint32_t row_bytes;      // bytes of one token in a message
   int32_t parts;           // wavefronts per token
   int32_t tokens_per_block;
-  int32_t block_cmds;      // the workgroup's first wave pushes the commands of all its tokens
+  int32_t blocks_per_group;  // per-token commands: workgroups whose commands are pushed together (0: other modes)
   int32_t reverse;         // workgroups take the tokens from the last one down (see ep_dispatch)
   int32_t cache_hinted;    // the caller promised (EP_FLAG_CACHE_HINTS) that the rows are consumed out of the caches
   int32_t msg_rows;        // FP8 only: 0 = codes and scales go to the two receive arrays; 1 = every row is one message
                            // (codes, scales, padding: row_bytes) at its destination row of `recv`; 2 = one message
                            // per token at row t of `recv` (the proxy forwards it to every destination)
   int32_t chunks_per_expert;
-  int32_t *chunk_cnt;      // scratch [E * chunks_per_expert], zero between calls
+  int32_t *chunk_cnt;      // scratch [E * chunks_per_expert], zero between calls (per-token commands: one per group)
   int32_t *expert_done;    // scratch [E], zero between calls
   unsigned *waves_done;    // scratch of the Drain epilogue [1 + workgroups / 64], zero between calls
   unsigned *ht_seq;        // scratch [S*R]: next sequence number of each communication channel

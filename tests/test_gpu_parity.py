@@ -278,6 +278,40 @@ def _check_commands(epmod, oracle, cfg, out, mode_name, payload="bf16", src=0, r
     return res
 
 
+# groups of workgroups that push together: a group of one, groups with a remainder in tokens and in workgroups, a top-k
+# that does not divide 64, more than 64 / 2 pairs per token, the last size with groups and the first without
+@pytest.mark.parametrize("T,K,E,R,H", [(1, 4, 16, 4, 7168), (33, 1, 8, 8, 7168), (57, 3, 24, 6, 4096), (129, 5, 48, 16, 7168),
+                                       (300, 7, 64, 8, 1024), (70, 33, 96, 12, 5120), (2048, 6, 16, 4, 640),
+                                       (2049, 6, 16, 4, 640)])
+def test_per_token_commands_of_workgroup_groups(epmod, oracle, T, K, E, R, H):
+    """Dispatches of one handle in per-token and chunk modes by turns (the counters they share go back to zero), taken
+    from either end of the token range."""
+    from paper_2512_19849_amd.runner import bits_to_bf16, bf16_to_bits
+    cfg = g.EPConfig("groups", T=T, H=H, E=E, K=K, R=R, routing="uniform", seed=K)
+    idx = g.mask_random(g.routing_all(cfg)[0], 0.05, seed=K)
+    x = g.activations(cfg)
+    rows = int((idx >= 0).sum()) + 1
+    lay = oracle.layout(idx, E, R)
+    want, _ = oracle.dispatch_bf16(x, idx[0], lay["dst_row"][0], cfg.E_loc, rows, -1, fill=0xBFC0)
+    flags = epmod.EP_FLAG_LOG_CMDS | epmod.EP_FLAG_LOG_EVENTS | epmod.EP_FLAG_CACHE_HINTS
+    with _runner(epmod, cfg, flags=flags, heap_rows=rows) as r:
+        d_idx, d_x = _dev(idx), bits_to_bf16(x)
+        lay_d = r.layout(d_idx)
+        recv = torch.empty((rows, H), dtype=torch.bfloat16, device="cuda")
+        cmds = type(oracle.cmd_multiset([]))()
+        for mode in ("per_token", "chunk32", "per_token", "per_token"):
+            recv.fill_(-1.5)
+            r.dispatch(d_x, d_idx[0], lay_d, recv, cmd_mode=epmod.CMD_MODES[mode])
+            r.wait()
+            torch.cuda.synchronize()
+            assert np.array_equal(bf16_to_bits(recv), want), mode
+            assert np.array_equal(r.counters()[0], lay["count"][0]), mode
+            cmds += oracle.expected_cmds(idx[0], lay, 0, cfg.E_loc, H, "bf16", mode)
+        assert oracle.cmd_multiset(epmod.ep_cmd_log(r.h)) == cmds
+        st = r.stats()
+        assert st["device_error"] == 0 and st["proxy_error"] == 0 and st["rejected"] == 0
+
+
 @pytest.mark.parametrize("cid,T,mask,window", [(1, None, 0.0, 0), (1, None, 0.2, 4), (2, 128, 0.0, 64),
                                                (4, 200, 0.0, 0), (5, 300, 0.1, 7)])
 def test_dispatch_per_token_commands(epmod, oracle, cid, T, mask, window):
