@@ -139,6 +139,9 @@ static int tuned_combine_vpl(int forced, const CombineArgs &a) {
   return 1;
 }
 
+// (An instance per top-k up to 8 keeps all K loads of a slice in flight.  Against the loop for any K: 4096 tokens x 7168
+// top-7 75 us, was 97, for a wave per token cannot hide one load at a time; with a slice per wave top-3 and top-5 gain up
+// to 5%.)
 template <int VPL>
 static void launch_combine_t(CombineArgs a, hipStream_t st, const LaunchTiming *tm) {
   const int nvec = a.H / 8;
@@ -149,8 +152,11 @@ static void launch_combine_t(CombineArgs a, hipStream_t st, const LaunchTiming *
   switch (a.K) {
     case 1: launch_kernel(combine_kernel<VPL, 1>, dim3(grid), dim3(256), 0, st, ev0, ev1, a); break;
     case 2: launch_kernel(combine_kernel<VPL, 2>, dim3(grid), dim3(256), 0, st, ev0, ev1, a); break;
+    case 3: launch_kernel(combine_kernel<VPL, 3>, dim3(grid), dim3(256), 0, st, ev0, ev1, a); break;
     case 4: launch_kernel(combine_kernel<VPL, 4>, dim3(grid), dim3(256), 0, st, ev0, ev1, a); break;
+    case 5: launch_kernel(combine_kernel<VPL, 5>, dim3(grid), dim3(256), 0, st, ev0, ev1, a); break;
     case 6: launch_kernel(combine_kernel<VPL, 6>, dim3(grid), dim3(256), 0, st, ev0, ev1, a); break;
+    case 7: launch_kernel(combine_kernel<VPL, 7>, dim3(grid), dim3(256), 0, st, ev0, ev1, a); break;
     case 8: launch_kernel(combine_kernel<VPL, 8>, dim3(grid), dim3(256), 0, st, ev0, ev1, a); break;
     default: launch_kernel(combine_kernel<VPL, 0>, dim3(grid), dim3(256), 0, st, ev0, ev1, a); break;
   }
@@ -238,6 +244,29 @@ int launch_gather_index(const GatherIndexArgs &a, void *stream) {
   return (int)hipGetLastError();
 }
 
+// The chain over the rows that the lanes in `ks` hold, ascending, for a top-k without an instance of its own: four loads
+// in flight (4096 tokens x 4096 top-9 90 us, one load at a time 92; 2048 x 4096 top-16 72 and 76.  The plain combine,
+// with a wave per slice and nothing else to do, is 3% faster without).
+EP_DEV void fma_rows(float (&acc)[8], unsigned long long ks, int row, float wt, const u32x4 *y, int nvec, int v) {
+  while (ks) {
+    u32x4 ld[4];
+    float w[4];
+    int n = 0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      if (!ks) break;
+      const int k = __builtin_ctzll(ks);
+      ks &= ks - 1;
+      ld[j] = __builtin_nontemporal_load(y + (size_t)__builtin_amdgcn_readlane(row, k) * nvec + v);
+      w[j] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(wt), k));
+      n = j + 1;
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (j < n) fma8(acc, w[j], ld[j]);
+  }
+}
+
 // First level of the hierarchical reduce: like the combine, but the K gathered
 // rows of a token are summed per group and every group's sum is written to the
 // group's own row.  Rows, weights and group leaders are wave-uniform.
@@ -272,9 +301,9 @@ __global__ __launch_bounds__(256) void combine_partial_kernel(CombinePartialArgs
   if (vmask == 0) return;
   const int nvec = a.H >> 3;
   const int vi = part * 64 + lane;
-  if (vi >= nvec) return;
   const u32x4 *y = (const u32x4 *)a.y;
   if constexpr (KT > 0) {
+    if (vi >= nvec) return;
     int rows[KT], fks[KT];
     float ws[KT];
     u32x4 ld[KT];
@@ -310,16 +339,12 @@ __global__ __launch_bounds__(256) void combine_partial_kernel(CombinePartialArgs
       const int j = __builtin_ctzll(lm);
       lm &= lm - 1;
       float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-      for (int k = 0; k < K; ++k) {
-        const int r = __builtin_amdgcn_readlane(row, k);
-        const int f = __builtin_amdgcn_readlane(fk, k);
-        const float w = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(wt), k));
-        if (r >= 0 && f == j) fma8(acc, w, __builtin_nontemporal_load(y + (size_t)r * nvec + vi));
-      }
+      // (lanes past the row's end stay to the end: every lane's entry counts in the ballot)
+      fma_rows(acc, __ballot(row >= 0 && fk == j), row, wt, y, nvec, min(vi, nvec - 1));
       const int pr = __builtin_amdgcn_readlane(prow, j);
       u32x4 o = {pack_bf16_rne(acc[0], acc[1]), pack_bf16_rne(acc[2], acc[3]),
                  pack_bf16_rne(acc[4], acc[5]), pack_bf16_rne(acc[6], acc[7])};
-      __builtin_nontemporal_store(o, (u32x4 *)a.partial + (size_t)pr * nvec + vi);
+      if (vi < nvec) __builtin_nontemporal_store(o, (u32x4 *)a.partial + (size_t)pr * nvec + vi);
     }
   }
 }
@@ -335,8 +360,11 @@ int launch_combine_partial(const CombinePartialArgs &a0, void *stream) {
   switch (a.K) {
     case 1: hipLaunchKernelGGL(combine_partial_kernel<1>, dim3(grid), dim3(256), 0, st, a); break;
     case 2: hipLaunchKernelGGL(combine_partial_kernel<2>, dim3(grid), dim3(256), 0, st, a); break;
+    case 3: hipLaunchKernelGGL(combine_partial_kernel<3>, dim3(grid), dim3(256), 0, st, a); break;
     case 4: hipLaunchKernelGGL(combine_partial_kernel<4>, dim3(grid), dim3(256), 0, st, a); break;
+    case 5: hipLaunchKernelGGL(combine_partial_kernel<5>, dim3(grid), dim3(256), 0, st, a); break;
     case 6: hipLaunchKernelGGL(combine_partial_kernel<6>, dim3(grid), dim3(256), 0, st, a); break;
+    case 7: hipLaunchKernelGGL(combine_partial_kernel<7>, dim3(grid), dim3(256), 0, st, a); break;
     case 8: hipLaunchKernelGGL(combine_partial_kernel<8>, dim3(grid), dim3(256), 0, st, a); break;
     default: hipLaunchKernelGGL(combine_partial_kernel<0>, dim3(grid), dim3(256), 0, st, a); break;
   }

@@ -1316,6 +1316,31 @@ def test_ht_dedup_parity(epmod, oracle, cid, G, T, mask):
         assert r.stats()["device_error"] == 0
 
 
+# a top-k with an instance of its own (7), and without: a remainder of one and of three rows per batch of four
+@pytest.mark.parametrize("K,E,R,G,H", [(3, 12, 4, 2, 640), (5, 16, 8, 4, 1024), (7, 24, 6, 1, 512), (9, 32, 4, 4, 640),
+                                       (13, 48, 2, 2, 1536), (33, 48, 3, 1, 256)])
+def test_partial_reduce_top_k_edges(epmod, oracle, K, E, R, G, H):
+    from paper_2512_19849_amd.runner import bits_to_bf16, bf16_to_bits
+    cfg = g.EPConfig("partial", T=61, H=H, E=E, K=K, R=R, seed=K)
+    idx, w = g.routing_all(cfg)
+    idx = g.mask_random(idx, 0.15, seed=K)
+    idx[0, 7, :] = -1
+    wg, wf = oracle.dedup(idx, cfg.E_loc, G)
+    lay, lay_g = oracle.layout(idx, E, R), oracle.layout(wg, R // G, R // G)
+    rows, rows_g = int((idx >= 0).sum()), int((wg >= 0).sum())
+    y = g.activations(cfg, 0, tid=g.TID_Y, T=rows)
+    want = oracle.combine_partial(y, w[0], lay["dst_row"][0], wf[0], lay_g["dst_row"][0], rows_g)
+    with _runner(epmod, cfg, num_proxy_threads=0) as r:
+        partial = torch.zeros((rows_g, H), dtype=torch.bfloat16, device="cuda")
+        epmod.ep_combine_partial(r.h, bits_to_bf16(y), _dev(w[0]), _dev(lay["dst_row"][0]), _dev(wf[0]),
+                                 _dev(lay_g["dst_row"][0]), cfg.T, rows, rows_g, partial)
+        out = torch.full((cfg.T, H), 7.0, dtype=torch.bfloat16, device="cuda")
+        r.combine(bits_to_bf16(y), _dev(w[0]), _dev(lay["dst_row"][0]), out)
+        torch.cuda.synchronize()
+        assert np.array_equal(bf16_to_bits(partial), want)
+        assert _combine_check(oracle, bf16_to_bits(out), y, w[0], lay["dst_row"][0], K) == 0
+
+
 # top-k that does not divide a workgroup's 256 threads, the largest, a single entry; tokens that leave a remainder
 @pytest.mark.parametrize("S,T,K,E,R,G", [(1, 1, 1, 8, 4, 2), (2, 129, 3, 12, 6, 3), (1, 52, 5, 16, 8, 1),
                                          (3, 37, 7, 64, 16, 4), (1, 29, 33, 96, 12, 6), (2, 9, 64, 128, 8, 2)])
