@@ -63,12 +63,10 @@ EP_DEV void emit_leading_atomics(const DispatchArgs &a, int lane) {
   }
 }
 
-// Called by the lanes holding a dispatched (t,k) after the token's rows are
-// stored and acknowledged (write-through, so they are in memory).  LL granularity: one Write per row.
-// Chunk granularity: the lane that completes a run of <= 32 consecutive rows of
-// an expert pushes the Write for the run.  Whoever completes the expert pushes
-// its count Atomic (Section 3.3: the receiver holds it until that many rows
-// arrived).  The scratch counters return to zero by themselves.
+// The chunk modes' commands (one Write per row: emit_group_cmds).  Called by the lanes holding a dispatched (t,k) after the
+// token's rows are stored and acknowledged (write-through, so they are in memory).  The lane that completes a run of
+// <= 32 consecutive rows of an expert pushes the Write for the run.  Whoever completes the expert pushes its count Atomic
+// (Section 3.3: the receiver holds it until that many rows arrived).  The scratch counters return to zero by themselves.
 // `rows` more rows of expert e (c in all) have been handed to the channel; whoever hands over the
 // last one pushes the expert's count Atomic.
 EP_DEV void account_rows(const DispatchArgs &a, int e, int c, int rows) {
@@ -79,7 +77,7 @@ EP_DEV void account_rows(const DispatchArgs &a, int e, int c, int rows) {
   }
 }
 
-EP_DEV void emit_row_cmds(const DispatchArgs &a, const TokenMeta &m, int t) {
+EP_DEV void emit_chunk_cmds(const DispatchArgs &a, const TokenMeta &m) {
   const int e = m.e;
   const unsigned dr = (unsigned)(e / a.E_loc), le = (unsigned)(e - (int)dr * a.E_loc);
   // Everything for one destination expert goes through one FIFO (and therefore one proxy thread):
@@ -87,46 +85,36 @@ EP_DEV void emit_row_cmds(const DispatchArgs &a, const TokenMeta &m, int t) {
   const unsigned ch = (unsigned)e % a.ring.channels;
   const int c = a.count[e];
   const int mode = a.cmd_mode & EP_CMD_MODE_MASK;
-  int finished_rows = 0;
-  if (mode == EP_CMD_PER_TOKEN) {
-    const unsigned long long so = (unsigned long long)t * a.row_bytes;
-    const unsigned long long dof = (unsigned long long)m.row * a.row_bytes;
-    ring_push_grouped(a.ring, ch, cmd_w0(EP_OP_WRITE, a.src, dr, le), a.row_bytes >> 4, (unsigned)(so >> 4),
-                      (unsigned)(dof >> 4));
-    finished_rows = 1;
-  } else {
-    const int slot = m.row - a.base[e];
-    const int j = slot >> 5;
-    if (slot < 0 || j >= a.chunks_per_expert || slot >= c) {
-      dev_set_error(a.ring.error, EP_EBOUNDS);
+  const int slot = m.row - a.base[e];
+  const int j = slot >> 5;
+  if (slot < 0 || j >= a.chunks_per_expert || slot >= c) {
+    dev_set_error(a.ring.error, EP_EBOUNDS);
+    return;
+  }
+  const int csize = min(kChunkRows, c - (j << 5));
+  int *cnt = a.chunk_cnt + (size_t)e * a.chunks_per_expert + j;
+  const int old = __hip_atomic_fetch_add(cnt, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (old + 1 == csize) {
+    __hip_atomic_store(cnt, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const unsigned long long off = (unsigned long long)(a.base[e] + (j << 5)) * a.row_bytes;
+    const unsigned len = (unsigned)csize * a.row_bytes;
+    if (mode == EP_CMD_CHUNK32_ORDERED) {
+      // High-throughput style: the chunk's Write and the Atomic that advances the receiver's tail
+      // take two consecutive sequence numbers of the communication channel (source, destination
+      // rank) and travel through that channel's FIFO; the receiver re-establishes the order.
+      const unsigned seq = __hip_atomic_fetch_add(a.ht_seq + (size_t)a.src * a.R + dr, 2u, __ATOMIC_RELAXED,
+                                                  __HIP_MEMORY_SCOPE_AGENT);
+      const unsigned och = dr % a.ring.channels;
+      ring_push(a.ring, och, cmd_w0(EP_OP_ORDERED_WRITE, a.src, dr, le),
+                ((unsigned)(csize - 1) << 26) | (len >> 4), seq, (unsigned)(off >> 4));
+      ring_push(a.ring, och, cmd_w0(EP_OP_ORDERED_ATOMIC, a.src, dr, 0), (unsigned)csize, seq + 1u,
+                (unsigned)(a.src * a.R) + dr);
       return;
     }
-    const int csize = min(kChunkRows, c - (j << 5));
-    int *cnt = a.chunk_cnt + (size_t)e * a.chunks_per_expert + j;
-    const int old = __hip_atomic_fetch_add(cnt, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (old + 1 == csize) {
-      __hip_atomic_store(cnt, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      const unsigned long long off = (unsigned long long)(a.base[e] + (j << 5)) * a.row_bytes;
-      const unsigned len = (unsigned)csize * a.row_bytes;
-      if (mode == EP_CMD_CHUNK32_ORDERED) {
-        // High-throughput style: the chunk's Write and the Atomic that advances the receiver's tail
-        // take two consecutive sequence numbers of the communication channel (source, destination
-        // rank) and travel through that channel's FIFO; the receiver re-establishes the order.
-        const unsigned seq = __hip_atomic_fetch_add(a.ht_seq + (size_t)a.src * a.R + dr, 2u, __ATOMIC_RELAXED,
-                                                    __HIP_MEMORY_SCOPE_AGENT);
-        const unsigned och = dr % a.ring.channels;
-        ring_push(a.ring, och, cmd_w0(EP_OP_ORDERED_WRITE, a.src, dr, le),
-                  ((unsigned)(csize - 1) << 26) | (len >> 4), seq, (unsigned)(off >> 4));
-        ring_push(a.ring, och, cmd_w0(EP_OP_ORDERED_ATOMIC, a.src, dr, 0), (unsigned)csize, seq + 1u,
-                  (unsigned)(a.src * a.R) + dr);
-        return;
-      }
-      ring_push(a.ring, ch, cmd_w0(EP_OP_WRITE, a.src, dr, le), ((unsigned)(csize - 1) << 26) | (len >> 4),
-                (unsigned)(off >> 4), (unsigned)(off >> 4));
-      finished_rows = csize;
-    }
+    ring_push(a.ring, ch, cmd_w0(EP_OP_WRITE, a.src, dr, le), ((unsigned)(csize - 1) << 26) | (len >> 4),
+              (unsigned)(off >> 4), (unsigned)(off >> 4));
+    account_rows(a, e, c, csize);
   }
-  if (finished_rows) account_rows(a, e, c, finished_rows);
 }
 
 // One command per row: a group of workgroups holds about 64 (token, k) pairs, and the first wave of the group's last
@@ -253,7 +241,7 @@ __global__ void dispatch_bf16_kernel(DispatchArgs a) {
     emit_group_cmds(a, wave, lane);
   } else {
     if (a.parts > 1) __syncthreads();
-    if (part == 0 && m.valid) emit_row_cmds(a, m, t);
+    if (part == 0 && m.valid) emit_chunk_cmds(a, m);
   }
   if (a.cmd_mode & EP_CMD_DRAIN) emit_drain(a, lane);
 }
@@ -375,7 +363,7 @@ __global__ void dispatch_fp8_kernel(DispatchArgs a) {
     emit_group_cmds(a, wave, lane);
   } else {
     if (a.parts > 1) __syncthreads();
-    if (part == 0 && m.valid) emit_row_cmds(a, m, t);
+    if (part == 0 && m.valid) emit_chunk_cmds(a, m);
   }
   if (a.cmd_mode & EP_CMD_DRAIN) emit_drain(a, lane);
 }
@@ -462,7 +450,7 @@ __global__ __launch_bounds__(1024) void dispatch_pipelined_kernel(DispatchArgs a
           if (active) account_rows(a, e, a.count[e], 1);
         } else if (active) {
           const TokenMeta m{p.x, p.y, true};
-          emit_row_cmds(a, m, t);
+          emit_chunk_cmds(a, m);
         }
       }
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");  // the pairs have been read: the slot may be refilled

@@ -37,30 +37,10 @@ EP_DEV unsigned long long ring_push(const RingDev &r, unsigned c, unsigned w0, u
   return ring_publish(r, c, idx, w0, w1, w2, w3);
 }
 
-// Push for the case where many lanes of a wave push at once (one command per row): lanes that aim at
-// the same channel share ONE atomic on its tail - the first of them reserves a run of Idx for all,
-// the others take their place in the run.  Atomics on one address serialise in the L2, and a
-// per-token dispatch sends tens of thousands of commands through a handful of tails.
-EP_DEV unsigned long long ring_push_grouped(const RingDev &r, unsigned c, unsigned w0, unsigned w1, unsigned w2,
-                                            unsigned w3) {
-  const int me = lane_id();
-  unsigned long long same = 0ull;
-  for (unsigned long long m = __ballot(true); m; m &= m - 1) {
-    const int j = __builtin_ctzll(m);
-    if ((unsigned)__builtin_amdgcn_readlane((int)c, j) == c) same |= 1ull << j;
-  }
-  const int leader = __builtin_ctzll(same);
-  unsigned long long base = 0ull;
-  if (me == leader)
-    base = __hip_atomic_fetch_add(&r.tail[c], (unsigned long long)__popcll(same), __ATOMIC_RELAXED,
-                                  __HIP_MEMORY_SCOPE_AGENT);
-  base = ((unsigned long long)(unsigned)__shfl((int)(base >> 32), leader) << 32) | (unsigned)__shfl((int)base, leader);
-  return ring_publish(r, c, base + (unsigned long long)__popcll(same & ((1ull << me) - 1ull)), w0, w1, w2, w3);
-}
-
 // Push for a whole wave whose lanes hold one command each (or none: `active`), called by all 64
-// lanes together.  Runs of Idx are reserved per channel as in ring_push_grouped; then the commands
-// change lanes through LDS (`scratch`, 2 KB) so that lane order is (channel, Idx) order: neighbouring
+// lanes together.  Lanes that aim at the same channel share ONE atomic on its tail - the first of them reserves a run of
+// Idx for all, the others take their place in the run (atomics on one address serialise in the L2, and a per-token
+// dispatch sends tens of thousands of commands through a handful of tails); then the commands change lanes through LDS (`scratch`, 2 KB) so that lane order is (channel, Idx) order: neighbouring
 // lanes store neighbouring slots, and the memory pipeline turns the slots of one 64-byte line into one
 // write.  A line of host memory that the proxy is polling costs the PCIe root a round of coherence
 // traffic per write that lands in it, whatever the size of the write.
