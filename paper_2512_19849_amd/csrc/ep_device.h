@@ -37,13 +37,13 @@ EP_DEV unsigned long long ring_push(const RingDev &r, unsigned c, unsigned w0, u
   return ring_publish(r, c, idx, w0, w1, w2, w3);
 }
 
-// Push for a whole wave whose lanes hold one command each (or none: `active`), called by all 64
-// lanes together.  Lanes that aim at the same channel share ONE atomic on its tail - the first of them reserves a run of
-// Idx for all, the others take their place in the run (atomics on one address serialise in the L2, and a per-token
-// dispatch sends tens of thousands of commands through a handful of tails); then the commands change lanes through LDS (`scratch`, 2 KB) so that lane order is (channel, Idx) order: neighbouring
-// lanes store neighbouring slots, and the memory pipeline turns the slots of one 64-byte line into one
-// write.  A line of host memory that the proxy is polling costs the PCIe root a round of coherence
-// traffic per write that lands in it, whatever the size of the write.
+// Push for a whole wave whose lanes hold one command each (or none: `active`), called by all 64 lanes together.  Lanes that
+// aim at the same channel share ONE atomic on its tail - the first of them reserves a run of Idx for all, the others take
+// their place in the run (atomics on one address serialise in the L2, and a per-token dispatch sends tens of thousands of
+// commands through a handful of tails).  Then the commands change lanes through LDS (`scratch`, 2 KB) so that lane order is
+// (channel, Idx) order: neighbouring lanes store neighbouring slots, and the memory pipeline turns the slots of one 64-byte
+// line into one write.  A line of host memory that the proxy is polling costs the PCIe root a round of coherence traffic
+// per write that lands in it, whatever the size of the write.
 // (The check for room reads the cached head after the reservation: read together with it, it is older, calls the channel
 // full more often, and a prefill dispatch of 65536 commands took 178 us instead of 162.)
 EP_DEV void ring_push_sorted(const RingDev &r, bool active, unsigned c, unsigned w0, unsigned w1, unsigned w2,
