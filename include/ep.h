@@ -179,7 +179,8 @@ int ep_proxy_stop(ep_handle *h);
  *   dst_row[s,t,k]   base + slot
  * d_topk_idx is int32 [S,T,K], -1 = masked entry (slot = dst_row = -1); the
  * unmasked experts of one token must be distinct.  T <= max_tokens.  All
- * outputs are int32 device arrays of the shapes named above. */
+ * outputs are int32 device arrays of the shapes named above; d_slot or
+ * d_dst_row (not both) may be d_topk_idx itself. */
 int ep_layout(ep_handle *h, const int32_t *d_topk_idx, int32_t T,
               int32_t *d_count, int32_t *d_expert_total, int32_t *d_rank_total,
               int32_t *d_base, int32_t *d_expert_offset, int32_t *d_rank_offset,

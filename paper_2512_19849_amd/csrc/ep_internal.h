@@ -52,6 +52,7 @@ struct LayoutArgs {
   unsigned *ticket;    // scratch: workgroups finished (self-resetting)
   int32_t *count, *expert_total, *rank_total, *base, *expert_offset, *rank_offset;
   int32_t *slot, *dst_row;
+  int32_t *rank;       // two-kernel form: ranks inside the tiles, on their way to the second kernel (set by the launcher)
   int *error;
 };
 
@@ -208,8 +209,11 @@ struct LaunchTiming {
 // on every compute unit costs more than the two kernels' fixed 14 us.  Kernel time in us, one launch / two kernels:
 // 65536 entries of 128 experts 13.1 / 16.5, of 16 experts 13.9 / 15.5 (queued back to back 14.1 / 13.0), of 256 over 32
 // sources 20.4 / 20.4 (20.5 / 18.1), of 1024 experts 23 / 33; 131072 of 256: 24 / 23.
+// Its workgroups read the whole table while others already write slots and rows, so not where one of these two arrays is
+// the table itself.
 inline bool layout_takes_one_launch(const LayoutArgs &a, const Tunables &tune) {
   const long long n = (long long)a.S * a.T * a.K;
+  if (n > 0 && (a.slot == a.idx || a.dst_row == a.idx)) return false;
   return tune.layout_small && n <= (a.S == 1 && a.E >= 64 ? 65536 : 40960);
 }
 int launch_layout(const LayoutArgs &a, const Tunables &tune, void *stream, const LaunchTiming *timing = nullptr);

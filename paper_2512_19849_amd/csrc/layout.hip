@@ -77,7 +77,7 @@ __global__ __launch_bounds__(1024) void layout_count_kernel(LayoutArgs a) {
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < 8; ++k)
-      if (active && k < K) a.slot[ebase + k] = (ev[k] >= 0 && ev[k] < E) ? __popcll(m[ev[k]] & below) : -1;
+      if (active && k < K) a.rank[ebase + k] = (ev[k] >= 0 && ev[k] < E) ? __popcll(m[ev[k]] & below) : -1;
   } else {
     if (active) {
       for (int k = 0; k < K; ++k) {
@@ -92,7 +92,7 @@ __global__ __launch_bounds__(1024) void layout_count_kernel(LayoutArgs a) {
     if (active) {
       for (int k = 0; k < K; ++k) {
         const int e = a.idx[ebase + k];
-        a.slot[ebase + k] = (e >= 0 && e < E) ? __popcll(m[e] & below) : -1;
+        a.rank[ebase + k] = (e >= 0 && e < E) ? __popcll(m[e] & below) : -1;
       }
     }
   }
@@ -196,7 +196,8 @@ __global__ __launch_bounds__(1024) void layout_count_kernel(LayoutArgs a) {
   }
 }
 
-// Kernel 2: per entry, slot and dst_row from the tile prefix and the expert offset.
+// Kernel 2: per entry, slot and dst_row from the tile prefix and the expert offset.  The entry's own thread reads its id
+// and its rank before it writes, so either output may be the table itself (the ranks come in the other one).
 __global__ __launch_bounds__(256) void layout_finish_kernel(LayoutArgs a) {
   const long long n = (long long)a.S * a.T * a.K;
   const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
@@ -212,7 +213,7 @@ __global__ __launch_bounds__(256) void layout_finish_kernel(LayoutArgs a) {
   const int t = (int)((i - (long long)s * tk) / a.K);
   const int before = a.tile_base[((size_t)s * a.ntiles + t / kLayoutTile) * a.E + e];
   const int first = a.tile_base[(size_t)s * a.ntiles * a.E + e];
-  const int rank = a.slot[i];
+  const int rank = a.rank[i];
   a.slot[i] = before - first + rank;
   a.dst_row[i] = a.expert_offset[e] + before + rank;
 }
@@ -430,6 +431,7 @@ int launch_layout(const LayoutArgs &a, const Tunables &tune, void *stream, const
   if (W != 1 && W != 2 && W != 4 && W != 8 && W != 16) W = 4;
   while (W > 1 && (size_t)W * a.E * sizeof(unsigned long long) > 65536 - 12288) W >>= 1;
   LayoutArgs b = a;
+  b.rank = a.slot != a.idx ? a.slot : a.dst_row;
   b.tiles_per_block = W;
   b.scan_split = 1;  // threads per expert in the scan: a power of two, at most 16, all in one workgroup
   while (b.scan_split < 16 && b.scan_split * 2 * a.E <= kBlock) b.scan_split *= 2;
@@ -443,7 +445,7 @@ int launch_layout(const LayoutArgs &a, const Tunables &tune, void *stream, const
   if (err != hipSuccess) return (int)err;
   if (n > 0) {
     launch_kernel(layout_finish_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, nullptr,
-                  timing ? timing->stop : nullptr, a);
+                  timing ? timing->stop : nullptr, b);
     err = hipGetLastError();
   }
   return (int)err;

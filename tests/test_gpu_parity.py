@@ -149,6 +149,32 @@ def test_layout_one_workgroup_per_expert(epmod, oracle, S, T, K, E, R, maskp):
         assert r.stats()["device_error"] == 0
 
 
+# smallest, a decode table over 32 sources, a batch (each of a size that takes one launch otherwise), more than 8 ids per
+# token, and a table that takes the two kernels anyway
+@pytest.mark.parametrize("S,T,K,E,R", [(1, 5, 2, 8, 2), (32, 128, 8, 256, 32), (1, 4096, 8, 256, 16), (2, 300, 12, 64, 8),
+                                       (1, 9000, 8, 64, 8)])
+@pytest.mark.parametrize("name", ["slot", "dst_row"])
+def test_layout_over_the_routing_table(epmod, oracle, S, T, K, E, R, name):
+    """An output that is the routing table's own buffer: with a handle, and from static scratch."""
+    rng = np.random.default_rng(T)
+    idx = g.mask_random(np.argsort(rng.random((S, T, E)), axis=-1)[..., :K].astype(np.int32), 0.05, seed=T)
+    i32 = dict(dtype=torch.int32, device="cuda")
+    with _runner(epmod, g.EPConfig("over", T=T, H=128, E=E, K=K, R=R, S=S)) as r:
+        for static in (False, True):
+            d_idx = _dev(idx)
+            out = dict(count=torch.empty((S, E), **i32), expert_total=torch.empty(E, **i32), rank_total=torch.empty(R, **i32),
+                       base=torch.empty((S, E), **i32), expert_offset=torch.empty(E + 1, **i32),
+                       rank_offset=torch.empty(R + 1, **i32), slot=torch.empty_like(d_idx), dst_row=torch.empty_like(d_idx))
+            out[name] = d_idx
+            if static:
+                epmod.ep_layout_static(d_idx, S, T, K, E, R, *out.values())
+            else:
+                epmod.ep_layout(r.h, d_idx, T, *out.values())
+            torch.cuda.synchronize()
+            _check_layout(oracle, {k: v.cpu().numpy() for k, v in out.items()}, idx, E, R)
+        assert r.stats()["device_error"] == 0
+
+
 # ---------------------------------------------------------- dispatch bf16
 def _dispatch_case(epmod, oracle, cfg, T, mask, cmd_mode, rank_filter=-1, src=0, extra_rows=3, proxy_writes=False,
                    extra_flags=0, **kw):
