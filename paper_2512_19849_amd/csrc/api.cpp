@@ -92,7 +92,7 @@ void free_all(ep_handle *h) {
     if (h->ring_head) (void)hipHostFree(h->ring_head);
     if (h->dev_error) (void)hipHostFree(h->dev_error);
     void *dev[] = {h->ring.tail, h->ring.cached_head, h->ring.stalls, h->ring.refresh_lock, h->tile_hist, h->tile_base,
-                   h->chunk_cnt, h->expert_done, h->ticket, h->waves_done, h->ht_seq,
+                   h->chunk_cnt, h->group_cnt, h->expert_done, h->ticket, h->waves_done, h->ht_seq,
                    h->ring_seq_fwd, h->ring_seq_rev, h->ring_cum_fwd, h->ring_cum_rev};
     for (void *p : dev)
       if (p) (void)hipFree(p);
@@ -246,6 +246,7 @@ int ep_proxy_start(const ep_config *cfg, ep_handle **out) {
     if (!rc) rc = dev_alloc_zero(&h->tile_hist, hist);
     if (!rc) rc = dev_alloc_zero(&h->tile_base, hist);
     if (!rc) rc = dev_alloc_zero(&h->chunk_cnt, (size_t)E * h->chunks_per_expert * 4);
+    if (!rc) rc = dev_alloc_zero(&h->group_cnt, (size_t)kGroupCmdsMax / 2 * 4);
     if (!rc) rc = dev_alloc_zero(&h->expert_done, (size_t)E * 4);
     if (!rc) rc = dev_alloc_zero(&h->ticket, 4);
     // grid-completion counters of the Drain epilogue: one per 64 workgroups (grids reach 2^19 workgroups) + 1
@@ -549,6 +550,7 @@ int ep_dispatch(ep_handle *h, const void *d_x, const int32_t *d_topk_idx, const 
   a.msg_rows = msg_rows ? (mode == EP_CMD_PER_TOKEN ? 2 : 1) : 0;
   a.chunks_per_expert = h->chunks_per_expert;
   a.chunk_cnt = h->chunk_cnt;
+  a.group_cnt = h->group_cnt;
   a.expert_done = h->expert_done;
   a.waves_done = h->waves_done;
   a.ht_seq = h->ht_seq;

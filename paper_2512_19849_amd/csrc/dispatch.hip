@@ -119,8 +119,9 @@ EP_DEV void emit_chunk_cmds(const DispatchArgs &a, const TokenMeta &m) {
 
 // One command per row: a group of workgroups holds about 64 (token, k) pairs, and the first wave of the group's last
 // workgroup to store its rows pushes for all of them, sorted by channel, so that the commands of a channel leave as one
-// run of consecutive slots written by neighbouring lanes (see ring_push_sorted).  The counters (chunk_cnt, which only the
-// chunk modes use otherwise) return to zero by themselves.
+// run of consecutive slots written by neighbouring lanes (see ring_push_sorted).  The groups' counters are
+// their own (a table may be dispatched in parts, which leaves chunk counters half way between two calls) and return to
+// zero by themselves.
 // What a small dispatch waits for is the proxy, which misses its caches once for every write that reaches a polled line.
 // Whole steps, groups / every workgroup on its own (us, rows of 7168, top-8 of 256 experts): 128 tokens 30 / 36, 256: 34 /
 // 51, 512: 48 / 73; 512 tokens x 4096: 41 / 49.
@@ -132,7 +133,7 @@ EP_DEV void emit_group_cmds(const DispatchArgs &a, int wave, int lane) {
   if (gb > 1) {
     int last = 0;
     if (lane == 0) {
-      int *cnt = a.chunk_cnt + group;
+      int *cnt = a.group_cnt + group;
       last = __hip_atomic_fetch_add(cnt, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 ==
              min(gb, (int)gridDim.x - group * gb);
       if (last) __hip_atomic_store(cnt, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -518,9 +519,7 @@ static size_t group_cmds_setup(DispatchArgs &a, int waves) {
   const int tpb = waves / a.parts;
   if (tpb >= 2) a.tokens_per_block = tpb;
   a.blocks_per_group =
-      (long long)a.T * a.K > 12288 ? 1 : max(1, min(64 / a.K, a.T / 16) / a.tokens_per_block);
-  const long long tokens = (long long)a.blocks_per_group * a.tokens_per_block;
-  if ((a.T + tokens - 1) / tokens > (long long)a.E * a.chunks_per_expert) a.blocks_per_group = 1;  // (counters)
+      (long long)a.T * a.K > kGroupCmdsMax ? 1 : max(1, min(64 / a.K, a.T / 16) / a.tokens_per_block);
   return 2048;
 }
 

@@ -232,7 +232,7 @@ struct ep_handle {
   void *d_recv_count = nullptr;
   // device state
   ep::RingDev ring{};
-  int32_t *tile_hist = nullptr, *tile_base = nullptr, *chunk_cnt = nullptr, *expert_done = nullptr;
+  int32_t *tile_hist = nullptr, *tile_base = nullptr, *chunk_cnt = nullptr, *group_cnt = nullptr, *expert_done = nullptr;
   unsigned *ticket = nullptr, *waves_done = nullptr, *ht_seq = nullptr;
   int ntiles_cap = 0, chunks_per_expert = 0;
   // host-only producer state

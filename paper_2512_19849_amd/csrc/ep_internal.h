@@ -13,6 +13,7 @@ namespace ep {
 // so proxy threads that own different channels never share a line.
 constexpr int kHeadStride = 8;  // in uint64 units
 constexpr int kChunkRows = 32;  // rows per Write in EP_CMD_CHUNK32 (Section 3.3: "typically 32 tokens")
+constexpr int kGroupCmdsMax = 12288;  // per-token commands of a dispatch whose workgroups push in groups, at most
 constexpr int kMaxChannels = 64;
 constexpr int kMaxThreads = 16;
 constexpr int kLayoutTile = 64;        // tokens per layout tile = one wavefront
@@ -79,7 +80,8 @@ struct DispatchArgs {
                            // (codes, scales, padding: row_bytes) at its destination row of `recv`; 2 = one message
                            // per token at row t of `recv` (the proxy forwards it to every destination)
   int32_t chunks_per_expert;
-  int32_t *chunk_cnt;      // scratch [E * chunks_per_expert], zero between calls (per-token commands: one per group)
+  int32_t *chunk_cnt;      // scratch [E * chunks_per_expert], zero between calls
+  int32_t *group_cnt;      // scratch [kGroupCmdsMax / 2]: workgroups of a group that are done, zero between calls
   int32_t *expert_done;    // scratch [E], zero between calls
   unsigned *waves_done;    // scratch of the Drain epilogue [1 + workgroups / 64], zero between calls
   unsigned *ht_seq;        // scratch [S*R]: next sequence number of each communication channel

@@ -338,6 +338,46 @@ def test_per_token_commands_of_workgroup_groups(epmod, oracle, T, K, E, R, H):
         assert st["device_error"] == 0 and st["proxy_error"] == 0 and st["rejected"] == 0
 
 
+@pytest.mark.parametrize("T,K,E,R,H,cut", [(128, 8, 256, 32, 7168, 61), (96, 4, 16, 4, 4096, 33)])
+def test_per_token_commands_between_two_parts_of_a_chunked_dispatch(epmod, oracle, T, K, E, R, H, cut):
+    """Sequenced chunks of a table that is dispatched in two parts: what the first part leaves half counted is not seen
+    by a per-token dispatch in between, and the second part completes it."""
+    from paper_2512_19849_amd.runner import bits_to_bf16, bf16_to_bits
+    cfg = g.EPConfig("parts", T=T, H=H, E=E, K=K, R=R, routing="uniform", seed=K)
+    idx, x = g.routing_all(cfg)[0], g.activations(cfg)
+    rows = T * K
+    lay = oracle.layout(idx, E, R)
+    want, _ = oracle.dispatch_bf16(x, idx[0], lay["dst_row"][0], cfg.E_loc, rows, -1, fill=0xBFC0)
+    with _runner(epmod, cfg, flags=epmod.EP_FLAG_LOG_CMDS | epmod.EP_FLAG_LOG_EVENTS, heap_rows=rows) as r:
+        d_idx, d_x = _dev(idx), bits_to_bf16(x)
+        lay_d = r.layout(d_idx)
+        bufs = [torch.full((rows, H), -1.5, dtype=torch.bfloat16, device="cuda") for _ in range(2)]
+
+        def part(lo, hi):
+            epmod.ep_dispatch(r.h, d_x[lo:hi], d_idx[0, lo:hi], lay_d.dst_row[0, lo:hi], lay_d.count[0], lay_d.base[0],
+                              hi - lo, 0, -1, epmod.EP_BF16, epmod.EP_CMD_CHUNK32_ORDERED, bufs[0], None, rows)
+
+        part(0, cut)
+        for _ in range(2):
+            bufs[1].fill_(-1.5)
+            r.dispatch(d_x, d_idx[0], lay_d, bufs[1], cmd_mode=epmod.EP_CMD_PER_TOKEN)
+            r.wait()
+            torch.cuda.synchronize()
+            assert np.array_equal(bf16_to_bits(bufs[1]), want)
+            assert np.array_equal(r.counters()[0], lay["count"][0])
+        part(cut, T)
+        r.wait()
+        torch.cuda.synchronize()
+        assert np.array_equal(bf16_to_bits(bufs[0]), want)
+        assert np.array_equal(epmod.ep_tail_counters(r.h, 1, R)[0], lay["count"][0].reshape(R, -1).sum(1))
+        writes = type(oracle.cmd_multiset([]))()
+        for _ in range(2):
+            writes += oracle.expected_cmds(idx[0], lay, 0, cfg.E_loc, H, "bf16", "per_token")
+        assert oracle.cmd_multiset(epmod.ep_cmd_log(r.h)) == writes
+        st = r.stats()
+        assert st["device_error"] == 0 and st["proxy_error"] == 0 and st["rejected"] == 0
+
+
 @pytest.mark.parametrize("cid,T,mask,window", [(1, None, 0.0, 0), (1, None, 0.2, 4), (2, 128, 0.0, 64),
                                                (4, 200, 0.0, 0), (5, 300, 0.1, 7)])
 def test_dispatch_per_token_commands(epmod, oracle, cid, T, mask, window):
