@@ -140,9 +140,14 @@ def _check(fn: str, rc: int) -> None:
         raise EPError(fn, rc)
 
 
+class Address(int):
+    """A memory address whose owner the caller keeps (a plain int, a size or a handle say, is not taken for one)."""
+    __slots__ = ()
+
+
 def _ptr(t) -> Optional[int]:
-    """Device (or host) address of a torch tensor / numpy array / None; an int is an address already."""
-    if t is None or t.__class__ is int:
+    """Device (or host) address of a torch tensor / numpy array / Address / None."""
+    if t is None or t.__class__ is Address:
         return t
     if hasattr(t, "data_ptr"):
         if not t.is_contiguous():
