@@ -206,17 +206,23 @@ struct Tunables {
 struct LaunchTiming {
   void *start, *stop;
 };
-// The one-launch layout (layout_expert_kernel, no scratch) takes every table up to 65536 entries (40960 with several
-// sources or few experts, whose busiest workgroup then has the more to number): beyond that, looking at every entry
-// on every compute unit costs more than the two kernels' fixed 14 us.  Kernel time in us, one launch / two kernels:
-// 65536 entries of 128 experts 13.1 / 16.5, of 16 experts 13.9 / 15.5 (queued back to back 14.1 / 13.0), of 256 over 32
-// sources 20.4 / 20.4 (20.5 / 18.1), of 1024 experts 23 / 33; 131072 of 256: 24 / 23.
+// The one-launch layout (layout_expert_kernel, no scratch) takes tables up to 65536 entries (40960 with several sources or
+// few experts): it looks at every entry on every compute unit, 3 us per 32768 of them, while the two kernels cost 11 to
+// 14 us whatever the size plus the scan of a histogram per 64 tokens.  And only as many tokens as it numbers in time should
+// every one of them name the same expert: with many experts a single workgroup numbers that one, and with several sources
+// each workgroup of an expert counts all its entries per source.  Host-to-host time of queued calls in us, one launch /
+// two kernels, experts drawn evenly and, after the colon, one expert in every token:
+//   one source    8192 tokens top-8 of 64 10 / 15 : 12 / 14, of 256 10 / 15 : 16 / 15, of 1024 21 / 32; 16384 top-4 of 64
+//                 10 / 13 : 13 / 13; 32768 top-2 of 64 11 / 14 : 18 / 14, of 128 - : 17 / 20; 40960 top-1 of 1 - : 13 / 17
+//   several       32 x 128 top-8 of 256 8 / 17; 8 x 768 top-4 of 8 9 / 12 : 10 / 12; 64 x 128 top-1 of 8 8 / 11 : 13 / 11,
+//                 of 64 8 / 14 : 14 / 13; 8 x 2048 top-2 of 64 9 / 13 : 16 / 13; 32 x 1280 top-1 of 256 - : 30 / 37
 // Its workgroups read the whole table while others already write slots and rows, so not where one of these two arrays is
 // the table itself.
 inline bool layout_takes_one_launch(const LayoutArgs &a, const Tunables &tune) {
-  const long long n = (long long)a.S * a.T * a.K;
+  const long long tokens = (long long)a.S * a.T, n = tokens * a.K;
   if (n > 0 && (a.slot == a.idx || a.dst_row == a.idx)) return false;
-  return tune.layout_small && n <= (a.S == 1 && a.E >= 64 ? 65536 : 40960);
+  const int most = a.S == 1 ? (a.E >= 64 && a.E < 128 ? 16384 : 65536) : a.E >= 256 ? 65536 : a.E >= 64 ? 8192 : 6144;
+  return tune.layout_small && tokens <= most && n <= (a.S == 1 && a.E >= 64 ? 65536 : 40960);
 }
 int launch_layout(const LayoutArgs &a, const Tunables &tune, void *stream, const LaunchTiming *timing = nullptr);
 int launch_dispatch(const DispatchArgs &a, int payload, const Tunables &tune, void *stream,

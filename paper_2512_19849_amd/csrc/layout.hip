@@ -228,12 +228,17 @@ __global__ __launch_bounds__(256) void layout_finish_kernel(LayoutArgs a) {
 // to the wave's list in LDS (its place and which of the four entries); after one barrier the waves know how many
 // entries of e come before theirs and number their lists, 64 quads at a time.
 //
+// Numbering is two scattered stores per entry, which a compute unit issues at about one address per clock: an expert that
+// every token names takes 5 us per 8192 tokens.  With fewer than 256 experts there are compute units to spare, so `parts`
+// workgroups count alike for the same expert and each numbers the lists of its own share of the waves (40960 entries of
+// one expert 12 us, as one workgroup 30; 65536 of 64 experts, 8192 of them alike, 12 instead of 15).
+//
 // Bound by instruction issue: every compute unit looks at every entry, about 30 vector instructions per 256 of them
 // (compares with e, the smaller-id count in per-lane registers - the same with scalar popcounts was no faster -
 // and the next group's load in flight), so about 3 us per 32768 entries on top of 4 us of launch, first load,
 // barrier and stores.  Measured on MI355X against the forms before it (kernel time, us): 128 entries of 16 experts
 // 4.2 (one-workgroup form with LDS masks 5.3), 1024 of 256: 4.1 (7.5), 4096: 4.1 (11.0), 32768: 8.0 (two kernels
-// 16.7), 32768 over 32 sources: 11.8 (19.2), 32768 of 1024 experts: 14.6 (24.6).
+// 16.7), 32768 over 32 sources: 7.2 (18.8), 32768 of 1024 experts: 14.6 (24.6).
 typedef int i32x4_any __attribute__((ext_vector_type(4), aligned(4)));  // 16 bytes at any 4-byte boundary
 
 __global__ __launch_bounds__(1024) void layout_expert_kernel(LayoutArgs a) {
@@ -241,7 +246,7 @@ __global__ __launch_bounds__(1024) void layout_expert_kernel(LayoutArgs a) {
   __shared__ int s_cnt[16], s_lt[16], s_rl[16];
   __shared__ int s_first[257];  // entries of e before source s
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), nw = blockDim.x >> 6;
-  const int e = blockIdx.x, E = a.E, S = a.S;
+  const int E = a.E, S = a.S, parts = gridDim.y, e = blockIdx.x, part = blockIdx.y;
   const unsigned rank_end = (unsigned)((e / a.E_loc + 1) * a.E_loc);
   const bool first_of_rank = e % a.E_loc == 0;
   const unsigned tk = (unsigned)a.T * a.K, n = (unsigned)S * tk, groups = (n + 255) / 256;
@@ -264,7 +269,7 @@ __global__ __launch_bounds__(1024) void layout_expert_kernel(LayoutArgs a) {
     return v;
   };
   // entries without an expert get -1: the table is shared out over all waves of the grid for that
-  const unsigned i_mine = (e * nw + wave) * 64 + lane;
+  const unsigned i_mine = ((part * E + e) * nw + wave) * 64 + lane;
   const int v_mine = i_mine < n ? a.idx[i_mine] : 0;
   int quads = 0;                // list length
   int cnt = 0, lt = 0, rl = 0;  // per lane: entries of e, of a smaller id, of an id below the end of e's rank
@@ -308,7 +313,7 @@ __global__ __launch_bounds__(1024) void layout_expert_kernel(LayoutArgs a) {
   }
   const int before = wave_sum(lane < wave ? c_of : 0), total = wave_sum(c_of), off = wave_sum(lt_of),
             end = wave_sum(rl_of);
-  if (tid == 0) {
+  if (tid == 0 && part == 0) {
     a.expert_total[e] = total;
     a.expert_offset[e] = off;
     if (e == E - 1) a.expert_offset[E] = a.rank_offset[a.R] = off + total;
@@ -318,9 +323,20 @@ __global__ __launch_bounds__(1024) void layout_expert_kernel(LayoutArgs a) {
     }
   }
   if (S > 1) {  // entries of e per source, then their prefix
-    for (int p = lane; p < quads; p += 64)
-      for (unsigned q = list[p], nib = q & 15u; nib; nib &= nib - 1)
-        atomicAdd(&s_first[(i0 + (q >> 4) * 4 + __builtin_ctz(nib)) / tk + 1], 1);
+    for (int p0 = 0; p0 < quads; p0 += 64) {
+      const int p = p0 + lane;
+      const unsigned q = p < quads ? list[p] : 0u;
+      unsigned nib = q & 15u;
+      if (p0 + 64 <= quads) {  // 64 quads, most often of one source: one addition
+        const unsigned lo = (i0 + (list[p0] >> 4) * 4u) / tk, hi = (i0 + (list[p0 + 63] >> 4) * 4u + 3u) / tk;
+        if (lo == hi) {
+          const int c = wave_sum(__popc(nib));
+          if (lane == 0) atomicAdd(&s_first[lo + 1], c);
+          continue;
+        }
+      }
+      for (; nib; nib &= nib - 1) atomicAdd(&s_first[(i0 + (q >> 4) * 4 + __builtin_ctz(nib)) / tk + 1], 1);
+    }
     __syncthreads();
     if (wave == 0) {
       int carry = 0;
@@ -329,19 +345,22 @@ __global__ __launch_bounds__(1024) void layout_expert_kernel(LayoutArgs a) {
         const int incl = carry + wave_inclusive_scan(c, lane);
         if (s < S) {
           s_first[s + 1] = incl;
-          a.count[(size_t)s * E + e] = c;
-          a.base[(size_t)s * E + e] = off + incl - c;
+          if (part == 0) {
+            a.count[(size_t)s * E + e] = c;
+            a.base[(size_t)s * E + e] = off + incl - c;
+          }
         }
         carry = __builtin_amdgcn_readlane(incl, 63);
       }
     }
     __syncthreads();
-  } else if (tid == 0) {
+  } else if (tid == 0 && part == 0) {
     a.count[e] = total;
     a.base[e] = off;
   }
   // the r-th entry of e in table order gets row off + r
   int run = before;
+  if (parts > 1 && wave % parts != part) quads = 0;  // (another workgroup of this expert numbers these)
   for (int p0 = 0; p0 < quads; p0 += 64) {
     const int p = p0 + lane;
     const unsigned q = p < quads ? list[p] : 0u;
@@ -362,7 +381,7 @@ __global__ __launch_bounds__(1024) void layout_expert_kernel(LayoutArgs a) {
       a.dst_row[i] = off + r;
     }
   }
-  for (unsigned i = i_mine; i < n; i += E * nw * 64) {
+  for (unsigned i = i_mine; i < n; i += parts * E * nw * 64) {
     const int w = i == i_mine ? v_mine : a.idx[i];
     if (w >= 0 && w < E) continue;
     if (w != -1) dev_set_error(a.error, EP_EBOUNDS);
@@ -420,7 +439,9 @@ int launch_layout(const LayoutArgs &a, const Tunables &tune, void *stream, const
     const int groups = (int)(((long long)a.S * a.T * a.K + 255) / 256);
     const int waves = groups < 1 ? 1 : (groups > 16 ? 16 : groups);
     const size_t lds = (size_t)waves * ((groups + waves - 1) / waves) * 64 * sizeof(unsigned short);
-    launch_kernel(layout_expert_kernel, dim3(a.E), dim3(64 * waves), lds, st, timing ? timing->start : nullptr,
+    // workgroups of an expert (up to 2048 tokens one numbers its entries in a microsecond)
+    const int parts = (long long)a.S * a.T <= 2048 ? 1 : max(1, min(waves, 256 / a.E));
+    launch_kernel(layout_expert_kernel, dim3(a.E, parts), dim3(64 * waves), lds, st, timing ? timing->start : nullptr,
                   timing ? timing->stop : nullptr, a);
     return (int)hipGetLastError();
   }

@@ -149,6 +149,28 @@ def test_layout_one_workgroup_per_expert(epmod, oracle, S, T, K, E, R, maskp):
         assert r.stats()["device_error"] == 0
 
 
+# several workgroups per expert: their shares of the waves (9 waves in 9 and in 6 parts, 16 in 16, 2 and 1), lists longer
+# than 64 quads with one and with several sources in 64 of them, both sides of the lines in tokens
+@pytest.mark.parametrize("S,T,K,E,R", [(1, 2048, 1, 7, 7), (1, 2049, 1, 7, 7), (1, 2049, 1, 40, 8), (1, 4097, 1, 1, 1),
+                                       (1, 13000, 3, 3, 1), (1, 6000, 8, 100, 10), (1, 3000, 8, 130, 10),
+                                       (1, 16384, 4, 64, 8), (1, 16385, 2, 64, 8), (3, 2048, 1, 2, 1), (2, 3072, 3, 5, 5),
+                                       (8, 768, 1, 1, 1), (64, 96, 2, 4, 2), (3, 2049, 1, 2, 1), (7, 1170, 5, 64, 4),
+                                       (7, 1171, 5, 64, 4), (5, 4000, 2, 256, 8)])
+def test_layout_busy_expert(epmod, oracle, S, T, K, E, R):
+    """Nearly every token names one expert, first among its entries or last."""
+    rng = np.random.default_rng(T)
+    score = rng.random((S, T, E))
+    score[:, :, E // 2] -= rng.random((S, T)) < 0.97
+    idx = np.argsort(score, axis=-1)[..., :K].astype(np.int32)
+    idx[:, T // 2:] = idx[:, T // 2:, ::-1]
+    idx[:, ::5, 0] = -1
+    with _runner(epmod, g.EPConfig("busy", T=T, H=128, E=E, K=K, R=R, S=S)) as r:
+        lay = r.layout(_dev(idx))
+        torch.cuda.synchronize()
+        _check_layout(oracle, lay.numpy(), idx, E, R)
+        assert r.stats()["device_error"] == 0
+
+
 # smallest, a decode table over 32 sources, a batch (each of a size that takes one launch otherwise), more than 8 ids per
 # token, and a table that takes the two kernels anyway
 @pytest.mark.parametrize("S,T,K,E,R", [(1, 5, 2, 8, 2), (32, 128, 8, 256, 32), (1, 4096, 8, 256, 16), (2, 300, 12, 64, 8),
