@@ -546,7 +546,6 @@ int ep_dispatch(ep_handle *h, const void *d_x, const int32_t *d_topk_idx, const 
   a.filter = dst_rank_filter;
   a.cmd_mode = cmd_mode;
   a.row_bytes = row_bytes_of(c.hidden, payload);
-  a.proxy_moves = proxy_moves ? 1 : 0;
   a.msg_rows = msg_rows ? (mode == EP_CMD_PER_TOKEN ? 2 : 1) : 0;
   a.chunks_per_expert = h->chunks_per_expert;
   a.chunk_cnt = h->chunk_cnt;

@@ -175,6 +175,9 @@ EP_DEV void emit_drain(const DispatchArgs &a, int lane) {
 // slice of the row ONCE into registers (VPL vectors per lane) and stores it to
 // every destination row; destination rows are wave-uniform and come from the
 // lanes that hold the token's (expert, row) pairs.
+// (Write-through stores without the streaming hint: with it the dispatch itself and a combine of other rows are up to 4%
+// faster, but whoever reads the rows next no longer finds any in the memory-side cache.  Step and a read of the received
+// rows, without / with, us: 4058 tokens x 7168 top-8 in FP8 182 / 194, 8116 tokens 365 / 380, 8239 x 4096 bf16 337 / 341.)
 // (The same placement as in dispatch_bf16_kernel below, as a function for the form with a command wave; the plain
 // kernel keeps its own copy: with the body moved into a function the compiler allocated 61 instead of 46
 // registers for it and spilled at 7 and 8 vectors per lane.)
@@ -220,20 +223,15 @@ __global__ void dispatch_bf16_kernel(DispatchArgs a) {
 #pragma unroll
     for (int i = 0; i < VPL; ++i)
       if (v0 + i * 64 < nvec) v[i] = __builtin_nontemporal_load(src + v0 + i * 64);
-    if (a.stream_rows) {
-      for (unsigned long long mm = vmask; mm; mm &= mm - 1) {
-        u32x4 *dst = (u32x4 *)a.recv + (size_t)__builtin_amdgcn_readlane(m.row, __builtin_ctzll(mm)) * nvec;
+    unsigned long long mm = vmask;
+    while (mm) {
+      const int k = __builtin_ctzll(mm);
+      mm &= mm - 1;
+      const int row = __builtin_amdgcn_readlane(m.row, k);
+      u32x4 *dst = (u32x4 *)a.recv + (size_t)row * nvec;
 #pragma unroll
-        for (int i = 0; i < VPL; ++i)
-          if (v0 + i * 64 < nvec) store_payload_once(dst + v0 + i * 64, v[i]);
-      }
-    } else {
-      for (unsigned long long mm = vmask; mm; mm &= mm - 1) {
-        u32x4 *dst = (u32x4 *)a.recv + (size_t)__builtin_amdgcn_readlane(m.row, __builtin_ctzll(mm)) * nvec;
-#pragma unroll
-        for (int i = 0; i < VPL; ++i)
-          if (v0 + i * 64 < nvec) store_payload(dst + v0 + i * 64, v[i]);
-      }
+      for (int i = 0; i < VPL; ++i)
+        if (v0 + i * 64 < nvec) store_payload(dst + v0 + i * 64, v[i]);
     }
   }
   if (!ring_on) return;
@@ -351,8 +349,7 @@ __global__ void dispatch_fp8_kernel(DispatchArgs a) {
 #pragma unroll
       for (int i = 0; i < VPL; ++i)
         if (p0 + i * 64 < npair) {
-          if (a.stream_rows) store_payload_once(dq + p0 + i * 64, q[i]);
-          else store_payload(dq + p0 + i * 64, q[i]);
+          store_payload(dq + p0 + i * 64, q[i]);
           if ((lane & 7) == 0)
             __hip_atomic_store(ds + ((p0 + i * 64) >> 3), sc[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
         }
@@ -566,21 +563,11 @@ static void launch_dispatch_fp8_t(DispatchArgs a, const Tunables &tune, hipStrea
                 tm ? tm->start : nullptr, tm ? tm->stop : nullptr, a);
 }
 
-int launch_dispatch(const DispatchArgs &a0, int payload, const Tunables &tune, void *stream,
+int launch_dispatch(const DispatchArgs &a, int payload, const Tunables &tune, void *stream,
                     const LaunchTiming *timing) {
   hipStream_t st = (hipStream_t)stream;
   // T == 0 with the ring on still launches one (idle) workgroup: it owes the zero-count atomics
-  if (a0.T <= 0 && (a0.cmd_mode & EP_CMD_MODE_MASK) == EP_CMD_NONE) return 0;
-  // Rows that the memory-side cache (256 MB) could not keep anyway are stored with the streaming hint: FP8 from 192 MB on
-  // (whole steps, us, with / without: 4096 tokens x 7168 156 / 164, 8192 x 4096 ring off 180 / 187; at 180 MB the same),
-  // bf16 from 384 MB on and with commands (4096 x 7168 in chunks 197 / 201, 8192 x 4096 per row 252 / 257; 200 to 240 MB
-  // and ring off 1% slower).  Not where the rows are read again at once - by the proxy's copies (446 / 417), or in place,
-  // as the caller has said.
-  const long long rows_at_most = (long long)a0.T * a0.K < a0.recv_rows ? (long long)a0.T * a0.K : a0.recv_rows;
-  DispatchArgs a = a0;
-  a.stream_rows = !a.cache_hinted && !a.proxy_moves &&
-                  (payload == EP_BF16 ? (a.cmd_mode & EP_CMD_MODE_MASK) != EP_CMD_NONE && rows_at_most * a.H * 2 >= 384000000ll
-                                      : rows_at_most * a.row_bytes >= 192000000ll);
+  if (a.T <= 0 && (a.cmd_mode & EP_CMD_MODE_MASK) == EP_CMD_NONE) return 0;
   if (payload == EP_BF16) {
     int vpl = tuned_dispatch_vpl(a.H, a.T, tune.dispatch_vpl);
     const int cmds = a.cmd_mode & EP_CMD_MODE_MASK;
@@ -598,6 +585,7 @@ int launch_dispatch(const DispatchArgs &a0, int payload, const Tunables &tune, v
     // (measured for 224 to 896 MiB of rows, hidden 4096..8192) - and also where the caller has said that the
     // rows are consumed in place, out of that cache.  (The sequenced chunk mode, bound by its hottest channel's
     // FIFO, was measured slower with one slice per wave on the skewed workload.)
+    const long long rows_at_most = (long long)a.T * a.K < a.recv_rows ? (long long)a.T * a.K : a.recv_rows;
     if (free_choice && !a.cache_hinted && (cmds == EP_CMD_NONE || cmds == EP_CMD_CHUNK32) &&
         rows_at_most * a.H * 2 >= 384000000ll && (a.H / 8 + 63) / 64 <= 16)
       vpl = 1;

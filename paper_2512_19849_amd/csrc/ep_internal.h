@@ -74,8 +74,6 @@ struct DispatchArgs {
   int32_t blocks_per_group;  // per-token commands: workgroups whose commands are pushed together (0: other modes)
   int32_t reverse;         // workgroups take the tokens from the last one down (see ep_dispatch)
   int32_t cache_hinted;    // the caller promised (EP_FLAG_CACHE_HINTS) that the rows are consumed out of the caches
-  int32_t proxy_moves;     // the rows are packed into a send heap that the proxy's copies read
-  int32_t stream_rows;     // rows are stored with the streaming hint (set by the launcher)
   int32_t msg_rows;        // FP8 only: 0 = codes and scales go to the two receive arrays; 1 = every row is one message
                            // (codes, scales, padding: row_bytes) at its destination row of `recv`; 2 = one message
                            // per token at row t of `recv` (the proxy forwards it to every destination)
