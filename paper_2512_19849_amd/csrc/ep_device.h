@@ -169,12 +169,6 @@ EP_DEV void store_payload(u32x4 *p, const u32x4 &v) {
   asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1" ::"v"(p), "v"(v) : "memory");
 }
 
-// The same for payload that passes through a buffer once and is read back soon (the slots of the ring-buffer channels):
-// write-through with the streaming hint on top.
-EP_DEV void store_payload_once(u32x4 *p, const u32x4 &v) {
-  asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1 nt" ::"v"(p), "v"(v) : "memory");
-}
-
 // All stores of this wave are acknowledged after this (hardware wait, then a compiler barrier).
 EP_DEV void wait_for_own_stores() {
   __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0); expcnt and lgkmcnt left alone

@@ -48,9 +48,10 @@ EP_DEV bool ht_valid(const HtRingArgs &a, int e, int row) {
 }
 
 // B 16-byte vectors per lane of a row, starting at vector v0: loads in flight together, stores
-// back to back.  Both ends store with the streaming hint, the sending end write-through as well: 4096 tokens x 7168
-// top-8 through 128 slices 472 us for the whole step (486 with write-through slots and plain rows, 510 with the hint
-// on the received rows only, 487 on the slots only, 484 with write-through received rows).
+// back to back.  The slots are stored write-through, the received rows plainly.  With the streaming hint on both, steps of
+// 235 MB of rows and more took 2 to 6% less (4096 tokens x 7168 top-8, 128 slices: 474 us, without 489), steps of up to
+// 110 MB 6 to 12% more (1024 x 4096, 64 slices: 155, without 139), and with a read of the received rows behind it a step of
+// 470 MB over 256 slices 3% more (555, without 537).
 template <bool STREAM, int B>
 EP_DEV void ht_load_piece(u32x4 (&r)[B], const u32x4 *src, int v0, int nvec) {
 #pragma unroll
@@ -62,8 +63,8 @@ EP_DEV void ht_store_piece(const u32x4 (&r)[B], u32x4 *dst, int v0, int nvec) {
 #pragma unroll
   for (int i = 0; i < B; ++i)
     if (v0 + i * 64 < nvec) {
-      if (THROUGH) store_payload_once(dst + v0 + i * 64, r[i]);
-      else __builtin_nontemporal_store(r[i], dst + v0 + i * 64);
+      if (THROUGH) store_payload(dst + v0 + i * 64, r[i]);
+      else dst[v0 + i * 64] = r[i];
     }
 }
 
@@ -156,7 +157,7 @@ EP_DEV bool ht_send_token(const HtRingArgs &a, HtShared &sh, int c, int t, HtTok
         for (int i = 0; i < kPairs; ++i) {
           const int p = p0 + i * 64 + lane;
           if (p < npair) {
-            store_payload_once((u32x4 *)dst + p, q[i]);
+            store_payload((u32x4 *)dst + p, q[i]);
             if ((lane & 7) == 0)
               __hip_atomic_store((float *)(dst + a.H) + (p >> 3), sc[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
           }
