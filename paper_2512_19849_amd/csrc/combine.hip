@@ -270,9 +270,11 @@ EP_DEV void fma_rows(float (&acc)[8], unsigned long long ks, int row, float wt, 
 // First level of the hierarchical reduce: like the combine, but the K gathered
 // rows of a token are summed per group and every group's sum is written to the
 // group's own row.  Rows, weights and group leaders are wave-uniform.
-// The sums are stored past the caches: nothing outside this stream reads them before the kernel ends, and the final
-// reduce that follows finds more of them in the memory-side cache (4096 tokens x 7168 top-8 over 16 groups, partial /
-// final reduce in us: streaming stores 155 / 75, write-through 146 / 99, plain 150 / 100).
+// The sums are stored write-through, like the rows of a dispatch.  Partial + final reduce, and both behind a kernel that
+// writes y as the experts do (its own time included), us: 4096 tokens x 7168 top-8 over 16 groups 216 and 392 (streaming
+// stores 233 and 400, plain 218 and 393), 8192 x 4096 215 and 412 (231 and 422, 220 and 418), 1024 x 7168 60 and 89 (62 and
+// 100, 58 and 90).  Directly behind a dispatch of the same volume, with y untouched, streaming stores gain: step of 4096 x
+// 7168 357, streaming 346.
 template <int KT>
 __global__ __launch_bounds__(256) void combine_partial_kernel(CombinePartialArgs a) {
   const int wave = threadIdx.x >> 6, lane = lane_id();
@@ -331,7 +333,7 @@ __global__ __launch_bounds__(256) void combine_partial_kernel(CombinePartialArgs
     for (int j = 0; j < KT; ++j) {
       if (!((leaders >> j) & 1)) continue;
       const int pr = __builtin_amdgcn_readlane(prow, j);
-      __builtin_nontemporal_store(res[j], (u32x4 *)a.partial + (size_t)pr * nvec + vi);
+      store_payload((u32x4 *)a.partial + (size_t)pr * nvec + vi, res[j]);
     }
   } else {
     unsigned long long lm = leaders;
@@ -344,7 +346,7 @@ __global__ __launch_bounds__(256) void combine_partial_kernel(CombinePartialArgs
       const int pr = __builtin_amdgcn_readlane(prow, j);
       u32x4 o = {pack_bf16_rne(acc[0], acc[1]), pack_bf16_rne(acc[2], acc[3]),
                  pack_bf16_rne(acc[4], acc[5]), pack_bf16_rne(acc[6], acc[7])};
-      if (vi < nvec) __builtin_nontemporal_store(o, (u32x4 *)a.partial + (size_t)pr * nvec + vi);
+      if (vi < nvec) store_payload((u32x4 *)a.partial + (size_t)pr * nvec + vi, o);
     }
   }
 }
