@@ -49,6 +49,7 @@ EP_DEV void push_count_atomics(const DispatchArgs &a, bool push, int e, int valu
 
 // Workgroup 0, wavefront 0: the count Atomics that no row completion will trigger - experts with count 0, or all of
 // them when the caller wants the atomics ahead of the writes.
+template <bool GROUPS>
 EP_DEV void emit_leading_atomics(const DispatchArgs &a, int lane) {
   extern __shared__ u32x4 s_dyn[];  // (per-token commands: the 2 KB of ring_push_sorted)
   const bool first = (a.cmd_mode & EP_CMD_ATOMICS_FIRST) != 0;
@@ -56,7 +57,7 @@ EP_DEV void emit_leading_atomics(const DispatchArgs &a, int lane) {
     const int e = e0 + lane;
     const int c = e < a.E ? a.count[e] : -1;
     const bool push = c >= 0 && (first || c == 0) && (a.filter < 0 || e / a.E_loc == a.filter);
-    if (a.blocks_per_group)
+    if (GROUPS)
       push_count_atomics(a, push, e, c, s_dyn);
     else if (push)
       push_count_atomic(a, e, c);
@@ -151,12 +152,12 @@ EP_DEV void emit_group_cmds(const DispatchArgs &a, int wave, int lane) {
     // (an entry out of range has been reported by its own wave)
     const bool active = e >= 0 && e < a.E && row >= 0 && row < a.recv_rows && (a.filter < 0 || e / a.E_loc == a.filter);
     if (!active) e = 0;
-    const int c = a.count[e];
     const unsigned dr = (unsigned)(e / a.E_loc), le = (unsigned)(e - (int)dr * a.E_loc);
     const unsigned long long so = (unsigned long long)(t0 + i / a.K) * a.row_bytes;
     const unsigned long long dof = (unsigned long long)row * a.row_bytes;
     ring_push_sorted(a.ring, active, (unsigned)e % a.ring.channels, cmd_w0(EP_OP_WRITE, a.src, dr, le),
                      a.row_bytes >> 4, (unsigned)(so >> 4), (unsigned)(dof >> 4), s_dyn);
+    const int c = a.count[e];
     bool complete = false;  // (as account_rows)
     if (active) {
       complete = __hip_atomic_fetch_add(a.expert_done + e, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 == c;
@@ -175,6 +176,12 @@ EP_DEV void emit_drain(const DispatchArgs &a, int lane) {
 // slice of the row ONCE into registers (VPL vectors per lane) and stores it to
 // every destination row; destination rows are wave-uniform and come from the
 // lanes that hold the token's (expert, row) pairs.
+// (A row's stores wait for those of the wave's row before.  Left to the compiler, which has to wait for the loads somewhere,
+// the wait is before every row, every store or the first row only, as the register allocation falls.  Before every row is
+// best on the whole, us: ring off 8192 tokens x 4096 112, without waits 119; 1536 x 12288 47 and 52; one command per row 1536
+// x 9216 54 and 52, with a wait before every store 64.)
+// (GROUPS: one command per row.  Instances of their own keep both below 100 scalar registers, eight waves per SIMD: together
+// they take 103 to 105, and workgroups of 16 waves, two per compute unit, no longer all fit: 1536 x 16384 94 us, apart 90.)
 // (Write-through stores without the streaming hint: with it the dispatch itself and a combine of other rows are up to 4%
 // faster, but whoever reads the rows next no longer finds any in the memory-side cache.  Step and a read of the received
 // rows, without / with, us: 4058 tokens x 7168 top-8 in FP8 182 / 194, 8116 tokens 365 / 380, 8239 x 4096 bf16 337 / 341.)
@@ -204,14 +211,14 @@ EP_DEV void place_token_bf16(const DispatchArgs &a, const int row_of_lane, unsig
   }
 }
 
-template <int VPL>
+template <int VPL, bool GROUPS>
 __global__ void dispatch_bf16_kernel(DispatchArgs a) {
   const int wave = threadIdx.x >> 6, lane = lane_id();
   const int part = wave % a.parts;
   const int t = token_block(a) * a.tokens_per_block + wave / a.parts;
   const bool ring_on = (a.cmd_mode & EP_CMD_MODE_MASK) != EP_CMD_NONE;
   const bool ordered = (a.cmd_mode & EP_CMD_MODE_MASK) == EP_CMD_CHUNK32_ORDERED;
-  if (ring_on && !ordered && blockIdx.x == 0 && wave == 0) emit_leading_atomics(a, lane);
+  if (ring_on && !ordered && blockIdx.x == 0 && wave == 0) emit_leading_atomics<GROUPS>(a, lane);
 
   const TokenMeta m = load_meta(a, t, lane);
   unsigned long long vmask = __ballot(m.valid);
@@ -225,6 +232,7 @@ __global__ void dispatch_bf16_kernel(DispatchArgs a) {
       if (v0 + i * 64 < nvec) v[i] = __builtin_nontemporal_load(src + v0 + i * 64);
     unsigned long long mm = vmask;
     while (mm) {
+      __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
       const int k = __builtin_ctzll(mm);
       mm &= mm - 1;
       const int row = __builtin_amdgcn_readlane(m.row, k);
@@ -236,7 +244,7 @@ __global__ void dispatch_bf16_kernel(DispatchArgs a) {
   }
   if (!ring_on) return;
   wait_for_own_stores();  // the rows are in memory before a counter or command mentions them
-  if (a.blocks_per_group) {
+  if constexpr (GROUPS) {
     emit_group_cmds(a, wave, lane);
   } else {
     if (a.parts > 1) __syncthreads();
@@ -298,14 +306,14 @@ EP_DEV void place_token_fp8(const DispatchArgs &a, const TokenMeta &m, unsigned 
   }
 }
 
-template <int VPL>
+template <int VPL, bool GROUPS>
 __global__ void dispatch_fp8_kernel(DispatchArgs a) {
   const int wave = threadIdx.x >> 6, lane = lane_id();
   const int part = wave % a.parts;
   const int t = token_block(a) * a.tokens_per_block + wave / a.parts;
   const bool ring_on = (a.cmd_mode & EP_CMD_MODE_MASK) != EP_CMD_NONE;
   const bool ordered = (a.cmd_mode & EP_CMD_MODE_MASK) == EP_CMD_CHUNK32_ORDERED;
-  if (ring_on && !ordered && blockIdx.x == 0 && wave == 0) emit_leading_atomics(a, lane);
+  if (ring_on && !ordered && blockIdx.x == 0 && wave == 0) emit_leading_atomics<GROUPS>(a, lane);
 
   const TokenMeta m = load_meta(a, t, lane);
   unsigned long long vmask = __ballot(m.valid);
@@ -357,7 +365,7 @@ __global__ void dispatch_fp8_kernel(DispatchArgs a) {
   }
   if (!ring_on) return;
   wait_for_own_stores();
-  if (a.blocks_per_group) {
+  if constexpr (GROUPS) {
     emit_group_cmds(a, wave, lane);
   } else {
     if (a.parts > 1) __syncthreads();
@@ -424,7 +432,7 @@ __global__ __launch_bounds__(1024) void dispatch_pipelined_kernel(DispatchArgs a
       if (lane == 0) __hip_atomic_fetch_add(&ctl[slot], 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
   } else {
-    if (mode != EP_CMD_CHUNK32_ORDERED && blockIdx.x == 0) emit_leading_atomics(a, lane);
+    if (mode != EP_CMD_CHUNK32_ORDERED && blockIdx.x == 0) emit_leading_atomics<false>(a, lane);
     int it = 0;
 #pragma nounroll
     for (int b = blockIdx.x; b < nb; b += gridDim.x, ++it) {
@@ -505,18 +513,22 @@ static int tuned_dispatch_fp8_vpl(int H, int T, int forced) {
 }
 
 // One command per row: as many tokens per workgroup as 16 waves hold, and as many workgroups per group as share 64
-// pairs (at least 16 groups, so that a handful of tokens does not wait for its slowest).  Above 12288 commands the kernel
-// is bound by its row stores and a group only keeps its last workgroup busy for longer: a workgroup pushes its own
-// (steps with groups / without, us: 2048 tokens x 7168 top-8 120 / 117, 4096 tokens 220 / 207; 1500 tokens 91 / 92, 1024
-// tokens 65 / 73).  Returns the dynamic LDS bytes of the launch.
+// pairs (at least 16 groups, so that a handful of tokens does not wait for its slowest).  Where the kernel is bound by its row
+// stores a group only keeps its last workgroup busy for longer, and a workgroup pushes its own: above 256 MB of rows, which
+// stream to HBM while it runs (dispatch and wait with groups / without, us: 1024 tokens x 20480 86 / 83, 384 x 65536 103 / 98,
+// 1536 x 16384 104 / 99; 1536 x 8192 (201 MB) 55 / 66, 512 x 24576 50 / 65; in between it varies: 512 x 40960 82 / 91, 1024 x
+// 16384 74 / 69), and above 12288 commands, which keep the proxy busy all the while (steps: 2048 tokens x 7168 top-8 120 /
+// 117, 4096 tokens 220 / 207; 1500 tokens 91 / 92, 1024 tokens 65 / 73).  Returns the dynamic LDS bytes of the launch.
 static size_t group_cmds_setup(DispatchArgs &a, int waves) {
   a.blocks_per_group = 0;
   if ((a.cmd_mode & EP_CMD_MODE_MASK) != EP_CMD_PER_TOKEN) return 0;
   if (waves < 4 || waves > 16) waves = 16;  // (0 = not set)
   const int tpb = waves / a.parts;
   if (tpb >= 2) a.tokens_per_block = tpb;
-  a.blocks_per_group =
-      (long long)a.T * a.K > kGroupCmdsMax ? 1 : max(1, min(64 / a.K, a.T / 16) / a.tokens_per_block);
+  const long long cmds = (long long)a.T * a.K, placed = (a.cmd_mode & EP_CMD_NO_PLACEMENT) ? 0 : min(cmds, (long long)a.recv_rows);
+  a.blocks_per_group = cmds > kGroupCmdsMax || placed * a.row_bytes > kGroupBytesMax
+                           ? 1
+                           : max(1, min(64 / a.K, a.T / 16) / a.tokens_per_block);
   return 2048;
 }
 
@@ -547,7 +559,7 @@ static void launch_dispatch_bf16_t(DispatchArgs a, const Tunables &tune, hipStre
   a.tokens_per_block = a.parts >= 4 ? 1 : 4 / a.parts;
   const size_t lds = group_cmds_setup(a, tune.per_token_waves);
   const int grid = max(1, (a.T + a.tokens_per_block - 1) / a.tokens_per_block);
-  launch_kernel(dispatch_bf16_kernel<VPL>, dim3(grid), dim3(64 * a.parts * a.tokens_per_block), lds, st,
+  launch_kernel(a.blocks_per_group ? dispatch_bf16_kernel<VPL, true> : dispatch_bf16_kernel<VPL, false>, dim3(grid), dim3(64 * a.parts * a.tokens_per_block), lds, st,
                 tm ? tm->start : nullptr, tm ? tm->stop : nullptr, a);
 }
 
@@ -559,7 +571,7 @@ static void launch_dispatch_fp8_t(DispatchArgs a, const Tunables &tune, hipStrea
   a.tokens_per_block = a.parts >= 4 ? 1 : 4 / a.parts;
   const size_t lds = group_cmds_setup(a, tune.per_token_waves);
   const int grid = max(1, (a.T + a.tokens_per_block - 1) / a.tokens_per_block);
-  launch_kernel(dispatch_fp8_kernel<VPL>, dim3(grid), dim3(64 * a.parts * a.tokens_per_block), lds, st,
+  launch_kernel(a.blocks_per_group ? dispatch_fp8_kernel<VPL, true> : dispatch_fp8_kernel<VPL, false>, dim3(grid), dim3(64 * a.parts * a.tokens_per_block), lds, st,
                 tm ? tm->start : nullptr, tm ? tm->stop : nullptr, a);
 }
 

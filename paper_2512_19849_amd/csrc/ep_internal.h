@@ -14,6 +14,7 @@ namespace ep {
 constexpr int kHeadStride = 8;  // in uint64 units
 constexpr int kChunkRows = 32;  // rows per Write in EP_CMD_CHUNK32 (Section 3.3: "typically 32 tokens")
 constexpr int kGroupCmdsMax = 12288;  // per-token commands of a dispatch whose workgroups push in groups, at most
+constexpr long long kGroupBytesMax = 256000000;  // ... and bytes of their rows
 constexpr int kMaxChannels = 64;
 constexpr int kMaxThreads = 16;
 constexpr int kLayoutTile = 64;        // tokens per layout tile = one wavefront

@@ -326,11 +326,15 @@ def _check_commands(epmod, oracle, cfg, out, mode_name, payload="bf16", src=0, r
     return res
 
 
-# groups of workgroups that push together: a group of one, groups with a remainder in tokens and in workgroups, a top-k
-# that does not divide 64, more than 64 / 2 pairs per token, the last size with groups and the first without
-@pytest.mark.parametrize("T,K,E,R,H", [(1, 4, 16, 4, 7168), (33, 1, 8, 8, 7168), (57, 3, 24, 6, 4096), (129, 5, 48, 16, 7168),
-                                       (300, 7, 64, 8, 1024), (70, 33, 96, 12, 5120), (2048, 6, 16, 4, 640),
-                                       (2049, 6, 16, 4, 640)])
+# groups of workgroups that push together.  One token per workgroup: 33 and 129 tokens.  Several: 301 tokens in pairs, four
+# workgroups to a group (the last group and its last workgroup not full), 300 tokens by eights, two workgroups to a group.
+# The last size with groups and the first without: 12288 commands, 256 MB of rows.  Groups of one: a single token, a top-k
+# that does not divide 64, more than 64 / 2 pairs per token, workgroups that hold 64 pairs by themselves.
+@pytest.mark.parametrize("T,K,E,R,H", [(33, 1, 8, 8, 7168), (129, 5, 48, 16, 7168), (301, 8, 64, 8, 4096),
+                                       (300, 3, 64, 8, 1024), (2048, 6, 16, 4, 7168), (2049, 6, 16, 4, 7168),
+                                       (488, 8, 16, 4, 32768), (489, 8, 16, 4, 32768), (1, 4, 16, 4, 7168),
+                                       (57, 3, 24, 6, 4096), (300, 7, 64, 8, 1024), (70, 33, 96, 12, 5120),
+                                       (2048, 6, 16, 4, 640)])
 def test_per_token_commands_of_workgroup_groups(epmod, oracle, T, K, E, R, H):
     """Dispatches of one handle in per-token and chunk modes by turns (the counters they share go back to zero), taken
     from either end of the token range."""
