@@ -37,10 +37,12 @@ def _check_layout(oracle, got: dict, idx, E, R):
 
 
 # ------------------------------------------------------------------ layout
+@pytest.mark.parametrize("one_launch", ["1", "0"])
 @pytest.mark.parametrize("cid,T,mask", [(1, None, 0.0), (1, 37, 0.3), (2, None, 0.0), (2, 100, 0.1),
                                         (4, None, 0.0), (4, 4095, 0.05), (5, None, 0.0), (5, 1, 0.0),
                                         (4, 65, 0.0), (1, 0, 0.0)])
-def test_layout_parity(epmod, oracle, cid, T, mask):
+def test_layout_parity(epmod, oracle, cid, T, mask, one_launch, monkeypatch):
+    monkeypatch.setenv("EP_LAYOUT_SMALL", one_launch)
     cfg = g.config(cid)
     idx, _ = g.routing_all(cfg, T)
     if mask:
@@ -53,10 +55,12 @@ def test_layout_parity(epmod, oracle, cid, T, mask):
         assert r.stats()["device_error"] == 0
 
 
-def test_layout_hand_over_between_workgroups_many_times(epmod, oracle):
-    """The tile histograms cross workgroups through write-through stores, a ticket and cache-bypassing loads (no
-    L2 write-back or invalidate): 300 layouts of the full 4096-token table, each compared on the device with the
-    oracle's arrays, other kernels' dirty lines in the caches in between."""
+def test_layout_hand_over_between_workgroups_many_times(epmod, oracle, monkeypatch):
+    """The two-kernel form, which the table would not take by itself: its tile histograms cross workgroups through
+    write-through stores, a ticket and cache-bypassing loads (no L2 write-back or invalidate).  300 layouts of the full
+    4096-token table, each compared on the device with the oracle's arrays, other kernels' dirty lines in the caches in
+    between."""
+    monkeypatch.setenv("EP_LAYOUT_SMALL", "0")
     cfg = g.config(4)
     idx, _ = g.routing_all(cfg)
     want = {k: _dev(v) for k, v in oracle.layout(idx, cfg.E, cfg.R).items()}
@@ -96,10 +100,9 @@ def test_layout_special_shapes(epmod, oracle):
 
 @pytest.mark.parametrize("one_launch", ["1", "0"])
 def test_layout_small_tables_both_forms(epmod, oracle, one_launch, monkeypatch):
-    """Routing tables of up to a dozen 64-token tiles take a one-launch, one-workgroup form of the layout, larger
-    ones the two-kernel form: shapes on both sides of that line (sources x tiles = 12 / 13, ragged last tiles,
-    several sources with few tiles each, 384 experts = the most the one-launch form holds, masked and fully masked
-    entries, one expert for everybody), each with the one-launch form allowed and switched off."""
+    """Small tables with the one-launch form of the layout, which they take, and with it switched off: a dozen 64-token
+    tiles and one more, ragged last tiles, several sources with few tiles each, experts that do not fill a rank's
+    share of the workgroups evenly, masked and fully masked entries, one expert for everybody."""
     monkeypatch.setenv("EP_LAYOUT_SMALL", one_launch)
     rng = np.random.default_rng(12)
     for (S, T, K, E, R, maskp) in [(1, 768, 8, 256, 16, 0.0), (1, 769, 8, 256, 16, 0.0), (4, 130, 3, 24, 4, 0.2),
@@ -136,7 +139,7 @@ def test_layout_small_tables_both_forms(epmod, oracle, one_launch, monkeypatch):
     (5, 1025, 8, 256, 32, 0.0), (1, 5120, 8, 63, 7, 0.0), (1, 5121, 8, 63, 7, 0.0),    # the two forms
     (1, 2000, 8, 1024, 256, 0.0), (1, 700, 64, 64, 2, 0.0)])
 def test_layout_one_workgroup_per_expert(epmod, oracle, S, T, K, E, R, maskp):
-    """The one-launch form at the edges of its groups (256 entries), of its waves' shares and of its range."""
+    """The one-launch form at the edges of its groups (256 entries), of its waves' shares and of its range in entries."""
     rng = np.random.default_rng(S * 1000 + T)
     idx = np.argsort(rng.random((S, T, E)), axis=-1)[..., :K].astype(np.int32)
     idx[:, ::3, 0] = np.where((idx[:, ::3, 1:] == E - 1).any(-1), idx[:, ::3, 0], E - 1)  # a busy last expert
@@ -295,10 +298,9 @@ def test_ring_on_dispatch_with_and_without_a_command_wave(epmod, oracle, mode, p
 @pytest.mark.parametrize("pipeline", ["1", "0"])
 @pytest.mark.parametrize("waves", [4, 8, 16])
 def test_per_token_commands_every_push_form(epmod, oracle, waves, pipeline, monkeypatch):
-    """One command per row leaves through the push of the token's own wave (a workgroup that holds one token:
-    lanes of a channel share the tail atomic), through the workgroup's first wave (several tokens: commands
-    sorted by channel) or through the command wave of a persistent workgroup; all must hand the proxy the same
-    multiset of commands, with rings of 8 and of 4096 slots."""
+    """One command per row leaves through the first wave of a workgroup that holds one token or several, through the
+    last workgroup of a group (commands sorted by channel each time), or through the command wave of a persistent
+    workgroup; all must hand the proxy the same multiset of commands, with rings of 8 and of 4096 slots."""
     monkeypatch.setenv("EP_PER_TOKEN_WAVES", str(waves))
     monkeypatch.setenv("EP_DISPATCH_PIPELINE", pipeline)
     for cid, T, entries in ((4, 70, 4096), (4, 70, 8), (2, None, 64), (1, 33, 8)):

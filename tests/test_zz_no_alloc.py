@@ -1,6 +1,6 @@
 """ep_layout_static, the entry point that allocates nothing (scratch in a static device array), against
-ep_layout, the entry point it is a variant of, through the C ABI: every output array bit for bit, on two
-calls in a row, the second with a smaller input; then the oracle as a second opinion."""
+ep_layout, the entry point it is a variant of, through the C ABI: every output array bit for bit, on several
+calls in a row, later ones with smaller inputs; then the oracle as a second opinion."""
 import numpy as np
 import pytest
 
@@ -42,6 +42,28 @@ def test_layout_static_equals_layout_on_two_calls_in_a_row(oracle, cid, T2):
             for n in NAMES:
                 assert np.array_equal(got[n].cpu().numpy(), ref[n]), (n, T, "vs ep_layout")
                 assert np.array_equal(ref[n], want[n]), (n, T, "vs oracle")
+    assert int(status.item()) == 0
+
+
+# tables of the two-kernel form, which uses the static scratch (ticket, histograms, prefixes) and finds there what the call
+# before has left: smaller tables behind larger ones, one of the one-launch form (which leaves it alone) in between
+@pytest.mark.parametrize("S,K,E,R,Ts", [(1, 8, 64, 8, (9000, 8193, 500, 8193)), (5, 8, 32, 4, (1300, 1025, 60, 1025)),
+                                        (3, 2, 1, 1, (7000, 2049, 2048, 2049)), (1, 12, 96, 6, (6000, 5462, 5461, 5462))])
+def test_layout_static_scratch_of_larger_tables(oracle, S, K, E, R, Ts):
+    import paper_2512_19849_amd as ep
+    ep.load_library(build_if_missing=False)
+    K = min(K, E)
+    status = torch.zeros(1, dtype=torch.int32, device="cuda")
+    for T in Ts:
+        rng = np.random.default_rng(T)
+        idx = np.argsort(rng.random((S, T, E)), axis=-1)[..., :K].astype(np.int32)
+        idx = g.mask_random(idx, 0.1, seed=T)
+        got = _outputs(S, T, K, E, R)
+        ep.ep_layout_static(torch.from_numpy(idx).cuda(), S, T, K, E, R, *(got[n] for n in NAMES), status)
+        torch.cuda.synchronize()
+        want = oracle.layout(idx, E, R)
+        for n in NAMES:
+            assert np.array_equal(got[n].cpu().numpy(), want[n]), (n, T)
     assert int(status.item()) == 0
 
 
