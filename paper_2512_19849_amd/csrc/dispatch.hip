@@ -64,10 +64,6 @@ EP_DEV void emit_leading_atomics(const DispatchArgs &a, int lane) {
   }
 }
 
-// The chunk modes' commands (one Write per row: emit_group_cmds).  Called by the lanes holding a dispatched (t,k) after the
-// token's rows are stored and acknowledged (write-through, so they are in memory).  The lane that completes a run of
-// <= 32 consecutive rows of an expert pushes the Write for the run.  Whoever completes the expert pushes its count Atomic
-// (Section 3.3: the receiver holds it until that many rows arrived).  The scratch counters return to zero by themselves.
 // `rows` more rows of expert e (c in all) have been handed to the channel; whoever hands over the
 // last one pushes the expert's count Atomic.
 EP_DEV void account_rows(const DispatchArgs &a, int e, int c, int rows) {
@@ -78,6 +74,10 @@ EP_DEV void account_rows(const DispatchArgs &a, int e, int c, int rows) {
   }
 }
 
+// The chunk modes' commands (one Write per row: emit_group_cmds).  Called by the lanes holding a dispatched (t,k) after the
+// token's rows are stored and acknowledged (write-through, so they are in memory).  The lane that completes a run of
+// <= 32 consecutive rows of an expert pushes the Write for the run.  Whoever completes the expert pushes its count Atomic
+// (Section 3.3: the receiver holds it until that many rows arrived).  The scratch counters return to zero by themselves.
 EP_DEV void emit_chunk_cmds(const DispatchArgs &a, const TokenMeta &m) {
   const int e = m.e;
   const unsigned dr = (unsigned)(e / a.E_loc), le = (unsigned)(e - (int)dr * a.E_loc);
@@ -517,8 +517,9 @@ static int tuned_dispatch_fp8_vpl(int H, int T, int forced) {
 // stores a group only keeps its last workgroup busy for longer, and a workgroup pushes its own: above 256 MB of rows, which
 // stream to HBM while it runs (dispatch and wait with groups / without, us: 1024 tokens x 20480 86 / 83, 384 x 65536 103 / 98,
 // 1536 x 16384 104 / 99; 1536 x 8192 (201 MB) 55 / 66, 512 x 24576 50 / 65; in between it varies: 512 x 40960 82 / 91, 1024 x
-// 16384 74 / 69), and above 12288 commands, which keep the proxy busy all the while (steps: 2048 tokens x 7168 top-8 120 /
-// 117, 4096 tokens 220 / 207; 1500 tokens 91 / 92, 1024 tokens 65 / 73).  Returns the dynamic LDS bytes of the launch.
+// 16384 74 / 69); and above 12288 commands, where whole steps got slower (2048 tokens x 7168 top-8 120 / 117, 4096 tokens 220 /
+// 207; 1500 tokens 91 / 92, 1024 tokens 65 / 73), though dispatch and wait by themselves do not (2048 x 7168 60 / 69, 2048 x
+// 1024 65 / 63, 16000 x 1024 top-1 53 / 76).  Returns the dynamic LDS bytes of the launch.
 static size_t group_cmds_setup(DispatchArgs &a, int waves) {
   a.blocks_per_group = 0;
   if ((a.cmd_mode & EP_CMD_MODE_MASK) != EP_CMD_PER_TOKEN) return 0;
@@ -555,7 +556,8 @@ template <int VPL>
 static void launch_dispatch_bf16_t(DispatchArgs a, const Tunables &tune, hipStream_t st, const LaunchTiming *tm) {
   const int nvec = a.H / 8;
   a.parts = (nvec + VPL * 64 - 1) / (VPL * 64);
-  if (launch_pipelined<VPL, false>(a, tune, st, tm)) return;
+  if constexpr (VPL != 7 && VPL != 8)  // (they spill there: launch_dispatch asks for 14 and 16 instead)
+    if (launch_pipelined<VPL, false>(a, tune, st, tm)) return;
   a.tokens_per_block = a.parts >= 4 ? 1 : 4 / a.parts;
   const size_t lds = group_cmds_setup(a, tune.per_token_waves);
   const int grid = max(1, (a.T + a.tokens_per_block - 1) / a.tokens_per_block);

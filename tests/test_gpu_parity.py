@@ -101,8 +101,8 @@ def test_layout_special_shapes(epmod, oracle):
 @pytest.mark.parametrize("one_launch", ["1", "0"])
 def test_layout_small_tables_both_forms(epmod, oracle, one_launch, monkeypatch):
     """Small tables with the one-launch form of the layout, which they take, and with it switched off: a dozen 64-token
-    tiles and one more, ragged last tiles, several sources with few tiles each, experts that do not fill a rank's
-    share of the workgroups evenly, masked and fully masked entries, one expert for everybody."""
+    tiles and one more, ragged last tiles, several sources with few tiles each, 392 experts over 8
+    ranks, masked and fully masked entries, one expert for everybody."""
     monkeypatch.setenv("EP_LAYOUT_SMALL", one_launch)
     rng = np.random.default_rng(12)
     for (S, T, K, E, R, maskp) in [(1, 768, 8, 256, 16, 0.0), (1, 769, 8, 256, 16, 0.0), (4, 130, 3, 24, 4, 0.2),
