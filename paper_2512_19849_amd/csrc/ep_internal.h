@@ -209,12 +209,16 @@ struct LaunchTiming {
 // few experts): it looks at every entry on every compute unit, 3 us per 32768 of them, while the two kernels cost 11 to
 // 14 us whatever the size plus the scan of a histogram per 64 tokens.  And only as many tokens as it numbers in time should
 // every one of them name the same expert: with many experts a single workgroup numbers that one, and with several sources
-// each workgroup of an expert counts all its entries per source.  Host-to-host time of queued calls in us, one launch /
-// two kernels, experts drawn evenly and, after the colon, one expert in every token:
-//   one source    8192 tokens top-8 of 64 10 / 15 : 12 / 14, of 256 10 / 15 : 16 / 15, of 1024 21 / 32; 16384 top-4 of 64
-//                 10 / 13 : 13 / 13; 32768 top-2 of 64 11 / 14 : 18 / 14, of 128 - : 17 / 20; 40960 top-1 of 1 - : 13 / 17
-//   several       32 x 128 top-8 of 256 8 / 17; 8 x 768 top-4 of 8 9 / 12 : 10 / 12; 64 x 128 top-1 of 8 8 / 11 : 13 / 11,
-//                 of 64 8 / 14 : 14 / 13; 8 x 2048 top-2 of 64 9 / 13 : 16 / 13; 32 x 1280 top-1 of 256 - : 30 / 37
+// each workgroup of an expert counts all its entries per source.  Time between queued calls in us, one launch / two
+// kernels, experts drawn evenly and, after the colon, one expert in every token:
+//   one source    8192 tokens top-8 of 64 10.3 / 14.1 : 11.2 / 14.0, of 160 9.9 / 14.3 : 15.7 / 14.1, of 256 9.6 / 15.0 :
+//                 15.8 / 14.9, of 1024 22 / 32 : 28 / 32; 16384 top-4 of 64 10.3 / 12.8 : 13.1 / 12.7; 32768 top-2 of 64
+//                 10.6 / 13.7 : 18.2 / 13.6, of 128 10.2 / 19.5 : 18.1 / 19.4; 40960 top-1 of 8 9.5 / 15.8 : 12.3 / 15.8
+//   several       32 x 128 top-8 of 256 7.6 / 16.8 : 12.1 / 16.7; 8 x 768 top-4 of 8 8.6 / 11.0 : 10.0 / 11.0; 64 x 128
+//                 top-1 of 8 6.7 / 10.8 : 12.6 / 10.8, of 64 6.7 / 13.4 : 13.3 / 13.4; 8 x 1024 top-4 of 64 7.9 / 12.2 :
+//                 13.0 / 12.1, of 256 7.5 / 13.9 : 14.3 / 13.8; 8 x 2048 top-2 of 64 8.1 / 12.2 : 16.2 / 12.2; 32 x 1280
+//                 top-1 of 256 8.6 / 36 : 30 / 36
+// (Where it is chosen, a table with one expert in every token costs it at most 1.6 us more than the two kernels.)
 // Its workgroups read the whole table while others already write slots and rows, so not where one of these two arrays is
 // the table itself.
 inline bool layout_takes_one_launch(const LayoutArgs &a, const Tunables &tune) {

@@ -231,7 +231,7 @@ __global__ __launch_bounds__(256) void layout_finish_kernel(LayoutArgs a) {
 // Numbering is two scattered stores per entry, which a compute unit issues at about one address per clock: an expert that
 // every token names takes 5 us per 8192 tokens.  With fewer than 256 experts there are compute units to spare, so `parts`
 // workgroups count alike for the same expert and each numbers the lists of its own share of the waves (40960 entries of
-// one expert 12 us, as one workgroup 30; 65536 of 64 experts, 8192 of them alike, 12 instead of 15).
+// one expert 12 us, as one workgroup 30; 65536 of 64 experts, 8192 of them alike, 11 instead of 16).
 //
 // Bound by instruction issue: every compute unit looks at every entry, about 30 vector instructions per 256 of them
 // (compares with e, the smaller-id count in per-lane registers - the same with scalar popcounts was no faster -
