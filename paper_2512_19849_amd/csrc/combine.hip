@@ -139,9 +139,10 @@ static int tuned_combine_vpl(int forced, const CombineArgs &a) {
   return 1;
 }
 
-// (An instance per top-k up to 8 keeps all K loads of a slice in flight.  Against the loop for any K: 4096 tokens x 7168
-// top-7 75 us, was 97, for a wave per token cannot hide one load at a time; with a slice per wave top-3 and top-5 gain up
-// to 5%.)
+// (An instance per top-k up to 8 keeps all K loads of a slice in flight.  Against the loop for any K, one load at a time: a
+// wave per token cannot hide that, 4096 tokens x 7168 top-7 75 us, was 97; with a slice per wave top-3 gains up to 8%, top-5
+// up to 5% (4096 x 4096 33 and 34 us), and top-5 from 320 MB of rows on and top-7 from 200 MB on lose 1 to 6% (8192 x 8192
+// 134 and 131, 186 and 176): those take the loop.)
 template <int VPL>
 static void launch_combine_t(CombineArgs a, hipStream_t st, const LaunchTiming *tm) {
   const int nvec = a.H / 8;
@@ -149,7 +150,9 @@ static void launch_combine_t(CombineArgs a, hipStream_t st, const LaunchTiming *
   const long long items = (long long)a.T * a.parts;
   const unsigned grid = (unsigned)((items + 3) / 4);
   void *ev0 = tm ? tm->start : nullptr, *ev1 = tm ? tm->stop : nullptr;
-  switch (a.K) {
+  const long long bytes = min((long long)a.T * a.K, a.y_rows) * a.H * 2;
+  const bool loop = VPL == 1 && ((a.K == 5 && bytes >= 320000000) || (a.K == 7 && bytes >= 200000000));
+  switch (loop ? 0 : a.K) {
     case 1: launch_kernel(combine_kernel<VPL, 1>, dim3(grid), dim3(256), 0, st, ev0, ev1, a); break;
     case 2: launch_kernel(combine_kernel<VPL, 2>, dim3(grid), dim3(256), 0, st, ev0, ev1, a); break;
     case 3: launch_kernel(combine_kernel<VPL, 3>, dim3(grid), dim3(256), 0, st, ev0, ev1, a); break;

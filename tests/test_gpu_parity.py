@@ -882,6 +882,23 @@ def test_combine_one_wave_per_token_for_mid_sized_rows(epmod, oracle, H, monkeyp
         assert r.stats()["device_error"] == 0
 
 
+# top-5 and top-7 with a wave per slice: the last volume with all loads of a slice in flight, the first with one at a time
+@pytest.mark.parametrize("K,T", [(5, 3906), (5, 3907), (7, 1743), (7, 1744)])
+def test_combine_loads_in_flight_by_volume(epmod, oracle, K, T):
+    from paper_2512_19849_amd.runner import bits_to_bf16, bf16_to_bits
+    cfg = g.EPConfig("volume", T=T, H=8192, E=16, K=K, R=4, routing="uniform", seed=T)
+    idx, w = g.routing_all(cfg)
+    idx[0, 5, :] = -1
+    lay = oracle.layout(idx, cfg.E, cfg.R)
+    y = np.resize(g.activations(cfg, 0, tid=g.TID_Y, T=T), (T * K, cfg.H))
+    with _runner(epmod, cfg, num_proxy_threads=0) as r:
+        out = torch.full((T, cfg.H), 7.0, dtype=torch.bfloat16, device="cuda")
+        r.combine(bits_to_bf16(y), _dev(w[0]), _dev(lay["dst_row"][0]), out)
+        torch.cuda.synchronize()
+        assert _combine_check(oracle, bf16_to_bits(out), y, w[0], lay["dst_row"][0], K) == 0
+        assert r.stats()["device_error"] == 0
+
+
 def test_round_trip_identity_expert(epmod, oracle):
     """dispatch -> identity expert -> combine returns the input scaled by the
     sum of its weights; with K = 1 and w = 1 it is the input, bit for bit."""
