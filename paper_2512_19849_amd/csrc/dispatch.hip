@@ -180,8 +180,8 @@ EP_DEV void emit_drain(const DispatchArgs &a, int lane) {
 // the wait is before every row, every store or the first row only, as the register allocation falls.  Before every row is
 // best on the whole, us: ring off 8192 tokens x 4096 112, without waits 119; 1536 x 12288 47 and 52; one command per row 1536
 // x 9216 54 and 52, with a wait before every store 64.)
-// (GROUPS: one command per row.  Instances of their own keep both below 100 scalar registers, eight waves per SIMD: together
-// they take 103 to 105, and workgroups of 16 waves, two per compute unit, no longer all fit: 1536 x 16384 94 us, apart 90.)
+// (GROUPS: one command per row.  Instances of their own keep both at or below 98 scalar registers, by the compiler's count
+// eight waves per SIMD; together they take 103 to 105, seven waves: 1536 x 16384, 16 waves per workgroup, 94 us, apart 90.)
 // (Write-through stores without the streaming hint: with it the dispatch itself and a combine of other rows are up to 4%
 // faster, but whoever reads the rows next no longer finds any in the memory-side cache.  Step and a read of the received
 // rows, without / with, us: 4058 tokens x 7168 top-8 in FP8 182 / 194, 8116 tokens 365 / 380, 8239 x 4096 bf16 337 / 341.)
@@ -526,7 +526,8 @@ static size_t group_cmds_setup(DispatchArgs &a, int waves) {
   if (waves < 4 || waves > 16) waves = 16;  // (0 = not set)
   const int tpb = waves / a.parts;
   if (tpb >= 2) a.tokens_per_block = tpb;
-  const long long cmds = (long long)a.T * a.K, placed = (a.cmd_mode & EP_CMD_NO_PLACEMENT) ? 0 : min(cmds, (long long)a.recv_rows);
+  const long long cmds = (long long)a.T * a.K;
+  const long long placed = (a.cmd_mode & EP_CMD_NO_PLACEMENT) ? 0 : min(cmds, (long long)a.recv_rows);
   a.blocks_per_group = cmds > kGroupCmdsMax || placed * a.row_bytes > kGroupBytesMax
                            ? 1
                            : max(1, min(64 / a.K, a.T / 16) / a.tokens_per_block);
@@ -561,8 +562,8 @@ static void launch_dispatch_bf16_t(DispatchArgs a, const Tunables &tune, hipStre
   a.tokens_per_block = a.parts >= 4 ? 1 : 4 / a.parts;
   const size_t lds = group_cmds_setup(a, tune.per_token_waves);
   const int grid = max(1, (a.T + a.tokens_per_block - 1) / a.tokens_per_block);
-  launch_kernel(a.blocks_per_group ? dispatch_bf16_kernel<VPL, true> : dispatch_bf16_kernel<VPL, false>, dim3(grid), dim3(64 * a.parts * a.tokens_per_block), lds, st,
-                tm ? tm->start : nullptr, tm ? tm->stop : nullptr, a);
+  launch_kernel(a.blocks_per_group ? dispatch_bf16_kernel<VPL, true> : dispatch_bf16_kernel<VPL, false>, dim3(grid),
+                dim3(64 * a.parts * a.tokens_per_block), lds, st, tm ? tm->start : nullptr, tm ? tm->stop : nullptr, a);
 }
 
 template <int VPL>
@@ -573,8 +574,8 @@ static void launch_dispatch_fp8_t(DispatchArgs a, const Tunables &tune, hipStrea
   a.tokens_per_block = a.parts >= 4 ? 1 : 4 / a.parts;
   const size_t lds = group_cmds_setup(a, tune.per_token_waves);
   const int grid = max(1, (a.T + a.tokens_per_block - 1) / a.tokens_per_block);
-  launch_kernel(a.blocks_per_group ? dispatch_fp8_kernel<VPL, true> : dispatch_fp8_kernel<VPL, false>, dim3(grid), dim3(64 * a.parts * a.tokens_per_block), lds, st,
-                tm ? tm->start : nullptr, tm ? tm->stop : nullptr, a);
+  launch_kernel(a.blocks_per_group ? dispatch_fp8_kernel<VPL, true> : dispatch_fp8_kernel<VPL, false>, dim3(grid),
+                dim3(64 * a.parts * a.tokens_per_block), lds, st, tm ? tm->start : nullptr, tm ? tm->stop : nullptr, a);
 }
 
 int launch_dispatch(const DispatchArgs &a, int payload, const Tunables &tune, void *stream,
