@@ -233,13 +233,17 @@ __global__ __launch_bounds__(256) void layout_finish_kernel(LayoutArgs a) {
 // workgroups count alike for the same expert and each numbers the lists of its own share of the waves (40960 entries of
 // one expert 12 us, as one workgroup 30; 65536 of 64 experts, 8192 of them alike, 11 instead of 16).
 //
-// Bound by instruction issue: every compute unit looks at every entry, about 30 vector instructions per 256 of them
-// (compares with e, the smaller-id count in per-lane registers - the same with scalar popcounts was no faster -
-// and the next group's load in flight), so about 3 us per 32768 entries on top of 4 us of launch, first load,
-// barrier and stores.  Measured on MI355X against the forms before it (kernel time, us): 128 entries of 16 experts
-// 4.2 (one-workgroup form with LDS masks 5.3), 1024 of 256: 4.1 (7.5), 4096: 4.1 (11.0), 32768: 8.0 (two kernels
-// 16.7), 32768 over 32 sources: 7.2 (18.8), 32768 of 1024 experts: 14.6 (24.6).
+// Bound by instruction issue: every compute unit looks at every entry, about 15 vector instructions per 256 of them on
+// pairs of 16-bit ids (32-bit compares and per-lane counts, 35 instructions, took a third longer), the next two groups'
+// loads in flight (one: 0.5 us more when the table comes from memory; four, or the whole table: no gain, and longer code,
+// which a kernel this short waits for).  On top of that 4 us of launch, first load, barrier and stores.  Measured on MI355X
+// against the forms before it, between queued calls (us): 128 entries of 16 experts 4.2 (one-workgroup form with LDS masks
+// 5.3), 4096 of 256: 4.1 (11.0), 32768: 7.3 (32-bit compares 8.0, two kernels 16.7), 32768 over 32 sources: 6.8 (7.4, 18.8),
+// 65536 of 128 experts 8.3 (9.6), 65536 of 256, Zipf 11.3 (13.1).
+typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 typedef int i32x4_any __attribute__((ext_vector_type(4), aligned(4)));  // 16 bytes at any 4-byte boundary
+
+constexpr int kLayoutAhead = 2;  // groups of a wave whose loads are in flight
 
 __global__ __launch_bounds__(1024) void layout_expert_kernel(LayoutArgs a) {
   extern __shared__ unsigned short s_list[];  // [waves][seg * 64]
@@ -256,46 +260,69 @@ __global__ __launch_bounds__(1024) void layout_expert_kernel(LayoutArgs a) {
   if (S > 1)
     for (int s = tid; s <= S; s += blockDim.x) s_first[s] = 0;
 
-  auto load = [&](unsigned ib) {
-    const unsigned i = ib + lane * 4;
-    i32x4_any v = {-1, -1, -1, -1};
-    if (ib + 256 <= n) {
-      v = *(const i32x4_any *)(a.idx + i);
-    } else {
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-        if (i + j < n) v[j] = a.idx[i + j];
-    }
-    return v;
-  };
   // entries without an expert get -1: the table is shared out over all waves of the grid for that
   const unsigned i_mine = ((part * E + e) * nw + wave) * 64 + lane;
   const int v_mine = i_mine < n ? a.idx[i_mine] : 0;
-  int quads = 0;                // list length
-  int cnt = 0, lt = 0, rl = 0;  // per lane: entries of e, of a smaller id, of an id below the end of e's rank
-  i32x4_any v, nxt;
-  if (i0 < lim) nxt = load(i0);
-#pragma nounroll
-  for (unsigned ib = i0; ib < lim; ib += 256) {
-    v = nxt;
-    if (ib + 256 < lim) nxt = load(ib + 256);
-    const bool hit = v[0] == e || v[1] == e || v[2] == e || v[3] == e;
-    const unsigned long long any = __ballot(hit);
+  int quads = 0;  // list length
+  int cnt = 0;    // per lane: entries of e
+  // Ids as pairs of 16 bits (saturated: -1 and ids out of range stay above every expert).  min(max(e + 1 - id, 0), 2) is 0,
+  // 1 or 2 for an id above, equal to or below e: its bit 0 finds the entries of e, its sum counts the smaller ones.  (A lane
+  // sees at most 64 entries.)
+  u16x2 weigh = {0, 0}, below = {0, 0};
+  const u16x2 e1 = (u16x2)(unsigned short)(e + 1), re = (u16x2)(unsigned short)rank_end;
+  auto look = [&](unsigned ib, const i32x4_any &v) {
+    const u16x2 p0 = __builtin_amdgcn_cvt_pk_u16(v[0], v[1]), p1 = __builtin_amdgcn_cvt_pk_u16(v[2], v[3]);
+    const u16x2 t0 = __builtin_elementwise_min(__builtin_elementwise_sub_sat(e1, p0), (u16x2)(unsigned short)2);
+    const u16x2 t1 = __builtin_elementwise_min(__builtin_elementwise_sub_sat(e1, p1), (u16x2)(unsigned short)2);
+    weigh += t0;
+    weigh += t1;
+    const unsigned b0 = __builtin_bit_cast(unsigned, t0), b1 = __builtin_bit_cast(unsigned, t1);
+    const bool hit = ((b0 | b1) & 0x10001u) != 0u;
+    const unsigned long long any = __builtin_amdgcn_ballot_w64(hit);
     if (any) {
       if (hit) {
-        const unsigned nib = (v[0] == e ? 1u : 0u) | (v[1] == e ? 2u : 0u) | (v[2] == e ? 4u : 0u) | (v[3] == e ? 8u : 0u);
+        const unsigned u = (b0 & 0x10001u) | (b1 & 0x10001u) << 2, nib = (u | u >> 15) & 15u;
         list[quads + __builtin_amdgcn_mbcnt_hi((unsigned)(any >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)any, 0u))] =
             (unsigned short)((((ib - i0) >> 2) + lane) << 4 | nib);
         cnt += __popc(nib);
       }
       quads += __popcll(any);
     }
+    if (first_of_rank) {
+      const u16x2 one = (u16x2)(unsigned short)1;
+      below += __builtin_elementwise_min(__builtin_elementwise_sub_sat(re, p0), one);
+      below += __builtin_elementwise_min(__builtin_elementwise_sub_sat(re, p1), one);
+    }
+  };
+  // full groups first, then what is left of the table (fewer than 256 entries, the last wave's)
+  const unsigned nf = n & ~255u, limf = min(lim, nf);
+  if (i0 < limf) {
+    auto load = [&](unsigned ib) { return *(const i32x4_any *)(a.idx + min(ib, nf - 256u) + lane * 4u); };
+    i32x4_any q[kLayoutAhead];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      lt += (unsigned)v[j] < (unsigned)e;
-      rl += (unsigned)v[j] < rank_end;
+    for (int j = 0; j < kLayoutAhead; ++j) q[j] = load(i0 + j * 256u);
+#pragma nounroll
+    for (unsigned ib = i0; ib < limf; ib += kLayoutAhead * 256u) {
+#pragma unroll
+      for (int j = 0; j < kLayoutAhead; ++j) {
+        const unsigned at = ib + j * 256u;
+        if (at >= limf) break;
+        const i32x4_any v = q[j];
+        q[j] = load(at + kLayoutAhead * 256u);
+        look(at, v);
+      }
     }
   }
+  if (i0 < lim && lim > nf) {
+    const unsigned i = nf + lane * 4u;
+    i32x4_any v = {-1, -1, -1, -1};
+#pragma unroll
+    for (unsigned j = 0; j < 4; ++j)
+      if (i + j < n) v[j] = a.idx[i + j];
+    look(nf, v);
+  }
+  int lt = ((int)weigh[0] + (int)weigh[1] - cnt) >> 1;  // per lane: entries of an id smaller than e
+  int rl = (int)below[0] + (int)below[1];              // ... and (first expert of a rank) below the end of e's rank
   cnt = wave_sum(cnt);
   lt = wave_sum(lt);
   rl = wave_sum(rl);

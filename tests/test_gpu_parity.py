@@ -174,6 +174,23 @@ def test_layout_busy_expert(epmod, oracle, S, T, K, E, R):
         assert r.stats()["device_error"] == 0
 
 
+# less than a group of 256, full groups, full groups and a rest, a lane's largest share, several sources
+@pytest.mark.parametrize("S,T,K,E,R", [(1, 41, 2, 8, 2), (1, 1024, 4, 256, 16), (1, 771, 5, 1024, 8), (1, 8192, 8, 128, 8),
+                                       (4, 300, 3, 40, 5)])
+def test_layout_ids_that_are_no_expert(epmod, oracle, S, T, K, E, R):
+    """Ids beyond the experts, in 16 bits and not (their low halves name experts), and negative ones: dropped, reported."""
+    rng = np.random.default_rng(E)
+    idx = np.argsort(rng.random((S, T, E)), axis=-1)[..., :K].astype(np.int32)
+    bad = np.array([E, 65535, 65536 + 3, 131072, 2**31 - 1, -2, -65536 + 1, -2**31], np.int32)
+    where = rng.random(idx.shape) < 0.2
+    idx = np.where(where, bad[rng.integers(0, len(bad), idx.shape)], idx).astype(np.int32)
+    with _runner(epmod, g.EPConfig("bad", T=T, H=128, E=E, K=K, R=R, S=S)) as r:
+        lay = r.layout(_dev(idx))
+        torch.cuda.synchronize()
+        _check_layout(oracle, lay.numpy(), np.where(where, -1, idx).astype(np.int32), E, R)
+        assert r.stats()["device_error"] == epmod.EP_EBOUNDS
+
+
 # smallest, a decode table over 32 sources, a batch (each of a size that takes one launch otherwise), more than 8 ids per
 # token, and a table that takes the two kernels anyway
 @pytest.mark.parametrize("S,T,K,E,R", [(1, 5, 2, 8, 2), (32, 128, 8, 256, 32), (1, 4096, 8, 256, 16), (2, 300, 12, 64, 8),
