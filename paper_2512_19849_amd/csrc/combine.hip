@@ -54,9 +54,9 @@ EP_DEV void combine_slices(const u32x4 *y, u32x4 *out, const int (&rows)[KT], co
 
 template <int VPL, int KT>
 __global__ __launch_bounds__(256) void combine_kernel(CombineArgs a) {
-  const int wave = threadIdx.x >> 6, lane = lane_id();
-  const long long item = (long long)blockIdx.x * 4 + wave;
-  const int t_launch = (int)(item / a.parts), part = (int)(item % a.parts);
+  const int lane = lane_id();
+  const unsigned item = blockIdx.x * 4 + wave_id();
+  const int t_launch = (int)(item / (unsigned)a.parts), part = (int)(item % (unsigned)a.parts);
   if (t_launch >= a.T) return;
   // With fresh rows the grid starts at the end of the token range where they are (the last tokens,
   // or the first ones when the kernel that wrote them went backwards) and takes the newest first:
@@ -280,9 +280,9 @@ EP_DEV void fma_rows(float (&acc)[8], unsigned long long ks, int row, float wt, 
 // 7168 357, streaming 346.
 template <int KT>
 __global__ __launch_bounds__(256) void combine_partial_kernel(CombinePartialArgs a) {
-  const int wave = threadIdx.x >> 6, lane = lane_id();
-  const long long item = (long long)blockIdx.x * 4 + wave;
-  const int t = (int)(item / a.parts), part = (int)(item % a.parts);
+  const int lane = lane_id();
+  const unsigned item = blockIdx.x * 4 + wave_id();
+  const int t = (int)(item / (unsigned)a.parts), part = (int)(item % (unsigned)a.parts);
   if (t >= a.T) return;
   const int K = KT > 0 ? KT : a.K;
   int row = -1, fk = -1, prow = -1;

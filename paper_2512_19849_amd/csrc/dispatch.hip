@@ -213,9 +213,9 @@ EP_DEV void place_token_bf16(const DispatchArgs &a, const int row_of_lane, unsig
 
 template <int VPL, bool GROUPS>
 __global__ void dispatch_bf16_kernel(DispatchArgs a) {
-  const int wave = threadIdx.x >> 6, lane = lane_id();
-  const int part = wave % a.parts;
-  const int t = token_block(a) * a.tokens_per_block + wave / a.parts;
+  const int wave = wave_id(), lane = lane_id();
+  const int part = (unsigned)wave % (unsigned)a.parts;
+  const int t = token_block(a) * a.tokens_per_block + (unsigned)wave / (unsigned)a.parts;
   const bool ring_on = (a.cmd_mode & EP_CMD_MODE_MASK) != EP_CMD_NONE;
   const bool ordered = (a.cmd_mode & EP_CMD_MODE_MASK) == EP_CMD_CHUNK32_ORDERED;
   if (ring_on && !ordered && blockIdx.x == 0 && wave == 0) emit_leading_atomics<GROUPS>(a, lane);
@@ -308,9 +308,9 @@ EP_DEV void place_token_fp8(const DispatchArgs &a, const TokenMeta &m, unsigned 
 
 template <int VPL, bool GROUPS>
 __global__ void dispatch_fp8_kernel(DispatchArgs a) {
-  const int wave = threadIdx.x >> 6, lane = lane_id();
-  const int part = wave % a.parts;
-  const int t = token_block(a) * a.tokens_per_block + wave / a.parts;
+  const int wave = wave_id(), lane = lane_id();
+  const int part = (unsigned)wave % (unsigned)a.parts;
+  const int t = token_block(a) * a.tokens_per_block + (unsigned)wave / (unsigned)a.parts;
   const bool ring_on = (a.cmd_mode & EP_CMD_MODE_MASK) != EP_CMD_NONE;
   const bool ordered = (a.cmd_mode & EP_CMD_MODE_MASK) == EP_CMD_CHUNK32_ORDERED;
   if (ring_on && !ordered && blockIdx.x == 0 && wave == 0) emit_leading_atomics<GROUPS>(a, lane);
