@@ -145,6 +145,7 @@ struct CopyBatchArgs {
   const CopyDesc *host_descs;  // the same array as the host sees it
   int n;
   unsigned max_len16;
+  void *done;                  // hipEvent_t that fires when the batch has been copied
 };
 // The descriptors of small batches and of chunks travel inside the kernel-argument block instead, up to this many
 // per launch.

@@ -200,11 +200,10 @@ void launch_batch(ep_handle *h, ProxyThread &P) {
   if (P.cur.n == 0) return;
   P.cur.descs = P.d_descs + (size_t)P.cur_slot * kCopyBatchMax;
   P.cur.host_descs = P.descs + (size_t)P.cur_slot * kCopyBatchMax;
+  P.cur.done = P.events[P.cur_slot];
   {
-    std::lock_guard<std::mutex> g(h->copy_mu);  // launch and event stay adjacent in the shared stream
-    if (launch_copy_batch(P.cur, h->copy_stream) != 0 ||
-        hipEventRecord(P.events[P.cur_slot], h->copy_stream) != hipSuccess)
-      fail_hip(h);
+    std::lock_guard<std::mutex> g(h->copy_mu);  // the launches of a batch stay adjacent in the shared stream
+    if (launch_copy_batch(P.cur, h->copy_stream) != 0) fail_hip(h);
   }
   bump(P.copy_batches, 1);
   P.inflight.push_back(ProxyThread::Batch{P.cur_slot, std::move(P.cur_notices)});

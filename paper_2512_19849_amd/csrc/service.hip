@@ -51,12 +51,15 @@ __global__ __launch_bounds__(256) void copy_batch_kernel(const CopyBatchArgs b, 
 // Up to 256 copies fit the argument block of one launch: 256 rows of 14 KB 3.3 us against 6.1 with the descriptors
 // read from pinned memory.  Beyond that a second launch (2.5 us of host time each) costs more than the reads - unless
 // the copies are chunks (over 32 KiB), which fill the chip by the launch.
+// The batch's event fires with the completion signal of the (last) kernel itself.  Recorded behind it, it is a packet of its
+// own that the next launch on the shared stream has to wait for: a step of 4096 tokens x 7168 in about twelve batches of chunks
+// took 418 us, now 380; 128 tokens x 7168 in FP8 in four batches 89, now 82.
 int launch_copy_batch(const CopyBatchArgs &b, void *stream) {
   if (b.n <= 0) return 0;
   const unsigned pieces = (b.max_len16 + 255) / 256;
   if (b.n > kCopyArgMax && b.max_len16 <= 2048) {
-    hipLaunchKernelGGL(copy_batch_kernel, dim3((unsigned)((b.n + kCopyGroup - 1) / kCopyGroup)), dim3(256), 0,
-                       (hipStream_t)stream, b, (int)pieces);
+    hipExtLaunchKernelGGL(copy_batch_kernel, dim3((unsigned)((b.n + kCopyGroup - 1) / kCopyGroup)), dim3(256), 0,
+                          (hipStream_t)stream, nullptr, (hipEvent_t)b.done, 0, b, (int)pieces);
     return (int)hipGetLastError();
   }
   CopyArgBatch a;
@@ -65,7 +68,8 @@ int launch_copy_batch(const CopyBatchArgs &b, void *stream) {
   for (int first = 0; first < b.n; first += kCopyArgMax) {
     const int m = b.n - first < kCopyArgMax ? b.n - first : kCopyArgMax;
     for (int i = 0; i < m; ++i) a.d[i] = b.host_descs[first + i];
-    hipLaunchKernelGGL(copy_args_kernel, dim3(pieces ? pieces : 1, (unsigned)m), dim3(256), 0, (hipStream_t)stream, a);
+    hipExtLaunchKernelGGL(copy_args_kernel, dim3(pieces ? pieces : 1, (unsigned)m), dim3(256), 0, (hipStream_t)stream, nullptr,
+                          first + m == b.n ? (hipEvent_t)b.done : nullptr, 0, a);
   }
   return (int)hipGetLastError();
 }
