@@ -144,7 +144,7 @@ struct CopyBatchArgs {
   const CopyDesc *descs;       // device address of the pinned array
   const CopyDesc *host_descs;  // the same array as the host sees it
   int n;
-  unsigned max_len16;
+  unsigned max_len16, min_len16;
   void *done;                  // hipEvent_t that fires when the batch has been copied
 };
 // The descriptors of small batches and of chunks travel inside the kernel-argument block instead, up to this many
@@ -155,6 +155,17 @@ struct CopyArgBatch {
   char *dst_base;
   CopyDesc d[kCopyArgMax];
 };
+// ... and copies of one length, which the rows of a per-token dispatch are, without it.
+constexpr int kCopyRowMax = 496;
+struct CopyRowBatch {
+  const char *src_base;
+  char *dst_base;
+  unsigned len16;
+  struct {
+    unsigned src16, dst16;
+  } d[kCopyRowMax];
+};
+static_assert(sizeof(CopyRowBatch) <= 4000 && sizeof(CopyArgBatch) <= 4000, "kernel arguments");
 
 // Ring-buffer channels of the high-throughput mode: one workgroup per slice, sending and receiving in turns.
 struct HtRingArgs {

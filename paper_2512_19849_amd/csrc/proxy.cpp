@@ -240,6 +240,7 @@ void queue_copy(ep_handle *h, ProxyThread &P, const char *sbase, char *dbase, ui
       CopyDesc{(unsigned)(so >> 4), (unsigned)(dof >> 4), (unsigned)(len >> 4)};
   if (notice) P.cur_notices.push_back(*notice);
   if ((unsigned)(len >> 4) > P.cur.max_len16) P.cur.max_len16 = (unsigned)(len >> 4);
+  if ((unsigned)(len >> 4) < P.cur.min_len16 || P.cur.n == 0) P.cur.min_len16 = (unsigned)(len >> 4);
   bump(P.copied_bytes, len);
   if (++P.cur.n == kCopyBatchMax) launch_batch(h, P);
 }

@@ -12,12 +12,24 @@ namespace ep {
 // kernel-argument block.  Short waves that load once and store once, past the caches, are what the memory system
 // takes best: 256 chunks of 6..458 KB per launch 5.8 TB/s (read + written), with plain stores 5.1, with four vectors
 // per thread 4.9, as 64 grid-striding workgroups per chunk (the form before) 5.1; 64 chunks per launch 4.8 against 4.2.
+// (Write-through as well as streaming: when a batch's event fires its rows are in memory, whatever the kernel's end does with
+// the caches.  Step of 4096 tokens x 7168 376 us, streaming alone 378, with a read of the rows behind it 513 and 517.)
+EP_DEV void store_streaming(u32x4 *p, const u32x4 &v) {
+  asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1 nt" ::"v"(p), "v"(v) : "memory");
+}
+
 __global__ __launch_bounds__(256) void copy_args_kernel(const CopyArgBatch b) {
   const CopyDesc d = b.d[blockIdx.y];
   const unsigned i = blockIdx.x * 256 + threadIdx.x;
   if (i < d.len16)
-    __builtin_nontemporal_store(__builtin_nontemporal_load((const u32x4 *)b.src_base + d.src16 + i),
-                                (u32x4 *)b.dst_base + d.dst16 + i);
+    store_streaming((u32x4 *)b.dst_base + d.dst16 + i, __builtin_nontemporal_load((const u32x4 *)b.src_base + d.src16 + i));
+}
+
+// The same for rows of one length.
+__global__ __launch_bounds__(256) void copy_rows_kernel(const CopyRowBatch b) {
+  const unsigned i = blockIdx.x * 256 + threadIdx.x, s = b.d[blockIdx.y].src16, o = b.d[blockIdx.y].dst16;
+  if (i < b.len16)
+    store_streaming((u32x4 *)b.dst_base + o + i, __builtin_nontemporal_load((const u32x4 *)b.src_base + s + i));
 }
 
 // Many rows: a workgroup fetches kCopyGroup descriptors with one read over PCIe, then each wave moves pieces of 256
@@ -44,12 +56,12 @@ __global__ __launch_bounds__(256) void copy_batch_kernel(const CopyBatchArgs b, 
       if (i0 + j * 64 < len16) v[j] = __builtin_nontemporal_load(s + i0 + j * 64);
 #pragma unroll
     for (int j = 0; j < 4; ++j)
-      if (i0 + j * 64 < len16) __builtin_nontemporal_store(v[j], o + i0 + j * 64);
+      if (i0 + j * 64 < len16) store_streaming(o + i0 + j * 64, v[j]);
   }
 }
 
-// Up to 256 copies fit the argument block of one launch: 256 rows of 14 KB 3.3 us against 6.1 with the descriptors
-// read from pinned memory.  Beyond that a second launch (2.5 us of host time each) costs more than the reads - unless
+// Up to 256 copies, or 496 rows of one length, fit the argument block of one launch: 256 rows of 7 KB 3.5 us against 6.0 with
+// the descriptors read from pinned memory (a step of 256 tokens x 7168 top-8 in bf16 94 us, now 89).  Beyond that a second launch (2.5 us of host time each) costs more than the reads - unless
 // the copies are chunks (over 32 KiB), which fill the chip by the launch.
 // The batch's event fires with the completion signal of the (last) kernel itself.  Recorded behind it, it is a packet of its
 // own that the next launch on the shared stream has to wait for: a step of 4096 tokens x 7168 in about twelve batches of chunks
@@ -57,6 +69,16 @@ __global__ __launch_bounds__(256) void copy_batch_kernel(const CopyBatchArgs b, 
 int launch_copy_batch(const CopyBatchArgs &b, void *stream) {
   if (b.n <= 0) return 0;
   const unsigned pieces = (b.max_len16 + 255) / 256;
+  if (b.n <= kCopyRowMax && b.min_len16 == b.max_len16) {
+    CopyRowBatch a;
+    a.src_base = b.src_base;
+    a.dst_base = b.dst_base;
+    a.len16 = b.max_len16;
+    for (int i = 0; i < b.n; ++i) a.d[i] = {b.host_descs[i].src16, b.host_descs[i].dst16};
+    hipExtLaunchKernelGGL(copy_rows_kernel, dim3(pieces ? pieces : 1, (unsigned)b.n), dim3(256), 0, (hipStream_t)stream,
+                          nullptr, (hipEvent_t)b.done, 0, a);
+    return (int)hipGetLastError();
+  }
   if (b.n > kCopyArgMax && b.max_len16 <= 2048) {
     hipExtLaunchKernelGGL(copy_batch_kernel, dim3((unsigned)((b.n + kCopyGroup - 1) / kCopyGroup)), dim3(256), 0,
                           (hipStream_t)stream, nullptr, (hipEvent_t)b.done, 0, b, (int)pieces);

@@ -482,6 +482,16 @@ def test_proxy_copies_rows_at_the_edges_of_pieces(epmod, oracle, H, T):
     _check_commands(epmod, oracle, cfg, out, "per_token")
 
 
+# batches of up to 496 rows of one length travel in one argument block: one row, a full block, a row more, pieces of 256
+# vectors and one vector more
+@pytest.mark.parametrize("H,T,K", [(1024, 1, 1), (2048, 62, 8), (2176, 71, 7), (4096, 31, 16), (128, 124, 4)])
+def test_proxy_copies_small_batches_of_rows(epmod, oracle, H, T, K):
+    cfg = g.EPConfig(f"rows{H}", T=T, H=H, E=32, K=K, R=4, routing="uniform")
+    out = _dispatch_case(epmod, oracle, cfg, T, 0.0, epmod.EP_CMD_PER_TOKEN, proxy_writes=True, num_proxy_threads=1,
+                         num_channels=1)
+    _check_commands(epmod, oracle, cfg, out, "per_token")
+
+
 @pytest.mark.parametrize("cid,T,mask,window,mode,threads", [
     (3, None, 0.0, 0, "per_token", 4), (3, 50, 0.25, 5, "per_token", 1), (3, None, 0.2, 6, "chunk32", 2),
     (5, 700, 0.0, 16, "per_token", 3), (5, 1000, 0.05, 0, "chunk32", 4), (4, 300, 0.0, 8, "chunk32_ordered", 4),
