@@ -340,14 +340,10 @@ int ep_proxy_stop(ep_handle *h) {
   h->stop.store(true, std::memory_order_release);
   for (int i = 0; i < h->nthreads; ++i)
     if (h->threads[i].th.joinable()) h->threads[i].th.join();
-  for (int i = 0; i < h->nthreads; ++i) {
-    ProxyThread &P = h->threads[i];
-    if (!P.gpu_ready) continue;
-    for (hipEvent_t &e : P.events)
-      if (e) (void)hipEventDestroy(e);
-    if (P.descs) (void)hipHostFree(P.descs);
-  }
-  if (h->copy_stream) (void)hipStreamDestroy(h->copy_stream);
+  for (hipEvent_t &e : h->copies.events)
+    if (e) (void)hipEventDestroy(e);
+  if (h->copies.descs) (void)hipHostFree(h->copies.descs);
+  if (h->copies.stream) (void)hipStreamDestroy(h->copies.stream);
   drop_timed(h);
   free_all(h);
   return rc;
@@ -367,26 +363,27 @@ int ep_register_heaps(ep_handle *h, const void *d_src_base, int64_t src_bytes, v
   if (src_bytes > (1ll << 36) || dst_bytes > (1ll << 36)) return EP_EINVAL;  // offsets travel as 32-bit counts of 16 bytes
   if (h->nthreads < 1) return EP_EINVAL;
   // What the proxy needs to issue the writes, made once, on first registration: ONE stream (default
-  // priority) shared by all proxy threads, and completion events per thread.  One stream, because a
+  // priority) and a set of batches shared by all proxy threads.  One stream, because a
   // process has few hardware queues (4 here) and streams beyond that share one: a copy kernel queued
   // behind a dispatch kernel that is itself blocked on a Drain (which waits for that copy) would never
   // start.  The caller's stream and this one get queues of their own as long as the process keeps
   // fewer streams than hardware queues; if they ever do collide, the kernel's bounded wait reports
   // EP_ETIMEOUT.
-  if (!h->copy_stream && !HIP_OK(hipStreamCreateWithFlags(&h->copy_stream, hipStreamNonBlocking))) return EP_EHIP;
-  for (int i = 0; i < h->nthreads; ++i) {
-    ProxyThread &P = h->threads[i];
-    if (P.gpu_ready) continue;
-    for (hipEvent_t &e : P.events)
-      if (!HIP_OK(hipEventCreateWithFlags(&e, hipEventDisableTiming))) return EP_EHIP;
-    void *q = nullptr, *dq = nullptr;
-    if (!HIP_OK(hipHostMalloc(&q, sizeof(CopyDesc) * ProxyThread::kBatchSlots * kCopyBatchMax,
+  CopyPool &C = h->copies;
+  if (!C.stream && !HIP_OK(hipStreamCreateWithFlags(&C.stream, hipStreamNonBlocking))) return EP_EHIP;
+  for (hipEvent_t &e : C.events)
+    if (!e && !HIP_OK(hipEventCreateWithFlags(&e, hipEventDisableTiming))) return EP_EHIP;
+  if (!C.descs) {
+    void *q = nullptr;
+    if (!HIP_OK(hipHostMalloc(&q, sizeof(CopyDesc) * CopyPool::kSlots * kCopyBatchMax,
                               hipHostMallocMapped | hipHostMallocCoherent)))
       return EP_ENOMEM;
-    P.descs = (CopyDesc *)q;
-    if (!HIP_OK(hipHostGetDevicePointer(&dq, q, 0))) return EP_EHIP;
-    P.d_descs = (CopyDesc *)dq;
-    P.gpu_ready = true;
+    C.descs = (CopyDesc *)q;
+  }
+  if (!C.d_descs) {
+    void *dq = nullptr;
+    if (!HIP_OK(hipHostGetDevicePointer(&dq, C.descs, 0))) return EP_EHIP;
+    C.d_descs = (CopyDesc *)dq;
   }
   h->src_bytes = (uint64_t)src_bytes;
   h->dst_bytes = (uint64_t)dst_bytes;

@@ -132,6 +132,23 @@ struct Outbound {
   uint64_t opened_ns = 0;     // packing: when its first row was polled
 };
 
+// The copies of all proxy threads on their way through the one shared stream, which takes batches one after the other.  A
+// thread adds its copies to the open batch; if nobody is launching it launches that batch, and what other threads add
+// meanwhile leaves together with the next one.
+struct CopyPool {
+  static constexpr int kSlots = 16;
+  std::mutex mu;           // guards `launching`, `open`, `number` and the open batch's descriptors
+  bool launching = false;  // a thread is handing batches to the device
+  CopyBatchArgs open{};    // the batch being filled
+  uint64_t number = 0;     // ... its number; descriptors and event are those of slot number % kSlots
+  hipStream_t stream = nullptr;
+  hipEvent_t events[kSlots] = {};
+  CopyDesc *descs = nullptr;    // pinned host [kSlots][kCopyBatchMax]
+  CopyDesc *d_descs = nullptr;  // the same memory as the device sees it
+  std::atomic<uint64_t> launched{0}, done{0};  // batches below `done` have been copied, those up to `launched` are under way
+  std::mutex poll_mu;      // held by the one thread that asks the device which batches are finished
+};
+
 struct alignas(64) ProxyThread {
   int tid = 0;
   // no pacing, packing, reordering transport, sender-side fence or event log configured: a Write whose
@@ -146,21 +163,17 @@ struct alignas(64) ProxyThread {
   std::vector<std::deque<int32_t>> sender_parked;  // sender-side fence: atomics not yet sent, per (source, expert)
   std::vector<uint8_t> atomic_flying;              // ... and whether one of that expert is on its way
   std::vector<WireEvent> window;            // in-flight immediates (reordering hook)
-  // proxy-performed peer writes (registered heaps): descriptors of the batch being filled, and the
-  // batches in flight with the arrival notices they will release when their copy kernel is done
-  static constexpr int kBatchSlots = 8;
-  hipEvent_t events[kBatchSlots] = {};
-  CopyDesc *descs = nullptr;    // pinned host [kBatchSlots][kCopyBatchMax]
-  CopyDesc *d_descs = nullptr;  // the same memory as the device sees it
-  CopyBatchArgs cur{};
+  // proxy-performed peer writes (registered heaps): this thread's copies that no batch holds yet, with the arrival
+  // notices behind them, and the notices of its copies in flight, by the number of their batch
+  std::vector<CopyDesc> copies;
+  const char *copies_src = nullptr;
+  char *copies_dst = nullptr;
+  std::vector<WireEvent> copies_notices;
   struct Batch {
-    int slot;
+    uint64_t number;
     std::vector<WireEvent> notices;
   };
   std::deque<Batch> inflight;
-  std::vector<WireEvent> cur_notices;
-  int cur_slot = 0;
-  bool gpu_ready = false;
   // ordered (high-throughput) channels: next sequence number and early arrivals per (source, destination rank)
   std::vector<uint32_t> next_seq;
   std::vector<ReorderBuf> early;
@@ -216,8 +229,7 @@ struct ep_handle {
   std::atomic<char *> dst_base{nullptr};
   uint64_t src_bytes = 0, dst_bytes = 0;
   int device = 0;
-  hipStream_t copy_stream = nullptr;  // the proxy's copy kernels (all threads; launches under copy_mu)
-  std::mutex copy_mu;
+  ep::CopyPool copies;
   // Barrier: a counter and a generation shared by the peer processes of one node
   struct SharedBarrier {
     std::atomic<uint32_t> arrived;

@@ -194,55 +194,116 @@ void fail_hip(ep_handle *h) {
   h->proxy_error.compare_exchange_strong(zero, EP_EHIP);
 }
 
-// Hands the batch being filled to the device: one copy kernel on this thread's stream, an event
-// behind it.  Its notices stay with the batch until the event has fired.
-void launch_batch(ep_handle *h, ProxyThread &P) {
-  if (P.cur.n == 0) return;
-  P.cur.descs = P.d_descs + (size_t)P.cur_slot * kCopyBatchMax;
-  P.cur.host_descs = P.descs + (size_t)P.cur_slot * kCopyBatchMax;
-  P.cur.done = P.events[P.cur_slot];
-  {
-    std::lock_guard<std::mutex> g(h->copy_mu);  // the launches of a batch stay adjacent in the shared stream
-    if (launch_copy_batch(P.cur, h->copy_stream) != 0) fail_hip(h);
-  }
-  bump(P.copy_batches, 1);
-  P.inflight.push_back(ProxyThread::Batch{P.cur_slot, std::move(P.cur_notices)});
-  P.cur_notices.clear();
-  P.cur.n = 0;
-  P.cur.max_len16 = 0;
-  P.cur_slot = (P.cur_slot + 1) % ProxyThread::kBatchSlots;
-}
-
-// Completion polling (the stand-in for polling the send completion queue): batches finish in
-// order; a finished batch releases its arrival notices to the receiver half.
-enum ReapMode { kReapReady, kReapOne, kReapAll };
-void reap_batches(ep_handle *h, ProxyThread &P, ReapMode mode) {
-  while (!P.inflight.empty()) {
-    ProxyThread::Batch &b = P.inflight.front();
-    hipError_t e = mode == kReapReady ? hipEventQuery(P.events[b.slot]) : hipEventSynchronize(P.events[b.slot]);
+// Takes note of finished batches (the stand-in for polling the send completion queue; batches finish in order).  One
+// thread at a time asks the device, the others read what it found.
+void poll_batches(ep_handle *h) {
+  CopyPool &C = h->copies;
+  std::unique_lock<std::mutex> g(C.poll_mu, std::try_to_lock);
+  if (!g.owns_lock()) return;
+  uint64_t n = C.done.load(std::memory_order_relaxed);
+  for (; n < C.launched.load(std::memory_order_acquire); C.done.store(++n, std::memory_order_release)) {
+    const hipError_t e = hipEventQuery(C.events[n % CopyPool::kSlots]);
     if (e == hipErrorNotReady) return;
     if (e != hipSuccess) fail_hip(h);
-    for (const WireEvent &ev : b.notices) transmit(h, P, ev);
-    P.inflight.pop_front();
-    if (mode == kReapOne) return;
+  }
+}
+
+// Hands the open batch to the device, and again what has been added meanwhile.  `lk` holds C.mu and C.launching is false.
+// With kCopiesAhead batches under way the open one waits and grows: more launches in the queue do not start any copy
+// earlier.  (Step of 4096 tokens x 7168 with chunks, us: no limit 372 in 26 batches, three 348 in 16, two 349, one at a time
+// 362; a batch per thread, each with its launches, 370.  512 x 4096 82, a batch per thread 115; 16 tokens by rows 60 and 84.)
+constexpr uint64_t kCopiesAhead = 3;
+void launch_open(ep_handle *h, ProxyThread &P, std::unique_lock<std::mutex> &lk) {
+  CopyPool &C = h->copies;
+  C.launching = true;
+  while (C.open.n && C.number - C.done.load(std::memory_order_acquire) < kCopiesAhead) {
+    CopyBatchArgs b = C.open;
+    const uint64_t number = C.number++;
+    const size_t slot = number % CopyPool::kSlots;
+    C.open.n = 0;
+    lk.unlock();
+    b.host_descs = C.descs + slot * kCopyBatchMax;
+    b.descs = C.d_descs + slot * kCopyBatchMax;
+    b.done = C.events[slot];
+    if (launch_copy_batch(b, C.stream) != 0) fail_hip(h);
+    C.launched.store(number + 1, std::memory_order_release);
+    bump(P.copy_batches, 1);
+    lk.lock();
+  }
+  C.launching = false;
+}
+
+// This thread's copies join the open batch.  Their notices stay with it until its event has fired (the last batch's, where
+// the copies did not fit one).
+void launch_copies(ep_handle *h, ProxyThread &P) {
+  if (P.copies.empty()) return;
+  CopyPool &C = h->copies;
+  std::unique_lock<std::mutex> lk(C.mu);
+  for (size_t at = 0; at < P.copies.size();) {
+    CopyBatchArgs &b = C.open;
+    const bool other = b.n && (b.src_base != P.copies_src || b.dst_base != P.copies_dst || b.n == kCopyBatchMax);
+    if (other && !C.launching && C.number - C.done.load(std::memory_order_acquire) < kCopiesAhead) {
+      launch_open(h, P, lk);
+      continue;
+    }
+    // (a slot is free once the batch that had it is done)
+    if (other || (b.n == 0 && C.number - C.done.load(std::memory_order_acquire) >= CopyPool::kSlots)) {
+      lk.unlock();
+      poll_batches(h);
+      std::this_thread::yield();
+      lk.lock();
+      continue;
+    }
+    if (b.n == 0) {
+      b.src_base = P.copies_src;
+      b.dst_base = P.copies_dst;
+      b.max_len16 = 0;
+      b.min_len16 = ~0u;
+    }
+    CopyDesc *descs = C.descs + C.number % CopyPool::kSlots * kCopyBatchMax;
+    for (; at < P.copies.size() && b.n < kCopyBatchMax; ++at) {
+      const CopyDesc &d = descs[b.n++] = P.copies[at];
+      if (d.len16 > b.max_len16) b.max_len16 = d.len16;
+      if (d.len16 < b.min_len16) b.min_len16 = d.len16;
+    }
+  }
+  P.inflight.push_back(ProxyThread::Batch{C.number, std::move(P.copies_notices)});
+  P.copies_notices.clear();
+  P.copies.clear();
+  if (!C.launching) launch_open(h, P, lk);
+}
+
+// Finished batches release this thread's arrival notices to the receiver half.
+enum ReapMode { kReapReady, kReapAll };
+void reap_batches(ep_handle *h, ProxyThread &P, ReapMode mode) {
+  for (bool polled = false; !P.inflight.empty();) {
+    ProxyThread::Batch &b = P.inflight.front();
+    if (b.number < h->copies.done.load(std::memory_order_acquire)) {
+      for (const WireEvent &ev : b.notices) transmit(h, P, ev);
+      P.inflight.pop_front();
+      continue;
+    }
+    if (polled && b.number == h->copies.launched.load(std::memory_order_acquire)) {  // not on the device yet
+      std::unique_lock<std::mutex> lk(h->copies.mu);
+      if (!h->copies.launching) launch_open(h, P, lk);
+    }
+    if (polled && mode == kReapReady) return;
+    if (polled) _mm_pause();
+    poll_batches(h);
+    polled = true;
   }
 }
 
 // Offsets and length are bytes relative to the registered heaps, multiples of 16 below 64 GiB.
 void queue_copy(ep_handle *h, ProxyThread &P, const char *sbase, char *dbase, uint64_t so, uint64_t dof,
                 uint64_t len, const WireEvent *notice) {
-  if (P.cur.n && (P.cur.src_base != sbase || P.cur.dst_base != dbase)) launch_batch(h, P);  // re-registered
-  // the event about to be used must not belong to a batch still in flight
-  while (P.cur.n == 0 && (int)P.inflight.size() >= ProxyThread::kBatchSlots - 1) reap_batches(h, P, kReapOne);
-  P.cur.src_base = sbase;
-  P.cur.dst_base = dbase;
-  P.descs[(size_t)P.cur_slot * kCopyBatchMax + P.cur.n] =
-      CopyDesc{(unsigned)(so >> 4), (unsigned)(dof >> 4), (unsigned)(len >> 4)};
-  if (notice) P.cur_notices.push_back(*notice);
-  if ((unsigned)(len >> 4) > P.cur.max_len16) P.cur.max_len16 = (unsigned)(len >> 4);
-  if ((unsigned)(len >> 4) < P.cur.min_len16 || P.cur.n == 0) P.cur.min_len16 = (unsigned)(len >> 4);
+  if (P.copies_src != sbase || P.copies_dst != dbase) launch_copies(h, P);  // re-registered
+  P.copies_src = sbase;
+  P.copies_dst = dbase;
+  P.copies.push_back(CopyDesc{(unsigned)(so >> 4), (unsigned)(dof >> 4), (unsigned)(len >> 4)});
+  if (notice) P.copies_notices.push_back(*notice);
   bump(P.copied_bytes, len);
-  if (++P.cur.n == kCopyBatchMax) launch_batch(h, P);
+  if (P.copies.size() == (size_t)kCopyBatchMax) launch_copies(h, P);
 }
 
 // ---- pacing (Section 6, "Congestion control with CPU proxy") ------------------------------------
@@ -559,11 +620,11 @@ void process_cmd(ep_handle *h, ProxyThread &P, int fifo, uint32_t w0, uint32_t w
       // copies in flight, messages in the transport, and those waiting for the pacing limit
       close_all_open(h, P);
       do {
-        launch_batch(h, P);
+        launch_copies(h, P);
         reap_batches(h, P, kReapAll);
         flush_window(h, P);
         pump_held(h, P);
-      } while (P.held_total || P.cur.n || !P.inflight.empty() || !P.window.empty());
+      } while (P.held_total || !P.copies.empty() || !P.inflight.empty() || !P.window.empty());
       // communication channels that travel through this FIFO (destination rank mod C == fifo) must
       // have nothing left waiting: a leftover means a sequence number never arrived
       for (int ss = 0; ss < c.num_src; ++ss)
@@ -669,11 +730,9 @@ void proxy_main(ep_handle *h, ProxyThread *Pp) {
       close_due_open(h, P);
       if (!P.open.empty()) any = true;  // keep sweeping: the open messages have a deadline
     }
-    // What has been collected goes out as one batch of peer writes - at once when nothing new came in,
-    // else when it is worth a launch of its own (launches on the shared stream run one after the other,
-    // ~10 us apart: during a burst few large batches beat many small ones); finished batches release
-    // their arrival notices.
-    if (P.cur.n && (!any || P.cur.n >= 2048)) launch_batch(h, P);
+    // What has been collected joins the open batch of peer writes - at once when nothing new came in, else
+    // when it is worth a launch of its own; finished batches release their arrival notices.
+    if (!P.copies.empty() && (!any || P.copies.size() >= 2048)) launch_copies(h, P);
     if (!P.inflight.empty()) {
       reap_batches(h, P, kReapReady);
       any = true;
