@@ -195,8 +195,9 @@ EP_DEV void drain_all_channels(const RingDev &ring, unsigned *done_cnt, unsigned
   if (threadIdx.x >= 64) return;
   unsigned last = 0;
   if (lane == 0) {
-    const unsigned group = blockIdx.x / kDrainGroup, ngroups = (gridDim.x + kDrainGroup - 1) / kDrainGroup;
-    const unsigned gsize = min(kDrainGroup, gridDim.x - group * kDrainGroup);
+    const unsigned block = blockIdx.y * gridDim.x + blockIdx.x, blocks = gridDim.x * gridDim.y;
+    const unsigned group = block / kDrainGroup, ngroups = (blocks + kDrainGroup - 1) / kDrainGroup;
+    const unsigned gsize = min(kDrainGroup, blocks - group * kDrainGroup);
     if (__hip_atomic_fetch_add(&done_cnt[1 + group], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u == gsize) {
       __hip_atomic_store(&done_cnt[1 + group], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       if (__hip_atomic_fetch_add(&done_cnt[0], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u == ngroups) {

@@ -1,4 +1,4 @@
-// Ring-buffer communication channels of the high-throughput mode: one workgroup per token slice plays the
+// Ring-buffer communication channels of the high-throughput mode: one or several workgroups per token slice play the
 // sending and the receiving end in turns, chunk slots reused under head/tail flow control.
 #include "ep_device.h"
 
@@ -9,9 +9,9 @@ namespace ep {
 // a slot only after the receiver released it (head), the receiver may read it only after it was
 // announced (tail); Write, tail Atomic and head Atomic are sequenced per channel and pass through the
 // proxy.
-// One workgroup owns a token slice and plays both ends of the slice's channels in turns: a sending
-// step (every wavefront takes a token, keeps its row in registers and stores it into the slot of
-// each of its destinations that is known to be free, then announces the chunks it completed) and a
+// A workgroup owns the channels of a token slice, or some of them (see launch_ht_ring), and plays
+// both ends of them in turns: a sending step (every wavefront takes a token, keeps its row in
+// registers and stores it into the slot of each of its destinations that is known to be free, then announces the chunks it completed) and a
 // receiving step (a sweep over the tails, the announced rows move to their final place, the slots
 // are released).  Neither step waits for the other end: a wavefront whose slot is still occupied
 // keeps its claimed position and tries again after the next sweep.  A workgroup therefore depends
@@ -38,6 +38,7 @@ struct HtShared {
   unsigned seqr[kHtMaxRanks];  // the channel's reverse sequence number before this dispatch
   unsigned cumr[kHtMaxRanks];  // rows the channel carried before this dispatch (receiver's count)
   int abort, remaining, progress, idle;
+  int split_mask, part;  // this workgroup's channels: r & split_mask == part (in LDS: scalar registers are short here)
 };
 
 #define HT_LD(p) __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)
@@ -46,6 +47,9 @@ struct HtShared {
 EP_DEV bool ht_valid(const HtRingArgs &a, int e, int row) {
   return e >= 0 && e / a.E_loc < a.R && row >= 0 && row < a.recv_rows;
 }
+
+// Is rank r's channel one of this workgroup's?  (See launch_ht_ring.)
+EP_DEV bool ht_mine(const HtShared &sh, int r) { return (r & sh.split_mask) == sh.part; }
 
 // B 16-byte vectors per lane of a row, starting at vector v0: loads in flight together, stores
 // back to back.  The slots are stored write-through, the received rows plainly.  With the streaming hint on both, steps of
@@ -87,7 +91,7 @@ EP_DEV bool ht_send_token(const HtRingArgs &a, HtShared &sh, int c, int t, HtTok
     e = a.idx[(size_t)t * a.K + lane];
     row = a.dst_row[(size_t)t * a.K + lane];
   }
-  const bool valid = lane < a.K && ht_valid(a, e, row);
+  const bool valid = lane < a.K && ht_valid(a, e, row) && ht_mine(sh, e / a.E_loc);
   const int r = valid ? e / a.E_loc : 0, chan = c * a.R + r;
   if (tk.pend == 0ull) {  // a new token: positions are handed out in arrival order
     tk.p = valid ? __hip_atomic_fetch_add(&sh.fill[r], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) : 0;
@@ -193,8 +197,8 @@ EP_DEV bool ht_send_token(const HtRingArgs &a, HtShared &sh, int c, int t, HtTok
 // when the wave has nothing left to send.
 constexpr int kHtStepRows = 16;
 EP_DEV bool ht_send_step(const HtRingArgs &a, HtShared &sh, int c, int t0, int ntok, int &q, HtToken &tk) {
-  const int wave = threadIdx.x >> 6, nwaves = blockDim.x >> 6;
-  const int budget = max(1, kHtStepRows / a.K);
+  const int wave = wave_id(), nwaves = blockDim.x >> 6;
+  const int budget = max(1, kHtStepRows * (sh.split_mask + 1) / a.K);
   for (int j = 0; j < budget; ++j) {
     const int tt = wave + q * nwaves;
     if (tt >= ntok) return true;
@@ -207,7 +211,7 @@ EP_DEV bool ht_send_step(const HtRingArgs &a, HtShared &sh, int c, int t0, int n
 // One receiving step of the workgroup: a sweep over the slice's tails, the announced rows move to
 // the rows their headers name, the consumed slots are released.  Called by every thread.
 EP_DEV void ht_receive_step(const HtRingArgs &a, HtShared &sh, int c) {
-  const int tid = threadIdx.x, lane = lane_id(), wave = tid >> 6, nwaves = blockDim.x >> 6;
+  const int tid = threadIdx.x, lane = lane_id(), wave = wave_id(), nwaves = blockDim.x >> 6;
   const bool fp8 = a.payload != EP_BF16;
   const int nvec = fp8 ? a.H >> 4 : a.H >> 3;  // 16-byte vectors of payload per row
   const unsigned rb = a.row_bytes;
@@ -306,16 +310,22 @@ __global__ __launch_bounds__(1024) void ht_ring_kernel(HtRingArgs a) {
     sh.cumr[r] = a.cum_rev[c * a.R + r];
   }
   for (int i = tid; i < a.R * a.W; i += blockDim.x) sh.done[i] = 0;
-  if (tid == 0) sh.abort = sh.remaining = sh.progress = sh.idle = 0;
+  if (tid == 0) {
+    sh.abort = sh.remaining = sh.progress = sh.idle = 0;
+    sh.split_mask = a.split - 1;
+    sh.part = blockIdx.y;
+  }
   __syncthreads();
   // rows per channel of this slice: both ends count them from the routing table (the count
   // notification that precedes a high-throughput dispatch)
   for (int i = tid; i < (t1 - t0) * a.K; i += blockDim.x) {
     const int e = a.idx[(size_t)t0 * a.K + i], row = a.dst_row[(size_t)t0 * a.K + i];
-    if (ht_valid(a, e, row))
-      __hip_atomic_fetch_add(&sh.total[e / a.E_loc], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    else if (e >= 0)
+    if (ht_valid(a, e, row)) {
+      if (ht_mine(sh, e / a.E_loc))
+        __hip_atomic_fetch_add(&sh.total[e / a.E_loc], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    } else if (e >= 0) {
       dev_set_error(a.fifo.error, EP_EBOUNDS);
+    }
   }
   __syncthreads();
   if (tid == 0) {
@@ -353,6 +363,7 @@ __global__ __launch_bounds__(1024) void ht_ring_kernel(HtRingArgs a) {
   __syncthreads();
   // the channels' running sequence numbers and row totals, for the next dispatch
   for (int r = tid; r < a.R; r += blockDim.x) {
+    if (!ht_mine(sh, r)) continue;
     const unsigned nch = (unsigned)(sh.total[r] + 31) >> 5;
     a.seq_fwd[c * a.R + r] = sh.seqf[r] + 2u * nch;
     a.cum_fwd[c * a.R + r] = sh.cumf[r] + (unsigned)sh.total[r];
@@ -362,10 +373,24 @@ __global__ __launch_bounds__(1024) void ht_ring_kernel(HtRingArgs a) {
   drain_all_channels(a.fifo, a.waves_done, (unsigned)a.src, lane_id());
 }
 
+// A workgroup's sixteen waves fill a compute unit, so fewer than 256 slices leave some idle: then 2 or 4 workgroups share a
+// slice, each with the channels of every 2nd or 4th rank (a channel's state is its own, so they have nothing to say to each
+// other).  As long as each still has half a megabyte to move; with less, the polls and the reads of the tokens, which every
+// one of them does, cost more.  Whole steps, one / two / four workgroups a slice, us:
+//   64 slices   4096 tokens x 7168 top-8 656 / 514 / 441, 1536 x 7168 265 / 223 / 218, 1024 x 7168 179 / 170 / 168 (0.46 MB
+//               each), 768 x 7168 141 / 138 / 148 (0.34 MB), 1024 x 4096 113 / 109 / 127 (0.26 MB), in FP8 101 / 104 (0.27
+//               MB) / 129, 2048 x 2048 125 / 124 / 143 (0.26 MB)
+//   128 slices  4096 x 7168 474 / 439, 2048 x 7168 top-6 211 / 202, 4096 x 4096 in FP8 242 / 240, 1024 x 7168 188 / 194 (0.46
+//               MB), 1536 x 2048 in FP8 121 / 148 (0.1 MB)
+constexpr long long kHtSplitBytes = 500000;
 int launch_ht_ring(const HtRingArgs &a, const Tunables &tune, void *stream) {
   int threads = tune.ht_threads;
   if (threads < 64 || threads > 1024 || (threads & 63)) threads = 1024;
-  hipLaunchKernelGGL(ht_ring_kernel, dim3((unsigned)a.slices), dim3((unsigned)threads), 0, (hipStream_t)stream, a);
+  HtRingArgs b = a;
+  const long long bytes = (long long)a.T * a.K * a.row_bytes;
+  b.split = 1;
+  while (b.split * 2 <= a.R && b.split * 2 * a.slices <= 256 && bytes >= kHtSplitBytes * a.slices * b.split * 2) b.split *= 2;
+  hipLaunchKernelGGL(ht_ring_kernel, dim3((unsigned)b.slices, (unsigned)b.split), dim3((unsigned)threads), 0, (hipStream_t)stream, b);
   return (int)hipGetLastError();
 }
 

@@ -1752,6 +1752,48 @@ def test_ht_ring_dispatch(epmod, oracle, cid, T, mask, slices, W, window, thread
         assert np.array_equal(tail[0], 2 * per_channel) and np.array_equal(head[0], 2 * per_channel)
 
 
+# workgroups of a slice: 2 (rows of half a megabyte each, and one row less: one), 4 of 6 ranks, 8 of 9 ranks, 4 with a rank
+# each and most rows for one of them, 16 with a slot per channel
+@pytest.mark.parametrize("T,H,E,K,R,slices,W,mask", [
+    (245, 2048, 6, 2, 3, 2, 2, 0.0), (244, 2048, 6, 2, 3, 2, 2, 0.0), (700, 2048, 48, 5, 6, 3, 2, 0.2),
+    (520, 4096, 45, 7, 9, 7, 1, 0.0), (1100, 2048, 4, 1, 4, 2, 3, 0.1), (600, 8192, 64, 8, 16, 9, 1, 0.05)])
+def test_ht_ring_dispatch_slices_shared_by_workgroups(epmod, oracle, T, H, E, K, R, slices, W, mask):
+    rng = np.random.default_rng(T)
+    score = rng.random((1, T, E))
+    if K == 1:
+        score[:, :, 1] -= rng.random((1, T)) < 0.9
+    idx = g.mask_random(np.argsort(score, axis=-1)[..., :K].astype(np.int32), mask, seed=T)
+    rows = int((idx >= 0).sum())
+    cfg = g.EPConfig("shared", T=T, H=H, E=E, K=K, R=R, S=1)
+    from paper_2512_19849_amd.runner import bits_to_bf16, bf16_to_bits
+    want_lay = oracle.layout(idx, E, R)
+    per_channel = oracle.ring_channel_rows(idx[0], cfg.E_loc, R, slices)
+    nch = -(-per_channel // 32)
+    with _runner(epmod, cfg, T, flags=epmod.EP_FLAG_LOG_CMDS | epmod.EP_FLAG_LOG_EVENTS, heap_rows=rows,
+                 ht_slices=slices, ht_ring_slots=W) as r:
+        d_idx = _dev(idx)
+        lay = r.layout(d_idx)
+        ring = torch.zeros(r.ht_ring_bytes(), dtype=torch.uint8, device="cuda")
+        recv = torch.empty((rows, H), dtype=torch.bfloat16, device="cuda")
+        want_cmds = None
+        for it in range(2):
+            x = g.activations(cfg, it, T=T)
+            recv.fill_(-1.5)
+            r.ht_dispatch(bits_to_bf16(x), d_idx[0], lay, ring, recv)
+            r.wait()
+            torch.cuda.synchronize()
+            want, _ = oracle.dispatch_bf16(x, idx[0], want_lay["dst_row"][0], cfg.E_loc, rows, -1, fill=0xBFC0)
+            assert np.array_equal(bf16_to_bits(recv), want), it
+            exp = oracle.expected_ring_cmds(idx[0], 0, cfg.E_loc, R, H, slices, W, 2 * nch * it, nch * it)
+            want_cmds = exp if want_cmds is None else want_cmds + exp
+        st = r.stats()
+        assert st["device_error"] == 0 and st["proxy_error"] == 0 and st["rejected"] == 0
+        assert oracle.ring_cmd_multiset(epmod.ep_cmd_log(r.h)) == want_cmds
+        oracle.check_ring_trace(epmod.ep_event_log(r.h), W)
+        tail, head = epmod.ep_ring_counters(r.h, 1, slices, R)
+        assert np.array_equal(tail[0], 2 * per_channel) and np.array_equal(head[0], 2 * per_channel)
+
+
 @pytest.mark.parametrize("cid,T,mask,slices,W,window", [(3, None, 0.0, 4, 2, 0), (3, 50, 0.3, 3, 1, 4),
                                                         (5, 700, 0.0, 8, 2, 8), (4, 300, 0.1, 2, 1, 0),
                                                         ("h128", 90, 0.0, 3, 2, 0)])
