@@ -47,18 +47,22 @@ EP_DEV void push_count_atomics(const DispatchArgs &a, bool push, int e, int valu
                    (unsigned)(a.src * a.E_loc) + le, scratch);
 }
 
-// Workgroup 0, wavefront 0: the count Atomics that no row completion will trigger - experts with count 0, or all of
-// them when the caller wants the atomics ahead of the writes.
+// Workgroup 0, ahead of its rows: the count Atomics that no row completion will trigger - experts with count 0, or all of
+// them when the caller wants the atomics ahead of the writes.  With one command per row the wave that pushes for the group
+// has no part in it: up to kLeadWaves others take 64 experts each at a time.
+constexpr int kLeadWaves = 4;
 template <bool GROUPS>
-EP_DEV void emit_leading_atomics(const DispatchArgs &a, int lane) {
-  extern __shared__ u32x4 s_dyn[];  // (per-token commands: the 2 KB of ring_push_sorted)
+EP_DEV void emit_leading_atomics(const DispatchArgs &a, int wave, int lane) {
+  extern __shared__ u32x4 s_dyn[];  // (one command per row: the scratch of ring_push_sorted for waves 0 to kLeadWaves)
   const bool first = (a.cmd_mode & EP_CMD_ATOMICS_FIRST) != 0;
-  for (int e0 = 0; e0 < a.E; e0 += 64) {
+  const int waves = GROUPS ? min(kLeadWaves, (int)(blockDim.x >> 6) - 1) : 1, w = GROUPS ? wave - 1 : wave;
+  if (w < 0 || w >= waves) return;
+  for (int e0 = w * 64; e0 < a.E; e0 += waves * 64) {
     const int e = e0 + lane;
     const int c = e < a.E ? a.count[e] : -1;
     const bool push = c >= 0 && (first || c == 0) && (a.filter < 0 || e / a.E_loc == a.filter);
     if (GROUPS)
-      push_count_atomics(a, push, e, c, s_dyn);
+      push_count_atomics(a, push, e, c, s_dyn + wave * (kSortScratch / 16));
     else if (push)
       push_count_atomic(a, e, c);
   }
@@ -126,8 +130,14 @@ EP_DEV void emit_chunk_cmds(const DispatchArgs &a, const TokenMeta &m) {
 // What a small dispatch waits for is the proxy, which misses its caches once for every write that reaches a polled line.
 // Whole steps, groups / every workgroup on its own (us, rows of 7168, top-8 of 256 experts): 128 tokens 30 / 36, 256: 34 /
 // 51, 512: 48 / 73; 512 tokens x 4096: 41 / 49.
+// Bound by the chain of round trips behind the last row: the group's counter, the pairs, the reservation, then the experts'
+// counters and the cached heads together, and for complete experts a reservation and the heads once more.  With the experts'
+// counters on their own, and the leading Atomics pushed by the same wave ahead of its row (64 experts after the other), whole
+// steps of 8192 tokens x 1024 top-4 took 126 us, now 100; 4096 x 7168 top-8 in FP8 195 and 182; one token of 256 experts,
+// alone, 40.2 and 38.7.  With the pairs loaded ahead of the rows, which then wait for them too, 8192 x 1024 takes 114; with
+// the leading Atomics in a workgroup of their own, where the proxy sees them first, 128 tokens 1 us more.
 EP_DEV void emit_group_cmds(const DispatchArgs &a, int wave, int lane) {
-  extern __shared__ u32x4 s_dyn[];  // the 2 KB of ring_push_sorted
+  extern __shared__ u32x4 s_dyn[];  // the scratch of ring_push_sorted
   __syncthreads();  // every wave has waited for its own stores before it came here
   if (wave != 0) return;
   const int gb = a.blocks_per_group, group = token_block(a) / gb;
@@ -152,17 +162,18 @@ EP_DEV void emit_group_cmds(const DispatchArgs &a, int wave, int lane) {
     // (an entry out of range has been reported by its own wave)
     const bool active = e >= 0 && e < a.E && row >= 0 && row < a.recv_rows && (a.filter < 0 || e / a.E_loc == a.filter);
     if (!active) e = 0;
-    const unsigned dr = (unsigned)(e / a.E_loc), le = (unsigned)(e - (int)dr * a.E_loc);
+    const int c = a.count[e];
+    const unsigned dr = (unsigned)(e / a.E_loc), le = (unsigned)(e - (int)dr * a.E_loc), ch = (unsigned)e % a.ring.channels;
     const unsigned long long so = (unsigned long long)(t0 + i / a.K) * a.row_bytes;
     const unsigned long long dof = (unsigned long long)row * a.row_bytes;
-    ring_push_sorted(a.ring, active, (unsigned)e % a.ring.channels, cmd_w0(EP_OP_WRITE, a.src, dr, le),
-                     a.row_bytes >> 4, (unsigned)(so >> 4), (unsigned)(dof >> 4), s_dyn);
-    const int c = a.count[e];
-    bool complete = false;  // (as account_rows)
-    if (active) {
-      complete = __hip_atomic_fetch_add(a.expert_done + e, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 == c;
-      if (complete) __hip_atomic_store(a.expert_done + e, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
+    const SortedRun run = ring_reserve_sorted(a.ring, active, ch);
+    // (As account_rows.  Counted once the Writes have their Idx: an expert's Atomic gets a later one.)
+    int done = 0;
+    if (active) done = __hip_atomic_fetch_add(a.expert_done + e, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    ring_publish_sorted(a.ring, active, run, ch, cmd_w0(EP_OP_WRITE, a.src, dr, le), a.row_bytes >> 4, (unsigned)(so >> 4),
+                        (unsigned)(dof >> 4), s_dyn);
+    const bool complete = active && done + 1 == c;
+    if (complete) __hip_atomic_store(a.expert_done + e, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     push_count_atomics(a, complete && !(a.cmd_mode & EP_CMD_ATOMICS_FIRST), e, c, s_dyn);
   }
 }
@@ -218,7 +229,7 @@ __global__ void dispatch_bf16_kernel(DispatchArgs a) {
   const int t = token_block(a) * a.tokens_per_block + (unsigned)wave / (unsigned)a.parts;
   const bool ring_on = (a.cmd_mode & EP_CMD_MODE_MASK) != EP_CMD_NONE;
   const bool ordered = (a.cmd_mode & EP_CMD_MODE_MASK) == EP_CMD_CHUNK32_ORDERED;
-  if (ring_on && !ordered && blockIdx.x == 0 && wave == 0) emit_leading_atomics<GROUPS>(a, lane);
+  if (ring_on && !ordered && blockIdx.x == 0) emit_leading_atomics<GROUPS>(a, wave, lane);
 
   const TokenMeta m = load_meta(a, t, lane);
   unsigned long long vmask = __ballot(m.valid);
@@ -313,7 +324,7 @@ __global__ void dispatch_fp8_kernel(DispatchArgs a) {
   const int t = token_block(a) * a.tokens_per_block + (unsigned)wave / (unsigned)a.parts;
   const bool ring_on = (a.cmd_mode & EP_CMD_MODE_MASK) != EP_CMD_NONE;
   const bool ordered = (a.cmd_mode & EP_CMD_MODE_MASK) == EP_CMD_CHUNK32_ORDERED;
-  if (ring_on && !ordered && blockIdx.x == 0 && wave == 0) emit_leading_atomics<GROUPS>(a, lane);
+  if (ring_on && !ordered && blockIdx.x == 0) emit_leading_atomics<GROUPS>(a, wave, lane);
 
   const TokenMeta m = load_meta(a, t, lane);
   unsigned long long vmask = __ballot(m.valid);
@@ -432,7 +443,7 @@ __global__ __launch_bounds__(1024) void dispatch_pipelined_kernel(DispatchArgs a
       if (lane == 0) __hip_atomic_fetch_add(&ctl[slot], 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
   } else {
-    if (mode != EP_CMD_CHUNK32_ORDERED && blockIdx.x == 0) emit_leading_atomics<false>(a, lane);
+    if (mode != EP_CMD_CHUNK32_ORDERED && blockIdx.x == 0) emit_leading_atomics<false>(a, 0, lane);
     int it = 0;
 #pragma nounroll
     for (int b = blockIdx.x; b < nb; b += gridDim.x, ++it) {
@@ -531,7 +542,7 @@ static size_t group_cmds_setup(DispatchArgs &a, int waves) {
   a.blocks_per_group = cmds > kGroupCmdsMax || placed * a.row_bytes > kGroupBytesMax
                            ? 1
                            : max(1, min(64 / a.K, a.T / 16) / a.tokens_per_block);
-  return 2048;
+  return (1 + kLeadWaves) * kSortScratch;
 }
 
 // Ring-on launches take the form with a command wave when it is switched on and the row needs at most 15 data
@@ -545,7 +556,7 @@ static bool launch_pipelined(DispatchArgs a, const Tunables &tune, hipStream_t s
   const int D = a.parts * a.tokens_per_block;
   const int nb = (a.T + a.tokens_per_block - 1) / a.tokens_per_block;
   const int n = a.tokens_per_block * a.K;
-  const size_t lds = 16 + (size_t)((n + 1) & ~1) * 2 * sizeof(int2) + 2048;
+  const size_t lds = 16 + (size_t)((n + 1) & ~1) * 2 * sizeof(int2) + kSortScratch;
   // two workgroups per compute unit (256 of them) keep the chip full; each walks its batches with stride gridDim
   const int grid = nb < 1 ? 1 : (nb < 512 ? nb : 512);
   launch_kernel(dispatch_pipelined_kernel<VPL, FP8>, dim3(grid), dim3(64 * (D + 1)), lds, st, tm ? tm->start : nullptr,

@@ -46,17 +46,23 @@ EP_DEV unsigned long long ring_push(const RingDev &r, unsigned c, unsigned w0, u
 // Push for a whole wave whose lanes hold one command each (or none: `active`), called by all 64 lanes together.  Lanes that
 // aim at the same channel share ONE atomic on its tail - the first of them reserves a run of Idx for all, the others take
 // their place in the run (atomics on one address serialise in the L2, and a per-token dispatch sends tens of thousands of
-// commands through a handful of tails).  Then the commands change lanes through LDS (`scratch`, 2 KB) so that lane order is
-// (channel, Idx) order: neighbouring lanes store neighbouring slots, and the memory pipeline turns the slots of one 64-byte
-// line into one write.  A line of host memory that the proxy is polling costs the PCIe root a round of coherence traffic
-// per write that lands in it, whatever the size of the write.
+// commands through a handful of tails).  Then the commands change lanes through LDS (`scratch`, kSortScratch) so that lane
+// order is (channel, Idx) order: neighbouring lanes store neighbouring slots, and the memory pipeline turns the slots of one
+// 64-byte line into one write.  A line of host memory that the proxy is polling costs the PCIe root a round of coherence
+// traffic per write that lands in it, whatever the size of the write.
 // (The check for room reads the cached head after the reservation: read together with it, it is older, calls the channel
 // full more often, and a prefill dispatch of 65536 commands took 178 us instead of 162.)
-EP_DEV void ring_push_sorted(const RingDev &r, bool active, unsigned c, unsigned w0, unsigned w1, unsigned w2,
-                             unsigned w3, u32x4 *scratch) {
+// In two halves, so that a caller can have other round trips under way with the second.
+constexpr unsigned kSortScratch = 2048;  // bytes
+struct SortedRun {
+  unsigned long long idx;  // this lane's Idx
+  int place, n;            // its place among the n commands of the wave
+};
+EP_DEV SortedRun ring_reserve_sorted(const RingDev &r, bool active, unsigned c) {
   const int me = lane_id();
   const unsigned long long act = __ballot(active);
-  if (act == 0ull) return;
+  SortedRun run{0ull, 0, (int)__popcll(act)};
+  if (act == 0ull) return run;
   unsigned long long same = 0ull;
   int less = 0;
   for (unsigned long long m = act; m;) {  // once per distinct channel
@@ -73,19 +79,30 @@ EP_DEV void ring_push_sorted(const RingDev &r, bool active, unsigned c, unsigned
     base = __hip_atomic_fetch_add(&r.tail[c], (unsigned long long)__popcll(same), __ATOMIC_RELAXED,
                                   __HIP_MEMORY_SCOPE_AGENT);
   base = ((unsigned long long)(unsigned)__shfl((int)(base >> 32), leader) << 32) | (unsigned)__shfl((int)base, leader);
+  run.idx = base + (unsigned long long)before;
+  run.place = less + before;
+  return run;
+}
+EP_DEV void ring_publish_sorted(const RingDev &r, bool active, const SortedRun &run, unsigned c, unsigned w0, unsigned w1,
+                                unsigned w2, unsigned w3, u32x4 *scratch) {
+  if (run.n == 0) return;
+  const int me = lane_id();
   if (active) {
-    const unsigned long long idx = base + (unsigned long long)before;
-    scratch[less + before] = u32x4{w0, w1, w2, w3};
-    scratch[64 + less + before] = u32x4{c, (unsigned)idx, (unsigned)(idx >> 32), 0u};
+    scratch[run.place] = u32x4{w0, w1, w2, w3};
+    scratch[64 + run.place] = u32x4{c, (unsigned)run.idx, (unsigned)(run.idx >> 32), 0u};
   }
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  if (me < __popcll(act)) {
+  if (me < run.n) {
     const u32x4 w = scratch[me], q = scratch[64 + me];
     ring_publish(r, q.x, ((unsigned long long)q.z << 32) | q.y, w.x, w.y, w.z, w.w);
   }
   __builtin_amdgcn_wave_barrier();  // (the next round writes the scratch again)
+}
+EP_DEV void ring_push_sorted(const RingDev &r, bool active, unsigned c, unsigned w0, unsigned w1, unsigned w2,
+                             unsigned w3, u32x4 *scratch) {
+  ring_publish_sorted(r, active, ring_reserve_sorted(r, active, c), c, w0, w1, w2, w3, scratch);
 }
 
 // Second half of a Push: wait for room for the reserved Idx, then publish the command.
