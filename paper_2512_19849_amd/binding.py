@@ -156,18 +156,29 @@ def _ptr(t) -> Optional[int]:
     return t.ctypes.data
 
 
+class _General:
+    """In the place of _epcall until torch has initialised the device: every call takes the general path."""
+
+    def __getattr__(self, name):
+        return lambda *args: NotImplemented
+
+
 _torch_c = None  # torch._C, once torch has initialised the device
+_fast = _General()  # then _epcall: the calls of a step without ctypes; NotImplemented where an argument is not a plain one
 
 
 def _stream(stream) -> Optional[int]:
     """The stream's handle; None is torch's current stream, whose raw handle costs 0.2 us a call (through a
     torch.cuda.Stream object: 2.9 us, as much as a kernel launch)."""
-    global _torch_c
+    global _torch_c, _fast
     if stream is None:
         if _torch_c is None:
             import torch
             torch.cuda.current_stream()
-            _torch_c = torch._C
+            load_library()
+            from . import _epcall
+            _epcall.set_address_type(Address)
+            _torch_c, _fast = torch._C, _epcall
         return _torch_c._cuda_getCurrentRawStream(_torch_c._cuda_getDevice())
     return getattr(stream, "cuda_stream", stream)
 
@@ -194,9 +205,13 @@ def ep_proxy_stop(h: int) -> None:
 
 def ep_layout(h: int, topk_idx, T: int, count, expert_total, rank_total, base, expert_offset, rank_offset, slot,
               dst_row, stream=None) -> None:
-    _check("ep_layout", load_library().ep_layout(h, _ptr(topk_idx), T, _ptr(count), _ptr(expert_total),
-                                                 _ptr(rank_total), _ptr(base), _ptr(expert_offset),
-                                                 _ptr(rank_offset), _ptr(slot), _ptr(dst_row), _stream(stream)))
+    rc = _fast.ep_layout(h, topk_idx, T, count, expert_total, rank_total, base, expert_offset, rank_offset,
+                         slot, dst_row, stream)
+    if rc is NotImplemented:
+        rc = load_library().ep_layout(h, _ptr(topk_idx), T, _ptr(count), _ptr(expert_total), _ptr(rank_total),
+                                      _ptr(base), _ptr(expert_offset), _ptr(rank_offset), _ptr(slot), _ptr(dst_row), _stream(stream))
+    if rc:
+        raise EPError("ep_layout", rc)
 
 
 def ep_layout_static(topk_idx, S: int, T: int, K: int, E: int, R: int, count, expert_total, rank_total, base,
@@ -209,36 +224,58 @@ def ep_layout_static(topk_idx, S: int, T: int, K: int, E: int, R: int, count, ex
 
 def ep_dispatch(h: int, x, topk_idx, dst_row, count, base, T: int, src_rank: int, dst_rank_filter: int,
                 payload: int, cmd_mode: int, recv, recv_scale, recv_rows: int, stream=None) -> None:
-    _check("ep_dispatch", load_library().ep_dispatch(h, _ptr(x), _ptr(topk_idx), _ptr(dst_row), _ptr(count),
-                                                     _ptr(base), T, src_rank, dst_rank_filter, payload, cmd_mode,
-                                                     _ptr(recv), _ptr(recv_scale), recv_rows, _stream(stream)))
+    rc = _fast.ep_dispatch(h, x, topk_idx, dst_row, count, base, T, src_rank, dst_rank_filter, payload,
+                           cmd_mode, recv, recv_scale, recv_rows, stream)
+    if rc is NotImplemented:
+        rc = load_library().ep_dispatch(h, _ptr(x), _ptr(topk_idx), _ptr(dst_row), _ptr(count), _ptr(base), T,
+                                        src_rank, dst_rank_filter, payload, cmd_mode, _ptr(recv), _ptr(recv_scale), recv_rows,
+                                        _stream(stream))
+    if rc:
+        raise EPError("ep_dispatch", rc)
 
 
 def ep_combine(h: int, y, topk_w, dst_row, T: int, y_rows: int, out, stream=None) -> None:
-    _check("ep_combine", load_library().ep_combine(h, _ptr(y), _ptr(topk_w), _ptr(dst_row), T, y_rows, _ptr(out),
-                                                   _stream(stream)))
+    rc = _fast.ep_combine(h, y, topk_w, dst_row, T, y_rows, out, stream)
+    if rc is NotImplemented:
+        rc = load_library().ep_combine(h, _ptr(y), _ptr(topk_w), _ptr(dst_row), T, y_rows, _ptr(out), _stream(stream))
+    if rc:
+        raise EPError("ep_combine", rc)
 
 
 def ep_fp8_unpack(h: int, msgs, rows: int, recv, recv_scale, stream=None) -> None:
-    _check("ep_fp8_unpack", load_library().ep_fp8_unpack(h, _ptr(msgs), rows, _ptr(recv), _ptr(recv_scale),
-                                                         _stream(stream)))
+    rc = _fast.ep_fp8_unpack(h, msgs, rows, recv, recv_scale, stream)
+    if rc is NotImplemented:
+        rc = load_library().ep_fp8_unpack(h, _ptr(msgs), rows, _ptr(recv), _ptr(recv_scale), _stream(stream))
+    if rc:
+        raise EPError("ep_fp8_unpack", rc)
 
 
 def ep_dedup(h: int, topk_idx, T: int, ranks_per_group: int, group_idx, first_k, stream=None) -> None:
-    _check("ep_dedup", load_library().ep_dedup(h, _ptr(topk_idx), T, ranks_per_group, _ptr(group_idx),
-                                               _ptr(first_k), _stream(stream)))
+    rc = _fast.ep_dedup(h, topk_idx, T, ranks_per_group, group_idx, first_k, stream)
+    if rc is NotImplemented:
+        rc = load_library().ep_dedup(h, _ptr(topk_idx), T, ranks_per_group, _ptr(group_idx), _ptr(first_k),
+                                     _stream(stream))
+    if rc:
+        raise EPError("ep_dedup", rc)
 
 
 def ep_gather_index(h: int, dst_row, dst_row_g, first_k, T: int, rows: int, index, stream=None) -> None:
-    _check("ep_gather_index", load_library().ep_gather_index(h, _ptr(dst_row), _ptr(dst_row_g), _ptr(first_k), T,
-                                                             rows, _ptr(index), _stream(stream)))
+    rc = _fast.ep_gather_index(h, dst_row, dst_row_g, first_k, T, rows, index, stream)
+    if rc is NotImplemented:
+        rc = load_library().ep_gather_index(h, _ptr(dst_row), _ptr(dst_row_g), _ptr(first_k), T, rows,
+                                            _ptr(index), _stream(stream))
+    if rc:
+        raise EPError("ep_gather_index", rc)
 
 
 def ep_combine_partial(h: int, y, topk_w, dst_row, first_k, dst_row_g, T: int, y_rows: int, rows_g: int, partial,
                        stream=None) -> None:
-    _check("ep_combine_partial", load_library().ep_combine_partial(h, _ptr(y), _ptr(topk_w), _ptr(dst_row),
-                                                                   _ptr(first_k), _ptr(dst_row_g), T, y_rows,
-                                                                   rows_g, _ptr(partial), _stream(stream)))
+    rc = _fast.ep_combine_partial(h, y, topk_w, dst_row, first_k, dst_row_g, T, y_rows, rows_g, partial, stream)
+    if rc is NotImplemented:
+        rc = load_library().ep_combine_partial(h, _ptr(y), _ptr(topk_w), _ptr(dst_row), _ptr(first_k),
+                                               _ptr(dst_row_g), T, y_rows, rows_g, _ptr(partial), _stream(stream))
+    if rc:
+        raise EPError("ep_combine_partial", rc)
 
 
 def ep_register_heaps(h: int, src, dst) -> None:
@@ -252,8 +289,11 @@ def ep_barrier(h: int, stream=None) -> None:
 
 
 def ep_recv_wait(h: int, src_rank: int, dst_rank_filter: int, counts_out, stream=None) -> None:
-    _check("ep_recv_wait", load_library().ep_recv_wait(h, src_rank, dst_rank_filter, _ptr(counts_out),
-                                                       _stream(stream)))
+    rc = _fast.ep_recv_wait(h, src_rank, dst_rank_filter, counts_out, stream)
+    if rc is NotImplemented:
+        rc = load_library().ep_recv_wait(h, src_rank, dst_rank_filter, _ptr(counts_out), _stream(stream))
+    if rc:
+        raise EPError("ep_recv_wait", rc)
 
 
 def ep_wait(h: int) -> None:
@@ -270,10 +310,14 @@ def ep_counters(h: int, S: int, E: int) -> np.ndarray:
 
 def ep_ht_dispatch(h: int, x, topk_idx, dst_row, T: int, src_rank: int, ring, recv, recv_rows: int,
                    stream=None, payload: int = EP_BF16, recv_scale=None) -> None:
-    _check("ep_ht_dispatch", load_library().ep_ht_dispatch(h, _ptr(x), _ptr(topk_idx), _ptr(dst_row), T, src_rank,
-                                                           payload, _ptr(ring), ring.numel() * ring.element_size(),
-                                                           _ptr(recv), _ptr(recv_scale), recv_rows,
-                                                           _stream(stream)))
+    rc = _fast.ep_ht_dispatch(h, x, topk_idx, dst_row, T, src_rank, payload, ring, ring.numel() *
+                              ring.element_size(), recv, recv_scale, recv_rows, stream)
+    if rc is NotImplemented:
+        rc = load_library().ep_ht_dispatch(h, _ptr(x), _ptr(topk_idx), _ptr(dst_row), T, src_rank, payload,
+                                           _ptr(ring), ring.numel() * ring.element_size(), _ptr(recv), _ptr(recv_scale), recv_rows,
+                                           _stream(stream))
+    if rc:
+        raise EPError("ep_ht_dispatch", rc)
 
 
 def ep_fifo_stress(h: int, pushers: int, cmds_per_pusher: int, lat_sum, lat_max, stream=None) -> None:

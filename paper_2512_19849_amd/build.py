@@ -8,6 +8,8 @@ import subprocess
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libep.so")
+CALL = os.path.join(HERE, "_epcall.so")
+CALL_SRC = os.path.join(CSRC, "pycall.cpp")
 SOURCES = ["layout.hip", "dispatch.hip", "combine.hip", "ht_ring.hip", "service.hip", "proxy.cpp", "api.cpp"]
 HEADERS = ["ep_internal.h", "ep_device.h", "ep_host.h", os.path.join("..", "..", "include", "ep.h"),
            os.path.join("..", "..", "include", "ep_diag.h")]
@@ -21,14 +23,14 @@ def hipcc() -> str:
 
 
 def stale() -> bool:
-    if not os.path.exists(LIB):
+    if not os.path.exists(LIB) or not os.path.exists(CALL) or os.path.getmtime(CALL_SRC) > os.path.getmtime(CALL):
         return True
     t = os.path.getmtime(LIB)
     return any(os.path.getmtime(os.path.join(CSRC, f)) > t for f in SOURCES + HEADERS)
 
 
 def build_lib(force: bool = True, verbose: bool = False) -> str:
-    """Compile every HIP/C++ source of the library for gfx950 into libep.so."""
+    """Compile every HIP/C++ source of the library for gfx950 into libep.so, and the module that calls it from Python."""
     if not force and not stale():
         return LIB
     objs = []
@@ -47,7 +49,26 @@ def build_lib(force: bool = True, verbose: bool = False) -> str:
     if verbose:
         print(" ".join(cmd))
     subprocess.run(cmd, check=True)
+    build_call(verbose)
     return LIB
+
+
+def build_call(verbose: bool = False) -> str:
+    """_epcall, the module that takes tensors to the calls of a step (host code only)."""
+    import sysconfig
+
+    import torch
+    home = os.path.dirname(torch.__file__)
+    lib = os.path.join(home, "lib")
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-I" + os.path.join(home, "include"),
+           "-I" + os.path.join(home, "include", "torch", "csrc", "api", "include"),
+           "-I" + sysconfig.get_paths()["include"], "-I/opt/rocm/include", CALL_SRC, "-o", CALL, "-L" + HERE, "-l:libep.so",
+           "-L" + lib, "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10", "-lc10_hip", "-Wl,-rpath,$ORIGIN"]
+    if verbose:
+        print(" ".join(cmd))
+    subprocess.run(cmd, check=True)
+    return CALL
 
 
 PROBE_SRC = os.path.join(HERE, "probes", "mem_patterns.hip")

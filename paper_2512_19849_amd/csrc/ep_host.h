@@ -188,6 +188,7 @@ struct alignas(64) ProxyThread {
   // ring-buffer channels: the same per (source, slice, destination rank, direction)
   std::vector<uint32_t> ring_next;
   std::vector<ReorderBuf> ring_early;
+  uint64_t ring_waiting = 0;  // messages in ring_early, so that a Drain looks through them only if there are any
   uint64_t rng = 0;
   uint64_t applied_unpublished = 0;  // atomics applied but not yet added to `applied` (owner thread only)
   bool stamp_apply = false;          // last_apply_ns is due

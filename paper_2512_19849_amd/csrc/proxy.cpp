@@ -148,14 +148,16 @@ void deliver_ring(ep_handle *h, ProxyThread &P, const WireEvent &ev) {
   const uint32_t where = ((uint32_t)ev.slice << 8) | ev.dst_rank;
   log_event(h, P, ev.ordered == 3 ? 10 : ((ev.imm >> 31) ? 9 : 8), ev.src, where, seq);
   ReorderBuf &q = P.ring_early[dir];
+  P.ring_waiting -= q.count;
   if (seq != next) {
     q.put(next, seq, ev);
     bump(P.ordered_parked, 1);
-    return;
+  } else {
+    apply_ring(h, P, chan, ev, seq);
+    ++next;
+    for (WireEvent held; q.take(next, held); ++next) apply_ring(h, P, chan, held, next);
   }
-  apply_ring(h, P, chan, ev, seq);
-  ++next;
-  for (WireEvent held; q.take(next, held); ++next) apply_ring(h, P, chan, held, next);
+  P.ring_waiting += q.count;
 }
 
 // The "network" between the two halves.  With reorder_window == 0 immediates
@@ -634,7 +636,7 @@ void process_cmd(ep_handle *h, ProxyThread &P, int fifo, uint32_t w0, uint32_t w
             h->proxy_error.compare_exchange_strong(zero, EP_ESTATE);
           }
       // ... and the ring-buffer channels of this FIFO ((slice * R + rank) mod C == fifo), both directions
-      for (size_t ch = 0, n = P.ring_early.size() / 2; ch < n; ++ch)
+      for (size_t ch = 0, n = P.ring_waiting ? P.ring_early.size() / 2 : 0; ch < n; ++ch)
         if ((int)((ch % ((size_t)c.ht_slices * c.num_ranks)) % c.num_channels) == fifo &&
             (!P.ring_early[2 * ch].empty() || !P.ring_early[2 * ch + 1].empty())) {
           int zero = 0;

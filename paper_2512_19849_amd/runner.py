@@ -38,6 +38,9 @@ class LayoutOut:
 
 def _row(t: torch.Tensor, src: int):
     """t[src] as an address (making the tensor object costs 0.8 us)."""
+    row = ep._fast.row(t, src)
+    if row is not NotImplemented:
+        return row
     if src.__class__ is int and t.is_contiguous() and 0 <= src < t.shape[0]:
         return ep.Address(t.data_ptr() + src * t.stride(0) * t.element_size()) if src else ep.Address(t.data_ptr())
     return t[src]

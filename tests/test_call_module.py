@@ -1,0 +1,57 @@
+"""The module that takes tensors to the C calls: plain arguments go through, everything else is left to the general path."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from paper_2512_19849_amd import binding, runner  # noqa: E402
+
+
+@pytest.fixture(scope="module")
+def call():
+    binding.load_library()
+    from paper_2512_19849_amd import _epcall
+    _epcall.set_address_type(binding.Address)
+    return _epcall
+
+
+T8, TK = torch.zeros(8), torch.zeros(4, 2, dtype=torch.int32)
+
+
+def combine(call, h=0, y=T8, w=T8, dst=TK, T=4, rows=8, out=T8, stream=0):
+    return call.ep_combine(h, y, w, dst, T, rows, out, stream)
+
+
+@pytest.mark.parametrize("change", [{}, dict(y=None), dict(y=binding.Address(64)), dict(rows=2**40), dict(T=-1),
+                                    dict(w=torch.nn.Parameter(torch.zeros(8))), dict(out=torch.zeros(0))])
+def test_plain_arguments_reach_the_call(call, change):
+    assert combine(call, **change) == binding.EP_EINVAL          # (no handle)
+
+
+@pytest.mark.parametrize("change", [dict(y=8), dict(y=np.zeros(8)), dict(y=torch.zeros(4, 4).t()), dict(y=True), dict(T=4.0),
+                                    dict(T=True), dict(T=np.int64(4)), dict(T=2**31), dict(rows=2**63), dict(T=T8),
+                                    dict(h=True), dict(h=2**70), dict(stream=object()), dict(dst=TK.to_sparse()),
+                                    dict(out=type("Sub", (torch.Tensor,), {})(8))])
+def test_anything_else_is_left_alone(call, change):
+    assert combine(call, **change) is NotImplemented
+    assert call.ep_combine(0, T8, T8, TK, 4, 8, T8) is NotImplemented
+
+
+def test_batched_tensors_are_left_alone(call):
+    seen = []
+    torch.vmap(lambda y: (seen.append(combine(call, y=y)), y)[1])(torch.zeros(3, 8))
+    assert seen == [NotImplemented]
+
+
+@pytest.mark.parametrize("src", [0, 2, -1, 3, np.int32(2), True, torch.tensor(1)])
+def test_rows(call, src, monkeypatch):
+    monkeypatch.setattr(binding, "_fast", call)
+    for t in (torch.zeros(3, 5, 2, dtype=torch.int32), torch.zeros(3, 10)[:, :5], torch.zeros(3, 7, dtype=torch.float64)):
+        if src.__class__ is int and src == 3:
+            with pytest.raises(IndexError):
+                runner._row(t, src)
+        elif src is True:
+            assert runner._row(t, src).shape == t[src].shape
+        else:
+            assert binding._ptr(runner._row(t, src)) == t[src].data_ptr()
+    assert call.row(torch.zeros(()), 0) is NotImplemented and call.row(torch.zeros(0, 3), 0) is NotImplemented
