@@ -68,57 +68,61 @@ EP_DEV void emit_leading_atomics(const DispatchArgs &a, int wave, int lane) {
   }
 }
 
-// `rows` more rows of expert e (c in all) have been handed to the channel; whoever hands over the
-// last one pushes the expert's count Atomic.
-EP_DEV void account_rows(const DispatchArgs &a, int e, int c, int rows) {
-  const int done = __hip_atomic_fetch_add(a.expert_done + e, rows, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + rows;
-  if (done == c) {
-    __hip_atomic_store(a.expert_done + e, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (!(a.cmd_mode & EP_CMD_ATOMICS_FIRST)) push_count_atomic(a, e, c);
-  }
-}
-
-// The chunk modes' commands (one Write per row: emit_group_cmds).  Called by the lanes holding a dispatched (t,k) after the
-// token's rows are stored and acknowledged (write-through, so they are in memory).  The lane that completes a run of
-// <= 32 consecutive rows of an expert pushes the Write for the run.  Whoever completes the expert pushes its count Atomic
-// (Section 3.3: the receiver holds it until that many rows arrived).  The scratch counters return to zero by themselves.
+// The chunk modes' commands (one Write per row: emit_group_cmds).  Called by a whole wave, whose valid lanes hold a dispatched
+// (t,k) each, after the token's rows are stored and acknowledged (write-through, so they are in memory).  The lane that
+// completes a run of <= 32 consecutive rows of an expert pushes the Write for the run.  Whoever completes the expert pushes its
+// count Atomic (Section 3.3: the receiver holds it until that many rows arrived).  The scratch counters return to zero by
+// themselves.
 EP_DEV void emit_chunk_cmds(const DispatchArgs &a, const TokenMeta &m) {
-  const int e = m.e;
+  const int e = m.valid ? m.e : 0;
   const unsigned dr = (unsigned)(e / a.E_loc), le = (unsigned)(e - (int)dr * a.E_loc);
-  // Everything for one destination expert goes through one FIFO (and therefore one proxy thread):
-  // in-FIFO order is the only order the channel guarantees (Section 3.1, "GPU-side contention").
-  const unsigned ch = (unsigned)e % a.ring.channels;
-  const int c = a.count[e];
   const int mode = a.cmd_mode & EP_CMD_MODE_MASK;
-  const int slot = m.row - a.base[e];
-  const int j = slot >> 5;
-  if (slot < 0 || j >= a.chunks_per_expert || slot >= c) {
-    dev_set_error(a.ring.error, EP_EBOUNDS);
+  int c = 0, csize = 0;
+  unsigned len = 0, off16 = 0;
+  bool whole = false;  // this lane's row was the last one of its chunk
+  if (m.valid) {
+    c = a.count[e];
+    const int base = a.base[e], slot = m.row - base, j = slot >> 5;
+    if (slot < 0 || j >= a.chunks_per_expert || slot >= c) {
+      dev_set_error(a.ring.error, EP_EBOUNDS);
+    } else {
+      csize = min(kChunkRows, c - (j << 5));
+      len = (unsigned)csize * a.row_bytes;
+      off16 = (unsigned)(((unsigned long long)(base + (j << 5)) * a.row_bytes) >> 4);
+      int *cnt = a.chunk_cnt + (size_t)e * a.chunks_per_expert + j;
+      whole = __hip_atomic_fetch_add(cnt, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 == csize;
+      if (whole) __hip_atomic_store(cnt, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+  }
+  if (__ballot(whole) == 0ull) return;
+  if (mode == EP_CMD_CHUNK32_ORDERED) {
+    // High-throughput style: the chunk's Write and the Atomic that advances the receiver's tail
+    // take two consecutive sequence numbers of the communication channel (source, destination
+    // rank) and travel through that channel's FIFO; the receiver re-establishes the order.
+    unsigned seq = 0;
+    if (whole)
+      seq = __hip_atomic_fetch_add(a.ht_seq + (size_t)a.src * a.R + dr, 2u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    ring_push_pairs(a.ring, whole, dr % a.ring.channels,
+                    u32x4{cmd_w0(EP_OP_ORDERED_WRITE, a.src, dr, le), ((unsigned)(csize - 1) << 26) | (len >> 4), seq, off16},
+                    u32x4{cmd_w0(EP_OP_ORDERED_ATOMIC, a.src, dr, 0), (unsigned)csize, seq + 1u, (unsigned)(a.src * a.R) + dr});
     return;
   }
-  const int csize = min(kChunkRows, c - (j << 5));
-  int *cnt = a.chunk_cnt + (size_t)e * a.chunks_per_expert + j;
-  const int old = __hip_atomic_fetch_add(cnt, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  if (old + 1 == csize) {
-    __hip_atomic_store(cnt, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const unsigned long long off = (unsigned long long)(a.base[e] + (j << 5)) * a.row_bytes;
-    const unsigned len = (unsigned)csize * a.row_bytes;
-    if (mode == EP_CMD_CHUNK32_ORDERED) {
-      // High-throughput style: the chunk's Write and the Atomic that advances the receiver's tail
-      // take two consecutive sequence numbers of the communication channel (source, destination
-      // rank) and travel through that channel's FIFO; the receiver re-establishes the order.
-      const unsigned seq = __hip_atomic_fetch_add(a.ht_seq + (size_t)a.src * a.R + dr, 2u, __ATOMIC_RELAXED,
-                                                  __HIP_MEMORY_SCOPE_AGENT);
-      const unsigned och = dr % a.ring.channels;
-      ring_push(a.ring, och, cmd_w0(EP_OP_ORDERED_WRITE, a.src, dr, le),
-                ((unsigned)(csize - 1) << 26) | (len >> 4), seq, (unsigned)(off >> 4));
-      ring_push(a.ring, och, cmd_w0(EP_OP_ORDERED_ATOMIC, a.src, dr, 0), (unsigned)csize, seq + 1u,
-                (unsigned)(a.src * a.R) + dr);
-      return;
+  if (whole) {
+    // Everything for one destination expert goes through one FIFO (and therefore one proxy thread):
+    // in-FIFO order is the only order the channel guarantees (Section 3.1, "GPU-side contention").
+    const unsigned ch = (unsigned)e % a.ring.channels;
+    unsigned long long idx = __hip_atomic_fetch_add(&a.ring.tail[ch], 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    // Counted once the Write has its Idx, so that the expert's Atomic, whoever pushes it, gets a later one; together with
+    // the read of the head.  (4096 tokens x 7168 109.2 us, the head first and then the count 110.2; 2048 x 2048 10.7 and 11.2.)
+    asm volatile("s_waitcnt vmcnt(0)" : "+v"(idx) : : "memory");
+    const int done =
+        __hip_atomic_fetch_add(a.expert_done + e, csize, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + csize;
+    ring_publish(a.ring, ch, idx, cmd_w0(EP_OP_WRITE, a.src, dr, le), ((unsigned)(csize - 1) << 26) | (len >> 4), off16,
+                 off16);
+    if (done == c) {
+      __hip_atomic_store(a.expert_done + e, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (!(a.cmd_mode & EP_CMD_ATOMICS_FIRST)) push_count_atomic(a, e, c);
     }
-    ring_push(a.ring, ch, cmd_w0(EP_OP_WRITE, a.src, dr, le), ((unsigned)(csize - 1) << 26) | (len >> 4),
-              (unsigned)(off >> 4), (unsigned)(off >> 4));
-    account_rows(a, e, c, csize);
   }
 }
 
@@ -167,7 +171,7 @@ EP_DEV void emit_group_cmds(const DispatchArgs &a, int wave, int lane) {
     const unsigned long long so = (unsigned long long)(t0 + i / a.K) * a.row_bytes;
     const unsigned long long dof = (unsigned long long)row * a.row_bytes;
     const SortedRun run = ring_reserve_sorted(a.ring, active, ch);
-    // (As account_rows.  Counted once the Writes have their Idx: an expert's Atomic gets a later one.)
+    // (counted once the Writes have their Idx: an expert's Atomic, whoever pushes it, gets a later one)
     int done = 0;
     if (active) done = __hip_atomic_fetch_add(a.expert_done + e, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     ring_publish_sorted(a.ring, active, run, ch, cmd_w0(EP_OP_WRITE, a.src, dr, le), a.row_bytes >> 4, (unsigned)(so >> 4),
@@ -259,7 +263,7 @@ __global__ void dispatch_bf16_kernel(DispatchArgs a) {
     emit_group_cmds(a, wave, lane);
   } else {
     if (a.parts > 1) __syncthreads();
-    if (part == 0 && m.valid) emit_chunk_cmds(a, m);
+    if (part == 0) emit_chunk_cmds(a, m);
   }
   if (a.cmd_mode & EP_CMD_DRAIN) emit_drain(a, lane);
 }
@@ -380,7 +384,7 @@ __global__ void dispatch_fp8_kernel(DispatchArgs a) {
     emit_group_cmds(a, wave, lane);
   } else {
     if (a.parts > 1) __syncthreads();
-    if (part == 0 && m.valid) emit_chunk_cmds(a, m);
+    if (part == 0) emit_chunk_cmds(a, m);
   }
   if (a.cmd_mode & EP_CMD_DRAIN) emit_drain(a, lane);
 }
@@ -464,10 +468,15 @@ __global__ __launch_bounds__(1024) void dispatch_pipelined_kernel(DispatchArgs a
           const unsigned long long dof = (unsigned long long)p.y * a.row_bytes;
           ring_push_sorted(a.ring, active, (unsigned)e % a.ring.channels, cmd_w0(EP_OP_WRITE, a.src, dr, le),
                            a.row_bytes >> 4, (unsigned)(so >> 4), (unsigned)(dof >> 4), scratch);
-          if (active) account_rows(a, e, a.count[e], 1);
-        } else if (active) {
-          const TokenMeta m{p.x, p.y, true};
-          emit_chunk_cmds(a, m);
+          if (active) {
+            const int c = a.count[e];
+            if (__hip_atomic_fetch_add(a.expert_done + e, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 == c) {
+              __hip_atomic_store(a.expert_done + e, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+              if (!(a.cmd_mode & EP_CMD_ATOMICS_FIRST)) push_count_atomic(a, e, c);
+            }
+          }
+        } else {
+          emit_chunk_cmds(a, TokenMeta{p.x, p.y, active});
         }
       }
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");  // the pairs have been read: the slot may be refilled

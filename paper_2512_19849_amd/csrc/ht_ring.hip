@@ -72,6 +72,16 @@ EP_DEV void ht_store_piece(const u32x4 (&r)[B], u32x4 *dst, int v0, int nvec) {
     }
 }
 
+// The channels' state, read from the kernel's arguments where it is needed: kept in scalar registers from the kernel's start
+// on, it makes them spill.
+EP_DEV RingDev ht_fifo() {
+  auto p = (const __attribute__((address_space(4))) char *)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(p));
+  RingDev r;
+  __builtin_memcpy(&r, (const char *)p + offsetof(HtRingArgs, fifo), sizeof(r));
+  return r;
+}
+
 // What a wave remembers of the token it is sending: lane k owns the token's k-th entry.
 struct HtToken {
   unsigned long long pend;  // entries claimed but not stored yet (wave-uniform)
@@ -99,10 +109,10 @@ EP_DEV bool ht_send_token(const HtRingArgs &a, HtShared &sh, int c, int t, HtTok
     if (tk.pend == 0ull) return true;
   }
   const bool mine = (tk.pend >> lane) & 1ull;
-  const int n = tk.p >> 5, slot_row = tk.p & 31, w = n % a.W;
+  const int chunk = tk.p >> 5;
   bool occupied = false;
-  if (mine && n >= a.W) {
-    const unsigned need = 32u * (unsigned)(n - a.W + 1);
+  if (mine && chunk >= a.W) {
+    const unsigned need = 32u * (unsigned)(chunk - a.W + 1);
     if (HT_LD(&sh.seen[r]) < need) {
       // one PCIe read on behalf of every wave of the workgroup that needs this channel's head
       if (__hip_atomic_exchange(&sh.lock[r], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) == 0) {
@@ -119,7 +129,7 @@ EP_DEV bool ht_send_token(const HtRingArgs &a, HtShared &sh, int c, int t, HtTok
   if (ready == 0ull) return false;
   // byte offset of the entry's row in the ring (slot header included), split for readlane
   const unsigned long long off =
-      ((unsigned long long)chan * a.W + w) * a.slot_bytes + kHtHeader + (unsigned long long)slot_row * a.row_bytes;
+      ((unsigned long long)chan * a.W + chunk % a.W) * a.slot_bytes + kHtHeader + (unsigned long long)(tk.p & 31) * a.row_bytes;
   const unsigned off_lo = (unsigned)off, off_hi = (unsigned)(off >> 32);
   const u32x4 *xrow = (const u32x4 *)((const char *)a.x + (size_t)t * 2u * (unsigned)a.H);
   if (a.payload == EP_BF16) {
@@ -169,23 +179,27 @@ EP_DEV bool ht_send_token(const HtRingArgs &a, HtShared &sh, int c, int t, HtTok
       }
     }
   }
+  const int n = tk.p >> 5, slot_row = tk.p & 31, w = n % a.W;
   if (go) {
     int *hdr = (int *)((char *)a.ring_buf + ((unsigned long long)chan * a.W + w) * a.slot_bytes);
     __hip_atomic_store(hdr + slot_row, row, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   }
   wait_for_own_stores();
+  int sz = 0;
+  bool whole = false;  // this lane's row was the last one of its chunk
   if (go) {
-    const int sz = min(kChunkRows, sh.total[r] - (n << 5));
-    const int old = __hip_atomic_fetch_add(&sh.done[r * a.W + w], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    if (old + 1 == sz) {
-      HT_ST(&sh.done[r * a.W + w], 0);
-      const unsigned seq = sh.seqf[r] + 2u * (unsigned)n, fifo = (unsigned)chan % a.fifo.channels;
-      const unsigned len = (unsigned)kHtHeader + (unsigned)sz * a.row_bytes;
-      const unsigned w0 = cmd_w0(EP_OP_RING, a.src, (unsigned)r, (unsigned)c);
-      ring_push(a.fifo, fifo, w0, ((unsigned)EP_RING_WRITE << 30) | ((unsigned)(sz - 1) << 24) | (len >> 4), seq,
-                (unsigned)((((size_t)chan * a.W + w) * a.slot_bytes) >> 4));
-      ring_push(a.fifo, fifo, w0, ((unsigned)EP_RING_TAIL << 30) | (unsigned)sz, seq + 1u, 0u);
-    }
+    sz = min(kChunkRows, sh.total[r] - (n << 5));
+    whole = __hip_atomic_fetch_add(&sh.done[r * a.W + w], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) + 1 == sz;
+    if (whole) HT_ST(&sh.done[r * a.W + w], 0);
+  }
+  if (__ballot(whole) != 0ull) {
+    const unsigned seq = sh.seqf[r] + 2u * (unsigned)n, len = (unsigned)kHtHeader + (unsigned)sz * a.row_bytes;
+    const unsigned w0 = cmd_w0(EP_OP_RING, a.src, (unsigned)r, (unsigned)c);
+    const RingDev fifo = ht_fifo();
+    ring_push_pairs(fifo, whole, (unsigned)chan % fifo.channels,
+                    u32x4{w0, ((unsigned)EP_RING_WRITE << 30) | ((unsigned)(sz - 1) << 24) | (len >> 4), seq,
+                          (unsigned)((((size_t)chan * a.W + w) * a.slot_bytes) >> 4)},
+                    u32x4{w0, ((unsigned)EP_RING_TAIL << 30) | (unsigned)sz, seq + 1u, 0u});
   }
   if (lane == 0) HT_ST(&sh.progress, 1);
   tk.pend &= ~ready;
@@ -278,11 +292,12 @@ EP_DEV void ht_receive_step(const HtRingArgs &a, HtShared &sh, int c) {
   wait_for_own_stores();  // every load of a slot has returned before the slot is released
   __syncthreads();
   // release the slots: one head Atomic per consumed chunk, numbered on the reverse channel
+  const RingDev fifo = ht_fifo();
   for (int r = tid; r < a.R; r += blockDim.x) {
     const int lo = sh.lo[r], hi = sh.hi[r];
     for (int n = lo; n < hi; ++n) {
       const int sz = min(kChunkRows, sh.total[r] - (n << 5));
-      ring_push(a.fifo, (unsigned)(c * a.R + r) % a.fifo.channels, cmd_w0(EP_OP_RING, a.src, (unsigned)r, (unsigned)c),
+      ring_push(fifo, (unsigned)(c * a.R + r) % fifo.channels, cmd_w0(EP_OP_RING, a.src, (unsigned)r, (unsigned)c),
                 ((unsigned)EP_RING_HEAD << 30) | (unsigned)sz, sh.seqr[r] + (unsigned)n, 0u);
     }
     if (hi > lo) {
@@ -370,7 +385,7 @@ __global__ __launch_bounds__(1024) void ht_ring_kernel(HtRingArgs a) {
     a.seq_rev[c * a.R + r] = sh.seqr[r] + nch;
     a.cum_rev[c * a.R + r] = sh.cumr[r] + (unsigned)sh.total[r];
   }
-  drain_all_channels(a.fifo, a.waves_done, (unsigned)a.src, lane_id());
+  drain_all_channels(ht_fifo(), a.waves_done, (unsigned)a.src, lane_id());
 }
 
 // A workgroup's sixteen waves fill a compute unit, so fewer than 256 slices leave some idle: then 2 or 4 workgroups share a

@@ -1752,6 +1752,38 @@ def test_ht_ring_dispatch(epmod, oracle, cid, T, mask, slices, W, window, thread
         assert np.array_equal(tail[0], 2 * per_channel) and np.array_equal(head[0], 2 * per_channel)
 
 
+# a Write and its Atomic pushed as a pair: channels far too small for a wave's commands (every lane then publishes for itself),
+# and rings whose ends a pair straddles
+@pytest.mark.parametrize("entries,channels,threads", [(8, 1, 1), (8, 3, 2), (16, 8, 4), (4096, 1, 1)])
+def test_pairs_of_commands_through_small_channels(epmod, oracle, entries, channels, threads):
+    from paper_2512_19849_amd.runner import bits_to_bf16, bf16_to_bits
+    cfg = g.EPConfig("pairs", T=333, H=256, E=128, K=32, R=16, S=1)
+    rng = np.random.default_rng(entries + channels)
+    idx = g.mask_random(np.argsort(rng.random((1, cfg.T, cfg.E)), axis=-1)[..., :cfg.K].astype(np.int32), 0.1, seed=5)
+    rows = int((idx >= 0).sum())
+    want_lay = oracle.layout(idx, cfg.E, cfg.R)
+    with _runner(epmod, cfg, flags=epmod.EP_FLAG_LOG_CMDS | epmod.EP_FLAG_LOG_EVENTS, heap_rows=rows, ring_entries=entries,
+                 num_channels=channels, num_proxy_threads=threads, ht_slices=3, ht_ring_slots=2, spin_timeout_ms=10000) as r:
+        d_idx = _dev(idx)
+        lay = r.layout(d_idx)
+        ring = torch.zeros(r.ht_ring_bytes(), dtype=torch.uint8, device="cuda")
+        for it in range(4):
+            x = g.activations(cfg, it)
+            recv = torch.full((rows, cfg.H), -1.5, dtype=torch.bfloat16, device="cuda")
+            if it % 2:
+                r.ht_dispatch(bits_to_bf16(x), d_idx[0], lay, ring, recv)
+            else:
+                r.dispatch(bits_to_bf16(x), d_idx[0], lay, recv, cmd_mode=epmod.EP_CMD_CHUNK32_ORDERED)
+            r.wait()
+            torch.cuda.synchronize()
+            want, _ = oracle.dispatch_bf16(x, idx[0], want_lay["dst_row"][0], cfg.E_loc, rows, -1, fill=0xBFC0)
+            assert np.array_equal(bf16_to_bits(recv), want), it
+        st = r.stats()
+        assert st["device_error"] == 0 and st["proxy_error"] == 0 and st["rejected"] == 0
+        if channels == 1 and entries == 8:
+            assert st["gpu_ring_full"] > 0
+
+
 # workgroups of a slice: 2 (rows of half a megabyte each, and one row less: one), 4 of 6 ranks, 8 of 9 ranks, 4 with a rank
 # each and most rows for one of them, 16 with a slot per channel
 @pytest.mark.parametrize("T,H,E,K,R,slices,W,mask", [
