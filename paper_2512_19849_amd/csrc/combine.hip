@@ -27,12 +27,9 @@ EP_DEV void fma8(float (&acc)[8], float w, const u32x4 &v) {
 // The slices of one wave, one after the other: K loads in flight, the chain in ascending k, the packed
 // result kept in registers; the stores of all slices leave together at the end, so that a wave's writes
 // do not trickle into its reads.  STREAM: non-temporal loads (rows that no cache is expected to hold).
-// Masked entries load nothing (a row is the same for all lanes, so that is a scalar branch; a second read of a valid row in
-// their place was not free).  Half of the entries masked: 8192 tokens x 4096 top-8 60 -> 55 us, 1024 x 7168 14.8 -> 12.3;
-// partial and final reduce of 8192 x 4096, where 5.2 of 8 rows per token remain, 210 -> 204; nothing masked: no difference.
-// (The partial reduce below, with nothing masked, is 1% slower without the second reads.)
 template <int VPL, int KT, bool STREAM>
-EP_DEV void combine_slices(const u32x4 *y, u32x4 *out, const int (&rows)[KT], const float (&ws)[KT], int nvec, int v0) {
+EP_DEV void combine_slices(const u32x4 *y, u32x4 *out, const int (&rows)[KT], const float (&ws)[KT], int safe, int nvec,
+                           int v0) {
   u32x4 res[VPL];
 #pragma unroll
   for (int i = 0; i < VPL; ++i)
@@ -40,10 +37,8 @@ EP_DEV void combine_slices(const u32x4 *y, u32x4 *out, const int (&rows)[KT], co
       u32x4 ld[KT];
 #pragma unroll
       for (int k = 0; k < KT; ++k) {
-        if (rows[k] >= 0) {
-          const u32x4 *p = y + (size_t)rows[k] * nvec + v0 + i * 64;
-          ld[k] = STREAM ? __builtin_nontemporal_load(p) : *p;
-        }
+        const u32x4 *p = y + (size_t)(rows[k] >= 0 ? rows[k] : safe) * nvec + v0 + i * 64;
+        ld[k] = STREAM ? __builtin_nontemporal_load(p) : *p;
       }
       float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -93,6 +88,7 @@ __global__ __launch_bounds__(256) void combine_kernel(CombineArgs a) {
   }
   const u32x4 *y = (const u32x4 *)a.y;
   if constexpr (KT > 0) {
+    const int safe = __builtin_amdgcn_readlane(row, __builtin_ctzll(vmask));
     int rows[KT];
     float ws[KT];
 #pragma unroll
@@ -102,11 +98,11 @@ __global__ __launch_bounds__(256) void combine_kernel(CombineArgs a) {
     }
     // (wave-uniform; two instances so that each keeps its own kind of load)
     if (fresh) {
-      combine_slices<VPL, KT, false>(y, out, rows, ws, nvec, v0);
+      combine_slices<VPL, KT, false>(y, out, rows, ws, safe, nvec, v0);
       // (keeps the optimiser from folding the two instances into one, which drops the streaming hint of the other)
       asm volatile("" ::: "memory");
     } else {
-      combine_slices<VPL, KT, true>(y, out, rows, ws, nvec, v0);
+      combine_slices<VPL, KT, true>(y, out, rows, ws, safe, nvec, v0);
     }
   } else {
 #pragma unroll
