@@ -9,6 +9,7 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+import warnings
 from typing import Optional
 
 import numpy as np
@@ -157,7 +158,8 @@ def _ptr(t) -> Optional[int]:
 
 
 class _General:
-    """In the place of _epcall until torch has initialised the device: every call takes the general path."""
+    """In the place of _epcall until torch has initialised the device, or where there is none: every call takes the general
+    path."""
 
     def __getattr__(self, name):
         return lambda *args: NotImplemented
@@ -167,18 +169,30 @@ _torch_c = None  # torch._C, once torch has initialised the device
 _fast = _General()  # then _epcall: the calls of a step without ctypes; NotImplemented where an argument is not a plain one
 
 
+def _use_direct_calls() -> None:
+    """_epcall, if it is there and can be loaded: the library is whole without it."""
+    global _fast
+    load_library()
+    try:
+        from . import _epcall
+    except ImportError as e:
+        if os.path.exists(_build.CALL):
+            warnings.warn(f"{_build.CALL} cannot be loaded, calls go through ctypes: {e}", RuntimeWarning)
+        return
+    _epcall.set_address_type(Address)
+    _fast = _epcall
+
+
 def _stream(stream) -> Optional[int]:
     """The stream's handle; None is torch's current stream, whose raw handle costs 0.2 us a call (through a
     torch.cuda.Stream object: 2.9 us, as much as a kernel launch)."""
-    global _torch_c, _fast
+    global _torch_c
     if stream is None:
         if _torch_c is None:
             import torch
             torch.cuda.current_stream()
-            load_library()
-            from . import _epcall
-            _epcall.set_address_type(Address)
-            _torch_c, _fast = torch._C, _epcall
+            _use_direct_calls()
+            _torch_c = torch._C
         return _torch_c._cuda_getCurrentRawStream(_torch_c._cuda_getDevice())
     return getattr(stream, "cuda_stream", stream)
 

@@ -1,4 +1,7 @@
 """The module that takes tensors to the C calls: plain arguments go through, everything else is left to the general path."""
+import contextlib
+import sys
+
 import numpy as np
 import pytest
 
@@ -55,3 +58,30 @@ def test_rows(call, src, monkeypatch):
         else:
             assert binding._ptr(runner._row(t, src)) == t[src].data_ptr()
     assert call.row(torch.zeros(()), 0) is NotImplemented and call.row(torch.zeros(0, 3), 0) is NotImplemented
+
+
+@pytest.fixture
+def fresh(monkeypatch):
+    """The binding as it is before the first call of a program whose device torch has initialised."""
+    import paper_2512_19849_amd as package
+    binding.load_library()
+    monkeypatch.setattr(binding, "_torch_c", None)
+    monkeypatch.setattr(binding, "_fast", binding._General())
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda *a: None)
+    monkeypatch.setattr(torch._C, "_cuda_getDevice", lambda: 0, raising=False)
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: 0, raising=False)
+    monkeypatch.delattr(package, "_epcall", raising=False)
+    return monkeypatch
+
+
+@pytest.mark.parametrize("file", [False, True])
+def test_the_library_is_whole_without_the_module(fresh, file, tmp_path):
+    fresh.setitem(sys.modules, "paper_2512_19849_amd._epcall", None)  # (its import fails)
+    fresh.setattr(binding._build, "CALL", str(tmp_path / "_epcall.so"))
+    if file:
+        (tmp_path / "_epcall.so").write_bytes(b"")
+    for _ in range(2):
+        with pytest.warns(RuntimeWarning) if file and binding._torch_c is None else contextlib.nullcontext():
+            with pytest.raises(binding.EPError) as e:
+                binding.ep_combine(0, T8, T8, TK, 4, 8, T8)
+        assert e.value.rc == binding.EP_EINVAL and isinstance(binding._fast, binding._General)
