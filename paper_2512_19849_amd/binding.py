@@ -9,6 +9,7 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+import sys
 import warnings
 from typing import Optional
 
@@ -157,22 +158,29 @@ def _ptr(t) -> Optional[int]:
     return t.ctypes.data
 
 
+def _leave(*args):
+    return NotImplemented
+
+
 class _General:
     """In the place of _epcall until torch has initialised the device, or where there is none: every call takes the general
     path."""
 
     def __getattr__(self, name):
-        return lambda *args: NotImplemented
+        setattr(self, name, _leave)
+        return _leave
 
 
 _torch_c = None  # torch._C, once torch has initialised the device
 _fast = _General()  # then _epcall: the calls of a step without ctypes; NotImplemented where an argument is not a plain one
+_fast_tried = False
 
 
 def _use_direct_calls() -> None:
     """_epcall, if it is there and can be loaded: the library is whole without it."""
-    global _fast
+    global _fast, _fast_tried
     load_library()
+    _fast_tried = True
     try:
         from . import _epcall
     except ImportError as e:
@@ -191,9 +199,14 @@ def _stream(stream) -> Optional[int]:
         if _torch_c is None:
             import torch
             torch.cuda.current_stream()
-            _use_direct_calls()
+            if not _fast_tried:
+                _use_direct_calls()
             _torch_c = torch._C
         return _torch_c._cuda_getCurrentRawStream(_torch_c._cuda_getDevice())
+    if not _fast_tried:
+        torch = sys.modules.get("torch")
+        if torch is not None and torch.cuda.is_initialized():
+            _use_direct_calls()
     return getattr(stream, "cuda_stream", stream)
 
 

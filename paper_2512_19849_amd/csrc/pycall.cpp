@@ -1,8 +1,8 @@
 // The calls of a step from Python: arguments straight from the tensors to the C ABI (include/ep.h).  Marshalling through
 // ctypes costs 2 us and more a call, nearly as much as the launch behind it, and steps of few tokens are bound by the calls of
-// the host.  What is not one of the plain argument kinds (exact contiguous
-// tensors, None, addresses, ints that fit) is left to the general path: the functions then return NotImplemented and have
-// done nothing.
+// the host.  What is not one of the plain argument kinds (exact contiguous tensors, None, addresses, ints that fit; a stream
+// as None, a handle or a stream object) is left to the general path: the functions then return NotImplemented and have done
+// nothing.
 #include <Python.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/autograd/python_variable.h>
@@ -38,7 +38,12 @@ struct Args {
   void *handle(size_t i) { return PyLong_CheckExact(a[i]) ? word(a[i]) : refuse(); }
   void *stream(size_t i) {
     if (a[i] == Py_None) return c10::hip::getCurrentHIPStream().stream();
-    return handle(i);
+    if (PyLong_CheckExact(a[i])) return word(a[i]);
+    PyObject *s = PyObject_GetAttrString(a[i], "cuda_stream");
+    if (!s) PyErr_Clear();
+    void *p = s && PyLong_CheckExact(s) ? word(s) : refuse();
+    Py_XDECREF(s);
+    return p;
   }
   long long number(size_t i, long long lowest, long long highest) {
     int overflow = 0;

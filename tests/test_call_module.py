@@ -67,6 +67,7 @@ def fresh(monkeypatch):
     binding.load_library()
     monkeypatch.setattr(binding, "_torch_c", None)
     monkeypatch.setattr(binding, "_fast", binding._General())
+    monkeypatch.setattr(binding, "_fast_tried", False, raising=False)
     monkeypatch.setattr(torch.cuda, "current_stream", lambda *a: None)
     monkeypatch.setattr(torch._C, "_cuda_getDevice", lambda: 0, raising=False)
     monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: 0, raising=False)
@@ -80,8 +81,23 @@ def test_the_library_is_whole_without_the_module(fresh, file, tmp_path):
     fresh.setattr(binding._build, "CALL", str(tmp_path / "_epcall.so"))
     if file:
         (tmp_path / "_epcall.so").write_bytes(b"")
-    for _ in range(2):
-        with pytest.warns(RuntimeWarning) if file and binding._torch_c is None else contextlib.nullcontext():
+    for first in (True, False):
+        with pytest.warns(RuntimeWarning) if file and first else contextlib.nullcontext():
             with pytest.raises(binding.EPError) as e:
                 binding.ep_combine(0, T8, T8, TK, 4, 8, T8)
         assert e.value.rc == binding.EP_EINVAL and isinstance(binding._fast, binding._General)
+
+
+class Stream:
+    cuda_stream = 0
+
+
+@pytest.mark.parametrize("stream", [0, Stream()])
+def test_callers_that_pass_a_stream_get_the_direct_calls(fresh, call, stream):
+    for ready in (False, True):
+        fresh.setattr(torch.cuda, "is_initialized", lambda: ready)
+        with pytest.raises(binding.EPError):
+            binding.ep_combine(0, T8, T8, TK, 4, 8, T8, stream=stream)
+        assert (binding._fast is call) == ready
+    assert combine(call, stream=stream) == binding.EP_EINVAL
+    assert combine(call, stream=type("Odd", (), {"cuda_stream": "0"})()) is NotImplemented
