@@ -182,7 +182,11 @@ def _use_direct_calls() -> None:
     load_library()
     _fast_tried = True
     try:
+        import torch
+
         from . import _epcall
+        if _epcall.built_for != "torch " + torch.__version__:
+            raise ImportError(f"built for {_epcall.built_for}")
     except ImportError as e:
         if os.path.exists(_build.CALL):
             warnings.warn(f"{_build.CALL} cannot be loaded, calls go through ctypes: {e}", RuntimeWarning)

@@ -22,53 +22,79 @@ def hipcc() -> str:
     raise RuntimeError("hipcc not found")
 
 
+def _torch_version() -> str:
+    """The version of the torch that runs, empty where there is none: libep.so needs none."""
+    try:
+        import torch
+    except ImportError:
+        return ""
+    return torch.__version__
+
+
 def stale() -> bool:
-    if not os.path.exists(LIB) or not os.path.exists(CALL) or os.path.getmtime(CALL_SRC) > os.path.getmtime(CALL):
+    if not os.path.exists(LIB):
         return True
     t = os.path.getmtime(LIB)
     return any(os.path.getmtime(os.path.join(CSRC, f)) > t for f in SOURCES + HEADERS)
 
 
+def call_stale() -> bool:
+    """_epcall is missing, older than what it is built from, or built for another torch (it carries the version's text)."""
+    if not os.path.exists(CALL):
+        return True
+    t = os.path.getmtime(CALL)
+    if any(os.path.getmtime(f) > t for f in (CALL_SRC, os.path.join(HERE, "..", "include", "ep.h"))):
+        return True
+    version = _torch_version()
+    with open(CALL, "rb") as f:
+        return bool(version) and f"torch {version}\0".encode() not in f.read()
+
+
 def build_lib(force: bool = True, verbose: bool = False) -> str:
-    """Compile every HIP/C++ source of the library for gfx950 into libep.so, and the module that calls it from Python."""
-    if not force and not stale():
-        return LIB
-    objs = []
-    common = ["-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function"]
-    for src in SOURCES:
-        obj = os.path.join(CSRC, src + ".o")
-        cmd = [hipcc(), *common, "-c", os.path.join(CSRC, src), "-o", obj]
-        if src.endswith(".hip"):
-            # packed fp32 ALU forms are kept off for all device code
-            cmd[1:1] = ["--offload-arch=gfx950", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
+    """Compile every HIP/C++ source of the library for gfx950 into libep.so, and the module that calls it from Python.
+    The library needs neither torch nor g++; without them it is built alone, and the binding calls it through ctypes."""
+    if force or stale():
+        objs = []
+        common = ["-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function"]
+        for src in SOURCES:
+            obj = os.path.join(CSRC, src + ".o")
+            cmd = [hipcc(), *common, "-c", os.path.join(CSRC, src), "-o", obj]
+            if src.endswith(".hip"):
+                # packed fp32 ALU forms are kept off for all device code
+                cmd[1:1] = ["--offload-arch=gfx950", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
+            if verbose:
+                print(" ".join(cmd))
+            subprocess.run(cmd, check=True)
+            objs.append(obj)
+        cmd = [hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs, "-lpthread"]
         if verbose:
             print(" ".join(cmd))
         subprocess.run(cmd, check=True)
-        objs.append(obj)
-    cmd = [hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs, "-lpthread"]
-    if verbose:
-        print(" ".join(cmd))
-    subprocess.run(cmd, check=True)
-    build_call(verbose)
+    if force or call_stale():
+        build_call(verbose)
     return LIB
 
 
-def build_call(verbose: bool = False) -> str:
+def build_call(verbose: bool = False) -> None:
     """_epcall, the module that takes tensors to the calls of a step (host code only)."""
     import sysconfig
 
+    if os.path.exists(CALL):
+        os.remove(CALL)  # (what is out of date is not left behind, whether or not a new one can be made)
+    if not _torch_version() or not shutil.which("g++"):
+        print(f"{os.path.basename(CALL)} is not built (it needs torch and g++): calls go through ctypes")
+        return
     import torch
     home = os.path.dirname(torch.__file__)
     lib = os.path.join(home, "lib")
     cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
-           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-I" + os.path.join(home, "include"),
-           "-I" + os.path.join(home, "include", "torch", "csrc", "api", "include"),
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", f'-DEP_TORCH="{_torch_version()}"',
+           "-I" + os.path.join(home, "include"), "-I" + os.path.join(home, "include", "torch", "csrc", "api", "include"),
            "-I" + sysconfig.get_paths()["include"], "-I/opt/rocm/include", CALL_SRC, "-o", CALL, "-L" + HERE, "-l:libep.so",
            "-L" + lib, "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10", "-lc10_hip", "-Wl,-rpath,$ORIGIN"]
     if verbose:
         print(" ".join(cmd))
     subprocess.run(cmd, check=True)
-    return CALL
 
 
 PROBE_SRC = os.path.join(HERE, "probes", "mem_patterns.hip")

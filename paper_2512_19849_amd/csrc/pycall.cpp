@@ -145,8 +145,14 @@ PyMethodDef methods[] = {EP_CALL(ep_layout),
                          {"row", (PyCFunction)(void (*)(void))row, METH_FASTCALL, nullptr},
                          {"set_address_type", set_address_type, METH_O, nullptr},
                          {nullptr, nullptr, 0, nullptr}};
+// The torch that this was built for (the binding asks: another one's tensors may be laid out otherwise).
+constexpr char built_for[] = "torch " EP_TORCH;
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_epcall", nullptr, -1, methods};
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__epcall(void) { return PyModule_Create(&module); }
+PyMODINIT_FUNC PyInit__epcall(void) {
+  PyObject *m = PyModule_Create(&module);
+  if (m && PyModule_AddStringConstant(m, "built_for", built_for)) Py_CLEAR(m);
+  return m;
+}

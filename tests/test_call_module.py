@@ -75,12 +75,15 @@ def fresh(monkeypatch):
     return monkeypatch
 
 
-@pytest.mark.parametrize("file", [False, True])
-def test_the_library_is_whole_without_the_module(fresh, file, tmp_path):
-    fresh.setitem(sys.modules, "paper_2512_19849_amd._epcall", None)  # (its import fails)
-    fresh.setattr(binding._build, "CALL", str(tmp_path / "_epcall.so"))
-    if file:
-        (tmp_path / "_epcall.so").write_bytes(b"")
+@pytest.mark.parametrize("file", [False, True, "of another torch"])
+def test_the_library_is_whole_without_the_module(fresh, call, file, tmp_path):
+    if file == "of another torch":
+        fresh.setattr(torch, "__version__", "0.0")
+    else:
+        fresh.setitem(sys.modules, "paper_2512_19849_amd._epcall", None)  # (its import fails)
+        fresh.setattr(binding._build, "CALL", str(tmp_path / "_epcall.so"))
+        if file:
+            (tmp_path / "_epcall.so").write_bytes(b"")
     for first in (True, False):
         with pytest.warns(RuntimeWarning) if file and first else contextlib.nullcontext():
             with pytest.raises(binding.EPError) as e:
