@@ -7,6 +7,7 @@
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/autograd/python_variable.h>
 
+#include <exception>
 #include <limits>
 #include <tuple>
 #include <type_traits>
@@ -78,17 +79,30 @@ T convert(Args &in, size_t i, size_t n) {
 template <class... A, size_t... I>
 PyObject *run(int (*f)(A...), PyObject *const *a, std::index_sequence<I...>) {
   Args in{a};
+  int rc = 0;
+  std::exception_ptr thrown;
   try {
     const std::tuple<A...> v{convert<A>(in, I, sizeof...(A))...};
     if (!in.plain) Py_RETURN_NOTIMPLEMENTED;
-    int rc;
     Py_BEGIN_ALLOW_THREADS
-    rc = std::apply(f, v);
+    try {  // (what the library throws must not pass the line that takes the interpreter's lock back)
+      rc = std::apply(f, v);
+    } catch (...) {
+      thrown = std::current_exception();
+    }
     Py_END_ALLOW_THREADS
-    return PyLong_FromLong(rc);
   } catch (...) {  // (from torch: the general path meets the same and reports it)
     Py_RETURN_NOTIMPLEMENTED;
   }
+  if (!thrown) return PyLong_FromLong(rc);
+  try {
+    std::rethrow_exception(thrown);
+  } catch (const std::exception &e) {
+    PyErr_SetString(PyExc_RuntimeError, e.what());
+  } catch (...) {
+    PyErr_SetString(PyExc_RuntimeError, "exception out of the library");
+  }
+  return nullptr;
 }
 template <class... A>
 PyObject *run(int (*f)(A...), PyObject *const *a, Py_ssize_t n) {

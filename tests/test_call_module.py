@@ -1,5 +1,7 @@
 """The module that takes tensors to the C calls: plain arguments go through, everything else is left to the general path."""
 import contextlib
+import shutil
+import subprocess
 import sys
 
 import numpy as np
@@ -104,3 +106,35 @@ def test_callers_that_pass_a_stream_get_the_direct_calls(fresh, call, stream):
         assert (binding._fast is call) == ready
     assert combine(call, stream=stream) == binding.EP_EINVAL
     assert combine(call, stream=type("Odd", (), {"cuda_stream": "0"})()) is NotImplemented
+
+
+THROWS = """
+import importlib.util, sys, threading, torch
+spec = importlib.util.spec_from_file_location("_epcall", sys.argv[1])
+call = importlib.util.module_from_spec(spec)
+spec.loader.exec_module(call)
+t = torch.zeros(4, 2, dtype=torch.int32)
+for _ in range(2):
+    try:
+        print("returned", call.ep_combine(0, t, t, t, 4, 8, t, 0))
+    except RuntimeError as e:
+        print("raised", e)
+worker = threading.Thread(target=print, args=("alive",))
+worker.start()
+worker.join()
+"""
+
+
+def test_an_exception_out_of_the_library_is_raised(monkeypatch, tmp_path):
+    from paper_2512_19849_amd import build
+    if not shutil.which("g++"):
+        pytest.skip("g++ is not available")
+    names = ["layout", "dispatch", "recv_wait", "fp8_unpack", "ht_dispatch", "dedup", "gather_index", "combine_partial"]
+    (tmp_path / "lib.cpp").write_text("#include <new>\nextern \"C\" {\nint ep_combine() { throw std::bad_alloc(); }\n" +
+                                      "".join(f"int ep_{n}() {{ return 0; }}\n" for n in names) + "}\n")
+    subprocess.run(["g++", "-shared", "-fPIC", "-o", str(tmp_path / "libep.so"), str(tmp_path / "lib.cpp")], check=True)
+    monkeypatch.setattr(build, "HERE", str(tmp_path))
+    monkeypatch.setattr(build, "CALL", str(tmp_path / "_epcall.so"))
+    build.build_call()
+    r = subprocess.run([sys.executable, "-c", THROWS, build.CALL], capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0 and r.stdout.split("\n")[:3] == ["raised std::bad_alloc"] * 2 + ["alive"], r.stdout + r.stderr
