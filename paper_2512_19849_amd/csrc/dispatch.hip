@@ -134,12 +134,14 @@ EP_DEV void emit_chunk_cmds(const DispatchArgs &a, const TokenMeta &m) {
 // What a small dispatch waits for is the proxy, which misses its caches once for every write that reaches a polled line.
 // Whole steps, groups / every workgroup on its own (us, rows of 7168, top-8 of 256 experts): 128 tokens 30 / 36, 256: 34 /
 // 51, 512: 48 / 73; 512 tokens x 4096: 41 / 49.
-// Bound by the chain of round trips behind the last row: the group's counter, the pairs, the reservation, then the experts'
-// counters and the cached heads together, and for complete experts a reservation and the heads once more.  With the experts'
-// counters on their own, and the leading Atomics pushed by the same wave ahead of its row (64 experts after the other), whole
-// steps of 8192 tokens x 1024 top-4 took 126 us, now 100; 4096 x 7168 top-8 in FP8 195 and 182; one token of 256 experts,
-// alone, 40.2 and 38.7.  With the pairs loaded ahead of the rows, which then wait for them too, 8192 x 1024 takes 114; with
-// the leading Atomics in a workgroup of their own, where the proxy sees them first, 128 tokens 1 us more.
+// Bound by the chain of round trips behind the last row: the group's counter, the pairs, the reservation, the experts'
+// counters, the cached heads, and for complete experts a reservation and the heads once more.  The experts are counted ahead
+// of the command stores: behind them, the wait for the counters is one for the host's acknowledgement of the stores as well.
+// Whole steps, counted behind the stores / ahead of them, us: 8192 tokens x 1024 top-4 of 128 experts 109 / 83, of 256 112 /
+// 94, 4096 x 7168 top-8 in FP8 178 / 177.  With the leading Atomics pushed by the same wave ahead of its row (64 experts after
+// the other) one token of 256 experts, alone, takes 35 us, now 33; larger steps are the same.  With the pairs loaded ahead of
+// the rows, which then wait for them too, 8192 x 1024 took 14 us more; with the leading Atomics in a workgroup of their own,
+// where the proxy sees them first, 128 tokens 1 us more.
 EP_DEV void emit_group_cmds(const DispatchArgs &a, int wave, int lane) {
   extern __shared__ u32x4 s_dyn[];  // the scratch of ring_push_sorted
   __syncthreads();  // every wave has waited for its own stores before it came here
@@ -170,8 +172,9 @@ EP_DEV void emit_group_cmds(const DispatchArgs &a, int wave, int lane) {
     const unsigned dr = (unsigned)(e / a.E_loc), le = (unsigned)(e - (int)dr * a.E_loc), ch = (unsigned)e % a.ring.channels;
     const unsigned long long so = (unsigned long long)(t0 + i / a.K) * a.row_bytes;
     const unsigned long long dof = (unsigned long long)row * a.row_bytes;
-    const SortedRun run = ring_reserve_sorted(a.ring, active, ch);
-    // (counted once the Writes have their Idx: an expert's Atomic, whoever pushes it, gets a later one)
+    SortedRun run = ring_reserve_sorted(a.ring, active, ch);
+    // Counted once the Writes have their Idx: an expert's Atomic, whoever pushes it, gets a later one.
+    asm volatile("s_waitcnt vmcnt(0)" : "+v"(run.idx) : : "memory");
     int done = 0;
     if (active) done = __hip_atomic_fetch_add(a.expert_done + e, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     ring_publish_sorted(a.ring, active, run, ch, cmd_w0(EP_OP_WRITE, a.src, dr, le), a.row_bytes >> 4, (unsigned)(so >> 4),

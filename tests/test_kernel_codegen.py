@@ -35,3 +35,18 @@ def test_combine_keeps_cached_and_streaming_loads_apart(tmp_path):
         loads = re.findall(r"global_load_dwordx4[^\n]*", _kernel_body(asm, mangled))
         nt = [l for l in loads if re.search(r"\bnt\b", l)]
         assert len(nt) > 0 and len(nt) * 2 == len(loads), (mangled, len(nt), len(loads))
+
+
+@pytest.mark.skipif(not os.path.exists(HIPCC), reason="hipcc not installed")
+def test_rows_are_counted_behind_their_reservation(tmp_path):
+    """One command per row: an expert's rows are counted (the add at an address of the lane's own) once the reservation of
+    their Idx has returned.  The wait stands in the source, for nothing else orders two relaxed adds."""
+    asm = _assembly("dispatch.hip", tmp_path)
+    kernels = re.findall(r"^(_ZN2ep\d+dispatch_(?:bf16|fp8)_kernelILi\d+ELb1E\w*):", asm, re.M)
+    assert len(kernels) == 10
+    for mangled in kernels:
+        body = _kernel_body(asm, mangled)
+        counted = list(re.finditer(r"global_atomic_add v\d+, v\[\d+:\d+\], v\d+, off sc0", body))
+        assert len(counted) == 1, mangled
+        reserved = body.rindex("global_atomic_add_x2", 0, counted[0].start())
+        assert re.search(r"#ASMSTART\s+s_waitcnt vmcnt\(0\)\s+;+#ASMEND", body[reserved:counted[0].start()]), mangled
