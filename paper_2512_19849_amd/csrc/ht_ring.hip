@@ -1,5 +1,8 @@
 // Ring-buffer communication channels of the high-throughput mode: one or several workgroups per token slice play the
 // sending and the receiving end in turns, chunk slots reused under head/tail flow control.
+#include <cstddef>
+#include <type_traits>
+
 #include "ep_device.h"
 
 namespace ep {
@@ -387,6 +390,8 @@ __global__ __launch_bounds__(1024) void ht_ring_kernel(HtRingArgs a) {
   }
   drain_all_channels(ht_fifo(), a.waves_done, (unsigned)a.src, lane_id());
 }
+static_assert(std::is_same_v<decltype(&ht_ring_kernel), void (*)(HtRingArgs)> && std::is_standard_layout_v<HtRingArgs>,
+              "ht_fifo takes the kernel's arguments for one HtRingArgs");
 
 // A workgroup's sixteen waves fill a compute unit, so fewer than 256 slices leave some idle: then 2 or 4 workgroups share a
 // slice, each with the channels of every 2nd or 4th rank (a channel's state is its own, so they have nothing to say to each

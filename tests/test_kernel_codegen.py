@@ -50,3 +50,24 @@ def test_rows_are_counted_behind_their_reservation(tmp_path):
         assert len(counted) == 1, mangled
         reserved = body.rindex("global_atomic_add_x2", 0, counted[0].start())
         assert re.search(r"#ASMSTART\s+s_waitcnt vmcnt\(0\)\s+;+#ASMEND", body[reserved:counted[0].start()]), mangled
+
+
+@pytest.mark.skipif(not os.path.exists(HIPCC), reason="hipcc not installed")
+def test_ring_kernel_with_another_first_argument_is_refused(tmp_path):
+    """The ring kernel reads its channels' state at an offset from the start of the argument block, so nothing may come to
+    stand before the one argument it has."""
+    def compiles(src):
+        f = tmp_path / "ht_ring.hip"
+        f.write_text(src)
+        r = subprocess.run([HIPCC, "--offload-arch=gfx950", "-std=c++17", "-fsyntax-only", "-I" + CSRC, str(f)],
+                           capture_output=True, text=True)
+        return r.returncode == 0, r.stderr
+
+    with open(os.path.join(CSRC, "ht_ring.hip")) as f:
+        src = f.read()
+    ok, err = compiles(src)
+    assert ok, err
+    moved = src.replace("ht_ring_kernel(HtRingArgs a)", "ht_ring_kernel(int first, HtRingArgs a)").replace(
+        "(hipStream_t)stream, b)", "(hipStream_t)stream, 0, b)")
+    ok, err = compiles(moved)
+    assert not ok and err.count("error: ") and "ht_fifo" in err, err
