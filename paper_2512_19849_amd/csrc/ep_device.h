@@ -135,6 +135,7 @@ EP_DEV unsigned long long ring_publish_run(const RingDev &r, unsigned c, unsigne
       if (idx + next - head < r.entries) {
         ring_store(r, c, idx + next, next == 0 ? first : second);
         ++next;
+        stalled = false;  // (the next command's wait is its own: a limit and a count for each)
       } else {
         // Full: wait for the proxy to pop.  Thousands of lanes can be waiting on one channel, and
         // each re-read of the head is a PCIe round trip, so only the lane that holds the channel's
