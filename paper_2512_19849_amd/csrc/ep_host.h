@@ -136,11 +136,12 @@ struct Outbound {
 // thread adds its copies to the open batch; if nobody is launching it launches that batch, and what other threads add
 // meanwhile leaves together with the next one.
 struct CopyPool {
-  static constexpr int kSlots = 16;
+  static constexpr int kAhead = 3;           // batches under way, at most (see launch_open)
+  static constexpr int kSlots = kAhead + 1;  // ... and the open one
   std::mutex mu;           // guards `launching`, `open`, `number` and the open batch's descriptors
   bool launching = false;  // a thread is handing batches to the device
   CopyBatchArgs open{};    // the batch being filled
-  uint64_t number = 0;     // ... its number; descriptors and event are those of slot number % kSlots
+  uint64_t number = 0;     // ... its number, less than done + kSlots; descriptors and event are those of slot number % kSlots
   hipStream_t stream = nullptr;
   hipEvent_t events[kSlots] = {};
   CopyDesc *descs = nullptr;    // pinned host [kSlots][kCopyBatchMax]

@@ -211,14 +211,13 @@ void poll_batches(ep_handle *h) {
 }
 
 // Hands the open batch to the device, and again what has been added meanwhile.  `lk` holds C.mu and C.launching is false.
-// With kCopiesAhead batches under way the open one waits and grows: more launches in the queue do not start any copy
+// With kAhead batches under way the open one waits and grows: more launches in the queue do not start any copy
 // earlier.  (Step of 4096 tokens x 7168 with chunks, us: no limit 372 in 26 batches, three 348 in 16, two 349, one at a time
 // 362; a batch per thread, each with its launches, 370.  512 x 4096 82, a batch per thread 115; 16 tokens by rows 60 and 84.)
-constexpr uint64_t kCopiesAhead = 3;
 void launch_open(ep_handle *h, ProxyThread &P, std::unique_lock<std::mutex> &lk) {
   CopyPool &C = h->copies;
   C.launching = true;
-  while (C.open.n && C.number - C.done.load(std::memory_order_acquire) < kCopiesAhead) {
+  while (C.open.n && C.number - C.done.load(std::memory_order_acquire) < CopyPool::kAhead) {
     CopyBatchArgs b = C.open;
     const uint64_t number = C.number++;
     const size_t slot = number % CopyPool::kSlots;
@@ -244,12 +243,11 @@ void launch_copies(ep_handle *h, ProxyThread &P) {
   for (size_t at = 0; at < P.copies.size();) {
     CopyBatchArgs &b = C.open;
     const bool other = b.n && (b.src_base != P.copies_src || b.dst_base != P.copies_dst || b.n == kCopyBatchMax);
-    if (other && !C.launching && C.number - C.done.load(std::memory_order_acquire) < kCopiesAhead) {
+    if (other && !C.launching && C.number - C.done.load(std::memory_order_acquire) < CopyPool::kAhead) {
       launch_open(h, P, lk);
       continue;
     }
-    // (a slot is free once the batch that had it is done)
-    if (other || (b.n == 0 && C.number - C.done.load(std::memory_order_acquire) >= CopyPool::kSlots)) {
+    if (other) {
       lk.unlock();
       poll_batches(h);
       std::this_thread::yield();

@@ -1,6 +1,7 @@
 // Stand-alone driver for the copies of the proxy threads on their way through the shared batches, built with sanitizers by
-// tests/test_host_sanitizers.py.  A "device" thread copies the batches in order and marks their events late; the Writes
-// come from producer threads over all channels, in bursts and in trickles, into heaps that change between rounds.
+// tests/test_host_copy_pool.py.  A "device" thread copies the batches in order and marks their events late; the Writes
+// come from producer threads over all channels, in bursts and in trickles, into heaps that change between rounds, and once
+// while batches of the old heaps are under way and open.
 #include <condition_variable>
 #include <cstdio>
 
@@ -8,7 +9,8 @@
 using namespace ep;
 
 struct Job {
-  std::vector<CopyDesc> d;
+  const CopyDesc *d;  // (read when the batch is copied, as the kernel for many rows does)
+  int n;
   const char *src;
   char *dst;
   std::atomic<int> *pending;
@@ -17,6 +19,7 @@ static std::mutex jobs_mu;
 static std::condition_variable jobs_cv;
 static std::deque<Job> jobs;
 static bool quit = false;
+static std::atomic<bool> hold{false};  // the device copies nothing
 
 static void device() {
   for (int n = 0;; ++n) {
@@ -26,7 +29,8 @@ static void device() {
     Job j = std::move(jobs.front());
     jobs.pop_front();
     l.unlock();
-    for (auto &d : j.d) memcpy(j.dst + d.dst16 * 16ull, j.src + d.src16 * 16ull, d.len16 * 16ull);
+    while (hold.load()) std::this_thread::yield();
+    for (const CopyDesc *d = j.d; d < j.d + j.n; ++d) memcpy(j.dst + d->dst16 * 16ull, j.src + d->src16 * 16ull, d->len16 * 16ull);
     std::this_thread::sleep_for(std::chrono::microseconds(n % 5 * 20));
     j.pending->store(0, std::memory_order_release);
   }
@@ -51,9 +55,9 @@ int launch_row_probe(int, const int32_t *, int, long long, int, long long, void 
 int launch_ht_ring(const HtRingArgs &, const Tunables &, void *) { return 0; }
 int launch_fifo_stress(const RingDev &, int, int, unsigned long long *, unsigned long long *, void *) { return 0; }
 int launch_copy_batch(const CopyBatchArgs &b, void *) {
-  Job j{{b.host_descs, b.host_descs + b.n}, b.src_base, b.dst_base, (std::atomic<int> *)b.done};
+  Job j{b.host_descs, b.n, b.src_base, b.dst_base, (std::atomic<int> *)b.done};
   unsigned most = 0, least = ~0u;
-  for (auto &d : j.d) most = std::max(most, d.len16), least = std::min(least, d.len16);
+  for (int i = 0; i < b.n; ++i) most = std::max(most, j.d[i].len16), least = std::min(least, j.d[i].len16);
   if (b.n < 1 || b.n > kCopyBatchMax || most != b.max_len16 || least != b.min_len16 || j.pending->exchange(1)) return 1;
   std::lock_guard<std::mutex> l(jobs_mu);
   jobs.push_back(std::move(j));
@@ -61,6 +65,59 @@ int launch_copy_batch(const CopyBatchArgs &b, void *) {
   return 0;
 }
 }  // namespace ep
+
+// Heaps change with as many batches of the old ones under way as may be, and copies of the old ones in the open batch.
+static int change_under_way(ep_handle *h, char *a, char *b, size_t bytes) {
+  CopyPool &C = h->copies;
+  const auto until = [](auto f) {
+    while (!f()) std::this_thread::yield();
+  };
+  const auto heaps = [&](int i) {
+    h->src_base.store(a + i * bytes);
+    h->dst_base.store(b + i * bytes);
+  };
+  const auto write = [&](int e, uint32_t from, uint32_t row) {
+    uint64_t idx;
+    ep_host_push(h, e, 1u << 28 | (uint32_t)e, 16, from * 16, row * 16, &idx);
+    return idx;
+  };
+  memset(b, 0, 2 * bytes);
+  heaps(0);
+  hold.store(true);
+  const uint64_t before = C.launched.load();
+  uint32_t n = 0;
+  for (int i = 0; i < CopyPool::kAhead; ++i) {
+    write(0, n * 7, n), ++n;
+    until([&] { return C.launched.load() == before + i + 1; });
+  }
+  write(0, n * 7, n), ++n;
+  until([&] {
+    std::lock_guard<std::mutex> l(C.mu);
+    return C.open.n == 1;
+  });
+  heaps(1);
+  for (int e = 0; e < 4; ++e) {  // (a channel, and with it a proxy thread, for each)
+    const uint64_t idx = write(e, 1000 + e, 100 + e);
+    until([&] { return ep_host_check_completion(h, e, idx) == 1; });
+  }
+  std::this_thread::sleep_for(std::chrono::milliseconds(5));  // (they meet the open batch)
+  int bad = 0;
+  {
+    std::lock_guard<std::mutex> l(C.mu);
+    bad += C.open.n != 1 || C.open.dst_base != b || C.launched.load() != before + CopyPool::kAhead;
+  }
+  hold.store(false);
+  ep_host_expect_atomics(h, 4);
+  for (uint32_t e = 0; e < 4; ++e) {
+    uint64_t idx;
+    ep_host_push(h, (int)e, 2u << 28 | e, e ? 1 : 1 + n, 0, e, &idx);
+  }
+  bad += ep_wait(h) != 0;
+  for (uint32_t r = 0; r < n; ++r) bad += memcmp(b + r * 256, a + r * 7 * 256, 256) != 0;
+  for (uint32_t e = 0; e < 4; ++e) bad += memcmp(b + bytes + (100 + e) * 256, a + bytes + (1000 + e) * 256, 256) != 0;
+  for (size_t i = 0; i < 256; ++i) bad += b[100 * 256 + i] != 0 || b[bytes + i] != 0;
+  return bad;
+}
 
 int main() {
   std::thread dev(device);
@@ -104,6 +161,7 @@ int main() {
     bad += ep_wait(h) != 0;
     for (size_t r = 0; r < 16ull * per; ++r) bad += memcmp(dst + r * 256, src + r * 7 % rows * 256, r % per % 3 ? 256 : 128) != 0;
   }
+  bad += change_under_way(h, a.data(), b.data(), bytes);
   h->copies.descs = nullptr;
   for (auto &e : h->copies.events) e = nullptr;
   ep_proxy_stop(h);
