@@ -24,8 +24,8 @@ EP_DEV int lane_id() { return threadIdx.x & 63; }
 
 // This wave's place in its workgroup, in a scalar register: what is worked out from it (token, part of the row, addresses)
 // is then scalar work too.  As a vector value, the 64-bit division of a wave's number alone was 150 vector instructions ahead
-// of the combine's first load.  Whole steps: 128 tokens x 7168 over 32 sources 38.1 -> 35.9 us, 8192 x 4096 with a command
-// per row 257.6 -> 254.1, deduplicated 4096 x 7168 343.7 -> 342.0.
+// of the combine's first load.  Whole steps do not show it beyond what two runs differ by (vector / scalar, us: 128 tokens x
+// 7168 over 32 sources 34.2 / 34.8, 8192 x 4096 with a command per row 253.3 / 253.5, deduplicated 4096 x 7168 355.8 / 355.4).
 EP_DEV unsigned wave_id() { return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); }
 
 // ------------------------------------------------- FIFO channel, GPU side

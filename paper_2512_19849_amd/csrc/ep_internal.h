@@ -167,7 +167,7 @@ struct CopyRowBatch {
 };
 static_assert(sizeof(CopyRowBatch) <= 4000 && sizeof(CopyArgBatch) <= 4000, "kernel arguments");
 
-// Ring-buffer channels of the high-throughput mode: one workgroup per slice, sending and receiving in turns.
+// Ring-buffer channels of the high-throughput mode: one or more workgroups per slice, sending and receiving in turns.
 struct HtRingArgs {
   const void *x;           // bf16 [T,H]
   const int32_t *idx;      // [T,K]

@@ -14,9 +14,9 @@ namespace ep {
 // proxy.
 // A workgroup owns the channels of a token slice, or some of them (see launch_ht_ring), and plays
 // both ends of them in turns: a sending step (every wavefront takes a token, keeps its row in
-// registers and stores it into the slot of each of its destinations that is known to be free, then announces the chunks it completed) and a
-// receiving step (a sweep over the tails, the announced rows move to their final place, the slots
-// are released).  Neither step waits for the other end: a wavefront whose slot is still occupied
+// registers and stores it into the slot of each of its destinations that is known to be free, then
+// announces the chunks it completed) and a receiving step (a sweep over the tails, the announced
+// rows move to their final place, the slots are released).  Neither step waits for the other end: a wavefront whose slot is still occupied
 // keeps its claimed position and tries again after the next sweep.  A workgroup therefore depends
 // on nothing but the proxy, whatever the grid size and however many workgroups are resident, and
 // every compute unit has rows to store all the time.
@@ -393,10 +393,14 @@ __global__ __launch_bounds__(1024) void ht_ring_kernel(HtRingArgs a) {
 static_assert(std::is_same_v<decltype(&ht_ring_kernel), void (*)(HtRingArgs)> && std::is_standard_layout_v<HtRingArgs>,
               "ht_fifo takes the kernel's arguments for one HtRingArgs");
 
-// A workgroup's sixteen waves fill a compute unit, so fewer than 256 slices leave some idle: then 2 or 4 workgroups share a
-// slice, each with the channels of every 2nd or 4th rank (a channel's state is its own, so they have nothing to say to each
-// other).  As long as each still has half a megabyte to move; with less, the polls and the reads of the tokens, which every
-// one of them does, cost more.  Whole steps, one / two / four workgroups a slice, us:
+// A workgroup's sixteen waves fill a compute unit, so fewer than 256 slices leave some idle: then 2, 4, ... workgroups share a
+// slice, up to the number of ranks, each with the channels of every 2nd, 4th, ... rank (a channel's state is its own, so they
+// have nothing to say to each other).  As long as each still has half a megabyte to move; with less, the polls and the reads
+// of the tokens, which every one of them does, cost more.  Whole steps, 1 / 2 / 4 / 8 / 16 workgroups a slice, us:
+//   4 slices    4096 tokens x 7168 top-8 4783 / 3045 / 2662 / 2344 / 2415, 1024 x 7168 1151 / 780 / 683 / 515 / 404, 4096 x
+//               2048 1831 / 1402 / 1422 / 1486 / 1704 (16 by this rule: rows this narrow would be better off with 2)
+//   8 slices    4096 x 7168 2536 / 1610 / 1396 / 1234 / 1174, 4096 x 2048 972 / 713 / 732 / 755 / 787
+//   16 slices   4096 x 7168 1435 / 1003 / 873 / 698 / 631, 1024 x 7168 332 / 234 / 202 / 169 / 161 (0.46 MB each)
 //   64 slices   4096 tokens x 7168 top-8 656 / 514 / 441, 1536 x 7168 265 / 223 / 218, 1024 x 7168 179 / 170 / 168 (0.46 MB
 //               each), 768 x 7168 141 / 138 / 148 (0.34 MB), 1024 x 4096 113 / 109 / 127 (0.26 MB), in FP8 101 / 104 (0.27
 //               MB) / 129, 2048 x 2048 125 / 124 / 143 (0.26 MB)
@@ -410,7 +414,8 @@ int launch_ht_ring(const HtRingArgs &a, const Tunables &tune, void *stream) {
   const long long bytes = (long long)a.T * a.K * a.row_bytes;
   b.split = 1;
   while (b.split * 2 <= a.R && b.split * 2 * a.slices <= 256 && bytes >= kHtSplitBytes * a.slices * b.split * 2) b.split *= 2;
-  hipLaunchKernelGGL(ht_ring_kernel, dim3((unsigned)b.slices, (unsigned)b.split), dim3((unsigned)threads), 0, (hipStream_t)stream, b);
+  hipLaunchKernelGGL(ht_ring_kernel, dim3((unsigned)b.slices, (unsigned)b.split), dim3((unsigned)threads), 0,
+                     (hipStream_t)stream, b);
   return (int)hipGetLastError();
 }
 

@@ -211,9 +211,11 @@ void poll_batches(ep_handle *h) {
 }
 
 // Hands the open batch to the device, and again what has been added meanwhile.  `lk` holds C.mu and C.launching is false.
-// With kAhead batches under way the open one waits and grows: more launches in the queue do not start any copy
-// earlier.  (Step of 4096 tokens x 7168 with chunks, us: no limit 372 in 26 batches, three 348 in 16, two 349, one at a time
-// 362; a batch per thread, each with its launches, 370.  512 x 4096 82, a batch per thread 115; 16 tokens by rows 60 and 84.)
+// With kAhead batches under way the open one waits and grows: more launches in the queue do not start any copy earlier.  It
+// leaves with the next copies that a thread adds while there is room, or when a thread has nothing but the open batch left to
+// wait for; a place that becomes free at another time stays empty until then.
+// (Step of 4096 tokens x 7168 with chunks, us: no limit 372 in 26 batches, three 348 in 16, two 349, one at a time 362; a
+// batch per thread, each with its launches, 370.  512 x 4096 82, a batch per thread 115; 16 tokens by rows 60 and 84.)
 void launch_open(ep_handle *h, ProxyThread &P, std::unique_lock<std::mutex> &lk) {
   CopyPool &C = h->copies;
   C.launching = true;

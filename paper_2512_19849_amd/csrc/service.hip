@@ -61,8 +61,9 @@ __global__ __launch_bounds__(256) void copy_batch_kernel(const CopyBatchArgs b, 
 }
 
 // Up to 256 copies, or 496 rows of one length, fit the argument block of one launch: 256 rows of 7 KB 3.5 us against 6.0 with
-// the descriptors read from pinned memory (a step of 256 tokens x 7168 top-8 in bf16 94 us, now 89).  Beyond that a second launch (2.5 us of host time each) costs more than the reads - unless
-// the copies are chunks (over 32 KiB), which fill the chip by the launch.
+// the descriptors read from pinned memory (a step of 256 tokens x 7168 top-8 in bf16 94 us, now 89).  Beyond that a second
+// launch (2.5 us of host time each) costs more than the reads - unless the copies are chunks (over 32 KiB), which fill the
+// chip by the launch.
 // The batch's event fires with the completion signal of the (last) kernel itself.  Recorded behind it, it is a packet of its
 // own that the next launch on the shared stream has to wait for: a step of 4096 tokens x 7168 in about twelve batches of chunks
 // took 418 us, now 380; 128 tokens x 7168 in FP8 in four batches 89, now 82.
