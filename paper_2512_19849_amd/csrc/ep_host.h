@@ -164,15 +164,21 @@ struct alignas(64) ProxyThread {
   std::vector<std::deque<int32_t>> sender_parked;  // sender-side fence: atomics not yet sent, per (source, expert)
   std::vector<uint8_t> atomic_flying;              // ... and whether one of that expert is on its way
   std::vector<WireEvent> window;            // in-flight immediates (reordering hook)
-  // proxy-performed peer writes (registered heaps): this thread's copies that no batch holds yet, with the arrival
-  // notices behind them, and the notices of its copies in flight, by the number of their batch
+  // proxy-performed peer writes (registered heaps): this thread's copies, of which the first `joined` are in a batch (where all
+  // are, none is kept), with the arrival notices behind them, of which the first `noticed` are with their batches, and the
+  // notices of its copies in flight, by the number of their batch
+  struct Notice {
+    uint32_t after;  // copies ahead of it in `copies`
+    WireEvent ev;
+  };
   std::vector<CopyDesc> copies;
+  size_t joined = 0, noticed = 0;
   const char *copies_src = nullptr;
   char *copies_dst = nullptr;
-  std::vector<WireEvent> copies_notices;
+  std::vector<Notice> copies_notices;
   struct Batch {
     uint64_t number;
-    std::vector<WireEvent> notices;
+    std::vector<Notice> notices;
   };
   std::deque<Batch> inflight;
   // ordered (high-throughput) channels: next sequence number and early arrivals per (source, destination rank)

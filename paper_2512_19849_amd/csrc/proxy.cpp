@@ -236,13 +236,31 @@ void launch_open(ep_handle *h, ProxyThread &P, std::unique_lock<std::mutex> &lk)
   C.launching = false;
 }
 
-// This thread's copies join the open batch.  Their notices stay with it until its event has fired (the last batch's, where
-// the copies did not fit one).
-void launch_copies(ep_handle *h, ProxyThread &P) {
+// The notices behind the copies that have joined, the last of them batch `number`, stay with it until its event has fired.
+void keep_notices(ProxyThread &P, uint64_t number) {
+  std::vector<ProxyThread::Notice> &all = P.copies_notices;
+  size_t n = P.joined == P.copies.size() ? all.size() : P.noticed;
+  while (n < all.size() && all[n].after <= P.joined) ++n;
+  P.inflight.push_back(ProxyThread::Batch{number, {}});
+  std::vector<ProxyThread::Notice> &kept = P.inflight.back().notices;
+  if (P.noticed == 0 && n == all.size())
+    kept.swap(all);
+  else
+    kept.assign(all.begin() + P.noticed, all.begin() + n);
+  P.noticed = all.empty() ? 0 : n;
+}
+
+// This thread's copies join the open batch, in order, as far as there is room; no more than `leave` may be left without a
+// batch, so with more it waits for room.
+// A thread that waits here polls no commands: with rings that a dispatch overruns the kernel then keeps the device busy
+// waiting for room in them, and the copies it waits for run beside it.  So it waits only for a large backlog (or a Drain, or
+// other heaps).  8192 tokens x 4096 by rows, rings of 4096: 720 us, waiting with the first full batch 4500.
+constexpr size_t kBacklog = 8 * (size_t)kCopyBatchMax;
+void launch_copies(ep_handle *h, ProxyThread &P, size_t leave) {
   if (P.copies.empty()) return;
   CopyPool &C = h->copies;
   std::unique_lock<std::mutex> lk(C.mu);
-  for (size_t at = 0; at < P.copies.size();) {
+  while (P.joined < P.copies.size()) {
     CopyBatchArgs &b = C.open;
     const bool other = b.n && (b.src_base != P.copies_src || b.dst_base != P.copies_dst || b.n == kCopyBatchMax);
     if (other && !C.launching && C.number - C.done.load(std::memory_order_acquire) < CopyPool::kAhead) {
@@ -250,6 +268,7 @@ void launch_copies(ep_handle *h, ProxyThread &P) {
       continue;
     }
     if (other) {
+      if (P.copies.size() - P.joined <= leave) break;
       lk.unlock();
       poll_batches(h);
       std::this_thread::yield();
@@ -263,16 +282,24 @@ void launch_copies(ep_handle *h, ProxyThread &P) {
       b.min_len16 = ~0u;
     }
     CopyDesc *descs = C.descs + C.number % CopyPool::kSlots * kCopyBatchMax;
-    for (; at < P.copies.size() && b.n < kCopyBatchMax; ++at) {
-      const CopyDesc &d = descs[b.n++] = P.copies[at];
+    for (; P.joined < P.copies.size() && b.n < kCopyBatchMax; ++P.joined) {
+      const CopyDesc &d = descs[b.n++] = P.copies[P.joined];
       if (d.len16 > b.max_len16) b.max_len16 = d.len16;
       if (d.len16 < b.min_len16) b.min_len16 = d.len16;
     }
+    const uint64_t number = C.number;
+    if (!C.launching) launch_open(h, P, lk);
+    lk.unlock();
+    keep_notices(P, number);
+    lk.lock();
   }
-  P.inflight.push_back(ProxyThread::Batch{C.number, std::move(P.copies_notices)});
-  P.copies_notices.clear();
-  P.copies.clear();
-  if (!C.launching) launch_open(h, P, lk);
+  lk.unlock();
+  if (P.joined == P.copies.size() || P.joined >= kBacklog) {
+    P.copies.erase(P.copies.begin(), P.copies.begin() + P.joined);
+    P.copies_notices.erase(P.copies_notices.begin(), P.copies_notices.begin() + P.noticed);
+    for (ProxyThread::Notice &n : P.copies_notices) n.after -= (uint32_t)P.joined;
+    P.joined = P.noticed = 0;
+  }
 }
 
 // Finished batches release this thread's arrival notices to the receiver half.
@@ -281,7 +308,7 @@ void reap_batches(ep_handle *h, ProxyThread &P, ReapMode mode) {
   for (bool polled = false; !P.inflight.empty();) {
     ProxyThread::Batch &b = P.inflight.front();
     if (b.number < h->copies.done.load(std::memory_order_acquire)) {
-      for (const WireEvent &ev : b.notices) transmit(h, P, ev);
+      for (const ProxyThread::Notice &n : b.notices) transmit(h, P, n.ev);
       P.inflight.pop_front();
       continue;
     }
@@ -299,13 +326,14 @@ void reap_batches(ep_handle *h, ProxyThread &P, ReapMode mode) {
 // Offsets and length are bytes relative to the registered heaps, multiples of 16 below 64 GiB.
 void queue_copy(ep_handle *h, ProxyThread &P, const char *sbase, char *dbase, uint64_t so, uint64_t dof,
                 uint64_t len, const WireEvent *notice) {
-  if (P.copies_src != sbase || P.copies_dst != dbase) launch_copies(h, P);  // re-registered
+  if (P.copies_src != sbase || P.copies_dst != dbase) launch_copies(h, P, 0);  // re-registered
   P.copies_src = sbase;
   P.copies_dst = dbase;
   P.copies.push_back(CopyDesc{(unsigned)(so >> 4), (unsigned)(dof >> 4), (unsigned)(len >> 4)});
-  if (notice) P.copies_notices.push_back(*notice);
+  if (notice) P.copies_notices.push_back({(uint32_t)P.copies.size(), *notice});
   bump(P.copied_bytes, len);
-  if (P.copies.size() == (size_t)kCopyBatchMax) launch_copies(h, P);
+  const size_t left = P.copies.size() - P.joined;
+  if (left >= (size_t)kCopyBatchMax && left % 1024 == 0) launch_copies(h, P, kBacklog);
 }
 
 // ---- pacing (Section 6, "Congestion control with CPU proxy") ------------------------------------
@@ -622,7 +650,7 @@ void process_cmd(ep_handle *h, ProxyThread &P, int fifo, uint32_t w0, uint32_t w
       // copies in flight, messages in the transport, and those waiting for the pacing limit
       close_all_open(h, P);
       do {
-        launch_copies(h, P);
+        launch_copies(h, P, 0);
         reap_batches(h, P, kReapAll);
         flush_window(h, P);
         pump_held(h, P);
@@ -734,7 +762,8 @@ void proxy_main(ep_handle *h, ProxyThread *Pp) {
     }
     // What has been collected joins the open batch of peer writes - at once when nothing new came in, else
     // when it is worth a launch of its own; finished batches release their arrival notices.
-    if (!P.copies.empty() && (!any || P.copies.size() >= 2048)) launch_copies(h, P);
+    if (!P.copies.empty() && (!any || P.copies.size() >= 2048)) launch_copies(h, P, kBacklog);
+    if (!P.copies.empty()) any = true;
     if (!P.inflight.empty()) {
       reap_batches(h, P, kReapReady);
       any = true;

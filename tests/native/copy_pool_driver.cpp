@@ -119,6 +119,27 @@ static int change_under_way(ep_handle *h, char *a, char *b, size_t bytes) {
   return bad;
 }
 
+// The proxy keeps polling while nothing is copied: one thread's commands, more than the batches and the ring hold.
+static int backlog(ep_handle *h, char *a, char *b, size_t bytes) {
+  const uint32_t per = 9000, rows = (uint32_t)(bytes / 256);
+  memset(b, 0, bytes);
+  h->src_base.store(a);
+  h->dst_base.store(b);
+  hold.store(true);
+  ep_host_expect_atomics(h, 4);
+  int bad = 0;
+  uint64_t idx = 0;
+  for (uint32_t i = 0; i < 4 * per && !bad; ++i)
+    bad += ep_host_push(h, 0, 1u << 28 | i % 4, 16, i * 7 % rows * 16, i % rows * 16, &idx) != 0;
+  for (uint32_t e = 0; e < 4; ++e) bad += ep_host_push(h, 0, 2u << 28 | e, per, 0, e, &idx) != 0;
+  for (int i = 0; i < 2000 && !ep_host_check_completion(h, 0, idx); ++i) std::this_thread::sleep_for(std::chrono::milliseconds(1));
+  bad += ep_host_check_completion(h, 0, idx) != 1 || h->copies.number - h->copies.done.load() > CopyPool::kAhead;
+  hold.store(false);
+  bad += ep_wait(h) != 0;
+  for (uint32_t i = 4 * per - rows; i < 4 * per; ++i) bad += memcmp(b + i % rows * 256, a + i * 7 % rows * 256, 256) != 0;
+  return bad;
+}
+
 int main() {
   std::thread dev(device);
   ep_config c{};
@@ -162,6 +183,7 @@ int main() {
     for (size_t r = 0; r < 16ull * per; ++r) bad += memcmp(dst + r * 256, src + r * 7 % rows * 256, r % per % 3 ? 256 : 128) != 0;
   }
   bad += change_under_way(h, a.data(), b.data(), bytes);
+  bad += backlog(h, a.data(), b.data(), bytes);
   h->copies.descs = nullptr;
   for (auto &e : h->copies.events) e = nullptr;
   ep_proxy_stop(h);
