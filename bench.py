@@ -137,8 +137,8 @@ def format_suite(out: dict) -> str:
             for a, b in v[key].items():
                 L.append(f"    {a:50s} {b}")
         for key in [k for k in v if k.startswith("ht_")]:
-            what = ("ring-buffer channels: sending step -> ring slot -> receiving step -> packed buffer (one workgroup "
-                    "per slice plays both ends in turns); Write / tail / head messages through the proxy; host clock "
+            what = ("ring-buffer channels: sending step -> ring slot -> receiving step -> packed buffer (one or more workgroups "
+                    "per slice, each plays both ends in turns); Write / tail / head messages through the proxy; host clock "
                     "from the ep_ht_dispatch call to ep_wait (Drains popped)" if key.startswith("ht_ring")
                     else "high-throughput mode: one copy per (token, group of ranks), two-level reduce")
             L.append(f"  [{key}]  {what}")
