@@ -16,10 +16,10 @@ namespace ep {
 // both ends of them in turns: a sending step (every wavefront takes a token, keeps its row in
 // registers and stores it into the slot of each of its destinations that is known to be free, then
 // announces the chunks it completed) and a receiving step (a sweep over the tails, the announced
-// rows move to their final place, the slots are released).  Neither step waits for the other end: a wavefront whose slot is still occupied
-// keeps its claimed position and tries again after the next sweep.  A workgroup therefore depends
-// on nothing but the proxy, whatever the grid size and however many workgroups are resident, and
-// every compute unit has rows to store all the time.
+// rows move to their final place, the slots are released).  Neither step waits for the other end: a
+// wavefront whose slot is still occupied keeps its claimed position and tries again after the next
+// sweep.  A workgroup therefore depends on nothing but the proxy, whatever the grid size and
+// however many workgroups are resident, and every compute unit has rows to store all the time.
 // On this hardware one counter tracks a wave's outstanding loads AND stores, so waiting for any load
 // also waits for every store issued before it; the sending step is shaped around that: all of a
 // token's metadata in one load, the row in one batch of loads, then nothing but stores.
