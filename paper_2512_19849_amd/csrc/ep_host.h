@@ -164,22 +164,23 @@ struct alignas(64) ProxyThread {
   std::vector<std::deque<int32_t>> sender_parked;  // sender-side fence: atomics not yet sent, per (source, expert)
   std::vector<uint8_t> atomic_flying;              // ... and whether one of that expert is on its way
   std::vector<WireEvent> window;            // in-flight immediates (reordering hook)
-  // proxy-performed peer writes (registered heaps): this thread's copies, of which the first `joined` are in a batch (where all
-  // are, none is kept), with the arrival notices behind them, of which the first `noticed` are with their batches, and the
-  // notices of its copies in flight, by the number of their batch
-  struct Notice {
-    uint32_t after;  // copies ahead of it in `copies`
-    WireEvent ev;
+  // proxy-performed peer writes (registered heaps): this thread's copies, each with the arrival notice behind it, if it has
+  // one.  The first `joined` are in a batch (where all are, none is kept); `inflight` holds them until the batch is done.
+  static constexpr uint8_t kNoNotice = 255;  // (notice.ordered)
+  struct Copy {
+    CopyDesc d;
+    WireEvent notice;
   };
-  std::vector<CopyDesc> copies;
-  size_t joined = 0, noticed = 0;
+  std::vector<Copy> copies;
+  size_t joined = 0;
+  size_t join_at = kCopyBatchMax;  // with this many copies they join the open batch without waiting for a pause
   const char *copies_src = nullptr;
   char *copies_dst = nullptr;
-  std::vector<Notice> copies_notices;
   struct Batch {
     uint64_t number;
-    std::vector<Notice> notices;
+    std::vector<Copy> copies;
   };
+  std::vector<Copy> spare;  // (empty: memory for the next batch's copies)
   std::deque<Batch> inflight;
   // ordered (high-throughput) channels: next sequence number and early arrivals per (source, destination rank)
   std::vector<uint32_t> next_seq;

@@ -238,18 +238,16 @@ void launch_open(ep_handle *h, ProxyThread &P, std::unique_lock<std::mutex> &lk)
   C.launching = false;
 }
 
-// The notices behind the copies that have joined, the last of them batch `number`, stay with it until its event has fired.
-void keep_notices(ProxyThread &P, uint64_t number) {
-  std::vector<ProxyThread::Notice> &all = P.copies_notices;
-  size_t n = P.joined == P.copies.size() ? all.size() : P.noticed;
-  while (n < all.size() && all[n].after <= P.joined) ++n;
-  P.inflight.push_back(ProxyThread::Batch{number, {}});
-  std::vector<ProxyThread::Notice> &kept = P.inflight.back().notices;
-  if (P.noticed == 0 && n == all.size())
-    kept.swap(all);
-  else
-    kept.assign(all.begin() + P.noticed, all.begin() + n);
-  P.noticed = all.empty() ? 0 : n;
+// The copies from `first` on that have joined, all of them batch `number`, are kept for their notices until its event has fired.
+void keep_notices(ProxyThread &P, uint64_t number, size_t first) {
+  P.inflight.push_back(ProxyThread::Batch{number, std::move(P.spare)});
+  std::vector<ProxyThread::Copy> &kept = P.inflight.back().copies;
+  if (first == 0 && P.joined == P.copies.size()) {
+    kept.swap(P.copies);
+    P.joined = 0;
+  } else {
+    kept.assign(P.copies.begin() + first, P.copies.begin() + P.joined);
+  }
 }
 
 // This thread's copies join the open batch, in order, as far as there is room; no more than `leave` may be left without a
@@ -283,25 +281,31 @@ void launch_copies(ep_handle *h, ProxyThread &P, size_t leave) {
       b.max_len16 = 0;
       b.min_len16 = ~0u;
     }
-    CopyDesc *descs = C.descs + C.number % CopyPool::kSlots * kCopyBatchMax;
-    for (; P.joined < P.copies.size() && b.n < kCopyBatchMax; ++P.joined) {
-      const CopyDesc &d = descs[b.n++] = P.copies[P.joined];
-      if (d.len16 > b.max_len16) b.max_len16 = d.len16;
-      if (d.len16 < b.min_len16) b.min_len16 = d.len16;
+    const size_t first = P.joined, n = std::min(P.copies.size() - first, (size_t)(kCopyBatchMax - b.n));
+    const ProxyThread::Copy *from = P.copies.data() + first;
+    CopyDesc *to = C.descs + C.number % CopyPool::kSlots * kCopyBatchMax + b.n;
+    unsigned longest = b.max_len16, shortest = b.min_len16;
+    for (size_t i = 0; i < n; ++i) {
+      to[i] = from[i].d;
+      longest = std::max(longest, from[i].d.len16);
+      shortest = std::min(shortest, from[i].d.len16);
     }
+    b.max_len16 = longest;
+    b.min_len16 = shortest;
+    b.n += (int)n;
+    P.joined += n;
     const uint64_t number = C.number;
     if (!C.launching) launch_open(h, P, lk);
     lk.unlock();
-    keep_notices(P, number);
+    keep_notices(P, number, first);
     lk.lock();
   }
   lk.unlock();
   if (P.joined == P.copies.size() || P.joined >= kBacklog) {
     P.copies.erase(P.copies.begin(), P.copies.begin() + P.joined);
-    P.copies_notices.erase(P.copies_notices.begin(), P.copies_notices.begin() + P.noticed);
-    for (ProxyThread::Notice &n : P.copies_notices) n.after -= (uint32_t)P.joined;
-    P.joined = P.noticed = 0;
+    P.joined = 0;
   }
+  P.join_at = std::max(P.joined + kCopyBatchMax, P.copies.size() + 1024);
 }
 
 // Finished batches release this thread's arrival notices to the receiver half.
@@ -310,7 +314,10 @@ void reap_batches(ep_handle *h, ProxyThread &P, ReapMode mode) {
   for (bool polled = false; !P.inflight.empty();) {
     ProxyThread::Batch &b = P.inflight.front();
     if (b.number < h->copies.done.load(std::memory_order_acquire)) {
-      for (const ProxyThread::Notice &n : b.notices) transmit(h, P, n.ev);
+      for (const ProxyThread::Copy &c : b.copies)
+        if (c.notice.ordered != ProxyThread::kNoNotice) transmit(h, P, c.notice);
+      b.copies.clear();
+      P.spare = std::move(b.copies);
       P.inflight.pop_front();
       continue;
     }
@@ -328,14 +335,15 @@ void reap_batches(ep_handle *h, ProxyThread &P, ReapMode mode) {
 // Offsets and length are bytes relative to the registered heaps, multiples of 16 below 64 GiB.
 void queue_copy(ep_handle *h, ProxyThread &P, const char *sbase, char *dbase, uint64_t so, uint64_t dof,
                 uint64_t len, const WireEvent *notice) {
-  if (P.copies_src != sbase || P.copies_dst != dbase) launch_copies(h, P, 0);  // re-registered
-  P.copies_src = sbase;
-  P.copies_dst = dbase;
-  P.copies.push_back(CopyDesc{(unsigned)(so >> 4), (unsigned)(dof >> 4), (unsigned)(len >> 4)});
-  if (notice) P.copies_notices.push_back({(uint32_t)P.copies.size(), *notice});
+  if (P.copies_src != sbase || P.copies_dst != dbase) {
+    launch_copies(h, P, 0);  // re-registered
+    P.copies_src = sbase;
+    P.copies_dst = dbase;
+  }
+  P.copies.push_back({CopyDesc{(unsigned)(so >> 4), (unsigned)(dof >> 4), (unsigned)(len >> 4)},
+                      notice ? *notice : WireEvent{0, 0, 0, ProxyThread::kNoNotice, 0}});
   bump(P.copied_bytes, len);
-  const size_t left = P.copies.size() - P.joined;
-  if (left >= (size_t)kCopyBatchMax && left % 1024 == 0) launch_copies(h, P, kBacklog);
+  if (P.copies.size() >= P.join_at) launch_copies(h, P, kBacklog);
 }
 
 // ---- pacing (Section 6, "Congestion control with CPU proxy") ------------------------------------
