@@ -164,23 +164,23 @@ struct alignas(64) ProxyThread {
   std::vector<std::deque<int32_t>> sender_parked;  // sender-side fence: atomics not yet sent, per (source, expert)
   std::vector<uint8_t> atomic_flying;              // ... and whether one of that expert is on its way
   std::vector<WireEvent> window;            // in-flight immediates (reordering hook)
-  // proxy-performed peer writes (registered heaps): this thread's copies, each with the arrival notice behind it, if it has
-  // one.  The first `joined` are in a batch (where all are, none is kept); `inflight` holds them until the batch is done.
+  // proxy-performed peer writes (registered heaps): this thread's copies, each with the arrival notice behind it or kNoNotice.
+  // The first `joined` are in a batch (where all are, none is kept), whose notices `inflight` holds until it is done.
+  // (One thread bound by 30720 rows, the proxy alone: 634 us; copy and notice in one record 692, notices only where there is
+  // one, with their place, and each batch's in memory of its own 860; before the shared batches 619.)
   static constexpr uint8_t kNoNotice = 255;  // (notice.ordered)
-  struct Copy {
-    CopyDesc d;
-    WireEvent notice;
-  };
-  std::vector<Copy> copies;
+  std::vector<CopyDesc> copies;
+  std::vector<WireEvent> notices;  // one for each
+  unsigned longest = 0, shortest = ~0u;  // of `copies`, in 16 bytes
   size_t joined = 0;
   size_t join_at = kCopyBatchMax;  // with this many copies they join the open batch without waiting for a pause
   const char *copies_src = nullptr;
   char *copies_dst = nullptr;
   struct Batch {
     uint64_t number;
-    std::vector<Copy> copies;
+    std::vector<WireEvent> notices;
   };
-  std::vector<Copy> spare;  // (empty: memory for the next batch's copies)
+  std::vector<WireEvent> spare;  // (empty: memory for the next batch's notices)
   std::deque<Batch> inflight;
   // ordered (high-throughput) channels: next sequence number and early arrivals per (source, destination rank)
   std::vector<uint32_t> next_seq;

@@ -241,13 +241,11 @@ void launch_open(ep_handle *h, ProxyThread &P, std::unique_lock<std::mutex> &lk)
 // The copies from `first` on that have joined, all of them batch `number`, are kept for their notices until its event has fired.
 void keep_notices(ProxyThread &P, uint64_t number, size_t first) {
   P.inflight.push_back(ProxyThread::Batch{number, std::move(P.spare)});
-  std::vector<ProxyThread::Copy> &kept = P.inflight.back().copies;
-  if (first == 0 && P.joined == P.copies.size()) {
-    kept.swap(P.copies);
-    P.joined = 0;
-  } else {
-    kept.assign(P.copies.begin() + first, P.copies.begin() + P.joined);
-  }
+  std::vector<WireEvent> &kept = P.inflight.back().notices;
+  if (first == 0 && P.joined == P.notices.size())
+    kept.swap(P.notices);
+  else
+    kept.assign(P.notices.begin() + first, P.notices.begin() + P.joined);
 }
 
 // This thread's copies join the open batch, in order, as far as there is room; no more than `leave` may be left without a
@@ -282,16 +280,19 @@ void launch_copies(ep_handle *h, ProxyThread &P, size_t leave) {
       b.min_len16 = ~0u;
     }
     const size_t first = P.joined, n = std::min(P.copies.size() - first, (size_t)(kCopyBatchMax - b.n));
-    const ProxyThread::Copy *from = P.copies.data() + first;
-    CopyDesc *to = C.descs + C.number % CopyPool::kSlots * kCopyBatchMax + b.n;
-    unsigned longest = b.max_len16, shortest = b.min_len16;
-    for (size_t i = 0; i < n; ++i) {
-      to[i] = from[i].d;
-      longest = std::max(longest, from[i].d.len16);
-      shortest = std::min(shortest, from[i].d.len16);
+    const CopyDesc *from = P.copies.data() + first;
+    memcpy(C.descs + C.number % CopyPool::kSlots * kCopyBatchMax + b.n, from, n * sizeof(CopyDesc));
+    unsigned longest = P.longest, shortest = P.shortest;
+    if (n < P.copies.size()) {
+      longest = 0;
+      shortest = ~0u;
+      for (size_t i = 0; i < n; ++i) {
+        longest = std::max(longest, from[i].len16);
+        shortest = std::min(shortest, from[i].len16);
+      }
     }
-    b.max_len16 = longest;
-    b.min_len16 = shortest;
+    b.max_len16 = std::max(b.max_len16, longest);
+    b.min_len16 = std::min(b.min_len16, shortest);
     b.n += (int)n;
     P.joined += n;
     const uint64_t number = C.number;
@@ -301,8 +302,15 @@ void launch_copies(ep_handle *h, ProxyThread &P, size_t leave) {
     lk.lock();
   }
   lk.unlock();
-  if (P.joined == P.copies.size() || P.joined >= kBacklog) {
+  if (P.joined == P.copies.size()) {
+    P.copies.clear();
+    P.notices.clear();
+    P.longest = 0;
+    P.shortest = ~0u;
+    P.joined = 0;
+  } else if (P.joined >= kBacklog) {
     P.copies.erase(P.copies.begin(), P.copies.begin() + P.joined);
+    P.notices.erase(P.notices.begin(), P.notices.begin() + P.joined);
     P.joined = 0;
   }
   P.join_at = std::max(P.joined + kCopyBatchMax, P.copies.size() + 1024);
@@ -314,10 +322,10 @@ void reap_batches(ep_handle *h, ProxyThread &P, ReapMode mode) {
   for (bool polled = false; !P.inflight.empty();) {
     ProxyThread::Batch &b = P.inflight.front();
     if (b.number < h->copies.done.load(std::memory_order_acquire)) {
-      for (const ProxyThread::Copy &c : b.copies)
-        if (c.notice.ordered != ProxyThread::kNoNotice) transmit(h, P, c.notice);
-      b.copies.clear();
-      P.spare = std::move(b.copies);
+      for (const WireEvent &ev : b.notices)
+        if (ev.ordered != ProxyThread::kNoNotice) transmit(h, P, ev);
+      b.notices.clear();
+      P.spare = std::move(b.notices);
       P.inflight.pop_front();
       continue;
     }
@@ -340,8 +348,11 @@ void queue_copy(ep_handle *h, ProxyThread &P, const char *sbase, char *dbase, ui
     P.copies_src = sbase;
     P.copies_dst = dbase;
   }
-  P.copies.push_back({CopyDesc{(unsigned)(so >> 4), (unsigned)(dof >> 4), (unsigned)(len >> 4)},
-                      notice ? *notice : WireEvent{0, 0, 0, ProxyThread::kNoNotice, 0}});
+  const unsigned len16 = (unsigned)(len >> 4);
+  P.copies.push_back(CopyDesc{(unsigned)(so >> 4), (unsigned)(dof >> 4), len16});
+  P.notices.push_back(notice ? *notice : WireEvent{0, 0, 0, ProxyThread::kNoNotice, 0});
+  if (len16 > P.longest) P.longest = len16;
+  if (len16 < P.shortest) P.shortest = len16;
   bump(P.copied_bytes, len);
   if (P.copies.size() >= P.join_at) launch_copies(h, P, kBacklog);
 }
