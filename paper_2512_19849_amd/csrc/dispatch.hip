@@ -200,6 +200,12 @@ EP_DEV void emit_drain(const DispatchArgs &a, int lane) {
 // x 9216 54 and 52, with a wait before every store 64.)
 // (GROUPS: one command per row.  Instances of their own keep both at or below 98 scalar registers, by the compiler's count
 // eight waves per SIMD; together they take 103 to 105, seven waves: 1536 x 16384, 16 waves per workgroup, 94 us, apart 90.)
+// (The row leaves for the registers ahead of the token's pairs, which say where it goes: one round trip instead of two before a
+// wave's first store.  Pairs first / together, whole steps, us: 4096 tokens x 7168 top-8 with chunks 197.3 / 195.2, in FP8
+// 164.4 / 163.2, deduplicated over 16 groups 357.3 / 352.4; 420 x 7552 in FP8 33.6 / 32.9.  With one command per row, where a
+// workgroup has its pairs to push and waits for them anyway, the pairs stay first: 8192 x 4096 249 / 257.  So they do for one
+// rank of several, whose rows are a few tokens' only, and with more than four vectors per lane, where two places to load from
+// make the compiler spill.)
 // (Write-through stores without the streaming hint: with it the dispatch itself and a combine of other rows are up to 4%
 // faster, but whoever reads the rows next no longer finds any in the memory-side cache.  Step and a read of the received
 // rows, without / with, us: 4058 tokens x 7168 top-8 in FP8 182 / 194, 8116 tokens 365 / 380, 8239 x 4096 bf16 337 / 341.)
@@ -238,16 +244,21 @@ __global__ void dispatch_bf16_kernel(DispatchArgs a) {
   const bool ordered = (a.cmd_mode & EP_CMD_MODE_MASK) == EP_CMD_CHUNK32_ORDERED;
   if (ring_on && !ordered && blockIdx.x == 0) emit_leading_atomics<GROUPS>(a, wave, lane);
 
-  const TokenMeta m = load_meta(a, t, lane);
-  unsigned long long vmask = __ballot(m.valid);
   const int nvec = a.H >> 3;
   const int v0 = part * VPL * 64 + lane;
-  if (vmask && !(a.cmd_mode & EP_CMD_NO_PLACEMENT)) {
-    const u32x4 *src = (const u32x4 *)a.x + (size_t)t * nvec;
-    u32x4 v[VPL];
+  const bool place = t < a.T && !(a.cmd_mode & EP_CMD_NO_PLACEMENT), ahead = !GROUPS && VPL <= 4 && place && a.filter < 0;
+  const u32x4 *src = (const u32x4 *)a.x + (size_t)t * nvec;
+  u32x4 v[VPL];
+  auto load = [&]() {
 #pragma unroll
     for (int i = 0; i < VPL; ++i)
       if (v0 + i * 64 < nvec) v[i] = __builtin_nontemporal_load(src + v0 + i * 64);
+  };
+  if (ahead) load();
+  const TokenMeta m = load_meta(a, t, lane);
+  unsigned long long vmask = __ballot(m.valid);
+  if (vmask && place) {
+    if (!ahead) load();
     unsigned long long mm = vmask;
     while (mm) {
       __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
@@ -333,15 +344,14 @@ __global__ void dispatch_fp8_kernel(DispatchArgs a) {
   const bool ordered = (a.cmd_mode & EP_CMD_MODE_MASK) == EP_CMD_CHUNK32_ORDERED;
   if (ring_on && !ordered && blockIdx.x == 0) emit_leading_atomics<GROUPS>(a, wave, lane);
 
-  const TokenMeta m = load_meta(a, t, lane);
-  unsigned long long vmask = __ballot(m.valid);
   const int npair = a.H >> 4;  // 16-channel groups per row
   const int nblk = a.H >> 7;   // 128-channel blocks per row
   const int p0 = part * VPL * 64 + lane;
-  if (vmask) {
-    const u32x4 *src = (const u32x4 *)a.x + (size_t)t * npair * 2;
-    u32x4 lo[VPL], hi[VPL], q[VPL];
-    float sc[VPL];
+  const bool ahead = !GROUPS && t < a.T && a.filter < 0;
+  const u32x4 *src = (const u32x4 *)a.x + (size_t)t * npair * 2;
+  u32x4 lo[VPL], hi[VPL], q[VPL];
+  float sc[VPL];
+  auto load = [&]() {
 #pragma unroll
     for (int i = 0; i < VPL; ++i)
       if (p0 + i * 64 < npair) {
@@ -351,6 +361,12 @@ __global__ void dispatch_fp8_kernel(DispatchArgs a) {
         lo[i] = u32x4{0, 0, 0, 0};
         hi[i] = u32x4{0, 0, 0, 0};
       }
+  };
+  if (ahead) load();  // (see dispatch_bf16_kernel)
+  const TokenMeta m = load_meta(a, t, lane);
+  unsigned long long vmask = __ballot(m.valid);
+  if (vmask) {
+    if (!ahead) load();
 #pragma unroll
     for (int i = 0; i < VPL; ++i) quant16(lo[i], hi[i], q[i], sc[i]);
     // Where a row goes: into the two receive arrays (codes, scales), or - when the proxy moves the rows -
