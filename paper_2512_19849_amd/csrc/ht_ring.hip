@@ -40,7 +40,7 @@ struct HtShared {
   int lo[kHtMaxRanks], hi[kHtMaxRanks];  // chunks [lo, hi) are consumed in the current sweep
   unsigned seqr[kHtMaxRanks];  // the channel's reverse sequence number before this dispatch
   unsigned cumr[kHtMaxRanks];  // rows the channel carried before this dispatch (receiver's count)
-  int abort, remaining, progress, idle;
+  int abort, remaining, progress, idle, announced;
   int split_mask, part;  // this workgroup's channels: r & split_mask == part (in LDS: scalar registers are short here)
 };
 
@@ -243,21 +243,23 @@ EP_DEV void ht_receive_step(const HtRingArgs &a, HtShared &sh, int c) {
     }
     sh.lo[r] = n0;
     sh.hi[r] = hi;
+    if (hi > n0) sh.announced = 1;
   }
   __syncthreads();
+  if (!sh.announced) return;
+  // What a tail announces reached memory from outside this compute unit's view (a network adapter in the paper; here the sending
+  // step's write-through stores), possibly into lines a cache still holds from the slot's previous use: drop those before the
+  // first read of the sweep (the acquire that pairs with the tail).  It empties the XCD's L2, so one wave does it for all, and
+  // none on idle sweeps.  Whole steps, by every wave / by one, us: 4096 tokens x 7168 top-8, 128 slices 430 / 411, 3000 x 5120,
+  // 256 slices 258 / 223, 1024 x 4096, 64 slices 99 / 82, 600 x 2048 top-4 59 / 54; 2048 x 7168 in FP8, 128 slices 216 / 207.
+  if (wave == 0) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+  __syncthreads();
+  if (tid == 0) sh.announced = 0;
   // move their rows to where the header says; rows are dealt out to the waves round-robin
   int q = 0;
   for (int r = 0; r < a.R; ++r) {
     const int lo = sh.lo[r], hi = sh.hi[r];
     for (int n = lo; n < hi; ++n) {
-      if (q == 0) {
-        // What a tail announces reached memory from outside this compute unit's view (a network
-        // adapter in the paper; here the sending step's write-through stores), possibly into lines
-        // a cache still holds from the slot's previous use: drop those before the first read of
-        // the sweep (the acquire that pairs with the tail; not done on idle sweeps, it empties
-        // the XCD's L2).
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-      }
       const int sz = min(kChunkRows, sh.total[r] - (n << 5));
       const char *slot = (const char *)a.ring_buf + ((size_t)(c * a.R + r) * a.W + n % a.W) * a.slot_bytes;
       // this wave's rows of the chunk: j = first, first + nwaves, ... (rows are dealt round-robin over all chunks)
@@ -329,7 +331,7 @@ __global__ __launch_bounds__(1024) void ht_ring_kernel(HtRingArgs a) {
   }
   for (int i = tid; i < a.R * a.W; i += blockDim.x) sh.done[i] = 0;
   if (tid == 0) {
-    sh.abort = sh.remaining = sh.progress = sh.idle = 0;
+    sh.abort = sh.remaining = sh.progress = sh.idle = sh.announced = 0;
     sh.split_mask = a.split - 1;
     sh.part = blockIdx.y;
   }
