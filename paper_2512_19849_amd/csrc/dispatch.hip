@@ -203,9 +203,9 @@ EP_DEV void emit_drain(const DispatchArgs &a, int lane) {
 // (The row leaves for the registers ahead of the token's pairs, which say where it goes: one round trip instead of two before a
 // wave's first store.  Pairs first / together, whole steps, us: 4096 tokens x 7168 top-8 with chunks 197.3 / 195.2, in FP8
 // 164.4 / 163.2, deduplicated over 16 groups 357.3 / 352.4; 420 x 7552 in FP8 33.6 / 32.9.  With one command per row, where a
-// workgroup has its pairs to push and waits for them anyway, the pairs stay first: 8192 x 4096 249 / 257.  So they do for one
-// rank of several, whose rows are a few tokens' only, and with more than four vectors per lane, where two places to load from
-// make the compiler spill.)
+// workgroup has its pairs to push and waits for them anyway, the pairs stay first: 8192 x 4096 249 / 257.  So they do for
+// sequenced chunks (1531 x 5120 top-6 57.6 / 59.6), for one rank of several, whose rows are a few tokens' only, and with more
+// than four vectors per lane, where two places to load from make the compiler spill.)
 // (Write-through stores without the streaming hint: with it the dispatch itself and a combine of other rows are up to 4%
 // faster, but whoever reads the rows next no longer finds any in the memory-side cache.  Step and a read of the received
 // rows, without / with, us: 4058 tokens x 7168 top-8 in FP8 182 / 194, 8116 tokens 365 / 380, 8239 x 4096 bf16 337 / 341.)
@@ -246,7 +246,7 @@ __global__ void dispatch_bf16_kernel(DispatchArgs a) {
 
   const int nvec = a.H >> 3;
   const int v0 = part * VPL * 64 + lane;
-  const bool place = t < a.T && !(a.cmd_mode & EP_CMD_NO_PLACEMENT), ahead = !GROUPS && VPL <= 4 && place && a.filter < 0;
+  const bool place = t < a.T && !(a.cmd_mode & EP_CMD_NO_PLACEMENT), ahead = !GROUPS && !ordered && VPL <= 4 && place && a.filter < 0;
   const u32x4 *src = (const u32x4 *)a.x + (size_t)t * nvec;
   u32x4 v[VPL];
   auto load = [&]() {
@@ -347,7 +347,7 @@ __global__ void dispatch_fp8_kernel(DispatchArgs a) {
   const int npair = a.H >> 4;  // 16-channel groups per row
   const int nblk = a.H >> 7;   // 128-channel blocks per row
   const int p0 = part * VPL * 64 + lane;
-  const bool ahead = !GROUPS && t < a.T && a.filter < 0;
+  const bool ahead = !GROUPS && !ordered && t < a.T && a.filter < 0;
   const u32x4 *src = (const u32x4 *)a.x + (size_t)t * npair * 2;
   u32x4 lo[VPL], hi[VPL], q[VPL];
   float sc[VPL];
