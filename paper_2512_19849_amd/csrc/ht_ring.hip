@@ -40,8 +40,8 @@ struct HtShared {
   int lo[kHtMaxRanks], hi[kHtMaxRanks];  // chunks [lo, hi) are consumed in the current sweep
   unsigned seqr[kHtMaxRanks];  // the channel's reverse sequence number before this dispatch
   unsigned cumr[kHtMaxRanks];  // rows the channel carried before this dispatch (receiver's count)
-  int abort, remaining, progress, idle, announced;
-  int split_mask, part;  // this workgroup's channels: r & split_mask == part (in LDS: scalar registers are short here)
+  bool mine[kHtMaxRanks];  // the channel of slice and rank is this workgroup's (see ht_share)
+  int abort, remaining, progress, idle, announced, split;
 };
 
 #define HT_LD(p) __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)
@@ -51,8 +51,25 @@ EP_DEV bool ht_valid(const HtRingArgs &a, int e, int row) {
   return e >= 0 && e / a.E_loc < a.R && row >= 0 && row < a.recv_rows;
 }
 
-// Is rank r's channel one of this workgroup's?  (See launch_ht_ring.)
-EP_DEV bool ht_mine(const HtShared &sh, int r) { return (r & sh.split_mask) == sh.part; }
+// Which of the slice's channels are workgroup `part`'s: ranks in descending order of their rows are dealt out to the `split`
+// workgroups there and back (0 1 1 0 0 1 ...), so that each moves about the same number.  All of them count the same table and
+// arrive at the same shares; a channel's state is read and written back by whoever has it in this dispatch.  Called by every
+// thread, with the rows of all ranks in sh.total; clears those of the others.
+// A dispatch ends with its slowest workgroup.  By rank number (r mod split) a skewed routing gave one half of the workgroups 165
+// rows and the other 91 (4096 tokens x 7168 top-8, 128 slices; now 128 and 128, the kernel 313 us, now 297).  Whole steps, by
+// rank number / by rows, us: this one 405 / 400, 2048 tokens 215 / 209, 3000 x 5120 over 64 slices 241 / 231, uniform routing
+// 394 / 391.
+EP_DEV void ht_share(const HtRingArgs &a, HtShared &sh, int split, int part) {
+  for (int r = threadIdx.x; r < a.R; r += blockDim.x) {
+    int ahead = 0;  // ranks in front of r in descending order
+    for (int j = 0; j < (split > 1 ? a.R : 0); ++j) ahead += sh.total[j] > sh.total[r] || (sh.total[j] == sh.total[r] && j < r);
+    const int at = ahead % split;
+    sh.mine[r] = ((ahead / split) & 1 ? split - 1 - at : at) == part;
+  }
+  __syncthreads();
+  for (int r = threadIdx.x; r < a.R; r += blockDim.x)
+    if (!sh.mine[r]) sh.total[r] = 0;
+}
 
 // B 16-byte vectors per lane of a row, starting at vector v0: loads in flight together, stores
 // back to back.  The slots are stored write-through, the received rows plainly.  With the streaming hint on both, steps of
@@ -104,7 +121,7 @@ EP_DEV bool ht_send_token(const HtRingArgs &a, HtShared &sh, int c, int t, HtTok
     e = a.idx[(size_t)t * a.K + lane];
     row = a.dst_row[(size_t)t * a.K + lane];
   }
-  const bool valid = lane < a.K && ht_valid(a, e, row) && ht_mine(sh, e / a.E_loc);
+  const bool valid = lane < a.K && ht_valid(a, e, row) && sh.mine[e / a.E_loc];
   const int r = valid ? e / a.E_loc : 0, chan = c * a.R + r;
   if (tk.pend == 0ull) {  // a new token: positions are handed out in arrival order
     tk.p = valid ? __hip_atomic_fetch_add(&sh.fill[r], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) : 0;
@@ -215,7 +232,7 @@ EP_DEV bool ht_send_token(const HtRingArgs &a, HtShared &sh, int c, int t, HtTok
 constexpr int kHtStepRows = 16;
 EP_DEV bool ht_send_step(const HtRingArgs &a, HtShared &sh, int c, int t0, int ntok, int &q, HtToken &tk) {
   const int wave = wave_id(), nwaves = blockDim.x >> 6;
-  const int budget = max(1, kHtStepRows * (sh.split_mask + 1) / a.K);
+  const int budget = max(1, kHtStepRows * sh.split / a.K);
   for (int j = 0; j < budget; ++j) {
     const int tt = wave + q * nwaves;
     if (tt >= ntok) return true;
@@ -332,8 +349,7 @@ __global__ __launch_bounds__(1024) void ht_ring_kernel(HtRingArgs a) {
   for (int i = tid; i < a.R * a.W; i += blockDim.x) sh.done[i] = 0;
   if (tid == 0) {
     sh.abort = sh.remaining = sh.progress = sh.idle = sh.announced = 0;
-    sh.split_mask = a.split - 1;
-    sh.part = blockIdx.y;
+    sh.split = a.split;
   }
   __syncthreads();
   // rows per channel of this slice: both ends count them from the routing table (the count
@@ -341,12 +357,13 @@ __global__ __launch_bounds__(1024) void ht_ring_kernel(HtRingArgs a) {
   for (int i = tid; i < (t1 - t0) * a.K; i += blockDim.x) {
     const int e = a.idx[(size_t)t0 * a.K + i], row = a.dst_row[(size_t)t0 * a.K + i];
     if (ht_valid(a, e, row)) {
-      if (ht_mine(sh, e / a.E_loc))
-        __hip_atomic_fetch_add(&sh.total[e / a.E_loc], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      __hip_atomic_fetch_add(&sh.total[e / a.E_loc], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     } else if (e >= 0) {
       dev_set_error(a.fifo.error, EP_EBOUNDS);
     }
   }
+  __syncthreads();
+  ht_share(a, sh, a.split, blockIdx.y);
   __syncthreads();
   if (tid == 0) {
     int chunks = 0;
@@ -383,7 +400,7 @@ __global__ __launch_bounds__(1024) void ht_ring_kernel(HtRingArgs a) {
   __syncthreads();
   // the channels' running sequence numbers and row totals, for the next dispatch
   for (int r = tid; r < a.R; r += blockDim.x) {
-    if (!ht_mine(sh, r)) continue;
+    if (!sh.mine[r]) continue;
     const unsigned nch = (unsigned)(sh.total[r] + 31) >> 5;
     a.seq_fwd[c * a.R + r] = sh.seqf[r] + 2u * nch;
     a.cum_fwd[c * a.R + r] = sh.cumf[r] + (unsigned)sh.total[r];

@@ -1826,6 +1826,38 @@ def test_ht_ring_dispatch_slices_shared_by_workgroups(epmod, oracle, T, H, E, K,
         assert np.array_equal(tail[0], 2 * per_channel) and np.array_equal(head[0], 2 * per_channel)
 
 
+# the workgroups of a slice take other ranks' channels in every dispatch (the hot rank moves on), 2 of 3 and 4 of 5 ranks
+@pytest.mark.parametrize("T,R,slices", [(300, 3, 2), (600, 5, 3)])
+def test_ht_ring_channels_change_hands_between_dispatches(epmod, oracle, T, R, slices):
+    from paper_2512_19849_amd.runner import bits_to_bf16, bf16_to_bits
+    H, E, K = 4096, 4 * R, 3
+    cfg = g.EPConfig("hands", T=T, H=H, E=E, K=K, R=R, S=1)
+    rows = T * K
+    carried = np.zeros((slices, R), np.int64)
+    with _runner(epmod, cfg, T, heap_rows=rows, ht_slices=slices, ht_ring_slots=2) as r:
+        ring = torch.zeros(r.ht_ring_bytes(), dtype=torch.uint8, device="cuda")
+        recv = torch.empty((rows, H), dtype=torch.bfloat16, device="cuda")
+        for it in range(4):
+            score = np.random.default_rng(it).random((1, T, E))
+            score[:, :, 4 * (it % R):4 * (it % R) + 2] -= 0.8
+            idx = np.argsort(score, axis=-1)[..., :K].astype(np.int32)
+            x = g.activations(cfg, it, T=T)
+            d_idx = _dev(idx)
+            lay = r.layout(d_idx)
+            recv.fill_(-1.5)
+            r.ht_dispatch(bits_to_bf16(x), d_idx[0], lay, ring, recv)
+            r.wait()
+            torch.cuda.synchronize()
+            want_lay = oracle.layout(idx, E, R)
+            want, _ = oracle.dispatch_bf16(x, idx[0], want_lay["dst_row"][0], cfg.E_loc, rows, -1, fill=0xBFC0)
+            assert np.array_equal(bf16_to_bits(recv), want), it
+            carried += oracle.ring_channel_rows(idx[0], cfg.E_loc, R, slices)
+        st = r.stats()
+        assert st["device_error"] == 0 and st["proxy_error"] == 0 and st["rejected"] == 0
+        tail, head = epmod.ep_ring_counters(r.h, 1, slices, R)
+        assert np.array_equal(tail[0], carried) and np.array_equal(head[0], carried)
+
+
 @pytest.mark.parametrize("cid,T,mask,slices,W,window", [(3, None, 0.0, 4, 2, 0), (3, 50, 0.3, 3, 1, 4),
                                                         (5, 700, 0.0, 8, 2, 8), (4, 300, 0.1, 2, 1, 0),
                                                         ("h128", 90, 0.0, 3, 2, 0)])
