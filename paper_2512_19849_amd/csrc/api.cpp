@@ -602,6 +602,7 @@ int ep_combine(ep_handle *h, const void *d_y, const float *d_topk_w, const int32
   a.T = T;
   a.K = h->cfg.top_k;
   a.H = h->cfg.hidden;
+  a.groups = h->cfg.num_experts == h->cfg.num_ranks ? h->cfg.num_ranks : 0;
   a.error = h->ring.error;
   a.fresh_from = T;
   if (h->cache_hints && d_y && h->fresh_buf.exchange(nullptr, std::memory_order_relaxed) == d_y &&

@@ -1,5 +1,7 @@
 // Combine (weighted sum over the top-k expert outputs in token order) and the kernels of the deduplicating
 // high-throughput mode: dedup, per-expert index list, partial reduce per group.
+#include <cmath>
+
 #include "ep_device.h"
 
 namespace ep {
@@ -53,9 +55,9 @@ EP_DEV void combine_slices(const u32x4 *y, u32x4 *out, const int (&rows)[KT], co
 }
 
 template <int VPL, int KT>
-__global__ __launch_bounds__(256) void combine_kernel(CombineArgs a) {
+__global__ __launch_bounds__(64) void combine_kernel(CombineArgs a) {
   const int lane = lane_id();
-  const unsigned item = blockIdx.x * 4 + wave_id();
+  const unsigned item = blockIdx.x;
   const int t_launch = (int)(item / (unsigned)a.parts), part = (int)(item % (unsigned)a.parts);
   if (t_launch >= a.T) return;
   // With fresh rows the grid starts at the end of the token range where they are (the last tokens,
@@ -121,47 +123,53 @@ __global__ __launch_bounds__(256) void combine_kernel(CombineArgs a) {
   }
 }
 
-// Column slices (64 lanes x 16 bytes) per wave.  One slice per wave - fewest registers, most waves in
-// flight - is the general choice.  One WAVE PER TOKEN (all slices of the row, its stores together at the
-// end) is faster by 3-5 us per 450 MB for rows of 9 to 15 slices (hidden 4608..7680) when the rows to read
-// exceed the memory-side cache (256 MB) by half or more; it is slower for rows whose size is a power of two
-// (hidden 4096, 8192: every wave is then at the same offset of a row that starts a multiple of that size
-// away, i.e. on the same memory channels at the same time), and mixed below that amount of rows (few tokens:
-// too few waves; a sparse table such as the second level of the hierarchical reduce: slower).  Measured for
-// hidden 4096..8192, 1024..8192 tokens, Zipf, softmax and uniform routing.
-static int tuned_combine_vpl(int forced, const CombineArgs &a) {
-  static const int c[] = {1, 2, 4, 7, 9, 10, 11, 12, 13, 14, 15};
-  for (int v : c)
-    if (v == forced) return v;
-  const int slices = (a.H / 8 + 63) / 64;
-  const long long rows = (long long)a.T * a.K < a.y_rows ? (long long)a.T * a.K : a.y_rows;
-  if (slices >= 9 && slices <= 15 && rows * a.H * 2 >= 384000000ll) return slices;
-  return 1;
-}
+// Dynamic LDS (not used) that lets about `waves` one-wave workgroups onto a compute unit: it has 160 KB, given out in pieces of
+// 1280 bytes.
+static size_t lds_for_waves(int waves) { return waves >= 32 ? 0 : 163840 / waves / 1280 * 1280; }
 
-// (An instance per top-k up to 8 keeps all K loads of a slice in flight.  Against the loop for any K, one load at a time: a
-// wave per token cannot hide that, 4096 tokens x 7168 top-7 75 us, was 97; with a slice per wave top-3 gains up to 8%, top-5
-// up to 5% (4096 x 4096 33 and 34 us), and top-5 from 320 MB of rows on and top-7 from 200 MB on lose 1 to 6% (8192 x 8192
-// 134 and 131, 186 and 176): those take the loop.)
+// One slice (64 lanes x 16 bytes) per wave, one wave per workgroup, and no more of them on a compute unit than have about 84 KB
+// of rows on their way.  The kernel is bound by the memory behind the L2, which keeps that many reads of scattered rows busy
+// and serves more of them in a worse order; a launch that does not fill the chip five times over has no such limit.  Whole
+// steps, ring off, waves per compute unit 10 / 11 / 12 / 14 / 16 / 20 / 32, us:
+//   top-8  4096 tokens x 4096 117.1 / 116.8 / 115.8 / 116.1 / 116.4 / 117.0 / 118.9, 8192 x 4096 223 / 223 / 223 / 224 / 225 /
+//          226 / 230, 4096 x 7168 188.7 / 188.3 / 188.8 / 190 / 191 / 192 / 191, 8000 x 7168 360 / 360 / - / - / - / - / 379
+//   top-7  6000 x 7168 244.2 / 242.2 / 242.3 / 243.5 / 245.5 / 247.6 / 249.0; top-6 216 / 213 / 211.5 / 210.7 / 212 / 215 / 217
+//   top-5  the same 193 / 189 / 187 / 183.4 / 182.5 / 184.7 / 186.4; top-4 173 / 170 / 167 / 163 / 160.2 / 158.8 / 161.6
+// (top-3 and less: best without.)  Two slices per wave, at their best number of waves, take 1% longer, four 5%; a wave per token
+// 2% (4096 x 7168 190, 8000 x 7168 368, 8192 x 6144 334, here 327); four waves per workgroup 1%.
+// A handle with one expert per rank is how the second level of the hierarchical reduce comes here, whose entries are masked but
+// for the first of each group: of K entries over G groups about G (1 - (1 - 1/G)^K) have a row, for which 100 KB is best.
+// Deduplicated steps with 10 / 12 / 14 / 16 / 18 / 20 / 25 / 32 waves, us: 4096 x 7168 top-8 over 16 groups 333 / 329 / 324 / 323 /
+// 324 / 327 / 330 / 331, over 8 (8192 x 4096) 340 / 334 / 332 / 330 / 329 / 328 / 328 / 328; top-6 over 16, 14 / 16 / 18 / 21 / 24 / 32
+// waves 258 / 254 / 250 / 251 / 255 / 260.
+// (Top-9 and more go through a loop with one load in flight per wave: no limit.  Nor where rows of a dispatch that has just
+// ended are read out of the memory-side cache.)
+static int combine_waves(const CombineArgs &a) {
+  if (a.K > 8 || a.fresh_from < a.T) return 32;
+  if (a.groups) return (int)(100.0 / (a.groups * (1.0 - pow(1.0 - 1.0 / a.groups, a.K))));
+  return 84 / a.K;
+}
+static int tuned_combine_vpl(int forced) { return forced == 2 || forced == 4 || forced == 7 ? forced : 1; }
+
 template <int VPL>
 static void launch_combine_t(CombineArgs a, hipStream_t st, const LaunchTiming *tm) {
   const int nvec = a.H / 8;
   a.parts = (nvec + VPL * 64 - 1) / (VPL * 64);
   const long long items = (long long)a.T * a.parts;
-  const unsigned grid = (unsigned)((items + 3) / 4);
+  const int waves = combine_waves(a);
+  const size_t lds = items >= 5ll * 256 * waves ? lds_for_waves(waves) : 0;
+  const unsigned grid = (unsigned)items;
   void *ev0 = tm ? tm->start : nullptr, *ev1 = tm ? tm->stop : nullptr;
-  const long long bytes = min((long long)a.T * a.K, a.y_rows) * a.H * 2;
-  const bool loop = VPL == 1 && ((a.K == 5 && bytes >= 320000000) || (a.K == 7 && bytes >= 200000000));
-  switch (loop ? 0 : a.K) {
-    case 1: launch_kernel(combine_kernel<VPL, 1>, dim3(grid), dim3(256), 0, st, ev0, ev1, a); break;
-    case 2: launch_kernel(combine_kernel<VPL, 2>, dim3(grid), dim3(256), 0, st, ev0, ev1, a); break;
-    case 3: launch_kernel(combine_kernel<VPL, 3>, dim3(grid), dim3(256), 0, st, ev0, ev1, a); break;
-    case 4: launch_kernel(combine_kernel<VPL, 4>, dim3(grid), dim3(256), 0, st, ev0, ev1, a); break;
-    case 5: launch_kernel(combine_kernel<VPL, 5>, dim3(grid), dim3(256), 0, st, ev0, ev1, a); break;
-    case 6: launch_kernel(combine_kernel<VPL, 6>, dim3(grid), dim3(256), 0, st, ev0, ev1, a); break;
-    case 7: launch_kernel(combine_kernel<VPL, 7>, dim3(grid), dim3(256), 0, st, ev0, ev1, a); break;
-    case 8: launch_kernel(combine_kernel<VPL, 8>, dim3(grid), dim3(256), 0, st, ev0, ev1, a); break;
-    default: launch_kernel(combine_kernel<VPL, 0>, dim3(grid), dim3(256), 0, st, ev0, ev1, a); break;
+  switch (a.K) {
+    case 1: launch_kernel(combine_kernel<VPL, 1>, dim3(grid), dim3(64), lds, st, ev0, ev1, a); break;
+    case 2: launch_kernel(combine_kernel<VPL, 2>, dim3(grid), dim3(64), lds, st, ev0, ev1, a); break;
+    case 3: launch_kernel(combine_kernel<VPL, 3>, dim3(grid), dim3(64), lds, st, ev0, ev1, a); break;
+    case 4: launch_kernel(combine_kernel<VPL, 4>, dim3(grid), dim3(64), lds, st, ev0, ev1, a); break;
+    case 5: launch_kernel(combine_kernel<VPL, 5>, dim3(grid), dim3(64), lds, st, ev0, ev1, a); break;
+    case 6: launch_kernel(combine_kernel<VPL, 6>, dim3(grid), dim3(64), lds, st, ev0, ev1, a); break;
+    case 7: launch_kernel(combine_kernel<VPL, 7>, dim3(grid), dim3(64), lds, st, ev0, ev1, a); break;
+    case 8: launch_kernel(combine_kernel<VPL, 8>, dim3(grid), dim3(64), lds, st, ev0, ev1, a); break;
+    default: launch_kernel(combine_kernel<VPL, 0>, dim3(grid), dim3(64), lds, st, ev0, ev1, a); break;
   }
 }
 
@@ -169,17 +177,10 @@ int launch_combine(const CombineArgs &a, const Tunables &tune, void *stream, con
   hipStream_t st = (hipStream_t)stream;
   if (a.T <= 0) return 0;
   if ((a.H / 8 + 63) / 64 > 65535) return (int)hipErrorInvalidValue;
-  switch (tuned_combine_vpl(tune.combine_vpl, a)) {
+  switch (tuned_combine_vpl(tune.combine_vpl)) {
     case 2: launch_combine_t<2>(a, st, timing); break;
     case 4: launch_combine_t<4>(a, st, timing); break;
     case 7: launch_combine_t<7>(a, st, timing); break;
-    case 9: launch_combine_t<9>(a, st, timing); break;
-    case 10: launch_combine_t<10>(a, st, timing); break;
-    case 11: launch_combine_t<11>(a, st, timing); break;
-    case 12: launch_combine_t<12>(a, st, timing); break;
-    case 13: launch_combine_t<13>(a, st, timing); break;
-    case 14: launch_combine_t<14>(a, st, timing); break;
-    case 15: launch_combine_t<15>(a, st, timing); break;
     default: launch_combine_t<1>(a, st, timing); break;
   }
   return (int)hipGetLastError();
@@ -279,9 +280,9 @@ EP_DEV void fma_rows(float (&acc)[8], unsigned long long ks, int row, float wt, 
 // 100, 58 and 90).  Directly behind a dispatch of the same volume, with y untouched, streaming stores gain: step of 4096 x
 // 7168 357, streaming 346.
 template <int KT>
-__global__ __launch_bounds__(256) void combine_partial_kernel(CombinePartialArgs a) {
+__global__ __launch_bounds__(64) void combine_partial_kernel(CombinePartialArgs a) {
   const int lane = lane_id();
-  const unsigned item = blockIdx.x * 4 + wave_id();
+  const unsigned item = blockIdx.x;
   const int t = (int)(item / (unsigned)a.parts), part = (int)(item % (unsigned)a.parts);
   if (t >= a.T) return;
   const int K = KT > 0 ? KT : a.K;
@@ -354,24 +355,30 @@ __global__ __launch_bounds__(256) void combine_partial_kernel(CombinePartialArgs
   }
 }
 
+// Waves per compute unit as in the combine, whose rule of 84 KB is 96 here.  Deduplicated steps with 11 / 12 / 14 / 16 / 20 / 32
+// waves, us: 4096 tokens x 7168 top-8 323.6 / 323.6 / 324.7 / 324.7 / 325.9 / 326.4, 8192 x 4096 372.6 / 373.0 / 374.2 / 374.8 /
+// 376.6 / 377.3; top-6 259.9 / 258.7 / 258.1 / 258.1 / 258.1 / 258.9; top-4 8192 wide 227 / 224 / 221.5 / 220.5 / 221.1 / 222.8.
+constexpr int kPartialKb = 96;
 int launch_combine_partial(const CombinePartialArgs &a0, void *stream) {
   if (a0.T <= 0) return 0;
   CombinePartialArgs a = a0;
   const int nvec = a.H / 8;
   a.parts = (nvec + 63) / 64;
   const long long items = (long long)a.T * a.parts;
-  const unsigned grid = (unsigned)((items + 3) / 4);
+  const unsigned grid = (unsigned)items;
+  const int waves = kPartialKb / (a.K > 8 ? 4 : a.K);  // (fma_rows has four loads in flight)
+  const size_t lds = items >= 5ll * 256 * waves ? lds_for_waves(waves) : 0;
   hipStream_t st = (hipStream_t)stream;
   switch (a.K) {
-    case 1: hipLaunchKernelGGL(combine_partial_kernel<1>, dim3(grid), dim3(256), 0, st, a); break;
-    case 2: hipLaunchKernelGGL(combine_partial_kernel<2>, dim3(grid), dim3(256), 0, st, a); break;
-    case 3: hipLaunchKernelGGL(combine_partial_kernel<3>, dim3(grid), dim3(256), 0, st, a); break;
-    case 4: hipLaunchKernelGGL(combine_partial_kernel<4>, dim3(grid), dim3(256), 0, st, a); break;
-    case 5: hipLaunchKernelGGL(combine_partial_kernel<5>, dim3(grid), dim3(256), 0, st, a); break;
-    case 6: hipLaunchKernelGGL(combine_partial_kernel<6>, dim3(grid), dim3(256), 0, st, a); break;
-    case 7: hipLaunchKernelGGL(combine_partial_kernel<7>, dim3(grid), dim3(256), 0, st, a); break;
-    case 8: hipLaunchKernelGGL(combine_partial_kernel<8>, dim3(grid), dim3(256), 0, st, a); break;
-    default: hipLaunchKernelGGL(combine_partial_kernel<0>, dim3(grid), dim3(256), 0, st, a); break;
+    case 1: hipLaunchKernelGGL(combine_partial_kernel<1>, dim3(grid), dim3(64), lds, st, a); break;
+    case 2: hipLaunchKernelGGL(combine_partial_kernel<2>, dim3(grid), dim3(64), lds, st, a); break;
+    case 3: hipLaunchKernelGGL(combine_partial_kernel<3>, dim3(grid), dim3(64), lds, st, a); break;
+    case 4: hipLaunchKernelGGL(combine_partial_kernel<4>, dim3(grid), dim3(64), lds, st, a); break;
+    case 5: hipLaunchKernelGGL(combine_partial_kernel<5>, dim3(grid), dim3(64), lds, st, a); break;
+    case 6: hipLaunchKernelGGL(combine_partial_kernel<6>, dim3(grid), dim3(64), lds, st, a); break;
+    case 7: hipLaunchKernelGGL(combine_partial_kernel<7>, dim3(grid), dim3(64), lds, st, a); break;
+    case 8: hipLaunchKernelGGL(combine_partial_kernel<8>, dim3(grid), dim3(64), lds, st, a); break;
+    default: hipLaunchKernelGGL(combine_partial_kernel<0>, dim3(grid), dim3(64), lds, st, a); break;
   }
   return (int)hipGetLastError();
 }

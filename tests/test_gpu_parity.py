@@ -890,9 +890,8 @@ def test_combine_generic_k_and_splits(epmod, oracle, K, vpl, monkeypatch):
 
 @pytest.mark.parametrize("H", [4608, 4736, 5120, 5632, 6144, 6656, 7168, 7680])
 def test_combine_one_wave_per_token_for_mid_sized_rows(epmod, oracle, H, monkeypatch):
-    """Rows of 9 to 15 column slices: one wave reduces a whole token (hidden 4736: a ragged last slice).  The
-    library picks this shape by itself once the rows exceed 384 MB (the full-size workloads of hidden 7168
-    do); here it is asked for, at 1600 tokens."""
+    """Rows of 9 to 15 column slices (hidden 4736: a ragged last one), at 1600 tokens.  One wave per token, which is
+    asked for here, is not offered any more: like any value that is not, it leaves a wave per slice."""
     from paper_2512_19849_amd.runner import bits_to_bf16, bf16_to_bits
     monkeypatch.setenv("EP_COMBINE_VPL", str((H // 8 + 63) // 64))
     cfg = g.EPConfig("cw", T=1600, H=H, E=32, K=8, R=4, routing="zipf", seed=1234 + H)
@@ -923,6 +922,36 @@ def test_combine_loads_in_flight_by_volume(epmod, oracle, K, T):
         r.combine(bits_to_bf16(y), _dev(w[0]), _dev(lay["dst_row"][0]), out)
         torch.cuda.synchronize()
         assert _combine_check(oracle, bf16_to_bits(out), y, w[0], lay["dst_row"][0], K) == 0
+        assert r.stats()["device_error"] == 0
+
+
+# the last launch without a limit on the waves of a compute unit and the first with one (84 KB / top-k; handles with one expert
+# per rank: 100 KB / expected rows), two slices per token and a ragged second one; then the partial reduce's rule (96 KB)
+@pytest.mark.parametrize("K,R,E,T", [(8, 4, 16, 6399), (8, 4, 16, 6400), (4, 4, 16, 13440), (8, 16, 16, 9600), (3, 2, 6, 18000),
+                                     (8, 4, 16, 7680)])
+def test_combine_with_few_waves_per_compute_unit(epmod, oracle, K, R, E, T):
+    from paper_2512_19849_amd.runner import bits_to_bf16, bf16_to_bits
+    cfg = g.EPConfig("few", T=T, H=640, E=E, K=K, R=R, routing="uniform", seed=T)
+    idx, w = g.routing_all(cfg)
+    idx = g.mask_random(idx, 0.3, seed=K)
+    idx[0, -1, :] = -1
+    lay = oracle.layout(idx, cfg.E, cfg.R)
+    rows = int((idx >= 0).sum())
+    y = np.resize(g.activations(cfg, 0, tid=g.TID_Y, T=997), (rows, cfg.H))
+    with _runner(epmod, cfg, num_proxy_threads=0) as r:
+        d_y, d_w, d_row = bits_to_bf16(y), _dev(w[0]), _dev(lay["dst_row"][0])
+        out = torch.full((T, cfg.H), 7.0, dtype=torch.bfloat16, device="cuda")
+        r.combine(d_y, d_w, d_row, out)
+        # every entry a group of its own: a partial sum per row, in the row's own place
+        own = torch.arange(K, dtype=torch.int32, device="cuda").repeat(T, 1)
+        partial = torch.full((rows, cfg.H), 7.0, dtype=torch.bfloat16, device="cuda")
+        epmod.ep_combine_partial(r.h, d_y, d_w, d_row, own, d_row, T, rows, rows, partial)
+        torch.cuda.synchronize()
+        assert _combine_check(oracle, bf16_to_bits(out), y, w[0], lay["dst_row"][0], K) == 0
+        weight = np.zeros((rows, 1), np.float32)
+        valid = lay["dst_row"][0] >= 0
+        weight[lay["dst_row"][0][valid], 0] = w[0][valid]
+        assert _combine_check(oracle, bf16_to_bits(partial), y, weight, np.arange(rows, dtype=np.int32)[:, None], 1) == 0
         assert r.stats()["device_error"] == 0
 
 
