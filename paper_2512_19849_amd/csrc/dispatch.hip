@@ -335,8 +335,14 @@ EP_DEV void place_token_fp8(const DispatchArgs &a, const TokenMeta &m, unsigned 
   }
 }
 
-template <int VPL, bool GROUPS>
+// (TOGETHER: a row's scales leave as one store, by one wave, out of LDS; else every wave stores those of its part, 32 bytes at a
+// time.  Each store that fills no line of its own costs the memory behind the L2 as much as a full one, and there are seven of
+// them beside the 56 lines of a 7168-wide row's codes; below 128 MB of rows the barrier costs more.  Whole steps, apart /
+// together, us: 4096 tokens x 7168 top-8 162.6 / 160.2, 8192 x 4096 193.6 / 188.9, 8192 x 2048 116.3 / 113.2, 3000 x 7168 127.3 /
+// 123.8; 6000 x 3072 117.3 / 117.4; 2000 x 7168 (118 MB) 82.9 / 85.6, 1000 x 5120 39.8 / 40.6.)
+template <int VPL, bool GROUPS, bool TOGETHER>
 __global__ void dispatch_fp8_kernel(DispatchArgs a) {
+  __shared__ float s_scale[TOGETHER ? 16 * VPL * 8 : 1];  // [wave][its blocks]: the parts of a token in a row
   const int wave = wave_id(), lane = lane_id();
   const int part = (unsigned)wave % (unsigned)a.parts;
   const int t = token_block(a) * a.tokens_per_block + (unsigned)wave / (unsigned)a.parts;
@@ -369,6 +375,9 @@ __global__ void dispatch_fp8_kernel(DispatchArgs a) {
     if (!ahead) load();
 #pragma unroll
     for (int i = 0; i < VPL; ++i) quant16(lo[i], hi[i], q[i], sc[i]);
+    if (TOGETHER && (lane & 7) == 0)
+#pragma unroll
+      for (int i = 0; i < VPL; ++i) s_scale[(wave * VPL + i) * 8 + (lane >> 3)] = sc[i];
     // Where a row goes: into the two receive arrays (codes, scales), or - when the proxy moves the rows -
     // as ONE message of row_bytes bytes (the H codes, then the H/128 fp32 scales, padded to 16 bytes:
     // the ~7 KB token of Section 2.1) into the send heap: at its destination row for chunk commands
@@ -392,9 +401,20 @@ __global__ void dispatch_fp8_kernel(DispatchArgs a) {
       for (int i = 0; i < VPL; ++i)
         if (p0 + i * 64 < npair) {
           store_payload(dq + p0 + i * 64, q[i]);
-          if ((lane & 7) == 0)
+          if (!TOGETHER && (lane & 7) == 0)
             __hip_atomic_store(ds + ((p0 + i * 64) >> 3), sc[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
         }
+    }
+  }
+  if constexpr (TOGETHER) {
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");  // (the codes' stores are not waited for)
+    const float *scales = s_scale + (wave - part) * VPL * 8;
+    int n = 0;
+    for (unsigned long long mm = vmask; mm; mm &= mm - 1, ++n) {
+      if (n % a.parts != part) continue;  // the token's waves take its rows in turns
+      const int row = __builtin_amdgcn_readlane(m.row, __builtin_ctzll(mm));
+      float *ds = a.msg_rows ? (float *)((char *)a.recv + (size_t)row * a.row_bytes + a.H) : a.recv_scale + (size_t)row * nblk;
+      for (int b = lane; b < nblk; b += 64) __hip_atomic_store(ds + b, scales[b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     }
   }
   if (!ring_on) return;
@@ -613,8 +633,11 @@ static void launch_dispatch_fp8_t(DispatchArgs a, const Tunables &tune, hipStrea
   a.tokens_per_block = a.parts >= 4 ? 1 : 4 / a.parts;
   const size_t lds = group_cmds_setup(a, tune.per_token_waves);
   const int grid = max(1, (a.T + a.tokens_per_block - 1) / a.tokens_per_block);
-  launch_kernel(a.blocks_per_group ? dispatch_fp8_kernel<VPL, true> : dispatch_fp8_kernel<VPL, false>, dim3(grid),
-                dim3(64 * a.parts * a.tokens_per_block), lds, st, tm ? tm->start : nullptr, tm ? tm->stop : nullptr, a);
+  const bool together = min((long long)a.T * a.K, (long long)a.recv_rows) * (a.H + a.H / 32) >= 128000000ll;
+  launch_kernel(a.blocks_per_group ? dispatch_fp8_kernel<VPL, true, false>
+                : together         ? dispatch_fp8_kernel<VPL, false, true>
+                                   : dispatch_fp8_kernel<VPL, false, false>,
+                dim3(grid), dim3(64 * a.parts * a.tokens_per_block), lds, st, tm ? tm->start : nullptr, tm ? tm->stop : nullptr, a);
 }
 
 int launch_dispatch(const DispatchArgs &a, int payload, const Tunables &tune, void *stream,

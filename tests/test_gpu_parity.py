@@ -760,6 +760,19 @@ def test_dispatch_fp8_parity(epmod, oracle, cid, T, mask, mode):
         _check_commands(epmod, oracle, cfg, out, mode, payload="fp8")
 
 
+# 128 MB of rows: a row's scales leave together from there on; 9 blocks over 2 waves, 63 over 4 waves, the last of them ragged
+@pytest.mark.parametrize("T,H,K,mask,mode", [(13468, 1152, 8, 0.0, "none"), (13469, 1152, 8, 0.0, "chunk32"),
+                                             (3900, 8064, 4, 0.01, "chunk32_ordered"), (15200, 1024, 8, 0.001, "none")])
+def test_dispatch_fp8_scales_stored_together(epmod, oracle, T, H, K, mask, mode):
+    cfg = g.EPConfig("scales", T=T, H=H, E=16, K=K, R=4, routing="uniform", seed=T)
+    idx, _ = g.routing_all(cfg)
+    if mask:
+        idx = g.mask_random(idx, mask, seed=K)
+        idx[0, 7, :] = -1
+    x = np.resize(g.activations(cfg, 0, T=499), (T, H))
+    _fp8_case(epmod, oracle, cfg, x, idx, epmod.CMD_MODES[mode])
+
+
 def test_fp8_quantiser_all_bf16_inputs_and_corner_blocks(epmod, oracle):
     """Every finite bf16 value goes through the kernel's quantiser, grouped so
     that blocks hold similar magnitudes (dense coverage of rounding cases),
