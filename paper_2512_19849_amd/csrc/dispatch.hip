@@ -142,6 +142,12 @@ EP_DEV void emit_chunk_cmds(const DispatchArgs &a, const TokenMeta &m) {
 // the other) one token of 256 experts, alone, takes 35 us, now 33; larger steps are the same.  With the pairs loaded ahead of
 // the rows, which then wait for them too, 8192 x 1024 took 14 us more; with the leading Atomics in a workgroup of their own,
 // where the proxy sees them first, 128 tokens 1 us more.
+// Where a workgroup pushes its own, the heads are read ahead (ring_refresh_ahead) up to the last quarter of the grid.  Whole steps,
+// without / with, us: 8192 tokens x 4096 top-8 247 / 240, in FP8 232 / 219, 4096 x 7168 205 / 203, 2048 x 7168 112 / 108; rings of
+// 2048 265 / 243; 16 channels 250 / 239; up to seven eighths of the grid the first 237, the last but two 109, with 16 channels
+// 243.  With 32 channels, which all come to the same place in their rings at once, 272 / 271, 230 / 236 and in FP8 248 / 258:
+// not there.  Small dispatches fill a ring once in thirty steps.
+constexpr unsigned kRefreshChannels = 16;
 EP_DEV void emit_group_cmds(const DispatchArgs &a, int wave, int lane) {
   extern __shared__ u32x4 s_dyn[];  // the scratch of ring_push_sorted
   __syncthreads();  // every wave has waited for its own stores before it came here
@@ -182,6 +188,8 @@ EP_DEV void emit_group_cmds(const DispatchArgs &a, int wave, int lane) {
     const bool complete = active && done + 1 == c;
     if (complete) __hip_atomic_store(a.expert_done + e, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     push_count_atomics(a, complete && !(a.cmd_mode & EP_CMD_ATOMICS_FIRST), e, c, s_dyn);
+    if (gb == 1 && a.ring.channels <= kRefreshChannels && blockIdx.x < gridDim.x / 4 * 3)
+      ring_refresh_ahead(a.ring, active, ch, run.idx);
   }
 }
 

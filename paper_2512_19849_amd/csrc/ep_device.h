@@ -172,6 +172,17 @@ EP_DEV unsigned long long ring_publish(const RingDev &r, unsigned c, unsigned lo
   return ring_publish_run<1>(r, c, idx, ring_head(r, c), v, v);
 }
 
+// For the lanes with `active`, which have published a command with Idx: the one with the first of half a ring reads the head for
+// all, so that the device-side copy keeps up with the proxy.  Left until the copy calls the ring full, as it does once per trip
+// round the ring whether the proxy is behind or not, the read over PCIe is one that everybody with a command for the channel
+// waits for.  To be called when nothing else of the wave is waited for, and not towards the end of a kernel, which the read (10
+// us and more behind a chip full of stores) would prolong.  Every half ring is as good as every quarter, an eighth costs 1%.
+EP_DEV void ring_refresh_ahead(const RingDev &r, bool active, unsigned c, unsigned long long idx) {
+  if (!active || ((unsigned)idx & ((r.entries >> 1) - 1u)) != 0u) return;
+  const unsigned long long h = __hip_atomic_load(&r.head[c * kHeadStride], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  __hip_atomic_fetch_max(&r.cached_head[c], h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 EP_DEV unsigned long long readlane64(unsigned long long v, int lane) {
   return ((unsigned long long)(unsigned)__builtin_amdgcn_readlane((int)(v >> 32), lane) << 32) |
          (unsigned)__builtin_amdgcn_readlane((int)v, lane);

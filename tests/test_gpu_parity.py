@@ -760,6 +760,34 @@ def test_dispatch_fp8_parity(epmod, oracle, cid, T, mask, mode):
         _check_commands(epmod, oracle, cfg, out, mode, payload="fp8")
 
 
+# one command per row beyond 12288 of them: the heads of up to 16 channels are read ahead every half ring
+@pytest.mark.parametrize("channels,entries", [(1, 2), (3, 64), (16, 1024), (17, 1024), (8, 4096)])
+def test_per_token_commands_read_heads_ahead(epmod, oracle, channels, entries):
+    from paper_2512_19849_amd.runner import bits_to_bf16, bf16_to_bits
+    T, K = 1700, 8
+    cfg = g.EPConfig("heads", T=T, H=128, E=32, K=K, R=4, routing="zipf", seed=entries)
+    idx, _ = g.routing_all(cfg)
+    idx = g.mask_random(idx, 0.05, seed=channels)
+    rows = int((idx >= 0).sum())
+    want_lay = oracle.layout(idx, cfg.E, cfg.R)
+    with _runner(epmod, cfg, T, num_channels=channels, ring_entries=entries, num_proxy_threads=min(channels, 4)) as r:
+        d_idx = _dev(idx)
+        lay = r.layout(d_idx)
+        recv = torch.empty((rows, cfg.H), dtype=torch.bfloat16, device="cuda")
+        for it in range(3):
+            x = g.activations(cfg, it, T=T)
+            recv.fill_(-1.5)
+            r.dispatch(bits_to_bf16(x), d_idx[0], lay, recv, cmd_mode=epmod.EP_CMD_PER_TOKEN)
+            r.wait()
+            torch.cuda.synchronize()
+            want, _ = oracle.dispatch_bf16(x, idx[0], want_lay["dst_row"][0], cfg.E_loc, rows, -1, fill=0xBFC0)
+            assert np.array_equal(bf16_to_bits(recv), want), it
+            assert np.array_equal(r.counters()[0], want_lay["count"][0])
+        st = r.stats()
+        assert st["device_error"] == 0 and st["proxy_error"] == 0 and st["rejected"] == 0
+        assert st["write_rows"] == 3 * rows
+
+
 # 128 MB of rows: a row's scales leave together from there on; 9 blocks over 2 waves, 63 over 4 waves, the last of them ragged
 @pytest.mark.parametrize("T,H,K,mask,mode", [(13468, 1152, 8, 0.0, "none"), (13469, 1152, 8, 0.0, "chunk32"),
                                              (3900, 8064, 4, 0.01, "chunk32_ordered"), (15200, 1024, 8, 0.001, "none")])
