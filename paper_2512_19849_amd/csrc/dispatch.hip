@@ -664,15 +664,18 @@ int launch_dispatch(const DispatchArgs &a, int payload, const Tunables &tune, vo
     if (free_choice && (cmds == EP_CMD_PER_TOKEN || cmds == EP_CMD_CHUNK32_ORDERED) &&
         !(a.cmd_mode & EP_CMD_NO_PLACEMENT) && vpl > 2 && (a.H / 8 + 127) / 128 <= 8)
       vpl = 2;
-    // Ring off or plain chunk commands: rows that exceed the memory-side cache (256 MB) by half or more have to
+    // Ring off or plain chunk commands: rows that exceed the memory-side cache (256 MB) by a quarter or more have to
     // stream to HBM while the kernel runs; then ONE slice per wave (many small waves, eight 1 KiB stores each)
-    // is faster by 5-10 us per 450-900 MB than four slices per wave, which wins below that size by as much
-    // (measured for 224 to 896 MiB of rows, hidden 4096..8192) - and also where the caller has said that the
-    // rows are consumed in place, out of that cache.  (The sequenced chunk mode, bound by its hottest channel's
+    // is faster by 5-10 us per 450-900 MB than four slices per wave, which wins below that size by as much when the
+    // buffer is the one of the call before - and also where the caller has said that the rows are consumed in place, out of
+    // that cache.  Whole steps, four slices / one, into the same buffer and into four in turn, us: 3000 tokens x 7168 top-8
+    // (344 MB) 140.5 / 134.7 and 146.0 / 140.7, 4000 x 5120 (328 MB) 136.0 / 129.6 and 140.7 / 137.8, 2800 x 8192 149.7 / 147.4
+    // and 155.8 / 150.5; 2600 x 7168 (298 MB) 114.0 / 118.3 and 128.2 / 123.9, 2000 x 7168 88.0 / 92.9 and 100.7 / 96.3, 4500 x
+    // 4096 (295 MB) 111.8 / 112.2 and 127.5 / 125.9.  (The sequenced chunk mode, bound by its hottest channel's
     // FIFO, was measured slower with one slice per wave on the skewed workload.)
     const long long rows_at_most = (long long)a.T * a.K < a.recv_rows ? (long long)a.T * a.K : a.recv_rows;
     if (free_choice && !a.cache_hinted && (cmds == EP_CMD_NONE || cmds == EP_CMD_CHUNK32) &&
-        rows_at_most * a.H * 2 >= 384000000ll && (a.H / 8 + 63) / 64 <= 16)
+        rows_at_most * a.H * 2 >= 320000000ll && (a.H / 8 + 63) / 64 <= 16)
       vpl = 1;
     // (7 and 8 vectors per lane make the compiler spill in the form with a command wave: rows that wide take 14 / 16)
     if ((a.cmd_mode & EP_CMD_MODE_MASK) != EP_CMD_NONE && tune.dispatch_pipeline && (vpl == 7 || vpl == 8)) vpl *= 2;
