@@ -274,11 +274,10 @@ EP_DEV void fma_rows(float (&acc)[8], unsigned long long ks, int row, float wt, 
 // First level of the hierarchical reduce: like the combine, but the K gathered
 // rows of a token are summed per group and every group's sum is written to the
 // group's own row.  Rows, weights and group leaders are wave-uniform.
-// The sums are stored write-through, like the rows of a dispatch.  Partial + final reduce, and both behind a kernel that
-// writes y as the experts do (its own time included), us: 4096 tokens x 7168 top-8 over 16 groups 216 and 392 (streaming
-// stores 233 and 400, plain 218 and 393), 8192 x 4096 215 and 412 (231 and 422, 220 and 418), 1024 x 7168 60 and 89 (62 and
-// 100, 58 and 90).  Directly behind a dispatch of the same volume, with y untouched, streaming stores gain: step of 4096 x
-// 7168 357, streaming 346.
+// The sums are stored write-through, like the rows of a dispatch.  Deduplicated steps with y as it was / written just before, as
+// the experts do (the copy's own time included), us: 4096 tokens x 7168 top-8 over 16 groups 327.5 and 500 (streaming stores 331.5
+// and 519, plain 334.5 and 505), 8192 x 4096 376 and 576 (386 and 594, 384 and 580), 1024 x 7168 96.3 and 138.0 (100 and 141.8,
+// 97.1 and 137.7).
 template <int KT>
 __global__ __launch_bounds__(64) void combine_partial_kernel(CombinePartialArgs a) {
   const int lane = lane_id();
