@@ -28,8 +28,9 @@ EP_DEV void fma8(float (&acc)[8], float w, const u32x4 &v) {
 
 // The slices of one wave, one after the other: K loads in flight, the chain in ascending k, the packed
 // result kept in registers; the stores of all slices leave together at the end, so that a wave's writes
-// do not trickle into its reads.  STREAM: non-temporal loads (rows that no cache is expected to hold).
-template <int VPL, int KT, bool STREAM>
+// do not trickle into its reads.  STREAM: non-temporal loads (rows that no cache is expected to hold).  SKIP: masked entries load
+// nothing, else a row that is loaded anyway.
+template <int VPL, int KT, bool STREAM, bool SKIP>
 EP_DEV void combine_slices(const u32x4 *y, u32x4 *out, const int (&rows)[KT], const float (&ws)[KT], int safe, int nvec,
                            int v0) {
   u32x4 res[VPL];
@@ -39,6 +40,7 @@ EP_DEV void combine_slices(const u32x4 *y, u32x4 *out, const int (&rows)[KT], co
       u32x4 ld[KT];
 #pragma unroll
       for (int k = 0; k < KT; ++k) {
+        if (SKIP && rows[k] < 0) continue;
         const u32x4 *p = y + (size_t)(rows[k] >= 0 ? rows[k] : safe) * nvec + v0 + i * 64;
         ld[k] = STREAM ? __builtin_nontemporal_load(p) : *p;
       }
@@ -100,11 +102,11 @@ __global__ __launch_bounds__(64) void combine_kernel(CombineArgs a) {
     }
     // (wave-uniform; two instances so that each keeps its own kind of load)
     if (fresh) {
-      combine_slices<VPL, KT, false>(y, out, rows, ws, safe, nvec, v0);
+      combine_slices<VPL, KT, false, false>(y, out, rows, ws, safe, nvec, v0);
       // (keeps the optimiser from folding the two instances into one, which drops the streaming hint of the other)
       asm volatile("" ::: "memory");
     } else {
-      combine_slices<VPL, KT, true>(y, out, rows, ws, safe, nvec, v0);
+      combine_slices<VPL, KT, true, false>(y, out, rows, ws, safe, nvec, v0);
     }
   } else {
 #pragma unroll
@@ -123,6 +125,33 @@ __global__ __launch_bounds__(64) void combine_kernel(CombineArgs a) {
   }
 }
 
+// The same for tables with many masked entries, one slice per wave: loads for the others only.  (Where nothing is masked the
+// loads behind branches take 0.3% more of a step: 4096 tokens x 7168 193.9 us, 194.4.)
+template <int KT>
+__global__ __launch_bounds__(64) void combine_sparse_kernel(CombineArgs a) {
+  const int lane = lane_id();
+  const int t = (int)(blockIdx.x / (unsigned)a.parts), part = (int)(blockIdx.x % (unsigned)a.parts);
+  int row = -1;
+  float wt = 0.0f;
+  if (lane < KT) {
+    row = a.dst_row[(size_t)t * KT + lane];
+    wt = a.w[(size_t)t * KT + lane];
+    if (row < -1 || row >= a.y_rows) {
+      dev_set_error(a.error, EP_EBOUNDS);
+      row = -1;
+    }
+  }
+  const int nvec = a.H >> 3;
+  int rows[KT];
+  float ws[KT];
+#pragma unroll
+  for (int k = 0; k < KT; ++k) {
+    rows[k] = __builtin_amdgcn_readlane(row, k);
+    ws[k] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(wt), k));
+  }
+  combine_slices<1, KT, true, true>((const u32x4 *)a.y, (u32x4 *)a.out + (size_t)t * nvec, rows, ws, 0, nvec, part * 64 + lane);
+}
+
 // Dynamic LDS (not used) that lets about `waves` one-wave workgroups onto a compute unit: it has 160 KB, given out in pieces of
 // 1280 bytes.
 static size_t lds_for_waves(int waves) { return waves >= 32 ? 0 : 163840 / waves / 1280 * 1280; }
@@ -139,9 +168,10 @@ static size_t lds_for_waves(int waves) { return waves >= 32 ? 0 : 163840 / waves
 // 2% (4096 x 7168 190, 8000 x 7168 368, 8192 x 6144 334, here 327); four waves per workgroup 1%.
 // A handle with one expert per rank is how the second level of the hierarchical reduce comes here, whose entries are masked but
 // for the first of each group: of K entries over G groups about G (1 - (1 - 1/G)^K) have a row, for which 100 KB is best.
-// Deduplicated steps with 10 / 12 / 14 / 16 / 18 / 20 / 25 / 32 waves, us: 4096 x 7168 top-8 over 16 groups 333 / 329 / 324 / 323 /
-// 324 / 327 / 330 / 331, over 8 (8192 x 4096) 340 / 334 / 332 / 330 / 329 / 328 / 328 / 328; top-6 over 16, 14 / 16 / 18 / 21 / 24 / 32
-// waves 258 / 254 / 250 / 251 / 255 / 260.
+// They take combine_sparse_kernel.  Deduplicated steps, combine_kernel at its best number of waves / this with 84 / 92 / 100 / 110
+// / 120 / 140 KB, us: 4096 x 7168 top-8 over 16 groups 324 / 321 / 322 / 322 / 326 / 326 / 330, 8192 x 4096 371 / 369 / 369 / 369 /
+// 372 / 372 / 375, over 8 groups 328 / 322 / 316 / 313 / 313 / 315 / 320, over 4 groups 293 / 271 / 271 / 266 / 266 / 266 / 266; 3001 x
+// 8192 265 / 264 / 264 / 260 / 262 / 262 / 265, top-6 260 / 264 / 259 / 257 / 258 / 261 / 267.
 // (Top-9 and more go through a loop with one load in flight per wave: no limit.  Nor where rows of a dispatch that has just
 // ended are read out of the memory-side cache.)
 static int combine_waves(const CombineArgs &a) {
@@ -160,6 +190,18 @@ static void launch_combine_t(CombineArgs a, hipStream_t st, const LaunchTiming *
   const size_t lds = items >= 5ll * 256 * waves ? lds_for_waves(waves) : 0;
   const unsigned grid = (unsigned)items;
   void *ev0 = tm ? tm->start : nullptr, *ev1 = tm ? tm->stop : nullptr;
+  if (VPL == 1 && a.groups && a.K > 1 && a.K <= 8 && a.fresh_from == a.T) {
+    switch (a.K) {
+      case 2: launch_kernel(combine_sparse_kernel<2>, dim3(grid), dim3(64), lds, st, ev0, ev1, a); break;
+      case 3: launch_kernel(combine_sparse_kernel<3>, dim3(grid), dim3(64), lds, st, ev0, ev1, a); break;
+      case 4: launch_kernel(combine_sparse_kernel<4>, dim3(grid), dim3(64), lds, st, ev0, ev1, a); break;
+      case 5: launch_kernel(combine_sparse_kernel<5>, dim3(grid), dim3(64), lds, st, ev0, ev1, a); break;
+      case 6: launch_kernel(combine_sparse_kernel<6>, dim3(grid), dim3(64), lds, st, ev0, ev1, a); break;
+      case 7: launch_kernel(combine_sparse_kernel<7>, dim3(grid), dim3(64), lds, st, ev0, ev1, a); break;
+      default: launch_kernel(combine_sparse_kernel<8>, dim3(grid), dim3(64), lds, st, ev0, ev1, a); break;
+    }
+    return;
+  }
   switch (a.K) {
     case 1: launch_kernel(combine_kernel<VPL, 1>, dim3(grid), dim3(64), lds, st, ev0, ev1, a); break;
     case 2: launch_kernel(combine_kernel<VPL, 2>, dim3(grid), dim3(64), lds, st, ev0, ev1, a); break;

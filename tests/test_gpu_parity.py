@@ -966,6 +966,27 @@ def test_combine_loads_in_flight_by_volume(epmod, oracle, K, T):
         assert r.stats()["device_error"] == 0
 
 
+# one expert per rank, up to top-8: masked entries load nothing (top-1 and top-9 as on other handles)
+@pytest.mark.parametrize("K", range(1, 10))
+def test_combine_on_a_handle_with_one_expert_per_rank(epmod, oracle, K):
+    from paper_2512_19849_amd.runner import bits_to_bf16, bf16_to_bits
+    cfg = g.EPConfig("sparse", T=90, H=1152, E=12, K=K, R=12, seed=K)
+    idx, w = g.routing_all(cfg)
+    idx = g.mask_random(idx, 0.4, seed=K)
+    idx[0, 5, :] = -1
+    lay = oracle.layout(idx, cfg.E, cfg.R)
+    rows = int((idx >= 0).sum())
+    y = g.activations(cfg, 0, tid=g.TID_Y, T=rows)
+    with _runner(epmod, cfg, num_proxy_threads=0) as r:
+        out = torch.full((cfg.T, cfg.H), 7.0, dtype=torch.bfloat16, device="cuda")
+        r.combine(bits_to_bf16(y), _dev(w[0]), _dev(lay["dst_row"][0]), out)
+        torch.cuda.synchronize()
+        ob = bf16_to_bits(out)
+        assert _combine_check(oracle, ob, y, w[0], lay["dst_row"][0], K) == 0
+        assert (ob[5] == 0).all()
+        assert r.stats()["device_error"] == 0
+
+
 # the last launch without a limit on the waves of a compute unit and the first with one (84 KB / top-k; handles with one expert
 # per rank: 100 KB / expected rows), two slices per token and a ragged second one; then the partial reduce's rule (96 KB)
 @pytest.mark.parametrize("K,R,E,T", [(8, 4, 16, 6399), (8, 4, 16, 6400), (4, 4, 16, 13440), (8, 16, 16, 9600), (3, 2, 6, 18000),
