@@ -1999,6 +1999,32 @@ def test_ht_ring_dispatch_fp8(epmod, oracle, cid, T, mask, slices, W, window):
         assert st["write_bytes"] == 2 * (128 * int(nch.sum()) + (rows - 2) * oracle.row_bytes(cfg.H, "fp8"))
 
 
+# rows of the groups that a lane quantises in one go (8192 channels), and of one block more; 64 blocks and 65 in the receiving step
+@pytest.mark.parametrize("H", [1024, 2176, 8192, 8320, 16512])
+def test_ht_ring_dispatch_fp8_row_widths(epmod, oracle, H):
+    from paper_2512_19849_amd.runner import bits_to_bf16
+    T, E, K, R = 70, 8, 3, 4
+    cfg = g.EPConfig("widths", T=T, H=H, E=E, K=K, R=R, S=1, seed=H)
+    idx, _ = g.routing_all(cfg)
+    rows = T * K
+    lay_want = oracle.layout(idx, E, R)
+    with _runner(epmod, cfg, T, heap_rows=rows, ht_slices=2, ht_ring_slots=2) as r:
+        d_idx = _dev(idx)
+        lay = r.layout(d_idx)
+        ring = torch.zeros(r.ht_ring_bytes(), dtype=torch.uint8, device="cuda")
+        rq = torch.full((rows, H), 0xA5, dtype=torch.uint8, device="cuda")
+        rs = torch.full((rows, H // 128), -1.0, dtype=torch.float32, device="cuda")
+        for it in range(2):
+            x = g.activations(cfg, it, T=T)
+            r.ht_dispatch(bits_to_bf16(x), d_idx[0], lay, ring, rq, recv_scale=rs)
+            r.wait()
+            torch.cuda.synchronize()
+            wq, ws, _ = oracle.dispatch_fp8(x, idx[0], lay_want["dst_row"][0], cfg.E_loc, rows)
+            assert np.array_equal(rs.cpu().numpy().view(np.uint32), ws.view(np.uint32)), "scales differ"
+            assert np.array_equal(rq.cpu().numpy(), wq), "codes differ"
+        assert r.stats()["device_error"] == 0
+
+
 def test_ht_ring_dispatch_of_several_sources(epmod, oracle):
     """Config 2's 32 routing tables: sources 0, 7 and 31 each send their tokens through their own set of
     channels (counters, sequence numbers and proxy state are per source) into the one receive buffer."""
