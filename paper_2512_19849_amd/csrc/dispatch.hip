@@ -212,8 +212,8 @@ EP_DEV void emit_drain(const DispatchArgs &a, int lane) {
 // wave's first store.  Pairs first / together, whole steps, us: 4096 tokens x 7168 top-8 with chunks 197.3 / 195.2, in FP8
 // 164.4 / 163.2, deduplicated over 16 groups 357.3 / 352.4; 420 x 7552 in FP8 33.6 / 32.9.  With one command per row, where a
 // workgroup has its pairs to push and waits for them anyway, the pairs stay first: 8192 x 4096 249 / 257.  So they do for
-// sequenced chunks (1531 x 5120 top-6 57.6 / 59.6), for one rank of several, whose rows are a few tokens' only, and with more
-// than four vectors per lane, where two places to load from make the compiler spill.)
+// sequenced chunks (1531 x 5120 top-6 57.6 / 59.6; with the choice made in the kernel 59), for one rank of several, whose rows
+// are a few tokens' only, and with more than four vectors per lane, for which it was not measured.)
 // (Write-through stores without the streaming hint: with it the dispatch itself and a combine of other rows are up to 4%
 // faster, but whoever reads the rows next no longer finds any in the memory-side cache.  Step and a read of the received
 // rows, without / with, us: 4058 tokens x 7168 top-8 in FP8 182 / 194, 8116 tokens 365 / 380, 8239 x 4096 bf16 337 / 341.)
@@ -243,7 +243,7 @@ EP_DEV void place_token_bf16(const DispatchArgs &a, const int row_of_lane, unsig
   }
 }
 
-template <int VPL, bool GROUPS>
+template <int VPL, bool GROUPS, bool AHEAD>
 __global__ void dispatch_bf16_kernel(DispatchArgs a) {
   const int wave = wave_id(), lane = lane_id();
   const int part = (unsigned)wave % (unsigned)a.parts;
@@ -254,7 +254,6 @@ __global__ void dispatch_bf16_kernel(DispatchArgs a) {
 
   const int nvec = a.H >> 3;
   const int v0 = part * VPL * 64 + lane;
-  const bool place = t < a.T && !(a.cmd_mode & EP_CMD_NO_PLACEMENT), ahead = !GROUPS && !ordered && VPL <= 4 && place && a.filter < 0;
   const u32x4 *src = (const u32x4 *)a.x + (size_t)t * nvec;
   u32x4 v[VPL];
   auto load = [&]() {
@@ -262,11 +261,11 @@ __global__ void dispatch_bf16_kernel(DispatchArgs a) {
     for (int i = 0; i < VPL; ++i)
       if (v0 + i * 64 < nvec) v[i] = __builtin_nontemporal_load(src + v0 + i * 64);
   };
-  if (ahead) load();
+  if (AHEAD && t < a.T) load();
   const TokenMeta m = load_meta(a, t, lane);
   unsigned long long vmask = __ballot(m.valid);
-  if (vmask && place) {
-    if (!ahead) load();
+  if (vmask && !(a.cmd_mode & EP_CMD_NO_PLACEMENT)) {
+    if (!AHEAD) load();
     unsigned long long mm = vmask;
     while (mm) {
       __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
@@ -376,7 +375,7 @@ __global__ void dispatch_fp8_kernel(DispatchArgs a) {
         hi[i] = u32x4{0, 0, 0, 0};
       }
   };
-  if (ahead) load();  // (see dispatch_bf16_kernel)
+  if (ahead) load();  // (see dispatch_bf16_kernel; as instances of their own the large ones lose 0.6%)
   const TokenMeta m = load_meta(a, t, lane);
   unsigned long long vmask = __ballot(m.valid);
   if (vmask) {
@@ -601,6 +600,12 @@ static size_t group_cmds_setup(DispatchArgs &a, int waves) {
   return (1 + kLeadWaves) * kSortScratch;
 }
 
+// Does a token's row leave for the registers together with its pairs?  (See dispatch_bf16_kernel.)
+static bool row_ahead(const DispatchArgs &a) {
+  const int cmds = a.cmd_mode & EP_CMD_MODE_MASK;
+  return (cmds == EP_CMD_NONE || cmds == EP_CMD_CHUNK32) && !(a.cmd_mode & EP_CMD_NO_PLACEMENT) && a.filter < 0;
+}
+
 // Ring-on launches take the form with a command wave when it is switched on and the row needs at most 15 data
 // waves: returns false when the launch has to take the plain form.
 template <int VPL, bool FP8>
@@ -629,8 +634,11 @@ static void launch_dispatch_bf16_t(DispatchArgs a, const Tunables &tune, hipStre
   a.tokens_per_block = a.parts >= 4 ? 1 : 4 / a.parts;
   const size_t lds = group_cmds_setup(a, tune.per_token_waves);
   const int grid = max(1, (a.T + a.tokens_per_block - 1) / a.tokens_per_block);
-  launch_kernel(a.blocks_per_group ? dispatch_bf16_kernel<VPL, true> : dispatch_bf16_kernel<VPL, false>, dim3(grid),
-                dim3(64 * a.parts * a.tokens_per_block), lds, st, tm ? tm->start : nullptr, tm ? tm->stop : nullptr, a);
+  auto kernel = a.blocks_per_group ? dispatch_bf16_kernel<VPL, true, false> : dispatch_bf16_kernel<VPL, false, false>;
+  if constexpr (VPL <= 4)
+    if (row_ahead(a)) kernel = dispatch_bf16_kernel<VPL, false, true>;
+  launch_kernel(kernel, dim3(grid), dim3(64 * a.parts * a.tokens_per_block), lds, st, tm ? tm->start : nullptr,
+                tm ? tm->stop : nullptr, a);
 }
 
 template <int VPL>
@@ -642,10 +650,11 @@ static void launch_dispatch_fp8_t(DispatchArgs a, const Tunables &tune, hipStrea
   const size_t lds = group_cmds_setup(a, tune.per_token_waves);
   const int grid = max(1, (a.T + a.tokens_per_block - 1) / a.tokens_per_block);
   const bool together = min((long long)a.T * a.K, (long long)a.recv_rows) * (a.H + a.H / 32) >= 128000000ll;
-  launch_kernel(a.blocks_per_group ? dispatch_fp8_kernel<VPL, true, false>
+  auto kernel = a.blocks_per_group ? dispatch_fp8_kernel<VPL, true, false>
                 : together         ? dispatch_fp8_kernel<VPL, false, true>
-                                   : dispatch_fp8_kernel<VPL, false, false>,
-                dim3(grid), dim3(64 * a.parts * a.tokens_per_block), lds, st, tm ? tm->start : nullptr, tm ? tm->stop : nullptr, a);
+                                   : dispatch_fp8_kernel<VPL, false, false>;
+  launch_kernel(kernel, dim3(grid), dim3(64 * a.parts * a.tokens_per_block), lds, st, tm ? tm->start : nullptr,
+                tm ? tm->stop : nullptr, a);
 }
 
 int launch_dispatch(const DispatchArgs &a, int payload, const Tunables &tune, void *stream,
