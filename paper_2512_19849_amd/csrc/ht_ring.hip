@@ -279,9 +279,16 @@ EP_DEV void ht_receive_step(const HtRingArgs &a, HtShared &sh, int c) {
   // What a tail announces reached memory from outside this compute unit's view (a network adapter in the paper; here the sending
   // step's write-through stores), possibly into lines a cache still holds from the slot's previous use: drop those before the
   // first read of the sweep (the acquire that pairs with the tail).  It empties the XCD's L2, so one wave does it for all, and
-  // none on idle sweeps.  Whole steps, by every wave / by one, us: 4096 tokens x 7168 top-8, 128 slices 430 / 411, 3000 x 5120,
-  // 256 slices 258 / 223, 1024 x 4096, 64 slices 99 / 82, 600 x 2048 top-4 59 / 54; 2048 x 7168 in FP8, 128 slices 216 / 207.
-  if (wave == 0) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+  // none on idle sweeps.  A wave's own loads are served behind its invalidate; for the others' the barrier alone says nothing, as
+  // the invalidate may still be on its way when its wave arrives there.  So that wave loads a word behind it, through the caches it
+  // empties, and waits for the word: by then the invalidate is through this compute unit's L1 and ahead of every later load in
+  // its queues to the L2.  Whole steps, by every wave / by one, us: 4096 tokens x 7168 top-8, 128 slices 423 / 403, 3000 x 5120,
+  // 256 slices 270 / 239, 1024 x 4096, 64 slices 107 / 98, 600 x 2048 top-4 63.8 / 62.5; 2048 x 7168 in FP8, 128 slices 204 / 194.
+  if (wave == 0) {
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    const int behind = __hip_atomic_load(a.idx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    asm volatile("s_waitcnt vmcnt(0)" ::"v"(behind) : "memory");
+  }
   __syncthreads();
   if (tid == 0) sh.announced = 0;
   // move their rows to where the header says; rows are dealt out to the waves round-robin

@@ -53,6 +53,18 @@ def test_rows_are_counted_behind_their_reservation(tmp_path):
 
 
 @pytest.mark.skipif(not os.path.exists(HIPCC), reason="hipcc not installed")
+def test_ring_kernel_waits_for_its_invalidate(tmp_path):
+    """One wave drops the stale lines for its whole workgroup.  The barrier behind it orders the other waves' loads only if
+    the invalidate is through by then: the wave waits for a load of its own behind it."""
+    body = _kernel_body(_assembly("ht_ring.hip", tmp_path), "_ZN2ep14ht_ring_kernelENS_10HtRingArgsE")
+    behind = [m.end() for m in re.finditer(r"\bbuffer_inv sc1\b", body)]
+    assert behind
+    for at in behind:
+        to_barrier = body[at:body.index("s_barrier", at)]
+        assert re.search(r"global_load_dword v\d+, [^\n]*\n(?:[^\n]*\n)*?\s*s_waitcnt vmcnt\(0\)", to_barrier), to_barrier
+
+
+@pytest.mark.skipif(not os.path.exists(HIPCC), reason="hipcc not installed")
 def test_ring_kernel_with_another_first_argument_is_refused(tmp_path):
     """The ring kernel reads its channels' state at an offset from the start of the argument block, so nothing may come to
     stand before the one argument it has."""
