@@ -347,7 +347,10 @@ EP_DEV void place_token_fp8(const DispatchArgs &a, const TokenMeta &m, unsigned 
 // them beside the 56 lines of a 7168-wide row's codes; below 128 MB of rows the barrier costs more.  Whole steps, apart /
 // together, us: 4096 tokens x 7168 top-8 162.6 / 160.2, 8192 x 4096 193.6 / 188.9, 8192 x 2048 116.3 / 113.2, 3000 x 7168 127.3 /
 // 123.8; 6000 x 3072 117.3 / 117.4; 2000 x 7168 (118 MB) 82.9 / 85.6, 1000 x 5120 39.8 / 40.6.)
-template <int VPL, bool GROUPS, bool TOGETHER>
+// (AHEAD: the row leaves together with the pairs, see dispatch_bf16_kernel, but for sequenced chunks: that choice is made here, as
+// with instances of their own those got slower, 2000 tokens x 7168 top-8 89.8 us, apart 93.9, 4096 tokens 167.8, 169.7.  For one rank
+// of several, whose launches are small, an instance without: ring off, one of 16 ranks, 4096 x 7168 10.6 us, apart 10.2.)
+template <int VPL, bool GROUPS, bool AHEAD, bool TOGETHER>
 __global__ void dispatch_fp8_kernel(DispatchArgs a) {
   __shared__ float s_scale[TOGETHER ? 16 * VPL * 8 : 1];  // [wave][its blocks]: the parts of a token in a row
   const int wave = wave_id(), lane = lane_id();
@@ -360,7 +363,7 @@ __global__ void dispatch_fp8_kernel(DispatchArgs a) {
   const int npair = a.H >> 4;  // 16-channel groups per row
   const int nblk = a.H >> 7;   // 128-channel blocks per row
   const int p0 = part * VPL * 64 + lane;
-  const bool ahead = !GROUPS && !ordered && t < a.T && a.filter < 0;
+  const bool ahead = AHEAD && !ordered && t < a.T;
   const u32x4 *src = (const u32x4 *)a.x + (size_t)t * npair * 2;
   u32x4 lo[VPL], hi[VPL], q[VPL];
   float sc[VPL];
@@ -375,7 +378,7 @@ __global__ void dispatch_fp8_kernel(DispatchArgs a) {
         hi[i] = u32x4{0, 0, 0, 0};
       }
   };
-  if (ahead) load();  // (see dispatch_bf16_kernel; as instances of their own the large ones lose 0.6%)
+  if (ahead) load();
   const TokenMeta m = load_meta(a, t, lane);
   unsigned long long vmask = __ballot(m.valid);
   if (vmask) {
@@ -650,9 +653,10 @@ static void launch_dispatch_fp8_t(DispatchArgs a, const Tunables &tune, hipStrea
   const size_t lds = group_cmds_setup(a, tune.per_token_waves);
   const int grid = max(1, (a.T + a.tokens_per_block - 1) / a.tokens_per_block);
   const bool together = min((long long)a.T * a.K, (long long)a.recv_rows) * (a.H + a.H / 32) >= 128000000ll;
-  auto kernel = a.blocks_per_group ? dispatch_fp8_kernel<VPL, true, false>
-                : together         ? dispatch_fp8_kernel<VPL, false, true>
-                                   : dispatch_fp8_kernel<VPL, false, false>;
+  auto kernel = a.blocks_per_group ? dispatch_fp8_kernel<VPL, true, false, false>
+                : a.filter >= 0    ? dispatch_fp8_kernel<VPL, false, false, false>
+                : together         ? dispatch_fp8_kernel<VPL, false, true, true>
+                                   : dispatch_fp8_kernel<VPL, false, true, false>;
   launch_kernel(kernel, dim3(grid), dim3(64 * a.parts * a.tokens_per_block), lds, st, tm ? tm->start : nullptr,
                 tm ? tm->stop : nullptr, a);
 }

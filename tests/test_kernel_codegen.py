@@ -53,6 +53,19 @@ def test_rows_are_counted_behind_their_reservation(tmp_path):
 
 
 @pytest.mark.skipif(not os.path.exists(HIPCC), reason="hipcc not installed")
+def test_fp8_form_for_one_rank_has_one_copy_of_the_row_loads(tmp_path):
+    """A dispatch to one rank of several reads every token's pairs first and few rows: a kernel without the row loads ahead of
+    the pairs, which cost it scalar registers though it never takes them."""
+    asm = _assembly("dispatch.hip", tmp_path)
+    kernels = re.findall(r"^(_ZN2ep19dispatch_fp8_kernelILi(\d+)ELb0ELb0ELb0E\w*):", asm, re.M)
+    assert len(kernels) == 3
+    for mangled, vpl in kernels:
+        body = _kernel_body(asm, mangled)
+        assert len(re.findall(r"global_load_dwordx4 [^\n]*\bnt\b", body)) == 2 * int(vpl), mangled
+        assert int(re.search(r"\.amdhsa_next_free_sgpr (\d+)", asm[asm.index(".amdhsa_kernel " + mangled):])[1]) <= 96, mangled
+
+
+@pytest.mark.skipif(not os.path.exists(HIPCC), reason="hipcc not installed")
 def test_ring_kernel_waits_for_its_invalidate(tmp_path):
     """One wave drops the stale lines for its whole workgroup.  The barrier behind it orders the other waves' loads only if
     the invalidate is through by then: the wave waits for a load of its own behind it."""
