@@ -243,13 +243,25 @@ EP_DEV void place_token_bf16(const DispatchArgs &a, const int row_of_lane, unsig
   }
 }
 
-template <int VPL, bool GROUPS, bool AHEAD>
+// A token without any expert (padding) has a row that nobody wants: the first of its pairs tells, a scalar load that the row then
+// waits for.  (A token whose first pair was dropped reads its row behind its pairs.)  Ring off, pairs first / every row ahead /
+// this, us: 4096 tokens x 7168 top-8 102.8 / 100.0 / 102.4, with every fifth token dropped 85.4 / 82.0 / 83.6, half of them 64.9 / 58.9 /
+// 62.4, 19 of 20 16.4 / 24.3 / 18.1; 16000 x 1024 48.3 / 45.2 / 45.0, 38.2 / 41.0 / 32.0, 20.7 / 32.7 / 20.7, 8.5 / 10.2 / 9.2; 4096 x 7168
+// in FP8 56.4 / 52.9 / 51.4, 54.5 / 45.3 / 48.5, 33.6 / 35.3 / 30.6, 7.0 / 14.8 / 7.9; 2000 x 7168 in FP8 25.8 / 23.9 / 23.8, 19.2 / 20.5 /
+// 19.1, 12.9 / 16.3 / 13.4, 5.2 / 7.7 / 5.4.
+EP_DEV bool names_an_expert(const DispatchArgs &a, int t) { return t < a.T && a.idx[(size_t)t * a.K] >= 0; }
+
+// Which rows leave ahead of their pairs: none, every one, or those of tokens that name an expert.
+enum { kAheadNone = 0, kAheadAll = 1, kAheadNamed = 2 };
+
+template <int VPL, bool GROUPS, int AHEAD>
 __global__ void dispatch_bf16_kernel(DispatchArgs a) {
   const int wave = wave_id(), lane = lane_id();
   const int part = (unsigned)wave % (unsigned)a.parts;
   const int t = token_block(a) * a.tokens_per_block + (unsigned)wave / (unsigned)a.parts;
   const bool ring_on = (a.cmd_mode & EP_CMD_MODE_MASK) != EP_CMD_NONE;
   const bool ordered = (a.cmd_mode & EP_CMD_MODE_MASK) == EP_CMD_CHUNK32_ORDERED;
+  const bool ahead = AHEAD == kAheadNamed ? names_an_expert(a, t) : AHEAD == kAheadAll && t < a.T;
   if (ring_on && !ordered && blockIdx.x == 0) emit_leading_atomics<GROUPS>(a, wave, lane);
 
   const int nvec = a.H >> 3;
@@ -261,11 +273,11 @@ __global__ void dispatch_bf16_kernel(DispatchArgs a) {
     for (int i = 0; i < VPL; ++i)
       if (v0 + i * 64 < nvec) v[i] = __builtin_nontemporal_load(src + v0 + i * 64);
   };
-  if (AHEAD && t < a.T) load();
+  if (ahead) load();
   const TokenMeta m = load_meta(a, t, lane);
   unsigned long long vmask = __ballot(m.valid);
   if (vmask && !(a.cmd_mode & EP_CMD_NO_PLACEMENT)) {
-    if (!AHEAD) load();
+    if (AHEAD != kAheadAll && !ahead) load();
     unsigned long long mm = vmask;
     while (mm) {
       __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
@@ -358,12 +370,12 @@ __global__ void dispatch_fp8_kernel(DispatchArgs a) {
   const int t = token_block(a) * a.tokens_per_block + (unsigned)wave / (unsigned)a.parts;
   const bool ring_on = (a.cmd_mode & EP_CMD_MODE_MASK) != EP_CMD_NONE;
   const bool ordered = (a.cmd_mode & EP_CMD_MODE_MASK) == EP_CMD_CHUNK32_ORDERED;
+  const bool ahead = AHEAD && !ordered && names_an_expert(a, t);
   if (ring_on && !ordered && blockIdx.x == 0) emit_leading_atomics<GROUPS>(a, wave, lane);
 
   const int npair = a.H >> 4;  // 16-channel groups per row
   const int nblk = a.H >> 7;   // 128-channel blocks per row
   const int p0 = part * VPL * 64 + lane;
-  const bool ahead = AHEAD && !ordered && t < a.T;
   const u32x4 *src = (const u32x4 *)a.x + (size_t)t * npair * 2;
   u32x4 lo[VPL], hi[VPL], q[VPL];
   float sc[VPL];
@@ -603,10 +615,15 @@ static size_t group_cmds_setup(DispatchArgs &a, int waves) {
   return (1 + kLeadWaves) * kSortScratch;
 }
 
-// Does a token's row leave for the registers together with its pairs?  (See dispatch_bf16_kernel.)
-static bool row_ahead(const DispatchArgs &a) {
+// Does a token's row of bf16 leave for the registers together with its pairs?  (See dispatch_bf16_kernel.)  Where all rows are
+// few (24 MB) without asking for an expert: such a launch waits for loads more than for memory.  Whole steps, asking / not, us: 1500
+// tokens x 7168 top-6 54.3 / 52.8, 777 x 2944 16.7 / 16.3, 4000 x 2048 57.0 / 56.7; ring off with 19 of 20 tokens dropped, 1400 x 7168
+// 5.9 / 6.2, 3000 x 4096 6.3 / 6.2, but 2000 x 7168 6.7 / 8.2.  (FP8 always asks: 1500 x 7168 45.3 / 45.0, 1000 x 7168 46.8 / 47.4, and
+// 1400 x 7168 with four of five dropped 6.3 / 6.7.)
+static int row_ahead(const DispatchArgs &a) {
   const int cmds = a.cmd_mode & EP_CMD_MODE_MASK;
-  return (cmds == EP_CMD_NONE || cmds == EP_CMD_CHUNK32) && !(a.cmd_mode & EP_CMD_NO_PLACEMENT) && a.filter < 0;
+  if ((cmds != EP_CMD_NONE && cmds != EP_CMD_CHUNK32) || (a.cmd_mode & EP_CMD_NO_PLACEMENT) || a.filter >= 0) return kAheadNone;
+  return (long long)a.T * a.H <= 24ll << 19 ? kAheadAll : kAheadNamed;
 }
 
 // Ring-on launches take the form with a command wave when it is switched on and the row needs at most 15 data
@@ -637,9 +654,11 @@ static void launch_dispatch_bf16_t(DispatchArgs a, const Tunables &tune, hipStre
   a.tokens_per_block = a.parts >= 4 ? 1 : 4 / a.parts;
   const size_t lds = group_cmds_setup(a, tune.per_token_waves);
   const int grid = max(1, (a.T + a.tokens_per_block - 1) / a.tokens_per_block);
-  auto kernel = a.blocks_per_group ? dispatch_bf16_kernel<VPL, true, false> : dispatch_bf16_kernel<VPL, false, false>;
-  if constexpr (VPL <= 4)
-    if (row_ahead(a)) kernel = dispatch_bf16_kernel<VPL, false, true>;
+  auto kernel = a.blocks_per_group ? dispatch_bf16_kernel<VPL, true, kAheadNone> : dispatch_bf16_kernel<VPL, false, kAheadNone>;
+  if constexpr (VPL <= 4) {
+    if (row_ahead(a) == kAheadAll) kernel = dispatch_bf16_kernel<VPL, false, kAheadAll>;
+    if (row_ahead(a) == kAheadNamed) kernel = dispatch_bf16_kernel<VPL, false, kAheadNamed>;
+  }
   launch_kernel(kernel, dim3(grid), dim3(64 * a.parts * a.tokens_per_block), lds, st, tm ? tm->start : nullptr,
                 tm ? tm->stop : nullptr, a);
 }

@@ -760,6 +760,36 @@ def test_dispatch_fp8_parity(epmod, oracle, cid, T, mask, mode):
         _check_commands(epmod, oracle, cfg, out, mode, payload="fp8")
 
 
+# tokens whose first expert was dropped read their row behind their pairs, the others ahead of them, those without any not at
+# all (bf16: from 24 MB of tokens on); one and four tokens per workgroup
+@pytest.mark.parametrize("payload", ["bf16", "fp8"])
+@pytest.mark.parametrize("mode", ["none", "chunk32"])
+@pytest.mark.parametrize("T,H", [(301, 7168), (1203, 1024), (1760, 7168), (12300, 1024)])
+def test_dispatch_rows_ahead_of_their_pairs(epmod, oracle, T, H, mode, payload):
+    cfg = g.EPConfig("ahead", T=T, H=H, E=32, K=4, R=4, routing="zipf", seed=H)
+    idx, _ = g.routing_all(cfg)
+    idx[0, ::3, 0] = -1
+    idx[0, 1::4, :] = -1
+    idx[0, -1, :] = -1
+    x = np.resize(g.activations(cfg, 0, T=499), (T, H))
+    if payload == "fp8":
+        _fp8_case(epmod, oracle, cfg, x, idx, epmod.CMD_MODES[mode])
+        return
+    from paper_2512_19849_amd.runner import bits_to_bf16, bf16_to_bits
+    rows = int((idx >= 0).sum()) + 2
+    with _runner(epmod, cfg, T) as r:
+        d_idx = _dev(idx)
+        lay = r.layout(d_idx)
+        recv = torch.full((rows, H), -1.5, dtype=torch.bfloat16, device="cuda")
+        r.dispatch(bits_to_bf16(x), d_idx[0], lay, recv, cmd_mode=epmod.CMD_MODES[mode])
+        if mode != "none":
+            r.wait()
+        torch.cuda.synchronize()
+        want, _ = oracle.dispatch_bf16(x, idx[0], oracle.layout(idx, cfg.E, cfg.R)["dst_row"][0], cfg.E_loc, rows, -1, fill=0xBFC0)
+        assert np.array_equal(bf16_to_bits(recv), want)
+        assert r.stats()["device_error"] == 0
+
+
 # one command per row beyond 12288 of them: the heads of up to 16 channels are read ahead every half ring
 @pytest.mark.parametrize("channels,entries", [(1, 2), (3, 64), (16, 1024), (17, 1024), (8, 4096)])
 def test_per_token_commands_read_heads_ahead(epmod, oracle, channels, entries):

@@ -66,6 +66,20 @@ def test_fp8_form_for_one_rank_has_one_copy_of_the_row_loads(tmp_path):
 
 
 @pytest.mark.skipif(not os.path.exists(HIPCC), reason="hipcc not installed")
+def test_rows_of_tokens_without_experts_are_not_read_ahead(tmp_path):
+    """A kernel that reads rows ahead of the tokens' pairs, and not in small launches only, asks for the first pair before: a
+    scalar load of the expert, and what comes of its sign.  Tokens that name none (padding) cost no read of their row."""
+    asm = _assembly("dispatch.hip", tmp_path)
+    kernels = re.findall(r"^(_ZN2ep20dispatch_bf16_kernelILi\d+ELb0ELi2E\w*|_ZN2ep19dispatch_fp8_kernelILi\d+ELb0ELb1E\w*):", asm, re.M)
+    assert len(kernels) == 3 + 6
+    for mangled in kernels:
+        body = _kernel_body(asm, mangled)
+        first_row = re.search(r"global_load_dwordx4 [^\n]*\bnt\b", body).start()
+        assert re.search(r"s_load_dword (s\d+), s\[\d+:\d+\], 0x0\s+s_waitcnt lgkmcnt\(0\)\s+s_cmp_gt_i32 \1, -1\b",
+                         body[:first_row]), mangled
+
+
+@pytest.mark.skipif(not os.path.exists(HIPCC), reason="hipcc not installed")
 def test_ring_kernel_waits_for_its_invalidate(tmp_path):
     """One wave drops the stale lines for its whole workgroup.  The barrier behind it orders the other waves' loads only if
     the invalidate is through by then: the wave waits for a load of its own behind it."""
