@@ -701,13 +701,17 @@ int launch_dispatch(const DispatchArgs &a, int payload, const Tunables &tune, vo
     // is faster by 5-10 us per 450-900 MB than four slices per wave, which wins below that size by as much when the
     // buffer is the one of the call before - and also where the caller has said that the rows are consumed in place, out of
     // that cache.  Whole steps, four slices / one, into the same buffer and into four in turn, us: 3000 tokens x 7168 top-8
-    // (344 MB) 140.5 / 134.7 and 146.0 / 140.7, 4000 x 5120 (328 MB) 136.0 / 129.6 and 140.7 / 137.8, 2800 x 8192 149.7 / 147.4
+    // (344 MB) 148.6 / 145.8 and 146.0 / 140.7, 4000 x 5120 (328 MB) 143.9 / 141.8 and 140.7 / 137.8, 2800 x 8192 158.3 / 151.9
     // and 155.8 / 150.5; 2600 x 7168 (298 MB) 114.0 / 118.3 and 128.2 / 123.9, 2000 x 7168 88.0 / 92.9 and 100.7 / 96.3, 4500 x
-    // 4096 (295 MB) 111.8 / 112.2 and 127.5 / 125.9.  (The sequenced chunk mode, bound by its hottest channel's
+    // 4096 (295 MB) 111.8 / 112.2 and 127.5 / 125.9.  The bytes are those of a table without dropped pairs, which only the GPU
+    // counts: 3000 x 7168 with a tenth dropped 138.4 / 135.4, three tenths 118.0 / 118.5, half 98.6 / 103.5; 4000 x 5120 133.5 / 130.5,
+    // 114.1 / 111.1, 93.6 / 96.4.  A handle with one expert per rank mostly places deduplicated rows, of which a fifth and more are
+    // dropped: there from 384 MB on.  Deduplicated steps over 16 groups, 2900 x 7168 221.4 / 228.1, with a tenth dropped 206.2 / 214.9,
+    // 3200 x 7168 (367 MB) 248.8 / 253.2 and 226.3 / 237.2.  (The sequenced chunk mode, bound by its hottest channel's
     // FIFO, was measured slower with one slice per wave on the skewed workload.)
     const long long rows_at_most = (long long)a.T * a.K < a.recv_rows ? (long long)a.T * a.K : a.recv_rows;
     if (free_choice && !a.cache_hinted && (cmds == EP_CMD_NONE || cmds == EP_CMD_CHUNK32) &&
-        rows_at_most * a.H * 2 >= 320000000ll && (a.H / 8 + 63) / 64 <= 16)
+        rows_at_most * a.H * 2 >= (a.E == a.R ? 384000000ll : 320000000ll) && (a.H / 8 + 63) / 64 <= 16)
       vpl = 1;
     // (7 and 8 vectors per lane make the compiler spill in the form with a command wave: rows that wide take 14 / 16)
     if ((a.cmd_mode & EP_CMD_MODE_MASK) != EP_CMD_NONE && tune.dispatch_pipeline && (vpl == 7 || vpl == 8)) vpl *= 2;

@@ -790,6 +790,26 @@ def test_dispatch_rows_ahead_of_their_pairs(epmod, oracle, T, H, mode, payload):
         assert r.stats()["device_error"] == 0
 
 
+# a handle with one expert per rank keeps to four slices of a row per wave up to 384 MB of rows, others up to 320 MB
+@pytest.mark.parametrize("E", [16, 32])
+@pytest.mark.parametrize("T", [2790, 2791, 3348, 3349])
+def test_dispatch_bf16_at_the_lines_of_one_slice_per_wave(epmod, E, T):
+    H, K, R = 7168, 8, 16
+    gen = torch.Generator(device="cuda").manual_seed(T)
+    idx = torch.rand((1, T, E), generator=gen, device="cuda").topk(K, dim=-1).indices.to(torch.int32)
+    idx = torch.where(torch.rand(idx.shape, generator=gen, device="cuda") < 0.1, -1, idx).contiguous()
+    x = torch.randn((T, H), generator=gen, device="cuda", dtype=torch.bfloat16)
+    with _runner(epmod, g.EPConfig("line", T=T, H=H, E=E, K=K, R=R), T, num_proxy_threads=0) as r:
+        lay = r.layout(idx)
+        recv = torch.full((T * K, H), -1.5, dtype=torch.bfloat16, device="cuda")
+        r.dispatch(x, idx[0], lay, recv)
+        valid = idx[0] >= 0
+        got = recv[lay.dst_row[0][valid].long()]
+        assert torch.equal(got, x[valid.nonzero()[:, 0]])
+        assert (recv[int(valid.sum()):] == -1.5).all()
+        assert r.stats()["device_error"] == 0
+
+
 # one command per row beyond 12288 of them: the heads of up to 16 channels are read ahead every half ring
 @pytest.mark.parametrize("channels,entries", [(1, 2), (3, 64), (16, 1024), (17, 1024), (8, 4096)])
 def test_per_token_commands_read_heads_ahead(epmod, oracle, channels, entries):
