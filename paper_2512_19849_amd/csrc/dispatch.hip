@@ -356,9 +356,11 @@ EP_DEV void place_token_fp8(const DispatchArgs &a, const TokenMeta &m, unsigned 
 
 // (TOGETHER: a row's scales leave as one store, by one wave, out of LDS; else every wave stores those of its part, 32 bytes at a
 // time.  Each store that fills no line of its own costs the memory behind the L2 as much as a full one, and there are seven of
-// them beside the 56 lines of a 7168-wide row's codes; below 128 MB of rows the barrier costs more.  Whole steps, apart /
-// together, us: 4096 tokens x 7168 top-8 162.6 / 160.2, 8192 x 4096 193.6 / 188.9, 8192 x 2048 116.3 / 113.2, 3000 x 7168 127.3 /
-// 123.8; 6000 x 3072 117.3 / 117.4; 2000 x 7168 (118 MB) 82.9 / 85.6, 1000 x 5120 39.8 / 40.6.)
+// them beside the 56 lines of a 7168-wide row's codes; where the rows fit the memory-side cache (256 MB) beside what else is in it,
+// the barrier costs more.  Whole steps, apart / together, us: 4096 tokens x 7168 top-8 (242 MB) 163.8 / 161.3, with a tenth of the
+// pairs dropped 152.6 / 152.1, three tenths 127.7 / 129.3; 12000 x 2048 (203 MB) 156.6 / 153.6, 142.7 / 145.1, 121.3 / 123.5; 6000 x 4096
+// (203 MB) 138.6 / 136.7, 125.9 / 127.2, 102.7 / 103.7; 3000 x 7168 (177 MB) 118.6 / 122.2, 2700 x 8192 122.6 / 123.3, 6000 x 3072 102.1 /
+// 105.3, 8192 x 2048 97.2 / 97.9.  A row that is one wave's has one store of scales anyway: ring off, 30000 x 1024 49.7 / 51.8.)
 // (AHEAD: the row leaves together with the pairs, see dispatch_bf16_kernel, but for sequenced chunks: that choice is made here, as
 // with instances of their own those got slower, 2000 tokens x 7168 top-8 89.8 us, apart 93.9, 4096 tokens 167.8, 169.7.  For one rank
 // of several, whose launches are small, an instance without: ring off, one of 16 ranks, 4096 x 7168 10.6 us, apart 10.2.)
@@ -671,7 +673,7 @@ static void launch_dispatch_fp8_t(DispatchArgs a, const Tunables &tune, hipStrea
   a.tokens_per_block = a.parts >= 4 ? 1 : 4 / a.parts;
   const size_t lds = group_cmds_setup(a, tune.per_token_waves);
   const int grid = max(1, (a.T + a.tokens_per_block - 1) / a.tokens_per_block);
-  const bool together = min((long long)a.T * a.K, (long long)a.recv_rows) * (a.H + a.H / 32) >= 128000000ll;
+  const bool together = a.parts > 1 && min((long long)a.T * a.K, (long long)a.recv_rows) * (a.H + a.H / 32) >= 200000000ll;
   auto kernel = a.blocks_per_group ? dispatch_fp8_kernel<VPL, true, false, false>
                 : a.filter >= 0    ? dispatch_fp8_kernel<VPL, false, false, false>
                 : together         ? dispatch_fp8_kernel<VPL, false, true, true>

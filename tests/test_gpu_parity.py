@@ -851,6 +851,39 @@ def test_dispatch_fp8_scales_stored_together(epmod, oracle, T, H, K, mask, mode)
     _fp8_case(epmod, oracle, cfg, x, idx, epmod.CMD_MODES[mode])
 
 
+# a row's scales leave together from 200 MB of rows on: both sides of the line, four groups of channels per lane with a ragged last
+# wave, a row that is one wave's, and messages that the proxy moves
+@pytest.mark.parametrize("T,H,K,mask,mode", [(3382, 7168, 8, 0.0, "none"), (3383, 7168, 8, 0.01, "chunk32"),
+                                             (2915, 8320, 8, 0.0, "chunk32_ordered"), (23700, 1024, 8, 0.0, "none")])
+def test_dispatch_fp8_scales_stored_together_from_200_mb_on(epmod, oracle, T, H, K, mask, mode):
+    test_dispatch_fp8_scales_stored_together(epmod, oracle, T, H, K, mask, mode)
+
+
+@pytest.mark.parametrize("mode", ["chunk32", "chunk32_ordered"])
+def test_proxy_performs_fp8_writes_with_scales_stored_together(epmod, oracle, mode):
+    test_proxy_performs_fp8_writes(epmod, oracle, 4, 3400, 0.0, 0, mode, 4)
+
+
+def test_dispatch_fp8_of_many_rows_to_one_rank(epmod):
+    """One rank's part of 200 MB of rows is what the dispatch to all ranks places there; other rows keep their bytes."""
+    T, H, E, K, R = 3400, 7168, 32, 8, 4
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    idx = torch.rand((1, T, E), generator=gen, device="cuda").topk(K, dim=-1).indices.to(torch.int32)
+    x = torch.randn((T, H), generator=gen, device="cuda", dtype=torch.bfloat16)
+    with _runner(epmod, g.EPConfig("part", T=T, H=H, E=E, K=K, R=R), T, num_proxy_threads=0) as r:
+        lay = r.layout(idx)
+        rows = T * K
+        got = [(torch.full((rows, H), 0xA5, dtype=torch.uint8, device="cuda"),
+                torch.full((rows, H // 128), -1.0, dtype=torch.float32, device="cuda")) for _ in range(2)]
+        for (rq, rs), rank in zip(got, (-1, 2)):
+            r.dispatch(x, idx[0], lay, rq, rs, payload=epmod.EP_FP8_E4M3, rank_filter=rank)
+        first, end = int(lay.rank_offset[2]), int(lay.rank_offset[3])
+        for whole, part, untouched in zip(*got, (0xA5, -1.0)):
+            assert torch.equal(whole[first:end], part[first:end])
+            assert (part[:first] == untouched).all() and (part[end:] == untouched).all()
+        assert r.stats()["device_error"] == 0
+
+
 def test_fp8_quantiser_all_bf16_inputs_and_corner_blocks(epmod, oracle):
     """Every finite bf16 value goes through the kernel's quantiser, grouped so
     that blocks hold similar magnitudes (dense coverage of rounding cases),
