@@ -125,10 +125,9 @@ __global__ __launch_bounds__(64) void combine_kernel(CombineArgs a) {
   }
 }
 
-// The same for tables with many masked entries, one slice per wave: loads for the others only.  (Where nothing is masked the
-// loads behind branches take 0.3% more of a step: 4096 tokens x 7168 193.9 us, 194.4.)
+// The same with one slice per wave and loads for the entries that have a row only, for rows that no cache is expected to hold.
 template <int KT>
-__global__ __launch_bounds__(64) void combine_sparse_kernel(CombineArgs a) {
+__global__ __launch_bounds__(64) void combine_slice_kernel(CombineArgs a) {
   const int lane = lane_id();
   const int t = (int)(blockIdx.x / (unsigned)a.parts), part = (int)(blockIdx.x % (unsigned)a.parts);
   int row = -1;
@@ -156,28 +155,32 @@ __global__ __launch_bounds__(64) void combine_sparse_kernel(CombineArgs a) {
 // 1280 bytes.
 static size_t lds_for_waves(int waves) { return waves >= 32 ? 0 : 163840 / waves / 1280 * 1280; }
 
-// One slice (64 lanes x 16 bytes) per wave, one wave per workgroup, and no more of them on a compute unit than have about 84 KB
-// of rows on their way.  The kernel is bound by the memory behind the L2, which keeps that many reads of scattered rows busy
-// and serves more of them in a worse order; a launch that does not fill the chip five times over has no such limit.  Whole
-// steps, ring off, waves per compute unit 10 / 11 / 12 / 14 / 16 / 20 / 32, us:
-//   top-8  4096 tokens x 4096 117.1 / 116.8 / 115.8 / 116.1 / 116.4 / 117.0 / 118.9, 8192 x 4096 223 / 223 / 223 / 224 / 225 /
-//          226 / 230, 4096 x 7168 188.7 / 188.3 / 188.8 / 190 / 191 / 192 / 191, 8000 x 7168 360 / 360 / - / - / - / - / 379
-//   top-7  6000 x 7168 244.2 / 242.2 / 242.3 / 243.5 / 245.5 / 247.6 / 249.0; top-6 216 / 213 / 211.5 / 210.7 / 212 / 215 / 217
-//   top-5  the same 193 / 189 / 187 / 183.4 / 182.5 / 184.7 / 186.4; top-4 173 / 170 / 167 / 163 / 160.2 / 158.8 / 161.6
-// (top-3 and less: best without.)  Two slices per wave, at their best number of waves, take 1% longer, four 5%; a wave per token
-// 2% (4096 x 7168 190, 8000 x 7168 368, 8192 x 6144 334, here 327); four waves per workgroup 1%.
+// One slice (64 lanes x 16 bytes) per wave, one wave per workgroup, and no more of them on a compute unit than have 96 KB of
+// rows on their way if no entry is masked.  The kernel is bound by the memory behind the L2, which about 84 KB of scattered reads
+// per compute unit keep busy and which serves more of them in a worse order; but masked entries load nothing, and how many there
+// are only the GPU knows: with 84 KB a table with three tenths of its entries masked leaves the memory idle.  A launch that does not
+// fill the chip five times over has no such limit, nor have top-4 and less.  The combine alone, 10
+// / 12 / 14 / 16 / 20 / 32 waves per compute unit, and four waves per workgroup with a load for every entry, us:
+//   top-8  3000 tokens x 7168 61.7 / 61.3 / 62.3 / 62.7 / 63.9 / 64.8, 66.2; a tenth masked 60.9 / 59.7 / 60.2 / 60.8 / 61.3 / 62.3,
+//          63.0; three tenths 51.8 / 48.8 / 47.4 / 47.0 / 47.7 / 48.4, 50.2; half 43.7 / 39.7 / 37.1 / 35.7 / 35.1 / 35.6, 40.1; eight
+//          tenths 35.4 / 31.5 / 28.5 / 26.3 / 23.1 / 20.7, 31.2; 6000 x 4096 71.5 / 71.9 / 72.8 / 73.1 / 74.1 / 75.6, 77.1, half masked
+//          49.9 / 45.2 / 42.3 / 40.6 / 39.9 / 40.5, 45.1; whole steps of 4096 x 7168 in chunks with 12 and 14 waves 193.7 and 195.4
+//   top-6  3000 x 7168, 14 / 16 / 18 / 20 / 32 waves 48.3 / 48.5 / 48.9 / 49.2 / 49.9, 51.5, half masked 32.5 / 30.8 / 29.6 / 28.6 / 28.1,
+//          32.0; top-5, 16 / 20 / 24 / 32 waves 41.9 / 42.4 / 42.6 / 42.9, 44.3, half masked 29.3 / 27.0 / 26.3 / 25.7, 28.9; top-4, 20 / 24 /
+//          32 waves 35.2 / 35.2 / 35.3, 36.4, half masked 24.3 / 23.3 / 22.6, 24.5
+// Two slices per wave, at their best number of waves, take 1% longer, four 5%; a wave per token 2%.
 // A handle with one expert per rank is how the second level of the hierarchical reduce comes here, whose entries are masked but
 // for the first of each group: of K entries over G groups about G (1 - (1 - 1/G)^K) have a row, for which 100 KB is best.
-// They take combine_sparse_kernel.  Deduplicated steps, combine_kernel at its best number of waves / this with 84 / 92 / 100 / 110
-// / 120 / 140 KB, us: 4096 x 7168 top-8 over 16 groups 324 / 321 / 322 / 322 / 326 / 326 / 330, 8192 x 4096 371 / 369 / 369 / 369 /
-// 372 / 372 / 375, over 8 groups 328 / 322 / 316 / 313 / 313 / 315 / 320, over 4 groups 293 / 271 / 271 / 266 / 266 / 266 / 266; 3001 x
-// 8192 265 / 264 / 264 / 260 / 262 / 262 / 265, top-6 260 / 264 / 259 / 257 / 258 / 261 / 267.
+// Deduplicated steps with 84 / 92 / 100 / 110 / 120 / 140 KB, us: 4096 x 7168 top-8 over 16 groups 321 / 322 / 322 / 326 / 326 / 330,
+// 8192 x 4096 369 / 369 / 369 / 372 / 372 / 375, over 8 groups 322 / 316 / 313 / 313 / 315 / 320, over 4 groups 271 / 271 / 266 / 266 /
+// 266 / 266; 3001 x 8192 264 / 264 / 260 / 262 / 262 / 265, top-6 264 / 259 / 257 / 258 / 261 / 267.  (Such a handle with nothing masked
+// gets 19 waves for top-8 over 8 ranks: 4096 x 7168 85.8 us, with 16 waves 83.2, four per workgroup with no limit 86.2.)
 // (Top-9 and more go through a loop with one load in flight per wave: no limit.  Nor where rows of a dispatch that has just
 // ended are read out of the memory-side cache.)
 static int combine_waves(const CombineArgs &a) {
   if (a.K > 8 || a.fresh_from < a.T) return 32;
   if (a.groups) return (int)(100.0 / (a.groups * (1.0 - pow(1.0 - 1.0 / a.groups, a.K))));
-  return 84 / a.K;
+  return a.K <= 4 ? 32 : 96 / a.K;
 }
 static int tuned_combine_vpl(int forced) { return forced == 2 || forced == 4 || forced == 7 ? forced : 1; }
 
@@ -190,15 +193,16 @@ static void launch_combine_t(CombineArgs a, hipStream_t st, const LaunchTiming *
   const size_t lds = items >= 5ll * 256 * waves ? lds_for_waves(waves) : 0;
   const unsigned grid = (unsigned)items;
   void *ev0 = tm ? tm->start : nullptr, *ev1 = tm ? tm->stop : nullptr;
-  if (VPL == 1 && a.groups && a.K > 1 && a.K <= 8 && a.fresh_from == a.T) {
+  if (VPL == 1 && a.K <= 8 && a.fresh_from == a.T) {
     switch (a.K) {
-      case 2: launch_kernel(combine_sparse_kernel<2>, dim3(grid), dim3(64), lds, st, ev0, ev1, a); break;
-      case 3: launch_kernel(combine_sparse_kernel<3>, dim3(grid), dim3(64), lds, st, ev0, ev1, a); break;
-      case 4: launch_kernel(combine_sparse_kernel<4>, dim3(grid), dim3(64), lds, st, ev0, ev1, a); break;
-      case 5: launch_kernel(combine_sparse_kernel<5>, dim3(grid), dim3(64), lds, st, ev0, ev1, a); break;
-      case 6: launch_kernel(combine_sparse_kernel<6>, dim3(grid), dim3(64), lds, st, ev0, ev1, a); break;
-      case 7: launch_kernel(combine_sparse_kernel<7>, dim3(grid), dim3(64), lds, st, ev0, ev1, a); break;
-      default: launch_kernel(combine_sparse_kernel<8>, dim3(grid), dim3(64), lds, st, ev0, ev1, a); break;
+      case 1: launch_kernel(combine_slice_kernel<1>, dim3(grid), dim3(64), lds, st, ev0, ev1, a); break;
+      case 2: launch_kernel(combine_slice_kernel<2>, dim3(grid), dim3(64), lds, st, ev0, ev1, a); break;
+      case 3: launch_kernel(combine_slice_kernel<3>, dim3(grid), dim3(64), lds, st, ev0, ev1, a); break;
+      case 4: launch_kernel(combine_slice_kernel<4>, dim3(grid), dim3(64), lds, st, ev0, ev1, a); break;
+      case 5: launch_kernel(combine_slice_kernel<5>, dim3(grid), dim3(64), lds, st, ev0, ev1, a); break;
+      case 6: launch_kernel(combine_slice_kernel<6>, dim3(grid), dim3(64), lds, st, ev0, ev1, a); break;
+      case 7: launch_kernel(combine_slice_kernel<7>, dim3(grid), dim3(64), lds, st, ev0, ev1, a); break;
+      default: launch_kernel(combine_slice_kernel<8>, dim3(grid), dim3(64), lds, st, ev0, ev1, a); break;
     }
     return;
   }

@@ -1100,6 +1100,12 @@ def test_combine_with_few_waves_per_compute_unit(epmod, oracle, K, R, E, T):
         assert r.stats()["device_error"] == 0
 
 
+# two slices per token: the last launch without a limit on the waves of a compute unit and the first with one, 96 KB / top-k
+@pytest.mark.parametrize("K,T", [(8, 7679), (8, 7680), (7, 8319), (7, 8320), (6, 10240), (5, 12160), (4, 15360), (1, 7680)])
+def test_combine_with_as_many_waves_as_masked_entries_need(epmod, oracle, K, T):
+    test_combine_with_few_waves_per_compute_unit(epmod, oracle, K, 4, 16, T)
+
+
 def test_round_trip_identity_expert(epmod, oracle):
     """dispatch -> identity expert -> combine returns the input scaled by the
     sum of its weights; with K = 1 and w = 1 it is the input, bit for bit."""
