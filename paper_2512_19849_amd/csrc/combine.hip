@@ -57,9 +57,9 @@ EP_DEV void combine_slices(const u32x4 *y, u32x4 *out, const int (&rows)[KT], co
 }
 
 template <int VPL, int KT>
-__global__ __launch_bounds__(64) void combine_kernel(CombineArgs a) {
+__global__ __launch_bounds__(256) void combine_kernel(CombineArgs a) {
   const int lane = lane_id();
-  const unsigned item = blockIdx.x;
+  const unsigned item = blockIdx.x * (unsigned)a.group_waves + wave_id();
   const int t_launch = (int)(item / (unsigned)a.parts), part = (int)(item % (unsigned)a.parts);
   if (t_launch >= a.T) return;
   // With fresh rows the grid starts at the end of the token range where they are (the last tokens,
@@ -127,9 +127,11 @@ __global__ __launch_bounds__(64) void combine_kernel(CombineArgs a) {
 
 // The same with one slice per wave and loads for the entries that have a row only, for rows that no cache is expected to hold.
 template <int KT>
-__global__ __launch_bounds__(64) void combine_slice_kernel(CombineArgs a) {
+__global__ __launch_bounds__(256) void combine_slice_kernel(CombineArgs a) {
   const int lane = lane_id();
-  const int t = (int)(blockIdx.x / (unsigned)a.parts), part = (int)(blockIdx.x % (unsigned)a.parts);
+  const unsigned item = blockIdx.x * (unsigned)a.group_waves + wave_id();
+  const int t = (int)(item / (unsigned)a.parts), part = (int)(item % (unsigned)a.parts);
+  if (t >= a.T) return;
   int row = -1;
   float wt = 0.0f;
   if (lane < KT) {
@@ -154,6 +156,13 @@ __global__ __launch_bounds__(64) void combine_slice_kernel(CombineArgs a) {
 // Dynamic LDS (not used) that lets about `waves` one-wave workgroups onto a compute unit: it has 160 KB, given out in pieces of
 // 1280 bytes.
 static size_t lds_for_waves(int waves) { return waves >= 32 ? 0 : 163840 / waves / 1280 * 1280; }
+
+// Waves per workgroup of both reduces: one, but four where all fit onto the chip at once (32 on each of 256 compute units) and
+// where a wave has little to do, top-3 and less.  There the rate at which workgroups start is what counts.  One / four, us:
+// combine of 512 tokens x 4096 top-4 5.3 / 4.6, top-6 6.3 / 5.8, top-8 7.6 / 7.1, top-12 12.3 / 11.8, 512 x 7168 top-8 11.9 / 11.7, but 1024
+// x 5120 (10240 waves) 16.6 / 17.0, 3000 x 7168 top-4 35.2 / 35.7; 3000 x 7168 top-2 22.6 / 22.5, with eight tenths masked 14.9 / 14.4,
+// top-1 13.6 / 11.4; partial reduce of 512 x 4096 top-4 7.3 / 5.8, top-6 9.6 / 7.8, top-8 12.5 / 11.7.
+static int reduce_group_waves(long long items, int K) { return items <= 8192 || K <= 3 ? 4 : 1; }
 
 // One slice (64 lanes x 16 bytes) per wave, one wave per workgroup, and no more of them on a compute unit than have 96 KB of
 // rows on their way if no entry is masked.  The kernel is bound by the memory behind the L2, which about 84 KB of scattered reads
@@ -190,32 +199,34 @@ static void launch_combine_t(CombineArgs a, hipStream_t st, const LaunchTiming *
   a.parts = (nvec + VPL * 64 - 1) / (VPL * 64);
   const long long items = (long long)a.T * a.parts;
   const int waves = combine_waves(a);
-  const size_t lds = items >= 5ll * 256 * waves ? lds_for_waves(waves) : 0;
-  const unsigned grid = (unsigned)items;
+  const size_t lds = items >= 5ll * 256 * waves ? lds_for_waves(waves) : 0;  // (never with more than one wave per workgroup)
+  a.group_waves = reduce_group_waves(items, a.K);
+  const unsigned grid = (unsigned)((items + a.group_waves - 1) / a.group_waves);
+  const dim3 block(64 * a.group_waves);
   void *ev0 = tm ? tm->start : nullptr, *ev1 = tm ? tm->stop : nullptr;
   if (VPL == 1 && a.K <= 8 && a.fresh_from == a.T) {
     switch (a.K) {
-      case 1: launch_kernel(combine_slice_kernel<1>, dim3(grid), dim3(64), lds, st, ev0, ev1, a); break;
-      case 2: launch_kernel(combine_slice_kernel<2>, dim3(grid), dim3(64), lds, st, ev0, ev1, a); break;
-      case 3: launch_kernel(combine_slice_kernel<3>, dim3(grid), dim3(64), lds, st, ev0, ev1, a); break;
-      case 4: launch_kernel(combine_slice_kernel<4>, dim3(grid), dim3(64), lds, st, ev0, ev1, a); break;
-      case 5: launch_kernel(combine_slice_kernel<5>, dim3(grid), dim3(64), lds, st, ev0, ev1, a); break;
-      case 6: launch_kernel(combine_slice_kernel<6>, dim3(grid), dim3(64), lds, st, ev0, ev1, a); break;
-      case 7: launch_kernel(combine_slice_kernel<7>, dim3(grid), dim3(64), lds, st, ev0, ev1, a); break;
-      default: launch_kernel(combine_slice_kernel<8>, dim3(grid), dim3(64), lds, st, ev0, ev1, a); break;
+      case 1: launch_kernel(combine_slice_kernel<1>, dim3(grid), block, lds, st, ev0, ev1, a); break;
+      case 2: launch_kernel(combine_slice_kernel<2>, dim3(grid), block, lds, st, ev0, ev1, a); break;
+      case 3: launch_kernel(combine_slice_kernel<3>, dim3(grid), block, lds, st, ev0, ev1, a); break;
+      case 4: launch_kernel(combine_slice_kernel<4>, dim3(grid), block, lds, st, ev0, ev1, a); break;
+      case 5: launch_kernel(combine_slice_kernel<5>, dim3(grid), block, lds, st, ev0, ev1, a); break;
+      case 6: launch_kernel(combine_slice_kernel<6>, dim3(grid), block, lds, st, ev0, ev1, a); break;
+      case 7: launch_kernel(combine_slice_kernel<7>, dim3(grid), block, lds, st, ev0, ev1, a); break;
+      default: launch_kernel(combine_slice_kernel<8>, dim3(grid), block, lds, st, ev0, ev1, a); break;
     }
     return;
   }
   switch (a.K) {
-    case 1: launch_kernel(combine_kernel<VPL, 1>, dim3(grid), dim3(64), lds, st, ev0, ev1, a); break;
-    case 2: launch_kernel(combine_kernel<VPL, 2>, dim3(grid), dim3(64), lds, st, ev0, ev1, a); break;
-    case 3: launch_kernel(combine_kernel<VPL, 3>, dim3(grid), dim3(64), lds, st, ev0, ev1, a); break;
-    case 4: launch_kernel(combine_kernel<VPL, 4>, dim3(grid), dim3(64), lds, st, ev0, ev1, a); break;
-    case 5: launch_kernel(combine_kernel<VPL, 5>, dim3(grid), dim3(64), lds, st, ev0, ev1, a); break;
-    case 6: launch_kernel(combine_kernel<VPL, 6>, dim3(grid), dim3(64), lds, st, ev0, ev1, a); break;
-    case 7: launch_kernel(combine_kernel<VPL, 7>, dim3(grid), dim3(64), lds, st, ev0, ev1, a); break;
-    case 8: launch_kernel(combine_kernel<VPL, 8>, dim3(grid), dim3(64), lds, st, ev0, ev1, a); break;
-    default: launch_kernel(combine_kernel<VPL, 0>, dim3(grid), dim3(64), lds, st, ev0, ev1, a); break;
+    case 1: launch_kernel(combine_kernel<VPL, 1>, dim3(grid), block, lds, st, ev0, ev1, a); break;
+    case 2: launch_kernel(combine_kernel<VPL, 2>, dim3(grid), block, lds, st, ev0, ev1, a); break;
+    case 3: launch_kernel(combine_kernel<VPL, 3>, dim3(grid), block, lds, st, ev0, ev1, a); break;
+    case 4: launch_kernel(combine_kernel<VPL, 4>, dim3(grid), block, lds, st, ev0, ev1, a); break;
+    case 5: launch_kernel(combine_kernel<VPL, 5>, dim3(grid), block, lds, st, ev0, ev1, a); break;
+    case 6: launch_kernel(combine_kernel<VPL, 6>, dim3(grid), block, lds, st, ev0, ev1, a); break;
+    case 7: launch_kernel(combine_kernel<VPL, 7>, dim3(grid), block, lds, st, ev0, ev1, a); break;
+    case 8: launch_kernel(combine_kernel<VPL, 8>, dim3(grid), block, lds, st, ev0, ev1, a); break;
+    default: launch_kernel(combine_kernel<VPL, 0>, dim3(grid), block, lds, st, ev0, ev1, a); break;
   }
 }
 
@@ -325,9 +336,9 @@ EP_DEV void fma_rows(float (&acc)[8], unsigned long long ks, int row, float wt, 
 // and 519, plain 334.5 and 505), 8192 x 4096 376 and 576 (386 and 594, 384 and 580), 1024 x 7168 96.3 and 138.0 (100 and 141.8,
 // 97.1 and 137.7).
 template <int KT>
-__global__ __launch_bounds__(64) void combine_partial_kernel(CombinePartialArgs a) {
+__global__ __launch_bounds__(256) void combine_partial_kernel(CombinePartialArgs a) {
   const int lane = lane_id();
-  const unsigned item = blockIdx.x;
+  const unsigned item = blockIdx.x * (unsigned)a.group_waves + wave_id();
   const int t = (int)(item / (unsigned)a.parts), part = (int)(item % (unsigned)a.parts);
   if (t >= a.T) return;
   const int K = KT > 0 ? KT : a.K;
@@ -410,20 +421,22 @@ int launch_combine_partial(const CombinePartialArgs &a0, void *stream) {
   const int nvec = a.H / 8;
   a.parts = (nvec + 63) / 64;
   const long long items = (long long)a.T * a.parts;
-  const unsigned grid = (unsigned)items;
   const int waves = kPartialKb / (a.K > 8 ? 4 : a.K);  // (fma_rows has four loads in flight)
   const size_t lds = items >= 5ll * 256 * waves ? lds_for_waves(waves) : 0;
+  a.group_waves = reduce_group_waves(items, a.K);
+  const unsigned grid = (unsigned)((items + a.group_waves - 1) / a.group_waves);
+  const dim3 block(64 * a.group_waves);
   hipStream_t st = (hipStream_t)stream;
   switch (a.K) {
-    case 1: hipLaunchKernelGGL(combine_partial_kernel<1>, dim3(grid), dim3(64), lds, st, a); break;
-    case 2: hipLaunchKernelGGL(combine_partial_kernel<2>, dim3(grid), dim3(64), lds, st, a); break;
-    case 3: hipLaunchKernelGGL(combine_partial_kernel<3>, dim3(grid), dim3(64), lds, st, a); break;
-    case 4: hipLaunchKernelGGL(combine_partial_kernel<4>, dim3(grid), dim3(64), lds, st, a); break;
-    case 5: hipLaunchKernelGGL(combine_partial_kernel<5>, dim3(grid), dim3(64), lds, st, a); break;
-    case 6: hipLaunchKernelGGL(combine_partial_kernel<6>, dim3(grid), dim3(64), lds, st, a); break;
-    case 7: hipLaunchKernelGGL(combine_partial_kernel<7>, dim3(grid), dim3(64), lds, st, a); break;
-    case 8: hipLaunchKernelGGL(combine_partial_kernel<8>, dim3(grid), dim3(64), lds, st, a); break;
-    default: hipLaunchKernelGGL(combine_partial_kernel<0>, dim3(grid), dim3(64), lds, st, a); break;
+    case 1: hipLaunchKernelGGL(combine_partial_kernel<1>, dim3(grid), block, lds, st, a); break;
+    case 2: hipLaunchKernelGGL(combine_partial_kernel<2>, dim3(grid), block, lds, st, a); break;
+    case 3: hipLaunchKernelGGL(combine_partial_kernel<3>, dim3(grid), block, lds, st, a); break;
+    case 4: hipLaunchKernelGGL(combine_partial_kernel<4>, dim3(grid), block, lds, st, a); break;
+    case 5: hipLaunchKernelGGL(combine_partial_kernel<5>, dim3(grid), block, lds, st, a); break;
+    case 6: hipLaunchKernelGGL(combine_partial_kernel<6>, dim3(grid), block, lds, st, a); break;
+    case 7: hipLaunchKernelGGL(combine_partial_kernel<7>, dim3(grid), block, lds, st, a); break;
+    case 8: hipLaunchKernelGGL(combine_partial_kernel<8>, dim3(grid), block, lds, st, a); break;
+    default: hipLaunchKernelGGL(combine_partial_kernel<0>, dim3(grid), block, lds, st, a); break;
   }
   return (int)hipGetLastError();
 }

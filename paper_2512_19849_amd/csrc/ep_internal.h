@@ -95,6 +95,7 @@ struct CombineArgs {
   void *out;               // bf16 [T,H]
   long long y_rows;
   int32_t T, K, H, parts;
+  int32_t group_waves;     // wavefronts per workgroup
   int32_t groups;          // of a handle with one expert per rank: its ranks, else 0 (see combine_waves)
   int *error;
   // Tokens >= fresh_from had their rows written last, by the kernel that ran just before on this
@@ -129,6 +130,7 @@ struct CombinePartialArgs {
   void *partial;       // bf16 [rows_g,H]
   long long y_rows, rows_g;
   int32_t T, K, H, parts;
+  int32_t group_waves; // wavefronts per workgroup
   int *error;
 };
 

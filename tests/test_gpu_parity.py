@@ -1106,6 +1106,35 @@ def test_combine_with_as_many_waves_as_masked_entries_need(epmod, oracle, K, T):
     test_combine_with_few_waves_per_compute_unit(epmod, oracle, K, 4, 16, T)
 
 
+# four waves per workgroup, three slices per token: the last workgroup holds one to four waves; the last launch that fits onto the
+# chip at once and the first that does not; top-3 and less at any size
+@pytest.mark.parametrize("K,T", [(8, 1), (8, 2), (4, 3), (9, 4), (8, 2730), (8, 2731), (12, 2730), (12, 2731), (3, 2733), (2, 6001),
+                                 (1, 2734)])
+def test_reduces_with_four_waves_per_workgroup(epmod, oracle, K, T):
+    from paper_2512_19849_amd.runner import bits_to_bf16, bf16_to_bits
+    cfg = g.EPConfig("four", T=T, H=1152, E=16, K=K, R=4, routing="uniform", seed=T)
+    idx, w = g.routing_all(cfg)
+    idx = g.mask_random(idx, 0.2, seed=K)
+    lay = oracle.layout(idx, cfg.E, cfg.R)
+    rows = max(1, int((idx >= 0).sum()))
+    y = np.resize(g.activations(cfg, 0, tid=g.TID_Y, T=499), (rows, cfg.H))
+    with _runner(epmod, cfg, num_proxy_threads=0) as r:
+        d_y, d_w, d_row = bits_to_bf16(y), _dev(w[0]), _dev(lay["dst_row"][0])
+        out = torch.full((T, cfg.H), 7.0, dtype=torch.bfloat16, device="cuda")
+        r.combine(d_y, d_w, d_row, out)
+        own = torch.arange(K, dtype=torch.int32, device="cuda").repeat(T, 1)  # every entry a group of its own
+        partial = torch.full((rows, cfg.H), 7.0, dtype=torch.bfloat16, device="cuda")
+        epmod.ep_combine_partial(r.h, d_y, d_w, d_row, own, d_row, T, rows, rows, partial)
+        torch.cuda.synchronize()
+        assert _combine_check(oracle, bf16_to_bits(out), y, w[0], lay["dst_row"][0], K) == 0
+        valid = lay["dst_row"][0] >= 0
+        if valid.any():
+            weight = np.zeros((rows, 1), np.float32)
+            weight[lay["dst_row"][0][valid], 0] = w[0][valid]
+            assert _combine_check(oracle, bf16_to_bits(partial), y, weight, np.arange(rows, dtype=np.int32)[:, None], 1) == 0
+        assert r.stats()["device_error"] == 0
+
+
 def test_round_trip_identity_expert(epmod, oracle):
     """dispatch -> identity expert -> combine returns the input scaled by the
     sum of its weights; with K = 1 and w = 1 it is the input, bit for bit."""
