@@ -158,11 +158,11 @@ __global__ __launch_bounds__(256) void combine_slice_kernel(CombineArgs a) {
 static size_t lds_for_waves(int waves) { return waves >= 32 ? 0 : 163840 / waves / 1280 * 1280; }
 
 // Waves per workgroup of both reduces: one, but four where all fit onto the chip at once (32 on each of 256 compute units) and
-// where a wave has little to do, top-3 and less.  There the rate at which workgroups start is what counts.  One / four, us:
+// where a wave has little to do: top-3 and less, in the partial reduce top-4.  There the rate at which workgroups start is what counts.  One / four, us:
 // combine of 512 tokens x 4096 top-4 5.3 / 4.6, top-6 6.3 / 5.8, top-8 7.6 / 7.1, top-12 12.3 / 11.8, 512 x 7168 top-8 11.9 / 11.7, but 1024
 // x 5120 (10240 waves) 16.6 / 17.0, 3000 x 7168 top-4 35.2 / 35.7; 3000 x 7168 top-2 22.6 / 22.5, with eight tenths masked 14.9 / 14.4,
 // top-1 13.6 / 11.4; partial reduce of 512 x 4096 top-4 7.3 / 5.8, top-6 9.6 / 7.8, top-8 12.5 / 11.7.
-static int reduce_group_waves(long long items, int K) { return items <= 8192 || K <= 3 ? 4 : 1; }
+static int reduce_group_waves(long long items, bool few) { return items <= 8192 || few ? 4 : 1; }
 
 // One slice (64 lanes x 16 bytes) per wave, one wave per workgroup, and no more of them on a compute unit than have 96 KB of
 // rows on their way if no entry is masked.  The kernel is bound by the memory behind the L2, which about 84 KB of scattered reads
@@ -200,7 +200,7 @@ static void launch_combine_t(CombineArgs a, hipStream_t st, const LaunchTiming *
   const long long items = (long long)a.T * a.parts;
   const int waves = combine_waves(a);
   const size_t lds = items >= 5ll * 256 * waves ? lds_for_waves(waves) : 0;  // (never with more than one wave per workgroup)
-  a.group_waves = reduce_group_waves(items, a.K);
+  a.group_waves = reduce_group_waves(items, a.K <= 3);
   const unsigned grid = (unsigned)((items + a.group_waves - 1) / a.group_waves);
   const dim3 block(64 * a.group_waves);
   void *ev0 = tm ? tm->start : nullptr, *ev1 = tm ? tm->stop : nullptr;
@@ -411,19 +411,25 @@ __global__ __launch_bounds__(256) void combine_partial_kernel(CombinePartialArgs
   }
 }
 
-// Waves per compute unit as in the combine, whose rule of 84 KB is 96 here.  Deduplicated steps with 11 / 12 / 14 / 16 / 20 / 32
-// waves, us: 4096 tokens x 7168 top-8 323.6 / 323.6 / 324.7 / 324.7 / 325.9 / 326.4, 8192 x 4096 372.6 / 373.0 / 374.2 / 374.8 /
-// 376.6 / 377.3; top-6 259.9 / 258.7 / 258.1 / 258.1 / 258.1 / 258.9; top-4 8192 wide 227 / 224 / 221.5 / 220.5 / 221.1 / 222.8.
-constexpr int kPartialKb = 96;
+// Waves per compute unit as in the combine, whose rule of 96 KB is 128 here, where every entry loads a row; top-4 and less have no
+// limit, and four waves per workgroup.  The reduce alone, 12 / 14 / 16 / 20 waves, and four per workgroup with no limit, us:
+//   top-8  4096 tokens x 7168 over 16 groups 153.1 / 156.1 / 155.8 / 157.7, 159.1, a tenth masked 138.3 / 140.2 / 140.7 / 142.3, 143.7, three
+//          tenths 107.3 / 101.5 / 100.4 / 100.5, 100.1, half 88.3 / 78.8 / 76.5 / 75.7, 76.3; 3000 x 7168 100.9 / 99.4 / 98.6 / 97.3, 98.3;
+//          over 8 groups 88.1 / 86.1 / 85.9 / 86.5, 86.9, a tenth masked 85.9 / 81.6 / 81.4 / 81.5, 81.9
+//   top-7  13 / 14 / 16 / 20 waves 4096 x 7168 136.1 / 135.6 / 137.1 / 137.2, 140.6, half masked 75.4 / 75.4 / 72.0 / 67.8, 67.0
+//   top-6  16 / 20 waves 4096 x 7168 114.6 / 116.1, 116.6; over 8 groups 93.9 / 93.2, 91.4; 8000 x 4096 129.7 / 130.8, 135.9
+//   top-4  one per workgroup with 24 waves, and four with no limit 8000 x 4096 over 16 groups 75.8, 74.4, 1500 x 7168 27.9, 28.0
+// (Loads for the entries that have a row only, as in the combine: 3000 x 7168 top-8 with 12 waves 118, with 20 102.)
+constexpr int kPartialKb = 128;
 int launch_combine_partial(const CombinePartialArgs &a0, void *stream) {
   if (a0.T <= 0) return 0;
   CombinePartialArgs a = a0;
   const int nvec = a.H / 8;
   a.parts = (nvec + 63) / 64;
   const long long items = (long long)a.T * a.parts;
-  const int waves = kPartialKb / (a.K > 8 ? 4 : a.K);  // (fma_rows has four loads in flight)
+  const int waves = a.K <= 4 ? 32 : a.K > 8 ? 24 : kPartialKb / a.K;  // (fma_rows has four loads in flight)
   const size_t lds = items >= 5ll * 256 * waves ? lds_for_waves(waves) : 0;
-  a.group_waves = reduce_group_waves(items, a.K);
+  a.group_waves = reduce_group_waves(items, a.K <= 4);
   const unsigned grid = (unsigned)((items + a.group_waves - 1) / a.group_waves);
   const dim3 block(64 * a.group_waves);
   hipStream_t st = (hipStream_t)stream;

@@ -1100,8 +1100,10 @@ def test_combine_with_few_waves_per_compute_unit(epmod, oracle, K, R, E, T):
         assert r.stats()["device_error"] == 0
 
 
-# two slices per token: the last launch without a limit on the waves of a compute unit and the first with one, 96 KB / top-k
-@pytest.mark.parametrize("K,T", [(8, 7679), (8, 7680), (7, 8319), (7, 8320), (6, 10240), (5, 12160), (4, 15360), (1, 7680)])
+# two slices per token: the last launch without a limit on the waves of a compute unit and the first with one, 96 KB / top-k;
+# then the same for the partial reduce, 128 KB
+@pytest.mark.parametrize("K,T", [(8, 7679), (8, 7680), (7, 8319), (7, 8320), (6, 10240), (5, 12160), (4, 15360), (1, 7680),
+                                 (8, 10239), (8, 10240), (6, 13440)])
 def test_combine_with_as_many_waves_as_masked_entries_need(epmod, oracle, K, T):
     test_combine_with_few_waves_per_compute_unit(epmod, oracle, K, 4, 16, T)
 
