@@ -171,6 +171,8 @@ EP_DEV bool ht_send_token(const HtRingArgs &a, HtShared &sh, int c, int t, HtTok
     // one store: a second half would wait for the stores of the first.  Whole steps, four groups and then the next four, scales
     // 32 bytes at a time, and in the receiving step behind the codes / this, us: 4096 tokens x 7168 top-8, 128 slices 299 / 293,
     // 2048 tokens 204 / 194, 3000 x 8064 over 256 264 / 246, 4096 x 4096 212 / 202, 1024 x 3072 over 64 91 / 89.
+    // Groups that a narrow row does not have are passed over: with all eight quantised whatever the width 4096 x 1024 over 64 slices
+    // takes 207, with four 196, like this 178; 2000 x 2048 117, 121 and 110; 4096 x 7168 the same.
     constexpr int kPairs = 8;
     const int npair = a.H >> 4;
     for (int p0 = 0; p0 < npair; p0 += 64 * kPairs) {
@@ -180,10 +182,13 @@ EP_DEV bool ht_send_token(const HtRingArgs &a, HtShared &sh, int c, int t, HtTok
       for (int i = 0; i < kPairs; ++i) {
         if (i && i % 2 == 0)  // (holds the next loads back)
           asm volatile("" : "+v"(q[i - 1]), "+v"(q[i - 2]), "+v"(sc[i - 1]), "+v"(sc[i - 2])::"memory");
-        const int p = p0 + i * 64 + lane;
+        const int first = __builtin_amdgcn_readfirstlane(p0 + i * 64);
+        q[i] = u32x4{0, 0, 0, 0};
+        sc[i] = 0.0f;
+        if (first >= npair) continue;  // (a narrow row has nothing left to quantise)
         u32x4 lo = {0, 0, 0, 0}, hi = {0, 0, 0, 0};
-        if (p < npair) {
-          const char *at = (const char *)xrow + (size_t)__builtin_amdgcn_readfirstlane(p0 + i * 64) * 32u;
+        if (first + lane < npair) {
+          const char *at = (const char *)xrow + (size_t)first * 32u;
           lo = *(const u32x4 *)(at + lane * 32u);
           hi = *(const u32x4 *)(at + lane * 32u + 16u);
         }

@@ -92,6 +92,17 @@ def test_ring_kernel_waits_for_its_invalidate(tmp_path):
 
 
 @pytest.mark.skipif(not os.path.exists(HIPCC), reason="hipcc not installed")
+def test_ring_kernel_passes_over_groups_that_a_narrow_row_does_not_have(tmp_path):
+    """A lane's eight groups of channels are quantised one behind the other; ahead of each stands a branch of the whole wave,
+    for rows that end before it."""
+    body = _kernel_body(_assembly("ht_ring.hip", tmp_path), "_ZN2ep14ht_ring_kernelENS_10HtRingArgsE")
+    converted = [m.start() for m in re.finditer(r"\bv_cvt_pk_fp8_f32\b", body)]
+    assert len(converted) == 8 * 8
+    for i in range(8, 64, 8):
+        assert re.search(r"\bs_cbranch_(?:scc|vcc)", body[converted[i - 1]:converted[i]]), i // 8
+
+
+@pytest.mark.skipif(not os.path.exists(HIPCC), reason="hipcc not installed")
 def test_ring_kernel_with_another_first_argument_is_refused(tmp_path):
     """The ring kernel reads its channels' state at an offset from the start of the argument block, so nothing may come to
     stand before the one argument it has."""
