@@ -158,32 +158,35 @@ __global__ __launch_bounds__(256) void combine_slice_kernel(CombineArgs a) {
 static size_t lds_for_waves(int waves) { return waves >= 32 ? 0 : 163840 / waves / 1280 * 1280; }
 
 // Waves per workgroup of both reduces: one, but four where all fit onto the chip at once (32 on each of 256 compute units) and
-// where a wave has little to do: top-3 and less, in the partial reduce top-4.  There the rate at which workgroups start is what counts.  One / four, us:
-// combine of 512 tokens x 4096 top-4 5.3 / 4.6, top-6 6.3 / 5.8, top-8 7.6 / 7.1, top-12 12.3 / 11.8, 512 x 7168 top-8 11.9 / 11.7, but 1024
-// x 5120 (10240 waves) 16.6 / 17.0, 3000 x 7168 top-4 35.2 / 35.7; 3000 x 7168 top-2 22.6 / 22.5, with eight tenths masked 14.9 / 14.4,
-// top-1 13.6 / 11.4; partial reduce of 512 x 4096 top-4 7.3 / 5.8, top-6 9.6 / 7.8, top-8 12.5 / 11.7.
+// where a wave has little to do: top-3 and less, in the partial reduce top-4.  There the rate at which workgroups start is what
+// counts.  One / four, us: combine of 512 tokens x 4096 top-4 5.3 / 4.6, top-6 6.3 / 5.8, top-8 7.6 / 7.1, top-12 12.3 / 11.8,
+// 512 x 7168 top-8 11.9 / 11.7, but 1024 x 5120 (10240 waves) 16.6 / 17.0, 3000 x 7168 top-4 35.2 / 35.7; 3000 x 7168 top-2
+// 22.6 / 22.5, with eight tenths masked 14.9 / 14.4, top-1 13.6 / 11.4; partial reduce of 512 x 4096 top-4 7.3 / 5.8, top-6 9.6
+// / 7.8, top-8 12.5 / 11.7.
 static int reduce_group_waves(long long items, bool few) { return items <= 8192 || few ? 4 : 1; }
 
 // One slice (64 lanes x 16 bytes) per wave, one wave per workgroup, and no more of them on a compute unit than have 96 KB of
-// rows on their way if no entry is masked.  The kernel is bound by the memory behind the L2, which about 84 KB of scattered reads
-// per compute unit keep busy and which serves more of them in a worse order; but masked entries load nothing, and how many there
-// are only the GPU knows: with 84 KB a table with three tenths of its entries masked leaves the memory idle.  A launch that does not
-// fill the chip five times over has no such limit, nor have top-4 and less.  The combine alone, 10
-// / 12 / 14 / 16 / 20 / 32 waves per compute unit, and four waves per workgroup with a load for every entry, us:
-//   top-8  3000 tokens x 7168 61.7 / 61.3 / 62.3 / 62.7 / 63.9 / 64.8, 66.2; a tenth masked 60.9 / 59.7 / 60.2 / 60.8 / 61.3 / 62.3,
-//          63.0; three tenths 51.8 / 48.8 / 47.4 / 47.0 / 47.7 / 48.4, 50.2; half 43.7 / 39.7 / 37.1 / 35.7 / 35.1 / 35.6, 40.1; eight
-//          tenths 35.4 / 31.5 / 28.5 / 26.3 / 23.1 / 20.7, 31.2; 6000 x 4096 71.5 / 71.9 / 72.8 / 73.1 / 74.1 / 75.6, 77.1, half masked
-//          49.9 / 45.2 / 42.3 / 40.6 / 39.9 / 40.5, 45.1; whole steps of 4096 x 7168 in chunks with 12 and 14 waves 193.7 and 195.4
-//   top-6  3000 x 7168, 14 / 16 / 18 / 20 / 32 waves 48.3 / 48.5 / 48.9 / 49.2 / 49.9, 51.5, half masked 32.5 / 30.8 / 29.6 / 28.6 / 28.1,
-//          32.0; top-5, 16 / 20 / 24 / 32 waves 41.9 / 42.4 / 42.6 / 42.9, 44.3, half masked 29.3 / 27.0 / 26.3 / 25.7, 28.9; top-4, 20 / 24 /
-//          32 waves 35.2 / 35.2 / 35.3, 36.4, half masked 24.3 / 23.3 / 22.6, 24.5
+// rows on their way if no entry is masked.  The kernel is bound by the memory behind the L2, which about 84 KB of scattered
+// reads per compute unit keep busy and which serves more of them in a worse order; but masked entries load nothing, and how
+// many there are only the GPU knows: with 84 KB a table with three tenths of its entries masked leaves the memory idle.  A
+// launch that does not fill the chip five times over has no such limit, nor have top-4 and less.  The combine alone, 10 / 12 /
+// 14 / 16 / 20 / 32 waves per compute unit, and four waves per workgroup with a load for every entry, us:
+//   top-8  3000 tokens x 7168 61.7 / 61.3 / 62.3 / 62.7 / 63.9 / 64.8, 66.2; a tenth masked 60.9 / 59.7 / 60.2 / 60.8 /
+//          61.3 / 62.3, 63.0; three tenths 51.8 / 48.8 / 47.4 / 47.0 / 47.7 / 48.4, 50.2; half 43.7 / 39.7 / 37.1 / 35.7 / 35.1
+//          / 35.6, 40.1; eight tenths 35.4 / 31.5 / 28.5 / 26.3 / 23.1 / 20.7, 31.2; 6000 x 4096 71.5 / 71.9 / 72.8 / 73.1 /
+//          74.1 / 75.6, 77.1, half masked 49.9 / 45.2 / 42.3 / 40.6 / 39.9 / 40.5, 45.1; whole steps of 4096 x 7168 in chunks
+//          with 12 and 14 waves 193.7 and 195.4
+//   top-6  3000 x 7168, 14 / 16 / 18 / 20 / 32 waves 48.3 / 48.5 / 48.9 / 49.2 / 49.9, 51.5, half masked 32.5 / 30.8 /
+//          29.6 / 28.6 / 28.1, 32.0; top-5, 16 / 20 / 24 / 32 waves 41.9 / 42.4 / 42.6 / 42.9, 44.3, half masked 29.3 / 27.0 /
+//          26.3 / 25.7, 28.9; top-4, 20 / 24 / 32 waves 35.2 / 35.2 / 35.3, 36.4, half masked 24.3 / 23.3 / 22.6, 24.5
 // Two slices per wave, at their best number of waves, take 1% longer, four 5%; a wave per token 2%.
 // A handle with one expert per rank is how the second level of the hierarchical reduce comes here, whose entries are masked but
 // for the first of each group: of K entries over G groups about G (1 - (1 - 1/G)^K) have a row, for which 100 KB is best.
-// Deduplicated steps with 84 / 92 / 100 / 110 / 120 / 140 KB, us: 4096 x 7168 top-8 over 16 groups 321 / 322 / 322 / 326 / 326 / 330,
-// 8192 x 4096 369 / 369 / 369 / 372 / 372 / 375, over 8 groups 322 / 316 / 313 / 313 / 315 / 320, over 4 groups 271 / 271 / 266 / 266 /
-// 266 / 266; 3001 x 8192 264 / 264 / 260 / 262 / 262 / 265, top-6 264 / 259 / 257 / 258 / 261 / 267.  (Such a handle with nothing masked
-// gets 19 waves for top-8 over 8 ranks: 4096 x 7168 85.8 us, with 16 waves 83.2, four per workgroup with no limit 86.2.)
+// Deduplicated steps with 84 / 92 / 100 / 110 / 120 / 140 KB, us: 4096 x 7168 top-8 over 16 groups 321 / 322 / 322 / 326 / 326
+// / 330, 8192 x 4096 369 / 369 / 369 / 372 / 372 / 375, over 8 groups 322 / 316 / 313 / 313 / 315 / 320, over 4 groups 271 /
+// 271 / 266 / 266 / 266 / 266; 3001 x 8192 264 / 264 / 260 / 262 / 262 / 265, top-6 264 / 259 / 257 / 258 / 261 / 267.  (Such a
+// handle with nothing masked gets 19 waves for top-8 over 8 ranks: 4096 x 7168 85.8 us, with 16 waves 83.2, four per workgroup
+// with no limit 86.2.)
 // (Top-9 and more go through a loop with one load in flight per wave: no limit.  Nor where rows of a dispatch that has just
 // ended are read out of the memory-side cache.)
 static int combine_waves(const CombineArgs &a) {
@@ -191,6 +194,7 @@ static int combine_waves(const CombineArgs &a) {
   if (a.groups) return (int)(100.0 / (a.groups * (1.0 - pow(1.0 - 1.0 / a.groups, a.K))));
   return a.K <= 4 ? 32 : 96 / a.K;
 }
+// (2, 4 and 7 slices per wave are for experiments, EP_COMBINE_VPL; anything else leaves one.)
 static int tuned_combine_vpl(int forced) { return forced == 2 || forced == 4 || forced == 7 ? forced : 1; }
 
 template <int VPL>
@@ -413,12 +417,16 @@ __global__ __launch_bounds__(256) void combine_partial_kernel(CombinePartialArgs
 
 // Waves per compute unit as in the combine, whose rule of 96 KB is 128 here, where every entry loads a row; top-4 and less have no
 // limit, and four waves per workgroup.  The reduce alone, 12 / 14 / 16 / 20 waves, and four per workgroup with no limit, us:
-//   top-8  4096 tokens x 7168 over 16 groups 153.1 / 156.1 / 155.8 / 157.7, 159.1, a tenth masked 138.3 / 140.2 / 140.7 / 142.3, 143.7, three
-//          tenths 107.3 / 101.5 / 100.4 / 100.5, 100.1, half 88.3 / 78.8 / 76.5 / 75.7, 76.3; 3000 x 7168 100.9 / 99.4 / 98.6 / 97.3, 98.3;
-//          over 8 groups 88.1 / 86.1 / 85.9 / 86.5, 86.9, a tenth masked 85.9 / 81.6 / 81.4 / 81.5, 81.9
-//   top-7  13 / 14 / 16 / 20 waves 4096 x 7168 136.1 / 135.6 / 137.1 / 137.2, 140.6, half masked 75.4 / 75.4 / 72.0 / 67.8, 67.0
-//   top-6  16 / 20 waves 4096 x 7168 114.6 / 116.1, 116.6; over 8 groups 93.9 / 93.2, 91.4; 8000 x 4096 129.7 / 130.8, 135.9
-//   top-4  one per workgroup with 24 waves, and four with no limit 8000 x 4096 over 16 groups 75.8, 74.4, 1500 x 7168 27.9, 28.0
+//   top-8  4096 tokens x 7168 over 16 groups 153.1 / 156.1 / 155.8 / 157.7, 159.1, a tenth masked 138.3 / 140.2 / 140.7
+//          / 142.3, 143.7, three tenths 107.3 / 101.5 / 100.4 / 100.5, 100.1, half 88.3 / 78.8 / 76.5 / 75.7, 76.3; 3000 x 7168
+//          100.9 / 99.4 / 98.6 / 97.3, 98.3; over 8 groups 88.1 / 86.1 / 85.9 / 86.5, 86.9, a tenth masked 85.9 / 81.6 / 81.4 /
+//          81.5, 81.9
+//   top-7  13 / 14 / 16 / 20 waves 4096 x 7168 136.1 / 135.6 / 137.1 / 137.2, 140.6, half masked 75.4 / 75.4 / 72.0 /
+//          67.8, 67.0
+//   top-6  16 / 20 waves 4096 x 7168 114.6 / 116.1, 116.6; over 8 groups 93.9 / 93.2, 91.4; 8000 x 4096 129.7 / 130.8,
+//          135.9
+//   top-4  one per workgroup with 24 waves, and four with no limit 8000 x 4096 over 16 groups 75.8, 74.4, 1500 x 7168
+//          27.9, 28.0
 // (Loads for the entries that have a row only, as in the combine: 3000 x 7168 top-8 with 12 waves 118, with 20 102.)
 constexpr int kPartialKb = 128;
 int launch_combine_partial(const CombinePartialArgs &a0, void *stream) {

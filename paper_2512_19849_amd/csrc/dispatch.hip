@@ -243,12 +243,12 @@ EP_DEV void place_token_bf16(const DispatchArgs &a, const int row_of_lane, unsig
   }
 }
 
-// A token without any expert (padding) has a row that nobody wants: the first of its pairs tells, a scalar load that the row then
-// waits for.  (A token whose first pair was dropped reads its row behind its pairs.)  Ring off, pairs first / every row ahead /
-// this, us: 4096 tokens x 7168 top-8 102.8 / 100.0 / 102.4, with every fifth token dropped 85.4 / 82.0 / 83.6, half of them 64.9 / 58.9 /
-// 62.4, 19 of 20 16.4 / 24.3 / 18.1; 16000 x 1024 48.3 / 45.2 / 45.0, 38.2 / 41.0 / 32.0, 20.7 / 32.7 / 20.7, 8.5 / 10.2 / 9.2; 4096 x 7168
-// in FP8 56.4 / 52.9 / 51.4, 54.5 / 45.3 / 48.5, 33.6 / 35.3 / 30.6, 7.0 / 14.8 / 7.9; 2000 x 7168 in FP8 25.8 / 23.9 / 23.8, 19.2 / 20.5 /
-// 19.1, 12.9 / 16.3 / 13.4, 5.2 / 7.7 / 5.4.
+// A token without any expert (padding) has a row that nobody wants: the first of its pairs tells, a scalar load that the row
+// then waits for.  (A token whose first pair was dropped reads its row behind its pairs.)  Ring off, pairs first / every row
+// ahead / this, us: 4096 tokens x 7168 top-8 102.8 / 100.0 / 102.4, with every fifth token dropped 85.4 / 82.0 / 83.6, half of
+// them 64.9 / 58.9 / 62.4, 19 of 20 16.4 / 24.3 / 18.1; 16000 x 1024 48.3 / 45.2 / 45.0, 38.2 / 41.0 / 32.0, 20.7 / 32.7 /
+// 20.7, 8.5 / 10.2 / 9.2; 4096 x 7168 in FP8 56.4 / 52.9 / 51.4, 54.5 / 45.3 / 48.5, 33.6 / 35.3 / 30.6, 7.0 / 14.8 / 7.9; 2000
+// x 7168 in FP8 25.8 / 23.9 / 23.8, 19.2 / 20.5 / 19.1, 12.9 / 16.3 / 13.4, 5.2 / 7.7 / 5.4.
 EP_DEV bool names_an_expert(const DispatchArgs &a, int t) { return t < a.T && a.idx[(size_t)t * a.K] >= 0; }
 
 // Which rows leave ahead of their pairs: none, every one, or those of tokens that name an expert.
@@ -354,16 +354,18 @@ EP_DEV void place_token_fp8(const DispatchArgs &a, const TokenMeta &m, unsigned 
   }
 }
 
-// (TOGETHER: a row's scales leave as one store, by one wave, out of LDS; else every wave stores those of its part, 32 bytes at a
-// time.  Each store that fills no line of its own costs the memory behind the L2 as much as a full one, and there are seven of
-// them beside the 56 lines of a 7168-wide row's codes; where the rows fit the memory-side cache (256 MB) beside what else is in it,
-// the barrier costs more.  Whole steps, apart / together, us: 4096 tokens x 7168 top-8 (242 MB) 163.8 / 161.3, with a tenth of the
-// pairs dropped 152.6 / 152.1, three tenths 127.7 / 129.3; 12000 x 2048 (203 MB) 156.6 / 153.6, 142.7 / 145.1, 121.3 / 123.5; 6000 x 4096
-// (203 MB) 138.6 / 136.7, 125.9 / 127.2, 102.7 / 103.7; 3000 x 7168 (177 MB) 118.6 / 122.2, 2700 x 8192 122.6 / 123.3, 6000 x 3072 102.1 /
-// 105.3, 8192 x 2048 97.2 / 97.9.  A row that is one wave's has one store of scales anyway: ring off, 30000 x 1024 49.7 / 51.8.)
-// (AHEAD: the row leaves together with the pairs, see dispatch_bf16_kernel, but for sequenced chunks: that choice is made here, as
-// with instances of their own those got slower, 2000 tokens x 7168 top-8 89.8 us, apart 93.9, 4096 tokens 167.8, 169.7.  For one rank
-// of several, whose launches are small, an instance without: ring off, one of 16 ranks, 4096 x 7168 10.6 us, apart 10.2.)
+// (TOGETHER: a row's scales leave as one store, by one wave, out of LDS; else every wave stores those of its part, 32 bytes at
+// a time.  Each store that fills no line of its own costs the memory behind the L2 as much as a full one, and there are seven
+// of them beside the 56 lines of a 7168-wide row's codes; where the rows fit the memory-side cache (256 MB) beside what else is
+// in it, the barrier costs more.  Whole steps, apart / together, us: 4096 tokens x 7168 top-8 (242 MB) 163.8 / 161.3, with a
+// tenth of the pairs dropped 152.6 / 152.1, three tenths 127.7 / 129.3; 12000 x 2048 (203 MB) 156.6 / 153.6, 142.7 / 145.1,
+// 121.3 / 123.5; 6000 x 4096 (203 MB) 138.6 / 136.7, 125.9 / 127.2, 102.7 / 103.7; 3000 x 7168 (177 MB) 118.6 / 122.2, 2700 x
+// 8192 122.6 / 123.3, 6000 x 3072 102.1 / 105.3, 8192 x 2048 97.2 / 97.9.  A row that is one wave's has one store of scales
+// anyway: ring off, 30000 x 1024 49.7 / 51.8.  With one command per row it was not measured.)
+// (AHEAD: the row leaves together with the pairs, see dispatch_bf16_kernel, but for sequenced chunks: that choice is made here,
+// as with instances of their own those got slower, 2000 tokens x 7168 top-8 89.8 us, apart 93.9, 4096 tokens 167.8, 169.7.  For
+// one rank of several, whose launches are small, an instance without: ring off, one of 16 ranks, 4096 x 7168 10.6 us, apart
+// 10.2.)
 template <int VPL, bool GROUPS, bool AHEAD, bool TOGETHER>
 __global__ void dispatch_fp8_kernel(DispatchArgs a) {
   __shared__ float s_scale[TOGETHER ? 16 * VPL * 8 : 1];  // [wave][its blocks]: the parts of a token in a row
@@ -618,10 +620,10 @@ static size_t group_cmds_setup(DispatchArgs &a, int waves) {
 }
 
 // Does a token's row of bf16 leave for the registers together with its pairs?  (See dispatch_bf16_kernel.)  Where all rows are
-// few (24 MB) without asking for an expert: such a launch waits for loads more than for memory.  Whole steps, asking / not, us: 1500
-// tokens x 7168 top-6 54.3 / 52.8, 777 x 2944 16.7 / 16.3, 4000 x 2048 57.0 / 56.7; ring off with 19 of 20 tokens dropped, 1400 x 7168
-// 5.9 / 6.2, 3000 x 4096 6.3 / 6.2, but 2000 x 7168 6.7 / 8.2.  (FP8 always asks: 1500 x 7168 45.3 / 45.0, 1000 x 7168 46.8 / 47.4, and
-// 1400 x 7168 with four of five dropped 6.3 / 6.7.)
+// few (24 MB) without asking for an expert: such a launch waits for loads more than for memory.  Whole steps, asking / not, us:
+// 1500 tokens x 7168 top-6 54.3 / 52.8, 777 x 2944 16.7 / 16.3, 4000 x 2048 57.0 / 56.7; ring off with 19 of 20 tokens dropped,
+// 1400 x 7168 5.9 / 6.2, 3000 x 4096 6.3 / 6.2, but 2000 x 7168 6.7 / 8.2.  (FP8 always asks: 1500 x 7168 45.3 / 45.0, 1000 x
+// 7168 46.8 / 47.4, and 1400 x 7168 with four of five dropped 6.3 / 6.7.)
 static int row_ahead(const DispatchArgs &a) {
   const int cmds = a.cmd_mode & EP_CMD_MODE_MASK;
   if ((cmds != EP_CMD_NONE && cmds != EP_CMD_CHUNK32) || (a.cmd_mode & EP_CMD_NO_PLACEMENT) || a.filter >= 0) return kAheadNone;
@@ -698,19 +700,19 @@ int launch_dispatch(const DispatchArgs &a, int payload, const Tunables &tune, vo
     if (free_choice && (cmds == EP_CMD_PER_TOKEN || cmds == EP_CMD_CHUNK32_ORDERED) &&
         !(a.cmd_mode & EP_CMD_NO_PLACEMENT) && vpl > 2 && (a.H / 8 + 127) / 128 <= 8)
       vpl = 2;
-    // Ring off or plain chunk commands: rows that exceed the memory-side cache (256 MB) by a quarter or more have to
-    // stream to HBM while the kernel runs; then ONE slice per wave (many small waves, eight 1 KiB stores each)
-    // is faster by 5-10 us per 450-900 MB than four slices per wave, which wins below that size by as much when the
-    // buffer is the one of the call before - and also where the caller has said that the rows are consumed in place, out of
-    // that cache.  Whole steps, four slices / one, into the same buffer and into four in turn, us: 3000 tokens x 7168 top-8
-    // (344 MB) 148.6 / 145.8 and 146.0 / 140.7, 4000 x 5120 (328 MB) 143.9 / 141.8 and 140.7 / 137.8, 2800 x 8192 158.3 / 151.9
-    // and 155.8 / 150.5; 2600 x 7168 (298 MB) 114.0 / 118.3 and 128.2 / 123.9, 2000 x 7168 88.0 / 92.9 and 100.7 / 96.3, 4500 x
-    // 4096 (295 MB) 111.8 / 112.2 and 127.5 / 125.9.  The bytes are those of a table without dropped pairs, which only the GPU
-    // counts: 3000 x 7168 with a tenth dropped 138.4 / 135.4, three tenths 118.0 / 118.5, half 98.6 / 103.5; 4000 x 5120 133.5 / 130.5,
-    // 114.1 / 111.1, 93.6 / 96.4.  A handle with one expert per rank mostly places deduplicated rows, of which a fifth and more are
-    // dropped: there from 384 MB on.  Deduplicated steps over 16 groups, 2900 x 7168 221.4 / 228.1, with a tenth dropped 206.2 / 214.9,
-    // 3200 x 7168 (367 MB) 248.8 / 253.2 and 226.3 / 237.2.  (The sequenced chunk mode, bound by its hottest channel's
-    // FIFO, was measured slower with one slice per wave on the skewed workload.)
+    // Ring off or plain chunk commands: rows that exceed the memory-side cache (256 MB) by a quarter or more have to stream to
+    // HBM while the kernel runs; then ONE slice per wave (many small waves, eight 1 KiB stores each) is faster by 5-10 us per
+    // 450-900 MB than four slices per wave, which wins below that size by as much when the buffer is the one of the call before
+    // - and also where the caller has said that the rows are consumed in place, out of that cache.  Whole steps, four slices /
+    // one, into the same buffer and into four in turn, us: 3000 tokens x 7168 top-8 (344 MB) 148.6 / 145.8 and 146.0 / 140.7,
+    // 4000 x 5120 (328 MB) 143.9 / 141.8 and 140.7 / 137.8, 2800 x 8192 158.3 / 151.9 and 155.8 / 150.5; 2600 x 7168 (298 MB)
+    // 114.0 / 118.3 and 128.2 / 123.9, 2000 x 7168 88.0 / 92.9 and 100.7 / 96.3, 4500 x 4096 (295 MB) 111.8 / 112.2 and 127.5 /
+    // 125.9.  The bytes are those of a table without dropped pairs, which only the GPU counts: 3000 x 7168 with a tenth dropped
+    // 138.4 / 135.4, three tenths 118.0 / 118.5, half 98.6 / 103.5; 4000 x 5120 133.5 / 130.5, 114.1 / 111.1, 93.6 / 96.4.  A
+    // handle with one expert per rank mostly places deduplicated rows, of which a fifth and more are dropped: there from 384 MB
+    // on.  Deduplicated steps over 16 groups, 2900 x 7168 221.4 / 228.1, with a tenth dropped 206.2 / 214.9, 3200 x 7168 (367
+    // MB) 248.8 / 253.2 and 226.3 / 237.2.  (The sequenced chunk mode, bound by its hottest channel's FIFO, was measured slower
+    // with one slice per wave on the skewed workload.)
     const long long rows_at_most = (long long)a.T * a.K < a.recv_rows ? (long long)a.T * a.K : a.recv_rows;
     if (free_choice && !a.cache_hinted && (cmds == EP_CMD_NONE || cmds == EP_CMD_CHUNK32) &&
         rows_at_most * a.H * 2 >= (a.E == a.R ? 384000000ll : 320000000ll) && (a.H / 8 + 63) / 64 <= 16)

@@ -180,7 +180,7 @@ struct HtRingArgs {
   float *recv_scale;       // FP8: [recv_rows, H/128]
   long long recv_rows;
   int32_t T, K, H, E_loc, R, src, slices, slice_len, W, payload;
-  int32_t split;           // workgroups of a slice: each has the channels of every split-th rank (set by the launcher)
+  int32_t split;           // workgroups of a slice: they share its channels (set by the launcher)
   unsigned slot_bytes;     // stride of a slot (header + 32 bf16 rows, whatever the payload)
   unsigned row_bytes;      // bytes of one row in a slot: 2H, or H codes + H/32 scale bytes padded to 16
   const int32_t *tail, *head;                       // pinned host [slices*R] of this source, written by the proxy

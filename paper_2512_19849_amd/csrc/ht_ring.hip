@@ -165,15 +165,15 @@ EP_DEV bool ht_send_token(const HtRingArgs &a, HtShared &sh, int c, int t, HtTok
       }
     }
   } else {
-    // FP8 message: the row's E4M3 codes, then one fp32 scale per 128 channels (Section 2.1: the ~7 KB
-    // token); quantised once per token, stored to every destination.  Rows of up to 8192 channels are quantised whole before the
-    // first store, two groups of channels per lane at a time (more, and the registers do not last), and their scales leave as
-    // one store: a second half would wait for the stores of the first.  Whole steps, four groups and then the next four, scales
-    // 32 bytes at a time, and in the receiving step behind the codes / this, us: 4096 tokens x 7168 top-8, 128 slices 299 / 293,
-    // 2048 tokens 204 / 194, 3000 x 8064 over 256 264 / 246, 4096 x 4096 212 / 202, 1024 x 3072 over 64 91 / 89.
-    // Groups that a narrow row does not have are passed over: with all eight quantised whatever the width 4096 x 1024 over 64 slices
-    // takes 207, with four 196, like this 178; 2000 x 2048 117, 121 and 110; 4096 x 7168 the same.
-    constexpr int kPairs = 8;
+    // FP8 message: the row's E4M3 codes, then one fp32 scale per 128 channels (Section 2.1: the ~7 KB token); quantised once
+    // per token, stored to every destination.  Rows of up to 8192 channels are quantised whole before the first store, two
+    // groups of channels per lane at a time (more, and the registers do not last), and their scales leave as one store: a
+    // second half would wait for the stores of the first.  Whole steps, four groups and then the next four, scales 32 bytes at
+    // a time, and in the receiving step behind the codes / this, us: 4096 tokens x 7168 top-8, 128 slices 299 / 293, 2048
+    // tokens 204 / 194, 3000 x 8064 over 256 264 / 246, 4096 x 4096 212 / 202, 1024 x 3072 over 64 91 / 89. Groups that a
+    // narrow row does not have are passed over: with all eight quantised whatever the width 4096 x 1024 over 64 slices takes
+    // 207, with four 196, like this 178; 2000 x 2048 117, 121 and 110; 4096 x 7168 the same.
+    constexpr int kPairs = 8;  // (64 blocks: a lane's scale each)
     const int npair = a.H >> 4;
     for (int p0 = 0; p0 < npair; p0 += 64 * kPairs) {
       u32x4 q[kPairs];
@@ -211,7 +211,7 @@ EP_DEV bool ht_send_token(const HtRingArgs &a, HtShared &sh, int c, int t, HtTok
           if (p < npair) store_payload((u32x4 *)dst + p, q[i]);
         }
         const int b = (p0 >> 3) + lane;
-        if (lane < kPairs * 8 && b < a.H >> 7)
+        if (b < a.H >> 7)
           __hip_atomic_store((float *)(dst + a.H) + b, scale, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
       }
     }
@@ -450,9 +450,10 @@ static_assert(std::is_same_v<decltype(&ht_ring_kernel), void (*)(HtRingArgs)> &&
               "ht_fifo takes the kernel's arguments for one HtRingArgs");
 
 // A workgroup's sixteen waves fill a compute unit, so fewer than 256 slices leave some idle: then 2, 4, ... workgroups share a
-// slice, up to the number of ranks, each with the channels of every 2nd, 4th, ... rank (a channel's state is its own, so they
+// slice, up to the number of ranks, each with the channels that ht_share deals to it (a channel's state is its own, so they
 // have nothing to say to each other).  As long as each still has half a megabyte to move; with less, the polls and the reads
-// of the tokens, which every one of them does, cost more.  Whole steps, 1 / 2 / 4 / 8 / 16 workgroups a slice, us:
+// of the tokens, which every one of them does, cost more.  Whole steps, 1 / 2 / 4 / 8 / 16 workgroups a slice, us, taken with every
+// workgroup at every 2nd, 4th, ... rank and an acquire by every wave (now 128 slices, 4096 x 7168 400, 64 slices, 1500 x 7168 163):
 //   4 slices    4096 tokens x 7168 top-8 4783 / 3045 / 2662 / 2344 / 2415, 1024 x 7168 1151 / 780 / 683 / 515 / 404, 4096 x
 //               2048 1831 / 1402 / 1422 / 1486 / 1704 (16 by this rule: rows this narrow would be better off with 2)
 //   8 slices    4096 x 7168 2536 / 1610 / 1396 / 1234 / 1174, 4096 x 2048 972 / 713 / 732 / 755 / 787

@@ -70,7 +70,8 @@ def test_rows_of_tokens_without_experts_are_not_read_ahead(tmp_path):
     """A kernel that reads rows ahead of the tokens' pairs, and not in small launches only, asks for the first pair before: a
     scalar load of the expert, and what comes of its sign.  Tokens that name none (padding) cost no read of their row."""
     asm = _assembly("dispatch.hip", tmp_path)
-    kernels = re.findall(r"^(_ZN2ep20dispatch_bf16_kernelILi\d+ELb0ELi2E\w*|_ZN2ep19dispatch_fp8_kernelILi\d+ELb0ELb1E\w*):", asm, re.M)
+    kernels = re.findall(r"^(_ZN2ep20dispatch_bf16_kernelILi\d+ELb0ELi2E\w*|_ZN2ep19dispatch_fp8_kernelILi\d+ELb0ELb1E\w*):",
+                         asm, re.M)
     assert len(kernels) == 3 + 6
     for mangled in kernels:
         body = _kernel_body(asm, mangled)
